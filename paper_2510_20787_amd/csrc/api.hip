@@ -322,8 +322,9 @@ size_t ltea_append_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int
                                    int32_t max_new) {
   (void)max_new;
   if (check_cfg(cfg) != LTEA_OK || !cnn || check_cnn(cfg, cnn) != LTEA_OK || n_seqs < 0 || total_new < 0) return 0;
-  const int64_t ext = append_ext_tokens(*cfg, n_seqs, total_new);
-  return align_up(append_workspace(*cfg, n_seqs, total_new, true), 256) + score_workspace(*cfg, *cnn, ext);
+  const int rho = cnn_rho(cnn);
+  return align_up(append_workspace(*cfg, n_seqs, total_new, rho), 256) +
+         score_workspace(*cfg, *cnn, append_score_tokens(n_seqs, total_new, rho));
 }
 
 int ltea_prefill_append(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* q, int64_t q_stride_tok,
@@ -363,38 +364,34 @@ int ltea_prefill_append_feat(const ltea_cfg* cfg, const ltea_cnn* cnn, const lte
   if (ext_len_max > INT32_MAX / 2) return LTEA_EUNSUPPORTED;
   const int64_t ext = append_ext_tokens(*cfg, n_seqs, total_new);
   if (ext >= (int64_t)1 << 31) return LTEA_EUNSUPPORTED;   // the packed extended sequences are indexed by int32 prefix sums
-  const size_t build_ws = align_up(append_workspace(*cfg, n_seqs, total_new, rope != nullptr), 256);
-  const size_t need = build_ws + score_workspace(*cfg, *cnn, ext);
+  const int rho = cnn_rho(cnn);
+  const int64_t scored = append_score_tokens(n_seqs, total_new, rho);
+  const size_t build_ws = align_up(append_workspace(*cfg, n_seqs, total_new, rho), 256);
+  const size_t need = build_ws + score_workspace(*cfg, *cnn, scored);
   if (!workspace || workspace_bytes < need) return LTEA_EWORKSPACE;
   if (workspace && !aligned256(workspace)) return LTEA_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int rho = cnn_rho(cnn);
   AppendBuffers buf;
   st = hip_status(launch_append_build(*cfg, k, v, k_feat, kv_stride_tok, kv_stride_head, cu_new, n_seqs, total_new,
-                                      max_new, rope, status, *cache, workspace, &buf, s));
+                                      max_new, rho, rope, status, *cache, workspace, &buf, s));
   if (st != LTEA_OK) return st;
-  SeqView sv_ext{buf.cu_ext, n_seqs, buf.total_ext, buf.max_ext_len};
-  SeqView sv_score{buf.cu_score, n_seqs, buf.total_ext, 2 * buf.max_ext_len};
-  st = do_score(*cfg, *cnn, buf.ext_kf, buf.ext_v, ext_stride_tok, cfg->D, sv_score, buf.ext_logits,
-                static_cast<char*>(workspace) + build_ws, s);
-  if (st != LTEA_OK) return st;
-  st = hip_status(launch_append_keys(*cfg, n_seqs, total_new, *cache, rho, workspace, buf, s));
-  if (st != LTEA_OK) return st;
-  ltea_cfg sel = *cfg;
-  sel.sink = 0;     // sinks already carry the key +inf in the extended sequence
-  st = hip_status(launch_retain(sel, buf.ext_logits, buf.ext_k, buf.ext_v, ext_stride_tok, cfg->D, sv_ext, rho, *cache, s));
-  if (st != LTEA_OK) return st;
-  st = hip_status(launch_append_fixup(*cfg, cu_new, n_seqs, total_new, *cache, rho, workspace, s));
+  if (scored > 0) {
+    SeqView sv_score{buf.plan.cu_score, n_seqs, scored, max_new + 2 * rho};
+    st = do_score(*cfg, *cnn, buf.score_k, buf.score_v, ext_stride_tok, cfg->D, sv_score, buf.score_logits,
+                  static_cast<char*>(workspace) + build_ws, s);
+    if (st != LTEA_OK) return st;
+  }
+  st = hip_status(launch_retain_append(*cfg, buf, n_seqs, rho, *cache, s));
   if (st != LTEA_OK) return st;
   if (total_new == 0) return LTEA_OK;
   ltea_cache local = *cache;
-  local.ret_pos = buf.local_pos;
+  local.ret_pos = buf.plan.local_pos;
   SeqView sv_q{cu_new, n_seqs, total_new, max_new};
   if (attention_mfma_supported(*cfg, ext_stride_tok, (int32_t)ext_len_max))
     return hip_status(launch_attention_mfma(*cfg, q, q_stride_tok, q_stride_head, buf.ext_k, buf.ext_v, ext_stride_tok,
-                                            cfg->D, sv_q, local, out, s, buf.kv_start, buf.kv_len));
+                                            cfg->D, sv_q, local, out, s, buf.plan.kv_start, buf.plan.kv_len));
   return hip_status(launch_attention_generic(*cfg, q, q_stride_tok, q_stride_head, buf.ext_k, buf.ext_v, ext_stride_tok,
-                                             cfg->D, sv_q, local, out, s, nullptr, buf.kv_start, buf.kv_len));
+                                             cfg->D, sv_q, local, out, s, nullptr, buf.plan.kv_start, buf.plan.kv_len));
 }
 
 int ltea_decode_step(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* q, const void* k, const void* v, void* out,

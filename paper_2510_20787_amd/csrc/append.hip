@@ -10,20 +10,23 @@
 // in the workspace:   [ pad | old kept entries ascending by position | ring tokens in position order | new tokens ]
 // with the prefix (pad + kept entries) given the same length F for every head of the sequence, F >= budget chosen
 // such that extended index and true position agree modulo the window (so that the ring slot of a token, position %
-// window, can be computed from either).  Then
-//   1. the scoring kernel runs over the extended sequence; logits of ring tokens that were already final are taken
-//      from the cache instead (their left context may be outside the ring), prefix entries get their stored keys,
-//      pad entries NaN (never candidates; their K/V rows are zero, and the scoring is told that a sequence which
-//      started inside the ring begins after them: cu_score);
-//   2. the retention kernel runs over the extended sequence (candidates, top-b, gather, ring fill) unchanged;
-//   3. kept positions are translated back from extended indices to true positions, counters are set;
+// window, can be computed from either).  Four launches:
+//   1. the kernel of this file ranks the old kept entries, copies their rows, the ring's and the new ones into the
+//      extended sequence and the keys that are already final (stored keys of the kept entries, ring logits below
+//      n_old - rho) into its key array; pad rows are never read and stay unwritten;
+//   2. the scoring kernel runs over the part whose logits are not final yet, packed on its own: the last
+//      min(n_old, 2 rho) ring tokens and the new ones (a ring token below n_old - rho needs no new logit, one above it
+//      has its whole left context in those rows);
+//   3. the retention kernel runs over the extended sequence (candidates, top-b, gather, ring fill), taking each key
+//      from the key array or from the fresh logits and writing kept positions back as true positions and, for the
+//      attention kernel, in the ring + new frame (old kept entries get negative positions there and are visible
+//      to every new query, as they should be); it also sets the counters;
 //   4. the attention kernel runs with the ring + new part of the extended sequence as keys and the new tokens as
-//      queries (kept positions expressed in that local frame; old kept entries get negative positions and are visible
-//      to every new query, as they should be).
+//      queries.
 // Rotary models cache the keys after the rotation while the CNN scores them as they were before it.  For them the
-// extended sequence gets a second key buffer that only the scoring kernel reads: ring rows rotated back with the
-// model's sinusoids (as in the batched scoring of the decode ring), new rows taken from the caller's unrotated keys or
-// rotated back as well.
+// scoring rows are rotated back with the model's sinusoids (as in the batched scoring of the decode ring) where the
+// caller does not pass the new tokens' unrotated keys.
+#include "append_plan.h"
 #include "ltea_common.h"
 #include "ltea_kernels.h"
 #include "rope_dev.h"
@@ -31,244 +34,182 @@
 namespace ltea {
 namespace {
 
-struct AppendPlan {        // device arrays in the workspace, one entry per sequence unless noted
-  int32_t* n_old;          // tokens in the cache before the call
-  int32_t* w_old;          // min(n_old, window): ring tokens
-  int32_t* prefix;         // F
-  int32_t* cu_ext;         // [n_seqs + 1] packing of the extended sequences
-  int32_t* cu_score;       // [n_seqs + 1] the same packing as the scoring kernels must see it (see the plan kernel)
-  int32_t* kv_start;       // first row of the ring + new part in the extended buffers
-  int32_t* kv_len;         // w_old + new tokens
-  int32_t* sorted_pos;     // [n_seqs][Hkv][budget] old kept positions ascending
-  int32_t* sorted_slot;    // [n_seqs][Hkv][budget] compact slot of the entry with that rank
-  int32_t* local_pos;      // [n_seqs][Hkv][budget] kept positions in the ring + new frame (for the attention kernel)
-};
-
-__device__ __forceinline__ void plan_body(const AppendPlan& P, const int32_t* __restrict__ cu_new,
-                                          const int32_t* __restrict__ n_seen, int n_seqs, int window, int budget) {
-  // one workgroup: sequential prefix sum over the sequences (a handful to a few thousand)
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int s0 = 0; s0 < n_seqs; s0 += 256) {
-    const int s = s0 + threadIdx.x;
-    int ext = 0, N = 0, wo = 0, F = 0, M = 0;
-    if (s < n_seqs) {
-      N = n_seen[s];
-      wo = N < window ? N : window;
-      M = cu_new[s + 1] - cu_new[s];
-      const int want = (N - wo) % window;             // true position of the first ring token, modulo the window
-      F = budget + ((want - budget) % window + window) % window;   // smallest F >= budget with F == want (mod window)
-      ext = F + wo + M;
-    }
-    // inclusive scan over the 256 threads (4 waves)
-    __shared__ int wave_tot[4];
-    int inc = ext;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int t = __shfl_up(inc, off, kWave);
-      if (lane >= off) inc += t;
-    }
-    if (lane == kWave - 1) wave_tot[wave] = inc;
-    __syncthreads();
-    int before = carry;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
-    if (s < n_seqs) {
-      const int start = before + inc - ext;
-      P.n_old[s] = N; P.w_old[s] = wo; P.prefix[s] = F;
-      P.cu_ext[s] = start;
-      // A sequence whose ring still begins at position 0 has only pad rows in its prefix.  For the scoring they
-      // must not exist at all (a conv stack pads with zeros at every layer, and a zero input row does not give a
-      // zero activation), so the scoring sees this sequence begin after its pad; the pad then trails the previous
-      // sequence, where it can only reach logits that are provisional anyway.
-      P.cu_score[s] = start + (N <= window ? F : 0);
-      P.kv_start[s] = start + F;
-      P.kv_len[s] = wo + M;
-      if (s == n_seqs - 1) { P.cu_ext[n_seqs] = start + ext; P.cu_score[n_seqs] = start + ext; }
-    }
-    __syncthreads();
-    if (threadIdx.x == 255) carry = before + inc;
-    __syncthreads();
-  }
-}
-
-// Rank of every old kept entry by position (positions are distinct): O(count^2 / threads), count <= budget.
-__device__ __forceinline__ void rank_body(const AppendPlan& P, int64_t head, const int32_t* __restrict__ ret_pos,
-                                          const int32_t* __restrict__ ret_count, int budget,
-                                          int32_t* __restrict__ old_count) {
-  const int cnt = budget > 0 ? ret_count[head] : 0;
-  if (threadIdx.x == 0) old_count[head] = cnt;   // the retention stage overwrites ret_count; the translation stage needs this
-  const int32_t* pos = ret_pos + head * budget;
-  for (int i = threadIdx.x; i < cnt; i += 256) {
-    const int p = pos[i];
-    int rank = 0;
-    for (int j = 0; j < cnt; ++j) rank += pos[j] < p;
-    P.sorted_pos[head * budget + rank] = p;
-    P.sorted_slot[head * budget + rank] = i;
-  }
-}
-
-// One launch for both preparations (they do not depend on each other): workgroup 0 plans, workgroup 1 + head ranks.
-__global__ void __launch_bounds__(256)
-append_plan_rank_kernel(AppendPlan P, const int32_t* __restrict__ cu_new, const int32_t* __restrict__ n_seen, int n_seqs,
-                        int window, int budget, const int32_t* __restrict__ ret_pos,
-                        const int32_t* __restrict__ ret_count, int32_t* __restrict__ old_count) {
-  if (blockIdx.x == 0) plan_body(P, cu_new, n_seen, n_seqs, window, budget);
-  else rank_body(P, (int64_t)blockIdx.x - 1, ret_pos, ret_count, budget, old_count);
-}
+constexpr int kThreads = 256;
+constexpr int kItems = 128;      // items (kept entries, ring tokens, new tokens in this order) per workgroup
+constexpr int kRankTile = 1024;  // positions compared against per LDS tile
 
 struct BuildArgs {
   const char* k_new; const char* v_new; int64_t tok_bytes, head_bytes;   // new tokens [T][Hkv][D] view, in bytes
   const char* kf_new;                // the new tokens' keys as the CNN wants them (same view), or null
   const int32_t* cu_new;
-  const char* k_win; const char* v_win; const char* k_ret; const char* v_ret; const int32_t* ret_count;
+  const char* k_win; const char* v_win; const float* win_score;
+  const char* k_ret; const char* v_ret; const float* ret_score; const int32_t* ret_pos; const int32_t* ret_count;
+  const int32_t* n_seen;
   char* k_ext; char* v_ext;          // [total_ext][Hkv][D] contiguous
-  char* kf_ext;                      // scoring keys of the extended rows, or null when they are the cached keys
+  char* k_score; char* v_score;      // [total_score][Hkv][D] contiguous
   RopeDev rope;                      // cos == null: no rotation to undo
   int32_t* status;
-  int Hkv, window, budget, row_bytes;
+  int n_seqs, Hkv, window, budget, rho, row_bytes;
 };
 
-// Extended K/V rows of one (sequence, head): blockIdx.y walks chunks of 128 extended rows.
+// Grid (sequence x KV head, chunks of kItems items).  Bound: launch latency and the copies (at most budget + window + M
+// rows of a head).  Every workgroup works its sequence's plan out itself (a sum over the sequences before it) and ranks
+// only its own kept entries, 128 of them against all positions from LDS: as a launch of its own, with the positions
+// read from memory one by one, the ranking of 512 entries took 39 us.
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kThreads)
 append_build_kernel(AppendPlan P, BuildArgs a) {
   constexpr int EPP = Elems<T>::N;
+  __shared__ int sums[2][kThreads / kWave];
+  __shared__ __align__(16) int pos_lds[kRankTile];
+  __shared__ int rank_lds[kItems];
   const int b = blockIdx.x / a.Hkv, h = blockIdx.x - b * a.Hkv;
   const int64_t head = (int64_t)b * a.Hkv + h;
-  const int N = P.n_old[b], wo = P.w_old[b], F = P.prefix[b];
-  const int e0 = P.cu_ext[b], len = P.cu_ext[b + 1] - e0;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+
+  // ---- plan: where this sequence's extended and scoring rows begin ----
+  auto shape = [&](int s, int& N, int& wo, int& F, int& M) {
+    N = a.n_seen[s];
+    wo = N < a.window ? N : a.window;
+    M = a.cu_new[s + 1] - a.cu_new[s];
+    const int want = (N - wo) % a.window;                    // true position of the first ring token, modulo the window
+    F = a.budget + ((want - a.budget) % a.window + a.window) % a.window;   // smallest F >= budget with F == want
+  };
+  int ext_before = 0, score_before = 0;
+  for (int s = tid; s < b; s += kThreads) {
+    int N, wo, F, M;
+    shape(s, N, wo, F, M);
+    ext_before += F + wo + M;
+    score_before += min(wo, 2 * a.rho) + M;
+  }
+  ext_before = wave_sum_i(ext_before);
+  score_before = wave_sum_i(score_before);
+  if (lane == 0) { sums[0][tid / kWave] = ext_before; sums[1][tid / kWave] = score_before; }
+  int N, wo, F, M;
+  shape(b, N, wo, F, M);
+  __syncthreads();
+  const int e0 = sums[0][0] + sums[0][1] + sums[0][2] + sums[0][3];
+  const int s0 = sums[1][0] + sums[1][1] + sums[1][2] + sums[1][3];
+  const int ctx = min(wo, 2 * a.rho);                        // ring tokens in front of the scored new ones
+  if (h == 0 && blockIdx.y == 0 && tid == 0) {
+    P.n_old[b] = N; P.w_old[b] = wo; P.prefix[b] = F;
+    P.cu_ext[b] = e0; P.cu_score[b] = s0;
+    P.kv_start[b] = e0 + F; P.kv_len[b] = wo + M;
+    if (b == a.n_seqs - 1) { P.cu_ext[b + 1] = e0 + F + wo + M; P.cu_score[b + 1] = s0 + ctx + M; }
+  }
+
   const int cnt = a.budget > 0 ? a.ret_count[head] : 0, pad = F - cnt;
-  const int pieces = a.row_bytes / 16, rows_per_pass = 256 / pieces;
-  const int sub = threadIdx.x / pieces, pc = threadIdx.x - sub * pieces;
-  const int row_end = min((int)(blockIdx.y + 1) * 128, len);
+  const int item0 = blockIdx.y * kItems, item_end = min(item0 + kItems, cnt + wo + M);
+  if (item0 >= item_end) return;
+
+  // ---- ranks of this workgroup's kept entries by position (positions are distinct): two threads per entry ----
+  if (item0 < cnt) {                                         // uniform
+    const int32_t* pos = a.ret_pos + head * a.budget;
+    const int i = item0 + tid / 2;
+    const int p = i < cnt ? pos[i] : 0;
+    int rank = 0;
+    for (int base = 0; base < cnt; base += kRankTile) {
+      if (base > 0) __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kRankTile / kThreads; ++u) {
+        const int j = base + u * kThreads + tid;
+        pos_lds[u * kThreads + tid] = j < cnt ? pos[j] : 0x7FFFFFFF;
+      }
+      __syncthreads();
+      const int quads = (min(cnt - base, kRankTile) + 3) / 4;
+      for (int j = tid & 1; j < quads; j += 2) {
+        const int4 x = reinterpret_cast<const int4*>(pos_lds)[j];
+        rank += (x.x < p) + (x.y < p) + (x.z < p) + (x.w < p);
+      }
+    }
+    rank += __shfl_xor(rank, 1, kWave);
+    if ((tid & 1) == 0 && i < cnt) {
+      rank_lds[tid / 2] = rank;
+      P.sorted_pos[head * a.budget + rank] = p;
+      P.ext_key[(int64_t)h * P.total_ext + e0 + pad + rank] = a.ret_score[head * a.budget + i];
+    }
+    __syncthreads();
+  }
+
+  // ---- rows ----
+  const int pieces = a.row_bytes / 16, rows_per_pass = kThreads / pieces;
+  const int sub = tid / pieces, pc = tid - sub * pieces;
   const int64_t new0 = a.cu_new[b];
   bool out_of_tables = false;
-  for (int e = blockIdx.y * 128 + sub; e < row_end; e += rows_per_pass) {
-    const char* sk = nullptr;
-    const char* sv = nullptr;
+  for (int item = item0 + sub; item < item_end; item += rows_per_pass) {
+    const char *sk, *sv;
+    int e;                      // extended index
+    int sr = -1;                // scoring row
+    int p_rot = -1;             // position whose rotation has to be undone for the scoring key
     const char* sf = nullptr;   // a row of ready-made scoring keys
-    int p_rot = -1;             // position whose rotation has to be undone for the scoring keys
-    if (e < pad) {
-      // zero rows
-    } else if (e < F) {
-      // an old kept entry: only its stored key takes part in the selection, its rows never reach a logit that is used
-      const int slot = P.sorted_slot[head * a.budget + (e - pad)];
-      sk = a.k_ret + (head * a.budget + slot) * a.row_bytes;
-      sv = a.v_ret + (head * a.budget + slot) * a.row_bytes;
-    } else if (e < F + wo) {
-      const int p = N - wo + (e - F);                       // true position of this ring token
+    if (item < cnt) {
+      e = pad + rank_lds[item - item0];
+      sk = a.k_ret + (head * a.budget + item) * a.row_bytes;
+      sv = a.v_ret + (head * a.budget + item) * a.row_bytes;
+    } else if (item < cnt + wo) {
+      const int r = item - cnt, p = N - wo + r;             // true position of this ring token
       const int slot = p % a.window;
+      e = F + r;
       sk = a.k_win + (head * a.window + slot) * a.row_bytes;
       sv = a.v_win + (head * a.window + slot) * a.row_bytes;
-      p_rot = p;
+      if (r >= wo - ctx) { sr = s0 + r - (wo - ctx); p_rot = p; }
+      if (a.rope.cos != nullptr && p >= a.rope.n_pos) out_of_tables = true;
+      if (pc == 0 && p < N - a.rho)                          // final before this call
+        P.ext_key[(int64_t)h * P.total_ext + e0 + e] = a.win_score[head * a.window + slot];
     } else {
-      const int64_t t = new0 + (e - F - wo);
+      const int r = item - cnt - wo;
+      const int64_t t = new0 + r;
+      e = F + wo + r;
       sk = a.k_new + t * a.tok_bytes + h * a.head_bytes;
       sv = a.v_new + t * a.tok_bytes + h * a.head_bytes;
+      sr = s0 + ctx + r;
       if (a.kf_new != nullptr) sf = a.kf_new + t * a.tok_bytes + h * a.head_bytes;
-      else p_rot = N + (e - F - wo);
+      else p_rot = N + r;
     }
-    u32x4 xk = {0u, 0u, 0u, 0u}, xv = {0u, 0u, 0u, 0u};
-    if (sk != nullptr) {
-      xk = reinterpret_cast<const u32x4*>(sk)[pc];
-      xv = reinterpret_cast<const u32x4*>(sv)[pc];
-    }
+    const u32x4 xk = reinterpret_cast<const u32x4*>(sk)[pc];
+    const u32x4 xv = reinterpret_cast<const u32x4*>(sv)[pc];
     const int64_t dst = ((int64_t)(e0 + e) * a.Hkv + h) * a.row_bytes;
     reinterpret_cast<u32x4*>(a.k_ext + dst)[pc] = xk;
     reinterpret_cast<u32x4*>(a.v_ext + dst)[pc] = xv;
-    if (a.kf_ext != nullptr) {
+    if (sr >= 0) {
       u32x4 xf = xk;
       if (sf != nullptr) {
         xf = reinterpret_cast<const u32x4*>(sf)[pc];
-      } else if (p_rot >= 0 && a.rope.cos != nullptr && pc * EPP < a.rope.rot_dim) {
+      } else if (a.rope.cos != nullptr && pc * EPP < a.rope.rot_dim) {
         if (p_rot >= a.rope.n_pos) out_of_tables = true;
         else xf = unrotate_piece<T>(a.rope, p_rot, pc * EPP, xk, reinterpret_cast<const T*>(sk));
       }
-      reinterpret_cast<u32x4*>(a.kf_ext + dst)[pc] = xf;
+      const int64_t sdst = ((int64_t)sr * a.Hkv + h) * a.row_bytes;
+      reinterpret_cast<u32x4*>(a.k_score + sdst)[pc] = xf;
+      reinterpret_cast<u32x4*>(a.v_score + sdst)[pc] = xv;
     }
   }
   if (out_of_tables && a.status != nullptr) atomicOr(a.status, LTEA_ROPE_RANGE);
-}
-
-// Selection keys over the extended sequence, written over the logits the scoring kernel produced.
-__global__ void __launch_bounds__(256)
-append_keys_kernel(AppendPlan P, float* __restrict__ ext_logits, int64_t total_ext, const float* __restrict__ win_score,
-                   const float* __restrict__ ret_score, const int32_t* __restrict__ ret_count, int Hkv, int window,
-                   int budget, int sink, int rho) {
-  const int b = blockIdx.x / Hkv, h = blockIdx.x - b * Hkv;
-  const int64_t head = (int64_t)b * Hkv + h;
-  const int N = P.n_old[b], wo = P.w_old[b], F = P.prefix[b];
-  const int e0 = P.cu_ext[b], len = P.cu_ext[b + 1] - e0;
-  const int cnt = budget > 0 ? ret_count[head] : 0, pad = F - cnt;
-  float* z = ext_logits + (int64_t)h * total_ext + e0;
-  for (int e = blockIdx.y * 1024 + threadIdx.x; e < min((int)(blockIdx.y + 1) * 1024, len); e += 256) {
-    if (e < pad) {
-      z[e] = __uint_as_float(0x7FC00000u);                   // NaN: never a candidate
-    } else if (e < F) {
-      z[e] = ret_score[head * budget + P.sorted_slot[head * budget + (e - pad)]];
-    } else {
-      const int p = N - wo + (e - F);                        // true position
-      // sinks always stay; only positions that leave the window now need the key (those that remain in the ring keep
-      // their logit, which is what the ring stores)
-      if (p < sink && e < len - window) z[e] = __uint_as_float(0x7F800000u);
-      else if (p < N - rho) z[e] = win_score[head * window + p % window];   // final before this call
-      // else: the logit just computed (final if its right context is complete, provisional otherwise)
-    }
-  }
-}
-
-// Kept positions back to true positions (and to the ring + new frame for the attention kernel); counters.
-__global__ void __launch_bounds__(256)
-append_fixup_kernel(AppendPlan P, const int32_t* __restrict__ cu_new, int32_t* __restrict__ ret_pos,
-                    const int32_t* __restrict__ ret_count, const int32_t* __restrict__ old_count,
-                    int32_t* __restrict__ n_seen, int32_t* __restrict__ n_scored, int Hkv, int budget, int rho) {
-  const int b = blockIdx.x / Hkv, h = blockIdx.x - b * Hkv;
-  const int64_t head = (int64_t)b * Hkv + h;
-  const int N = P.n_old[b], wo = P.w_old[b], F = P.prefix[b];
-  const int pad = F - old_count[head];
-  const int cnt = ret_count[head];
-  for (int i = threadIdx.x; i < cnt; i += 256) {
-    const int e = ret_pos[head * budget + i];
-    P.local_pos[head * budget + i] = e - F;
-    ret_pos[head * budget + i] = e < F ? P.sorted_pos[head * budget + (e - pad)] : N - wo + (e - F);
-  }
-  if (h == 0 && threadIdx.x == 0) {
-    const int total = N + (cu_new[b + 1] - cu_new[b]);
-    n_seen[b] = total;
-    n_scored[b] = total > rho ? total - rho : 0;
-  }
 }
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 }  // namespace
 
-// Upper bound of the extended tokens of all sequences (the true total depends on device-side state).
+// Upper bounds of the extended tokens and of the scored ones of all sequences (the true totals depend on device-side
+// state).
 int64_t append_ext_tokens(const ltea_cfg& cfg, int n_seqs, int64_t total_new) {
   return (int64_t)n_seqs * ((int64_t)cfg.budget + 2 * (int64_t)cfg.window) + total_new;
 }
+int64_t append_score_tokens(int n_seqs, int64_t total_new, int rho) { return total_new + (int64_t)n_seqs * 2 * rho; }
 
-size_t append_workspace(const ltea_cfg& cfg, int n_seqs, int64_t total_new, bool feature_keys) {
-  const int64_t ext = append_ext_tokens(cfg, n_seqs, total_new);
-  const size_t esz = cfg.dtype == LTEA_F32 ? 4 : 2;
-  size_t b = 0;
-  b += 7 * up256(sizeof(int32_t) * (size_t)(n_seqs + 1));                                 // per-sequence plan arrays
-  b += 4 * up256(sizeof(int32_t) * (size_t)n_seqs * cfg.Hkv * (size_t)(cfg.budget > 0 ? cfg.budget : 1));  // sorted_pos, sorted_slot, local_pos, old counts
-  b += (feature_keys ? 3 : 2) * up256((size_t)ext * cfg.Hkv * cfg.D * esz);                 // extended K, V (, scoring keys)
-  b += up256((size_t)ext * cfg.Hkv * sizeof(float));                                        // extended logits / keys
-  return b;
-}
+namespace {
 
-// Carves the workspace; returns the bytes used.  `ext_k`, `ext_v`, `ext_logits`, `old_count` receive the buffers.
-static size_t carve(const ltea_cfg& cfg, int n_seqs, int64_t total_new, char* ws, AppendPlan& P, char*& ext_k,
-                    char*& ext_v, float*& ext_logits, int32_t*& old_count) {
-  const int64_t ext = append_ext_tokens(cfg, n_seqs, total_new);
+struct Carved { AppendPlan plan; char *ext_k, *ext_v, *score_k, *score_v; float* score_logits; };
+
+// Carves the workspace (integer arithmetic: a size query carves from a null base); returns the bytes used.
+size_t carve(const ltea_cfg& cfg, int n_seqs, int64_t total_new, int rho, void* ws, Carved& c) {
+  const int64_t ext = append_ext_tokens(cfg, n_seqs, total_new), scored = append_score_tokens(n_seqs, total_new, rho);
   const size_t esz = cfg.dtype == LTEA_F32 ? 4 : 2;
-  uintptr_t p = reinterpret_cast<uintptr_t>(ws);   // integer arithmetic: a size query carves from a null base
+  uintptr_t p = reinterpret_cast<uintptr_t>(ws);
   auto take = [&](size_t bytes) { char* r = reinterpret_cast<char*>(p); p += up256(bytes); return r; };
-  const size_t per_seq = sizeof(int32_t) * (size_t)(n_seqs + 1);
+  const size_t per_seq = sizeof(int32_t) * ((size_t)n_seqs + 1);
+  AppendPlan& P = c.plan;
   P.n_old = reinterpret_cast<int32_t*>(take(per_seq));
   P.w_old = reinterpret_cast<int32_t*>(take(per_seq));
   P.prefix = reinterpret_cast<int32_t*>(take(per_seq));
@@ -278,81 +219,52 @@ static size_t carve(const ltea_cfg& cfg, int n_seqs, int64_t total_new, char* ws
   P.kv_len = reinterpret_cast<int32_t*>(take(per_seq));
   const size_t per_entry = sizeof(int32_t) * (size_t)n_seqs * cfg.Hkv * (size_t)(cfg.budget > 0 ? cfg.budget : 1);
   P.sorted_pos = reinterpret_cast<int32_t*>(take(per_entry));
-  P.sorted_slot = reinterpret_cast<int32_t*>(take(per_entry));
   P.local_pos = reinterpret_cast<int32_t*>(take(per_entry));
-  old_count = reinterpret_cast<int32_t*>(take(per_entry));
-  ext_k = take((size_t)ext * cfg.Hkv * cfg.D * esz);
-  ext_v = take((size_t)ext * cfg.Hkv * cfg.D * esz);
-  ext_logits = reinterpret_cast<float*>(take((size_t)ext * cfg.Hkv * sizeof(float)));
-  // an optional third key buffer (scoring keys) follows; launch_append_build takes it from here
+  P.ext_key = reinterpret_cast<float*>(take((size_t)ext * cfg.Hkv * sizeof(float)));
+  P.total_ext = ext;
+  c.ext_k = take((size_t)ext * cfg.Hkv * cfg.D * esz);
+  c.ext_v = take((size_t)ext * cfg.Hkv * cfg.D * esz);
+  c.score_k = take((size_t)scored * cfg.Hkv * cfg.D * esz);
+  c.score_v = take((size_t)scored * cfg.Hkv * cfg.D * esz);
+  c.score_logits = reinterpret_cast<float*>(take((size_t)scored * cfg.Hkv * sizeof(float)));
   return (size_t)(p - reinterpret_cast<uintptr_t>(ws));
 }
 
-// Stage 1 of the continuation: plan, ranks, extended K/V.  Returns the device arrays later stages need.
-// With `rope` or `kf_new` given, out->ext_kf is a third buffer with the keys as the scoring CNN wants them.
+}  // namespace
+
+size_t append_workspace(const ltea_cfg& cfg, int n_seqs, int64_t total_new, int rho) {
+  Carved c;
+  return carve(cfg, n_seqs, total_new, rho, nullptr, c);
+}
+
+// Stage 1 of the continuation; fills the device arrays that the later stages need.
 hipError_t launch_append_build(const ltea_cfg& cfg, const void* k_new, const void* v_new, const void* kf_new,
                                int64_t stride_tok, int64_t stride_head, const int32_t* cu_new, int n_seqs,
-                               int64_t total_new, int32_t max_new, const ltea_rope* rope, int32_t* status,
+                               int64_t total_new, int32_t max_new, int rho, const ltea_rope* rope, int32_t* status,
                                const ltea_cache& c, void* workspace, AppendBuffers* out, hipStream_t stream) {
-  AppendPlan P;
-  char *ext_k, *ext_v;
-  float* ext_logits;
-  int32_t* old_count;
-  const size_t used = carve(cfg, n_seqs, total_new, static_cast<char*>(workspace), P, ext_k, ext_v, ext_logits, old_count);
-  const bool feature_keys = rope != nullptr || kf_new != nullptr;
-  char* ext_kf = feature_keys ? static_cast<char*>(workspace) + used : nullptr;
+  Carved w;
+  carve(cfg, n_seqs, total_new, rho, workspace, w);
   const int64_t esz = cfg.dtype == LTEA_F32 ? 4 : 2;
-  const unsigned heads = (unsigned)n_seqs * (unsigned)cfg.Hkv;
-  hipLaunchKernelGGL(append_plan_rank_kernel, dim3(1u + heads), dim3(256), 0, stream, P, cu_new, c.n_seen, n_seqs, cfg.window,
-                     cfg.budget, c.ret_pos, c.ret_count, old_count);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   BuildArgs a;
   a.k_new = static_cast<const char*>(k_new); a.v_new = static_cast<const char*>(v_new);
   a.kf_new = static_cast<const char*>(kf_new);
   a.tok_bytes = stride_tok * esz; a.head_bytes = stride_head * esz; a.cu_new = cu_new;
-  a.k_win = static_cast<const char*>(c.k_win); a.v_win = static_cast<const char*>(c.v_win);
+  a.k_win = static_cast<const char*>(c.k_win); a.v_win = static_cast<const char*>(c.v_win); a.win_score = c.win_score;
   a.k_ret = static_cast<const char*>(c.k_ret); a.v_ret = static_cast<const char*>(c.v_ret);
-  a.ret_count = c.ret_count; a.k_ext = ext_k; a.v_ext = ext_v; a.kf_ext = ext_kf;
+  a.ret_score = c.ret_score; a.ret_pos = c.ret_pos; a.ret_count = c.ret_count; a.n_seen = c.n_seen;
+  a.k_ext = w.ext_k; a.v_ext = w.ext_v; a.k_score = w.score_k; a.v_score = w.score_v;
   a.rope = rope_dev(rope); a.status = status;
-  a.Hkv = cfg.Hkv; a.window = cfg.window; a.budget = cfg.budget; a.row_bytes = (int)(cfg.D * esz);
+  a.n_seqs = n_seqs; a.Hkv = cfg.Hkv; a.window = cfg.window; a.budget = cfg.budget; a.rho = rho;
+  a.row_bytes = (int)(cfg.D * esz);
+  const dim3 grid((unsigned)n_seqs * (unsigned)cfg.Hkv,
+                  (unsigned)(((int64_t)cfg.budget + cfg.window + max_new + kItems - 1) / kItems));
+  if (cfg.dtype == LTEA_F32) hipLaunchKernelGGL(append_build_kernel<float>, grid, dim3(kThreads), 0, stream, w.plan, a);
+  else hipLaunchKernelGGL(append_build_kernel<bf16_t>, grid, dim3(kThreads), 0, stream, w.plan, a);
+  out->plan = w.plan;
+  out->ext_k = w.ext_k; out->ext_v = w.ext_v;
+  out->score_k = w.score_k; out->score_v = w.score_v; out->score_logits = w.score_logits;
+  out->total_score = append_score_tokens(n_seqs, total_new, rho);
   out->max_ext_len = cfg.budget + 2 * cfg.window + max_new;
-  const unsigned chunks = (unsigned)((out->max_ext_len + 127) / 128);
-  if (cfg.dtype == LTEA_F32) hipLaunchKernelGGL(append_build_kernel<float>, dim3(heads, chunks), dim3(256), 0, stream, P, a);
-  else hipLaunchKernelGGL(append_build_kernel<bf16_t>, dim3(heads, chunks), dim3(256), 0, stream, P, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  out->ext_k = ext_k; out->ext_v = ext_v; out->ext_kf = ext_kf != nullptr ? ext_kf : ext_k;
-  out->ext_logits = ext_logits; out->cu_ext = P.cu_ext; out->cu_score = P.cu_score;
-  out->kv_start = P.kv_start; out->kv_len = P.kv_len; out->local_pos = P.local_pos;
-  out->total_ext = append_ext_tokens(cfg, n_seqs, total_new);
-  return hipSuccess;
-}
-
-hipError_t launch_append_keys(const ltea_cfg& cfg, int n_seqs, int64_t total_new, const ltea_cache& c, int rho,
-                              void* workspace, const AppendBuffers& buf, hipStream_t stream) {
-  AppendPlan P;
-  char *ext_k, *ext_v;
-  float* ext_logits;
-  int32_t* old_count;
-  carve(cfg, n_seqs, total_new, static_cast<char*>(workspace), P, ext_k, ext_v, ext_logits, old_count);
-  const unsigned heads = (unsigned)n_seqs * (unsigned)cfg.Hkv;
-  const unsigned chunks = (unsigned)((buf.max_ext_len + 1023) / 1024);
-  hipLaunchKernelGGL(append_keys_kernel, dim3(heads, chunks), dim3(256), 0, stream, P, ext_logits, buf.total_ext,
-                     c.win_score, c.ret_score, c.ret_count, cfg.Hkv, cfg.window, cfg.budget, cfg.sink, rho);
-  return hipGetLastError();
-}
-
-hipError_t launch_append_fixup(const ltea_cfg& cfg, const int32_t* cu_new, int n_seqs, int64_t total_new,
-                               const ltea_cache& c, int rho, void* workspace, hipStream_t stream) {
-  AppendPlan P;
-  char *ext_k, *ext_v;
-  float* ext_logits;
-  int32_t* old_count;
-  carve(cfg, n_seqs, total_new, static_cast<char*>(workspace), P, ext_k, ext_v, ext_logits, old_count);
-  const unsigned heads = (unsigned)n_seqs * (unsigned)cfg.Hkv;
-  hipLaunchKernelGGL(append_fixup_kernel, dim3(heads), dim3(256), 0, stream, P, cu_new, c.ret_pos, c.ret_count, old_count,
-                     c.n_seen, c.n_scored, cfg.Hkv, cfg.budget > 0 ? cfg.budget : 1, rho);
   return hipGetLastError();
 }
 

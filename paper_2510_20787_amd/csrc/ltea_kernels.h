@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/ltea.h"
+#include "append_plan.h"
 
 namespace ltea {
 
@@ -83,6 +84,11 @@ hipError_t launch_score_deep(const ltea_cfg& cfg, const ltea_cnn& cnn, const voi
 hipError_t launch_retain(const ltea_cfg& cfg, const float* logits, const void* k, const void* v,
                          int64_t stride_tok, int64_t stride_head, const SeqView& sv, int rho,
                          const ltea_cache& cache, hipStream_t stream);
+// The same over the extended sequences of a continued prefill: `score_logits` [Hkv][total_score] are the fresh logits,
+// k / v the extended rows; max_ext_len bounds one extended sequence.
+struct AppendBuffers;
+hipError_t launch_retain_append(const ltea_cfg& cfg, const AppendBuffers& buf, int n_seqs, int rho, const ltea_cache& cache,
+                                hipStream_t stream);
 
 // ---- (c) prefill attention -------------------------------------------------------------------------
 hipError_t launch_attention_generic(const ltea_cfg& cfg, const void* q, int64_t q_stride_tok, int64_t q_stride_head,
@@ -103,30 +109,22 @@ hipError_t launch_attention_mfma(const ltea_cfg& cfg, const void* q, int64_t q_s
 
 // ---- continuation of a prefill onto an existing cache ---------------------------------------------------
 // Device buffers of the "extended sequences" (pad | old kept entries by position | ring tokens | new tokens) that
-// the scoring, retention and attention launchers are then pointed at.
+// the retention and attention launchers are pointed at, and of the rows that still need a logit.
 struct AppendBuffers {
-  void* ext_k; void* ext_v;      // [total_ext][Hkv][D]
-  void* ext_kf;                  // the keys the scoring kernels read: ext_k, or a buffer of its own (rotary models)
-  float* ext_logits;             // [Hkv][total_ext]
-  const int32_t* cu_ext;         // [n_seqs + 1]
-  const int32_t* cu_score;       // [n_seqs + 1] packing handed to the scoring kernels (pad rows of sequences whose
-                                 // ring begins at position 0 are left out of them)
-  const int32_t* kv_start;       // first ring row of each sequence in the extended buffers
-  const int32_t* kv_len;         // ring + new tokens of each sequence
-  int32_t* local_pos;            // kept positions in the ring + new frame, [n_seqs][Hkv][budget]
-  int64_t total_ext;             // row count the buffers are sized for (an upper bound of cu_ext[n_seqs])
+  AppendPlan plan;
+  void* ext_k; void* ext_v;      // [plan.total_ext][Hkv][D]
+  void* score_k; void* score_v;  // [total_score][Hkv][D] packed by plan.cu_score
+  float* score_logits;           // [Hkv][total_score]
+  int64_t total_score;           // row count the scoring buffers are sized for (an upper bound of cu_score[n_seqs])
   int32_t max_ext_len;           // upper bound of one extended sequence
 };
 int64_t append_ext_tokens(const ltea_cfg& cfg, int n_seqs, int64_t total_new);
-size_t append_workspace(const ltea_cfg& cfg, int n_seqs, int64_t total_new, bool feature_keys);
+int64_t append_score_tokens(int n_seqs, int64_t total_new, int rho);
+size_t append_workspace(const ltea_cfg& cfg, int n_seqs, int64_t total_new, int rho);
 hipError_t launch_append_build(const ltea_cfg& cfg, const void* k_new, const void* v_new, const void* kf_new,
                                int64_t stride_tok, int64_t stride_head, const int32_t* cu_new, int n_seqs,
-                               int64_t total_new, int32_t max_new, const ltea_rope* rope, int32_t* status,
+                               int64_t total_new, int32_t max_new, int rho, const ltea_rope* rope, int32_t* status,
                                const ltea_cache& cache, void* workspace, AppendBuffers* out, hipStream_t stream);
-hipError_t launch_append_keys(const ltea_cfg& cfg, int n_seqs, int64_t total_new, const ltea_cache& cache, int rho,
-                              void* workspace, const AppendBuffers& buf, hipStream_t stream);
-hipError_t launch_append_fixup(const ltea_cfg& cfg, const int32_t* cu_new, int n_seqs, int64_t total_new,
-                               const ltea_cache& cache, int rho, void* workspace, hipStream_t stream);
 
 // ---- (d) decode step -------------------------------------------------------------------------------
 int decode_num_splits(const ltea_cfg& cfg, int n_seqs, bool scoring_inside);

@@ -10,6 +10,12 @@
 //   the compact segment.
 // Workgroups with blockIdx.y >= 1 copy the last min(n, window) tokens and their logits into the ring
 // (slot = position % window); that part does not depend on the selection and overlaps with it.
+//
+// The continuation of a prefill runs the same kernel over its extended sequences (append.hip): an element's key then
+// comes from the array of keys that were final before the call or from the fresh logits, by its true position, and kept
+// positions are written back as true positions.
+#include <type_traits>
+
 #include "ltea_common.h"
 #include "ltea_kernels.h"
 
@@ -56,6 +62,43 @@ struct RetainArgs {
   const char* k; const char* v; int64_t tok_bytes, head_bytes; int row_bytes;   // K/V views in bytes
   char* k_win; char* v_win; float* win_score; char* k_ret; char* v_ret;
   float* ret_score; int32_t* ret_pos; int32_t* ret_count; int32_t* n_seen; int32_t* n_scored;
+  AppendPlan plan;      // continuation only
+};
+
+// What element e of a sequence is.  A prefill's elements are its positions; an extended sequence of a continuation is
+// [pad | kept entries | ring | new tokens], with cu = plan.cu_ext and the fresh logits packed by plan.cu_score.
+template <bool APPEND> struct Elements;
+template <> struct Elements<false> {
+  const float* z;
+  __device__ Elements(const RetainArgs& a, int, int h, int64_t, int64_t lo, int) : z(a.logits + (int64_t)h * a.total + lo) {}
+  __device__ __forceinline__ float logit(int j) const { return z[j]; }
+  __device__ __forceinline__ bool is_sink(const RetainArgs& a, int j) const { return j < a.sink; }
+  __device__ __forceinline__ bool exists(int) const { return true; }
+  __device__ __forceinline__ int position(const RetainArgs&, int64_t, int j) const { return j; }
+  __device__ __forceinline__ int seen(int n) const { return n; }
+};
+template <> struct Elements<true> {
+  const float *key, *fresh;
+  int pad, prefix, shift, first_fresh, len;     // true position = element + shift from the prefix on
+  __device__ Elements(const RetainArgs& a, int b, int h, int64_t head, int64_t lo, int n) {
+    const int n_old = a.plan.n_old[b], w_old = a.plan.w_old[b];
+    prefix = a.plan.prefix[b];
+    pad = prefix - (a.budget > 0 ? a.ret_count[head] : 0);
+    shift = n_old - w_old - prefix;
+    first_fresh = n_old - a.rho - shift;
+    // fresh[e]: the scored rows begin with the last min(w_old, 2 rho) ring tokens
+    const int ctx = w_old < 2 * a.rho ? w_old : 2 * a.rho;
+    fresh = a.logits + (int64_t)h * a.total + a.plan.cu_score[b] - (prefix + w_old - ctx);
+    key = a.plan.ext_key + (int64_t)h * a.plan.total_ext + lo;
+    len = n;
+  }
+  __device__ __forceinline__ float logit(int j) const { return j >= first_fresh && j >= prefix ? fresh[j] : key[j]; }
+  __device__ __forceinline__ bool is_sink(const RetainArgs& a, int j) const { return j >= prefix && j + shift < a.sink; }
+  __device__ __forceinline__ bool exists(int j) const { return j >= pad; }
+  __device__ __forceinline__ int position(const RetainArgs& a, int64_t head, int j) const {
+    return j < prefix ? a.plan.sorted_pos[head * a.budget + (j - pad)] : j + shift;
+  }
+  __device__ __forceinline__ int seen(int n) const { return n + shift; }
 };
 
 // Copies one K row and one V row of row_bytes (a multiple of 16) in 16-byte pieces; piece index `pc`.
@@ -66,7 +109,7 @@ __device__ __forceinline__ void copy_piece(const RetainArgs& a, int64_t src_off,
 
 // CH > 0: the (sequence, head)'s out-of-window keys fit CH chunks and are held in registers;
 // CH == 0: any length, keys are re-read from memory in every pass.
-template <int CH>
+template <int CH, bool APPEND>
 __global__ void __launch_bounds__(kSelThreads)
 retain_kernel(const RetainArgs a) {
   __shared__ int scan_scratch[kSelWaves + 1];
@@ -78,7 +121,7 @@ retain_kernel(const RetainArgs a) {
   const int64_t lo = a.cu[b];
   const int n = (int)(a.cu[b + 1] - lo);
   const int64_t head = (int64_t)b * a.Hkv + h;
-  const float* z = a.logits + (int64_t)h * a.total + lo;
+  const Elements<APPEND> el(a, b, h, head, lo, n);
   const int pieces = a.row_bytes / 16;
 
   if (blockIdx.y > 0) {
@@ -95,7 +138,17 @@ retain_kernel(const RetainArgs a) {
         p = slot < n ? slot : -1;
       }
       if (p < 0) continue;
-      if (pc == 0) a.win_score[head * a.window + slot] = z[p];
+      if constexpr (APPEND) {
+        // fewer than `window` tokens so far (then nothing is kept and the whole prefix is pad): unused slots
+        if (p < el.prefix) {
+          if (pc == 0) a.win_score[head * a.window + slot] = __uint_as_float(0x7FC00000u);
+          const u32x4 zero4 = {0u, 0u, 0u, 0u};
+          reinterpret_cast<u32x4*>(a.k_win + (head * a.window + slot) * a.row_bytes)[pc] = zero4;
+          reinterpret_cast<u32x4*>(a.v_win + (head * a.window + slot) * a.row_bytes)[pc] = zero4;
+          continue;
+        }
+      }
+      if (pc == 0) a.win_score[head * a.window + slot] = el.logit(p);
       copy_piece(a, (lo + p) * a.tok_bytes + h * a.head_bytes, a.k_win + (head * a.window + slot) * a.row_bytes,
                  a.v_win + (head * a.window + slot) * a.row_bytes, pc);
     }
@@ -104,8 +157,9 @@ retain_kernel(const RetainArgs a) {
 
   const int n_out = n > a.window ? n - a.window : 0;
   if (h == 0 && tid == 0) {
-    a.n_seen[b] = n;
-    a.n_scored[b] = n > a.rho ? n - a.rho : 0;
+    const int seen = el.seen(n);
+    a.n_seen[b] = seen;
+    a.n_scored[b] = seen > a.rho ? seen - a.rho : 0;
   }
   if (a.budget == 0 || n_out == 0) {
     if (tid == 0) a.ret_count[head] = 0;
@@ -115,15 +169,18 @@ retain_kernel(const RetainArgs a) {
   // ---- keys: 0 = not a candidate (every candidate's order key is positive) ----
   auto fetch = [&](int j) -> uint32_t {
     if (j >= n_out) return 0u;
-    const float zj = z[j];
-    return ((j < a.sink) || (zj > a.tau)) ? order_key(select_key(zj, j, a.sink)) : 0u;
+    if (!el.exists(j)) return 0u;
+    if (el.is_sink(a, j)) return order_key(__uint_as_float(0x7F800000u));
+    const float zj = el.logit(j);
+    return zj > a.tau ? order_key(zj + 0.0f) : 0u;
   };
   constexpr int kHeld = CH > 0 ? CH : 1;
   uint32_t held[kHeld][kItems];
   if constexpr (CH > 0) {
     // a thread's four logits of a chunk are consecutive: one 16-byte load where the head's row allows it
     static_assert(kItems == 4, "one float4 per thread and chunk");
-    const bool quads = (reinterpret_cast<uintptr_t>(z) & 15u) == 0;
+    const float* z = a.logits + (int64_t)h * a.total + lo;
+    const bool quads = !APPEND && (reinterpret_cast<uintptr_t>(z) & 15u) == 0;
     auto key_of = [&](float zj, int j) -> uint32_t {
       return ((j < a.sink) || (zj > a.tau)) ? order_key(select_key(zj, j, a.sink)) : 0u;
     };
@@ -246,7 +303,8 @@ retain_kernel(const RetainArgs a) {
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
       if (keep[e]) {
-        a.ret_pos[head * a.budget + off] = j0 + e;
+        a.ret_pos[head * a.budget + off] = el.position(a, head, j0 + e);
+        if constexpr (APPEND) a.plan.local_pos[head * a.budget + off] = j0 + e - el.prefix;
         a.ret_score[head * a.budget + off] = key_of_order_key(u[e]);
         ++off;
       }
@@ -270,7 +328,8 @@ retain_kernel(const RetainArgs a) {
       const int ic = i < n_pieces ? i : i0;          // past the end: this thread's first piece once more, not stored
       r[u] = ic / pieces;
       pc[u] = ic - r[u] * pieces;
-      p[u] = a.ret_pos[head * a.budget + r[u]];
+      if constexpr (APPEND) p[u] = a.plan.local_pos[head * a.budget + r[u]] + el.prefix;
+      else p[u] = a.ret_pos[head * a.budget + r[u]];
     }
     u32x4 xk[kGather], xv[kGather];
 #pragma unroll
@@ -291,12 +350,13 @@ retain_kernel(const RetainArgs a) {
 
 }  // namespace
 
-hipError_t launch_retain(const ltea_cfg& cfg, const float* logits, const void* k, const void* v, int64_t stride_tok,
-                         int64_t stride_head, const SeqView& sv, int rho, const ltea_cache& c, hipStream_t stream) {
-  if (sv.n_seqs == 0) return hipSuccess;
+namespace {
+
+RetainArgs retain_args(const ltea_cfg& cfg, const float* logits, int64_t total, const int32_t* cu, const void* k, const void* v,
+                       int64_t stride_tok, int64_t stride_head, int rho, const ltea_cache& c) {
   const int64_t esz = cfg.dtype == LTEA_F32 ? 4 : 2;
   RetainArgs a;
-  a.logits = logits; a.total = sv.total_tokens; a.cu = sv.cu_seqlens; a.Hkv = cfg.Hkv; a.window = cfg.window;
+  a.logits = logits; a.total = total; a.cu = cu; a.Hkv = cfg.Hkv; a.window = cfg.window;
   a.budget = cfg.budget; a.sink = cfg.sink; a.tau = cfg.tau_logit; a.rho = rho;
   a.k = static_cast<const char*>(k); a.v = static_cast<const char*>(v);
   a.tok_bytes = stride_tok * esz; a.head_bytes = stride_head * esz; a.row_bytes = (int)(cfg.D * esz);
@@ -304,15 +364,40 @@ hipError_t launch_retain(const ltea_cfg& cfg, const float* logits, const void* k
   a.k_ret = static_cast<char*>(c.k_ret); a.v_ret = static_cast<char*>(c.v_ret);
   a.ret_score = c.ret_score; a.ret_pos = c.ret_pos; a.ret_count = c.ret_count; a.n_seen = c.n_seen;
   a.n_scored = c.n_scored;
-  const unsigned heads = (unsigned)sv.n_seqs * (unsigned)cfg.Hkv;
-  const dim3 grid(heads, 1u + (unsigned)((cfg.window + kRingRows - 1) / kRingRows));
-  const int64_t n_out_max = sv.max_seqlen > cfg.window ? sv.max_seqlen - cfg.window : 0;
-  if (n_out_max <= 1 * kChunk) hipLaunchKernelGGL(retain_kernel<1>, grid, dim3(kSelThreads), 0, stream, a);
-  else if (n_out_max <= 2 * kChunk) hipLaunchKernelGGL(retain_kernel<2>, grid, dim3(kSelThreads), 0, stream, a);
-  else if (n_out_max <= 4 * kChunk) hipLaunchKernelGGL(retain_kernel<4>, grid, dim3(kSelThreads), 0, stream, a);
-  else if (n_out_max <= 8 * kChunk) hipLaunchKernelGGL(retain_kernel<8>, grid, dim3(kSelThreads), 0, stream, a);
-  else hipLaunchKernelGGL(retain_kernel<0>, grid, dim3(kSelThreads), 0, stream, a);
+  a.plan = AppendPlan{};
+  return a;
+}
+
+template <bool APPEND>
+hipError_t run(const RetainArgs& a, int n_seqs, int64_t longest, hipStream_t stream) {
+  const dim3 grid((unsigned)n_seqs * (unsigned)a.Hkv, 1u + (unsigned)((a.window + kRingRows - 1) / kRingRows));
+  const int64_t n_out_max = longest > a.window ? longest - a.window : 0;
+  auto go = [&](auto ch) {
+    hipLaunchKernelGGL((retain_kernel<decltype(ch)::value, APPEND>), grid, dim3(kSelThreads), 0, stream, a);
+  };
+  if (n_out_max <= 1 * kChunk) go(std::integral_constant<int, 1>{});
+  else if (n_out_max <= 2 * kChunk) go(std::integral_constant<int, 2>{});
+  else if (n_out_max <= 4 * kChunk) go(std::integral_constant<int, 4>{});
+  else if (n_out_max <= 8 * kChunk) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 0>{});
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_retain(const ltea_cfg& cfg, const float* logits, const void* k, const void* v, int64_t stride_tok,
+                         int64_t stride_head, const SeqView& sv, int rho, const ltea_cache& c, hipStream_t stream) {
+  if (sv.n_seqs == 0) return hipSuccess;
+  const RetainArgs a = retain_args(cfg, logits, sv.total_tokens, sv.cu_seqlens, k, v, stride_tok, stride_head, rho, c);
+  return run<false>(a, sv.n_seqs, sv.max_seqlen, stream);
+}
+
+hipError_t launch_retain_append(const ltea_cfg& cfg, const AppendBuffers& buf, int n_seqs, int rho, const ltea_cache& c,
+                                hipStream_t stream) {
+  RetainArgs a = retain_args(cfg, buf.score_logits, buf.total_score, buf.plan.cu_ext, buf.ext_k, buf.ext_v,
+                             (int64_t)cfg.Hkv * cfg.D, cfg.D, rho, c);
+  a.plan = buf.plan;
+  return run<true>(a, n_seqs, buf.max_ext_len, stream);
 }
 
 }  // namespace ltea
