@@ -151,7 +151,7 @@ __device__ __forceinline__ int eviction_target(int t, int window, int budget, in
   const uint32_t worst_u = (uint32_t)(best >> 32);
   const int worst_pos = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));
   for (int r = tid; r < budget; r += kThreads)
-    if (ret_pos[r] == worst_pos) *slot_out = r;  // positions are unique
+    if (ret_pos[r] == worst_pos) atomicMax(slot_out, r);  // positions are unique; a caller's duplicates stay deterministic
   __syncthreads();
   const int victim = *slot_out;
   return order_key(select_key(z_e, e_pos, sink)) > worst_u ? victim : -1;
@@ -464,13 +464,43 @@ decode_windows_kernel(CacheDev C, const T* __restrict__ k_new, const T* __restri
                        row_valid, (int)blockIdx.x);
 }
 
+// ---- attention role for grouped queries (bf16): up to 16 query heads of a KV group per pass, on MFMA -----------------
+// One wave takes 32 ring slots or 32 compact slots at a time, every fourth block of the workgroup's share:
+//   S^T[row, head] = K . Q^T     v_mfma_f32_16x16x32_bf16, K rows straight from global memory into the A operand (a lane
+//                                holds 8 columns of one row), Q as the B operand (heads past the group are zeros)
+//   O^T[d, head] += V^T . P^T    V rows pass through 32 rows of LDS of the wave's own (no barrier: a wave's LDS operations
+//                                are in order) and come back transposed (ds_read_b64_tr_b16); P goes from the
+//                                accumulator registers of S^T into the B operand, as a bf16 hi + lo pair in two MFMAs, so
+//                                that the probabilities keep 16 bits of mantissa
+// In the accumulators a lane owns one head (lane % 16) and four rows per tile, so the softmax state is per lane.  The next
+// 32 rows are in flight from memory during this block.  Bound: HBM.  With fp32 VALU products instead (one row per 8
+// lanes, four heads) the paper's layer at B = 32 took 22.9 us for 84 MB of rows: the unpacking, the four dot products and
+// their shuffles were as much VALU time as the rows' flight.
+template <int D> struct MfmaStream {
+  static constexpr int QK = D / 32;              // matrix instructions over the head dimension, per 16 rows
+  static constexpr int DT = D / 16;              // output tiles
+  static constexpr int RPI = 64 / (D / 8);       // rows per wave load instruction of V
+  static constexpr int NV = 32 / RPI;
+  static constexpr int kTile = 32 * D;           // LDS elements per wave
+  struct Rows { u32x4 k[2][QK]; u32x4 v[NV]; };
+  // 32-byte chunk c of row r sits at chunk c ^ swz(r): eight consecutive rows of one chunk then cover all 64 banks
+  static __device__ __forceinline__ int swz(int r) { return D == 64 ? (r >> 1) & 3 : r & 7; }
+};
+
+__device__ __forceinline__ u32x2 read_transposed4(const bf16_t* p) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p)));
+}
+
 // Partial record per (sequence, query head, split): [max, sum, acc[D]] floats.
-// GT = query heads of a KV group handled per pass over the rows (1, 2 or 4): every K/V row is loaded once per pass
-// and used for GT queries, so grouped-query configurations do not re-stream the cache once per query head.
+// GT = query heads of a KV group handled per pass over the rows: every K/V row is loaded once per pass and used for GT
+// queries, so grouped-query configurations do not re-stream the cache once per query head.  1, 2 or 4 on the VALU (fp32
+// storage, and bf16 with one query head per KV head); 0: up to 16 on MFMA (bf16).
 // SK = kernel size of the batched MFMA scoring role compiled into this instance (3, 5 or 7), 0 for none: the role's
 // register needs grow with the kernel size, and one instance holding all three would carry the largest one's spills.
 template <typename T, int D, int GT, int SK>
-__global__ void __launch_bounds__(kThreads, 4)
+__global__ void __launch_bounds__(kThreads, GT == 0 && D == 128 ? 2 : 4)
 decode_main_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q, const T* __restrict__ k_new,
                    const T* __restrict__ v_new, float* __restrict__ partial, float* __restrict__ ws_logit,
                    int32_t* __restrict__ ws_t, int32_t* __restrict__ ws_dst) {
@@ -479,8 +509,10 @@ decode_main_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   constexpr int GPW = kWave / LPR;  // row groups per wave
   constexpr int GPB = GPW * kWaves;
   extern __shared__ float dyn_lds[];  // per-head scoring role: two activation buffers of (2*rho+1) rows
-  __shared__ float red_m[kWaves][GPW], red_l[kWaves][GPW];
-  __shared__ float red_acc[kWaves][GPW][D];
+  constexpr int kRows = GT == 0 ? 16 : GPW;   // merge rows per wave: query heads (MFMA), row groups (VALU)
+  __shared__ float red_m[kWaves][kRows], red_l[kWaves][kRows];
+  // merge of the waves; before that the wave-private V tiles of the MFMA stream, or the scoring role's sums
+  __shared__ __align__(16) float red_acc[kWaves][kRows][D];
   __shared__ unsigned long long red64[kWaves];
   __shared__ int slot_lds;
 
@@ -527,7 +559,8 @@ decode_main_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const T* kw = static_cast<const T*>(C.k_win) + head * window * D;
   const T* vw = static_cast<const T*>(C.v_win) + head * window * D;
   const int G = P.Hq / Hkv;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int sub = lane % LPR, grp = lane / LPR;
   const T* kr = static_cast<const T*>(C.k_ret) + head * budget * D;
   const T* vr = static_cast<const T*>(C.v_ret) + head * budget * D;
@@ -542,8 +575,12 @@ decode_main_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const int chunk = (window + budget + nsplit - 1) / nsplit;
   const int r_begin = split * chunk;
   const int r_end = r_begin + chunk < window + budget ? r_begin + chunk : window + budget;
+  // MFMA stream: shares are whole blocks of 32 ring slots or 32 compact slots
+  const int ring_blocks = (window + 31) / 32, all_blocks = ring_blocks + (budget + 31) / 32;
+  const int blk_chunk = (all_blocks + nsplit - 1) / nsplit, blk_begin = split * blk_chunk;
+  const int blk_end = blk_begin + blk_chunk < all_blocks ? blk_begin + blk_chunk : all_blocks;
   int dst = -1, cnt = 0;
-  if (r_end > window && budget > 0) {   // uniform across the workgroup
+  if ((GT == 0 ? blk_end > ring_blocks : r_end > window) && budget > 0) {   // uniform across the workgroup
     const int cnt_old = C.ret_count[head];
     const float z_e = t >= window ? C.win_score[head * window + slot] : 0.f;
     dst = eviction_target(t, window, budget, P.sink, P.tau, cnt_old, z_e, C.ret_score + head * budget,
@@ -555,6 +592,157 @@ decode_main_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const T* k_evicted = kw + (int64_t)slot * D;  // old ring row that moves to compact slot dst
   const T* v_evicted = vw + (int64_t)slot * D;
 
+  if constexpr (GT == 0) {
+    using MS = MfmaStream<D>;
+    static_assert(sizeof(red_acc) >= kWaves * MS::kTile * sizeof(bf16_t), "the V tiles of the four waves");
+    const int kg = lane >> 4, c16 = lane & 15;
+    bf16_t* vt = reinterpret_cast<bf16_t*>(&red_acc[0][0][0]) + wave * MS::kTile;
+    const float scale2 = P.scale * 1.4426950408889634f;
+    // V: this lane's row of an instruction and its 16-byte piece
+    const int v_row = lane / (D / 8), v_piece = lane % (D / 8);
+    // V^T operand: 16 lanes point at a 4-row x 16-column block; rows 4*kg.. of either half
+    const int tr_row = 4 * kg + (c16 >> 2);
+    const bf16_t* v_src = vt + tr_row * D + 4 * (lane & 3);
+    const uint32_t k_off = (uint32_t)(c16 * D + 8 * kg) * 2u, v_off = (uint32_t)(v_row * D + 8 * v_piece) * 2u;
+    for (int g0 = 0; g0 < G; g0 += 16) {
+      const int heads_here = G - g0 < 16 ? G - g0 : 16;
+      bf16x8 qf[MS::QK];
+#pragma unroll
+      for (int i = 0; i < MS::QK; ++i) {
+        const int hq = c16 < heads_here ? c16 : 0;
+        u32x4 x = *reinterpret_cast<const u32x4*>(q + ((int64_t)b * P.Hq + h * G + g0 + hq) * D + 32 * i + 8 * kg);
+        if (c16 >= heads_here) x = u32x4{0u, 0u, 0u, 0u};
+        qf[i] = __builtin_bit_cast(bf16x8, x);
+      }
+      // rows of block `blk`: ring or compact slots row0 .., `n_live` of them real (the others read as zeros)
+      auto where = [&](int blk, bool& ring, int& row0, int& n_live) {
+        ring = blk < ring_blocks;
+        row0 = 32 * (ring ? blk : blk - ring_blocks);
+        const int left = (ring ? n_valid : cnt) - row0;
+        n_live = left < 0 ? 0 : (left < 32 ? left : 32);
+      };
+      auto load = [&](int blk, typename MS::Rows& R) {
+        bool ring;
+        int row0, n_live;
+        where(blk, ring, row0, n_live);
+        const uint32_t bytes = (uint32_t)n_live * (uint32_t)(D * 2);
+        const auto rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>((ring ? kw : kr) + (int64_t)row0 * D), 0, bytes, 0x00020000);
+        const auto rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>((ring ? vw : vr) + (int64_t)row0 * D), 0, bytes, 0x00020000);
+        constexpr int kNonTemporal = 2;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < MS::QK; ++i)
+            R.k[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off + (uint32_t)(16 * j * D + 32 * i) * 2u, 0, kNonTemporal);
+#pragma unroll
+        for (int i = 0; i < MS::NV; ++i)
+          R.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off + (uint32_t)(MS::RPI * i * D) * 2u, 0, kNonTemporal);
+        // the one row whose contents after this step are somewhere else: the incoming token's, or the evicted one's
+        const int special = (ring ? slot : dst) - row0;      // dst = -1: none
+        if (special >= 0 && special < 32 && (ring || dst >= 0)) {
+          const T* ks = ring ? kn : k_evicted;
+          const T* vs = ring ? vn : v_evicted;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            if (16 * j + c16 == special) {
+#pragma unroll
+              for (int i = 0; i < MS::QK; ++i) R.k[j][i] = *reinterpret_cast<const u32x4*>(ks + 32 * i + 8 * kg);
+            }
+#pragma unroll
+          for (int i = 0; i < MS::NV; ++i)
+            if (MS::RPI * i + v_row == special) R.v[i] = *reinterpret_cast<const u32x4*>(vs + 8 * v_piece);
+        }
+      };
+      float m_run = -INFINITY, l_run = 0.f;
+      f32x4 o[MS::DT];
+#pragma unroll
+      for (int d = 0; d < MS::DT; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+      typename MS::Rows cur;
+      if (blk_begin + wave < blk_end) load(blk_begin + wave, cur);
+      for (int blk = blk_begin + wave; blk < blk_end; blk += kWaves) {
+        f32x4 sc[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < MS::QK; ++i)
+            sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.k[j][i]), qf[i], sc[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < MS::NV; ++i) {
+          const int r = MS::RPI * i + v_row;
+          *reinterpret_cast<u32x4*>(vt + r * D + (((v_piece >> 1) ^ MS::swz(r)) << 4) + (v_piece & 1) * 8) = cur.v[i];
+        }
+        if (blk + kWaves < blk_end) load(blk + kWaves, cur);
+        bool ring;
+        int row0, n_live;
+        where(blk, ring, row0, n_live);
+        float m_new = m_run;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            sc[j][r] = 16 * j + 4 * kg + r < n_live ? sc[j][r] * scale2 : -INFINITY;
+            m_new = fmaxf(m_new, sc[j][r]);
+          }
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 16, kWave));
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 32, kWave));
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;    // nothing live yet: every factor below is 0
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+        m_run = m_new;
+        l_run *= alpha;
+        bf16x8 hi, lo;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float p = __builtin_amdgcn_exp2f(sc[j][r] - m_use);
+            l_run += p;
+            hi[4 * j + r] = static_cast<bf16_t>(p);
+            lo[4 * j + r] = static_cast<bf16_t>(p - to_f32(hi[4 * j + r]));
+          }
+#pragma unroll
+        for (int d = 0; d < MS::DT; ++d) {
+          const u32x2 a0 = read_transposed4(v_src + ((d ^ MS::swz(tr_row)) << 4));
+          const u32x2 a1 = read_transposed4(v_src + 16 * D + ((d ^ MS::swz(tr_row)) << 4));
+          const bf16x8 av = __builtin_bit_cast(bf16x8, u32x4{a0[0], a0[1], a1[0], a1[1]});
+          o[d] *= alpha;
+          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, hi, o[d], 0, 0, 0);
+          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, lo, o[d], 0, 0, 0);
+        }
+      }
+      // merge of the waves, fixed order; register r of o[d] is column 16*d + 4*kg + r of head g0 + c16
+      l_run += __shfl_xor(l_run, 16, kWave);
+      l_run += __shfl_xor(l_run, 32, kWave);
+      __syncthreads();      // every wave is done with its V tile
+      if (c16 < heads_here) {
+        if (kg == 0) { red_m[wave][c16] = m_run; red_l[wave][c16] = l_run; }
+#pragma unroll
+        for (int d = 0; d < MS::DT; ++d) *reinterpret_cast<f32x4*>(&red_acc[wave][c16][16 * d + 4 * kg]) = o[d];
+      }
+      __syncthreads();
+      for (int item = threadIdx.x; item < heads_here * D; item += kThreads) {
+        const int g = item / D, d = item - g * D;
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, red_m[w][g]);
+        float L = 0.f, A = 0.f;
+        if (M != -INFINITY) {
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) {
+            const float f = __builtin_amdgcn_exp2f(red_m[w][g] - M);
+            L = fmaf(red_l[w][g], f, L);
+            A = fmaf(red_acc[w][g][d], f, A);
+          }
+        }
+        float* rec = partial + (((int64_t)b * P.Hq + h * G + g0 + g) * nsplit + split) * (D + 2);
+        if (d == 0) { rec[0] = M * 0.6931471805599453f; rec[1] = L; }      // records hold natural-log maxima
+        rec[2 + d] = A;
+      }
+      __syncthreads();
+    }
+    return;
+  } else {
   constexpr int RIF = GT >= 4 ? 2 : kRowsInFlight;   // rows in flight per lane group (registers: GT states per lane)
   for (int g0 = 0; g0 < G; g0 += GT) {
     float qf[GT][EPL];
@@ -661,6 +849,7 @@ decode_main_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       }
       __syncthreads();
     }
+  }
   }
 }
 
@@ -890,9 +1079,15 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const void* q, 
                        static_cast<const T*>(v), partial, ws_logit, ws_t, ws_dst);
   };
   auto launch_gt = [&](auto sk) {
-    if (G % 4 == 0) launch_main(std::integral_constant<int, 4>{}, sk);
-    else if (G % 2 == 0) launch_main(std::integral_constant<int, 2>{}, sk);
-    else launch_main(std::integral_constant<int, 1>{}, sk);
+    if constexpr (sizeof(T) == 2) {
+      // one query head leaves 15 of the 16 matrix columns idle and streams as fast on the VALU
+      if (G > 1) launch_main(std::integral_constant<int, 0>{}, sk);
+      else launch_main(std::integral_constant<int, 1>{}, sk);
+    } else {
+      if (G % 4 == 0) launch_main(std::integral_constant<int, 4>{}, sk);
+      else if (G % 2 == 0) launch_main(std::integral_constant<int, 2>{}, sk);
+      else launch_main(std::integral_constant<int, 1>{}, sk);
+    }
   };
   const int sk_run = (P.pre_logits == nullptr && !lazy) ? P.score_mfma : 0;
   if constexpr (sizeof(T) == 2) {
