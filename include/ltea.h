@@ -124,9 +124,8 @@ size_t ltea_workspace_bytes(const ltea_cfg *cfg, const ltea_cnn *cnn, int32_t n_
                             int32_t max_seqlen);
 
 /* Bytes of device workspace ltea_decode_step needs for n_seqs sequences (contents need no initialisation
- * and need not be preserved between steps).  With `cnn` given the size also covers the faster scoring path of
- * multi-layer bf16 CNNs (receptive-field windows of the whole batch packed and scored by the fused prefill kernel);
- * with cnn == NULL, or a smaller workspace passed to ltea_decode_step, that CNN is scored per (sequence, head). */
+ * and need not be preserved between steps).  With `cnn` given the size also covers CNNs that the step's own launch
+ * cannot hold (see ltea_decode_step); every other CNN runs with the size that cnn == NULL reports. */
 size_t ltea_decode_workspace_bytes(const ltea_cfg *cfg, const ltea_cnn *cnn, int32_t n_seqs);
 
 /* (a) Scoring (Section 3.1.1): logits[h][t] for every packed token t and KV
@@ -204,7 +203,9 @@ int ltea_prefill_feat(const ltea_cfg *cfg, const ltea_cnn *cnn, const void *q, i
  * the same workspace race.  A CNN whose per-step activation rows, 2 * (2*rho+1) *
  * max(2*D, widest layer) floats, exceed 48 KB of LDS is scored through the prefill
  * kernels instead (as ltea_decode_step_feat does): that needs the workspace
- * ltea_decode_workspace_bytes(cfg, cnn, n_seqs) reports, LTEA_EWORKSPACE otherwise. */
+ * ltea_decode_workspace_bytes(cfg, cnn, n_seqs) reports, LTEA_EWORKSPACE otherwise.
+ * ret_count holds at most `budget` on entry and on return; while a step runs its upper bits count the workgroups that
+ * are done, so nothing else may read it then. */
 int ltea_decode_step(const ltea_cfg *cfg, const ltea_cnn *cnn, const void *q, const void *k, const void *v,
                      void *out, const ltea_cache *cache, int32_t n_seqs, void *workspace, size_t workspace_bytes,
                      void *stream);
@@ -288,7 +289,7 @@ int ltea_rescore(const ltea_cfg *cfg, const ltea_cnn *cnn, const ltea_rope *rope
  * rotated back at position t.  k, the rotated key, is what is cached and attended.  Same state and outputs as
  * ltea_decode_step_lazy followed by ltea_rescore after every step.  rope == NULL scores the keys as they are (then
  * k_feat must be NULL too).  status_or_null receives LTEA_ROPE_RANGE.  Works for every CNN shape ltea_score
- * accepts (the windows are packed and scored by the prefill kernels: three more launches than ltea_decode_step).
+ * accepts (those that ltea_decode_step scores through the prefill kernels take three launches here as well).
  * Workspace: ltea_decode_feat_workspace_bytes. */
 size_t ltea_decode_feat_workspace_bytes(const ltea_cfg *cfg, const ltea_cnn *cnn, int32_t n_seqs);
 int ltea_decode_step_feat(const ltea_cfg *cfg, const ltea_cnn *cnn, const ltea_rope *rope_or_null, const void *q,

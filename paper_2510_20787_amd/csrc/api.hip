@@ -185,13 +185,6 @@ size_t ltea_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_
   return bytes;
 }
 
-// The per-(sequence, head) scoring of the eager step keeps two generations of (2 rho + 1) activation rows in LDS.
-static bool decode_pyramid_fits(const ltea_cfg* cfg, const ltea_cnn* cnn) {
-  int row_floats = 2 * cfg->D;
-  for (int l = 0; l < cnn->n_layers; ++l) row_floats = cnn->c_out[l] > row_floats ? cnn->c_out[l] : row_floats;
-  return (size_t)2 * (2 * cnn_rho(cnn) + 1) * row_floats * sizeof(float) <= 48 * 1024;
-}
-
 static size_t decode_scored_workspace(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_seqs) {
   const int rho = cnn_rho(cnn);
   return align_up(decode_workspace(*cfg, n_seqs), 256) + align_up(decode_windows_layout(*cfg, rho, n_seqs, nullptr, nullptr), 256) +
@@ -201,11 +194,12 @@ static size_t decode_scored_workspace(const ltea_cfg* cfg, const ltea_cnn* cnn, 
 size_t ltea_decode_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_seqs) {
   if (check_cfg(cfg) != LTEA_OK || n_seqs < 0) return 0;
   if (cnn && check_cnn(cfg, cnn) != LTEA_OK) return 0;
-  if (!cnn) return align_up(decode_workspace(*cfg, n_seqs), 256);
-  const size_t full = align_up(decode_workspace_full(*cfg, *cnn, n_seqs), 256);
-  if (decode_pyramid_fits(cfg, cnn)) return full;
-  const size_t scored = decode_scored_workspace(cfg, cnn, n_seqs);   // such CNNs are scored through the prefill kernels
-  return scored > full ? scored : full;
+  // CNNs that the step's own launch cannot hold are scored through the prefill kernels
+  const size_t step = align_up(decode_workspace(*cfg, n_seqs), 256);
+  if (!cnn) return step;
+  // the size for a stack stays above the minimum, which callers compare it with
+  if (decode_scores_inside(*cfg, *cnn)) return step + (cnn->n_layers > 1 ? 256 : 0);
+  return decode_scored_workspace(cfg, cnn, n_seqs);
 }
 
 int ltea_score(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* k, const void* v, int64_t stride_tok,
@@ -406,13 +400,13 @@ int ltea_decode_step(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* q, co
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(out)) return LTEA_EINVAL;
   // A CNN whose per-step activation rows do not fit LDS goes through the packed-window path (needs the workspace
   // ltea_decode_workspace_bytes(cfg, cnn, n_seqs) reports for it).
-  if (!decode_pyramid_fits(cfg, cnn))
+  if (!decode_scores_inside(*cfg, *cnn))
     return ltea_decode_step_feat(cfg, cnn, nullptr, q, k, v, nullptr, out, cache, n_seqs, nullptr, workspace,
                                  workspace_bytes, stream);
   const size_t need = align_up(decode_workspace(*cfg, n_seqs), 256);
   if (!workspace || workspace_bytes < need) return LTEA_EWORKSPACE;
   if (workspace && !aligned256(workspace)) return LTEA_EINVAL;
-  return hip_status(launch_decode_step(*cfg, *cnn, q, k, v, out, *cache, n_seqs, workspace, workspace_bytes,
+  return hip_status(launch_decode_step(*cfg, *cnn, nullptr, q, k, v, nullptr, out, *cache, n_seqs, nullptr, workspace,
                                        static_cast<hipStream_t>(stream)));
 }
 
@@ -487,6 +481,8 @@ int ltea_decode_step_feat(const ltea_cfg* cfg, const ltea_cnn* cnn, const ltea_r
   if (!workspace || workspace_bytes < step_ws + win_ws + score_workspace(*cfg, *cnn, rows)) return LTEA_EWORKSPACE;
   if (workspace && !aligned256(workspace)) return LTEA_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (decode_scores_inside(*cfg, *cnn))
+    return hip_status(launch_decode_step(*cfg, *cnn, rope, q, k, v, k_feat, out, *cache, n_seqs, status, workspace, s));
   char* base = static_cast<char*>(workspace);
   DecodeWindows w;
   decode_windows_layout(*cfg, rho, n_seqs, base + step_ws, &w);

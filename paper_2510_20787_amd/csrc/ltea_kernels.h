@@ -67,18 +67,15 @@ bool score_deep_reg_supported(const ltea_cfg& cfg, const ltea_cnn& cnn);
 // kernel; that needs the three tensors 16-byte aligned.
 bool score_deep_reg_takes_raw_weights(const ltea_cnn& cnn);
 hipError_t launch_score_deep_reg_panels(const ltea_cfg& cfg, const ltea_cnn& cnn, void* panels, hipStream_t stream);
-// row_valid (optional, device, one byte per token row): windows mode for the decode step.  The rows are many
-// independent short windows laid end to end with at least max(dilation) rows of zeros between them; a 0 byte marks a
-// row that is not a token, whose activations are then zero at every layer, as outside a sequence.
 hipError_t launch_score_deep_reg(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v,
                                  int64_t stride_tok, int64_t stride_head, const SeqView& sv, float* logits,
-                                 const void* panels, hipStream_t stream, const uint8_t* row_valid = nullptr);
+                                 const void* panels, hipStream_t stream);
 bool score_deep_supported(const ltea_cfg& cfg, const ltea_cnn& cnn);
 size_t score_deep_workspace(const ltea_cfg& cfg, const ltea_cnn& cnn);
 hipError_t launch_score_deep_panels(const ltea_cfg& cfg, const ltea_cnn& cnn, void* panels, hipStream_t stream);
 hipError_t launch_score_deep(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v,
                              int64_t stride_tok, int64_t stride_head, const SeqView& sv, float* logits,
-                             void* workspace, hipStream_t stream, const uint8_t* row_valid = nullptr);
+                             void* workspace, hipStream_t stream);
 
 // ---- (b) retention + cache fill -------------------------------------------------------------------
 hipError_t launch_retain(const ltea_cfg& cfg, const float* logits, const void* k, const void* v,
@@ -127,14 +124,16 @@ hipError_t launch_append_build(const ltea_cfg& cfg, const void* k_new, const voi
                                const ltea_cache& cache, void* workspace, AppendBuffers* out, hipStream_t stream);
 
 // ---- (d) decode step -------------------------------------------------------------------------------
-int decode_num_splits(const ltea_cfg& cfg, int n_seqs, bool scoring_inside);
-size_t decode_workspace(const ltea_cfg& cfg, int n_seqs);                               // minimum
-size_t decode_workspace_full(const ltea_cfg& cfg, const ltea_cnn& cnn, int n_seqs);     // enables every path
-hipError_t launch_decode_step(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* q, const void* k, const void* v,
-                              void* out, const ltea_cache& cache, int n_seqs, void* workspace, size_t workspace_bytes,
-                              hipStream_t stream);
+int decode_num_splits(const ltea_cfg& cfg, int n_seqs);
+size_t decode_workspace(const ltea_cfg& cfg, int n_seqs);
+// Whether the step's launch itself can run this CNN (its activation rows fit LDS beside the stream).
+bool decode_scores_inside(const ltea_cfg& cfg, const ltea_cnn& cnn);
+// rope, k_feat, status (all optional): rotary models, whose ring keys are rotated back for the scoring.
+hipError_t launch_decode_step(const ltea_cfg& cfg, const ltea_cnn& cnn, const ltea_rope* rope, const void* q, const void* k,
+                              const void* v, const void* k_feat, void* out, const ltea_cache& cache, int n_seqs,
+                              int32_t* status, void* workspace, hipStream_t stream);
 
-// Eager step of a rotary model in three parts: the receptive-field windows of the tokens being finalised are packed
+// The eager step of other CNNs in three parts: the receptive-field windows of the tokens being finalised are packed
 // (ring keys rotated back, the incoming key from k_feat or rotated back too), any prefill scoring launcher runs over
 // them (2 * n_seqs pseudo-sequences `cu2`, rows of [Hkv][D]), and the step proper picks its logits from `logits`.
 struct DecodeWindows {

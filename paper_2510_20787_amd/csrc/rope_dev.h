@@ -58,12 +58,22 @@ __device__ __forceinline__ u32x4 unrotate_piece(const RopeDev& rope, int p, int 
   const int half = rope.rot_dim / 2;
   const float* ct = rope.cos + (int64_t)p * half;
   const float* st = rope.sin + (int64_t)p * half;
+  // table entries in 16-byte loads (the tables are only known to be 4-byte aligned)
+  typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+  typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
   float x[EPP], y[EPP];
   Elems<T>::unpack(piece, x);
   if (rope.interleaved) {
+    float cs[EPP / 2], sn[EPP / 2];
+#pragma unroll
+    for (int j = 0; j < EPP / 2; j += 2) {
+      const f32x2_any c2 = *reinterpret_cast<const f32x2_any*>(ct + e0 / 2 + j);
+      const f32x2_any s2 = *reinterpret_cast<const f32x2_any*>(st + e0 / 2 + j);
+      cs[j] = c2[0]; cs[j + 1] = c2[1]; sn[j] = s2[0]; sn[j + 1] = s2[1];
+    }
 #pragma unroll
     for (int j = 0; j < EPP; j += 2) {
-      const float c = ct[(e0 + j) / 2], s = st[(e0 + j) / 2];
+      const float c = cs[j / 2], s = sn[j / 2];
       y[j] = fmaf(x[j + 1], s, x[j] * c);
       y[j + 1] = fmaf(x[j + 1], c, -(x[j] * s));
     }
@@ -73,9 +83,17 @@ __device__ __forceinline__ u32x4 unrotate_piece(const RopeDev& rope, int p, int 
     float o[EPP];
     Elems<T>::unpack(*reinterpret_cast<const u32x4*>(row + partner), o);
     const int i0 = is_b ? e0 - half : e0;
+    float cs[EPP], sn[EPP];
+#pragma unroll
+    for (int j = 0; j < EPP; j += 4) {
+      const f32x4_any c4 = *reinterpret_cast<const f32x4_any*>(ct + i0 + j);
+      const f32x4_any s4 = *reinterpret_cast<const f32x4_any*>(st + i0 + j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { cs[j + i] = c4[i]; sn[j + i] = s4[i]; }
+    }
 #pragma unroll
     for (int j = 0; j < EPP; ++j) {
-      const float c = ct[i0 + j], s = st[i0 + j];
+      const float c = cs[j], s = sn[j];
       y[j] = is_b ? fmaf(x[j], c, -(o[j] * s)) : fmaf(o[j], s, x[j] * c);
     }
   }
