@@ -168,8 +168,19 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without building a torch.cuda.Stream object around it: 0.2 us instead of 2.9 us, in calls that
+# take 4 us otherwise.
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream, _cuda_getDevice as _device
+except ImportError:             # a torch without them (or without a GPU build)
+    _raw_stream = None
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    torch.cuda._lazy_init()
+    return _raw_stream(_device())
 
 
 def torch_dtype(dtype: str) -> torch.dtype:
