@@ -33,6 +33,7 @@
 #include "ltea_common.h"
 #include "ltea_kernels.h"
 #include "mfma_tiles.h"
+#include "score_dma.h"
 
 namespace ltea {
 namespace {
@@ -43,20 +44,17 @@ constexpr float kBig = 1.8446744e19f;  // 2^64: a row sum above this (or not a n
 
 template <int D, int QB> struct Geo {
   static constexpr int BM = 128 * QB;           // queries per workgroup
-  static constexpr int KS = D + 8;              // K tile row stride (elements); 16-byte pad
-  static constexpr int VS = D;                  // V tile row stride (elements): unpadded, 64-byte chunks swizzled
-  static constexpr int PPR = D / 8;             // 16-byte pieces per K row
-  static constexpr int RPP = kThreads / PPR;    // K rows per pass
-  static constexpr int KPASS = BN / RPP;        // passes over the K tile
+  static constexpr int PPR = D / 8;             // 16-byte pieces per row
+  static constexpr int RPI = 64 / PPR;          // rows per wave load instruction
+  static constexpr int IPW = BN / RPI / 4;      // load instructions per wave, K tile and V tile each
   static constexpr int OS = D + 8;              // epilogue staging row stride (elements)
-  static constexpr int kBuf = BN * KS + BN * VS; // elements per LDS tile buffer (K tile then V tile)
+  static constexpr int kTile = BN * D;          // elements of one tile; K tile then V tile per buffer, rows unpadded
+  static constexpr int kBuf = 2 * kTile;
 };
 
-template <int D> struct TileRegs {
-  u32x4 k[BN / (kThreads / (D / 8))];
-  u32x4 v[BN / (kThreads / (D / 8))];
-  int pos;
-};
+// Which 16-byte piece of its row a K tile row keeps at slot p (p ^ term): the row reads of 16 consecutive lanes (16 rows at
+// one piece) then cover all 64 banks.
+template <int D> __device__ __forceinline__ int piece_swizzle(int row) { return D == 64 ? ((row >> 1) & 7) : (row & 15); }
 
 // HW = query heads per workgroup.  1: the four waves take four consecutive blocks of 32 query positions of one head.
 // 4 (grouped-query shapes with a multiple of four query heads per KV head): the four waves take the SAME 32 positions
@@ -74,13 +72,12 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
                       bf16_t* __restrict__ out, const int32_t* __restrict__ kv_start,
                       const int32_t* __restrict__ kv_len, float* __restrict__ lse, int64_t lse_stride) {
   using G = Geo<D, QB>;
-  using TR = TileRegs<D>;
-  constexpr int BM = G::BM, KS = G::KS, VS = G::VS, kBuf = G::kBuf;
+  constexpr int BM = G::BM, kBuf = G::kBuf, kTile = G::kTile;
   constexpr int BMQ = BM / HW;     // query positions per workgroup (BM = rows of all its waves)
   static_assert(HW == 1 || HW == 4, "one head, or one head per wave");
   static_assert(2 * kBuf >= BM * G::OS, "epilogue staging must fit in the tile buffers");
-  __shared__ __align__(16) bf16_t lds[2 * kBuf];
-  __shared__ int pos_lds[2][BN];
+  __shared__ __align__(1024) bf16_t lds[2 * kBuf];
+  __shared__ __align__(256) int pos_lds[2][BN];
   __shared__ int redo_flag;
 
   // ---- which (query head, sequence, query tile) is this workgroup? ------------------------------------
@@ -155,60 +152,47 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   const uint32_t row_bytes = (uint32_t)kv_st * 2u;
   const uint32_t win_bytes = (uint32_t)(n - 1) * row_bytes + (uint32_t)(D * 2);
   const uint32_t ret_bytes = (uint32_t)cnt * (uint32_t)(D * 2);
-  const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(k + lo * kv_st + (int64_t)h * kv_sh), 0, win_bytes, 0x00020000);
-  const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(v + lo * kv_st + (int64_t)h * kv_sh), 0, win_bytes, 0x00020000);
-  const auto rs_kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(k_ret + head * budget * D), 0, ret_bytes, 0x00020000);
-  const auto rs_vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(v_ret + head * budget * D), 0, ret_bytes, 0x00020000);
-  const int32_t* prbase = ret_pos + head * budget;
-  const int k_piece = tid % G::PPR, k_row = tid / G::PPR;
-  const uint32_t k_col = (uint32_t)k_piece * 16u;
-  const uint32_t k_loc = (uint32_t)k_row * row_bytes + k_col;          // first pass; later passes add RPP rows
-  const uint32_t kr_loc = (uint32_t)k_row * (uint32_t)(D * 2) + k_col;
+  const u32x4 rs_k = make_raw_rsrc(k + lo * kv_st + (int64_t)h * kv_sh, win_bytes);
+  const u32x4 rs_v = make_raw_rsrc(v + lo * kv_st + (int64_t)h * kv_sh, win_bytes);
+  const u32x4 rs_kr = make_raw_rsrc(k_ret + head * budget * D, ret_bytes);
+  const u32x4 rs_vr = make_raw_rsrc(v_ret + head * budget * D, ret_bytes);
+  const u32x4 rs_pos = make_raw_rsrc(ret_pos + head * budget, (uint32_t)cnt * 4u);
 
-  auto load_rows = [&](const auto& rk, const auto& rv, uint32_t b0, uint32_t rb, TR& R) {
+  // ---- global -> LDS: a wave instruction fills RPI rows (1 KB) of one tile; instruction wv + 4*i.  The tiles are swizzled
+  // by which piece a lane fetches: K for the row reads, V (its 64-byte chunks) for the transposing reads.  The swizzle terms
+  // of a lane's rows do not depend on i.
+  const int ld_row = G::RPI * wv + lane / G::PPR, ld_slot = lane % G::PPR;       // + 4 * RPI * i
+  const uint32_t ld_k = (uint32_t)(ld_slot ^ piece_swizzle<D>(ld_row)) * 16u;
+  const uint32_t ld_v = (uint32_t)((((ld_slot >> 2) ^ chunk_swizzle<D>(ld_row)) << 2) | (ld_slot & 3)) * 16u;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  const uint32_t pos_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&pos_lds[0][0];
+  auto load_tile = [&](int t) {
+    const bool win = t < n_win_tiles;
+    const int row0 = win ? jt0 + t * BN : (t - n_win_tiles) * BN;
+    const uint32_t rb = win ? row_bytes : (uint32_t)(D * 2);
+    const uint32_t dst = lds_base + (uint32_t)((t & 1) * kBuf * 2 + wv * 1024);
+    const u32x4 rk = win ? rs_k : rs_kr, rv = win ? rs_v : rs_vr;
+    uint32_t row_off = (uint32_t)(row0 + ld_row) * rb;
 #pragma unroll
-    for (int p = 0; p < G::KPASS; ++p) {
-      R.k[p] = __builtin_amdgcn_raw_buffer_load_b128(rk, b0 + (uint32_t)(p * G::RPP) * rb, 0, 0);
-      R.v[p] = __builtin_amdgcn_raw_buffer_load_b128(rv, b0 + (uint32_t)(p * G::RPP) * rb, 0, 0);
+    for (int i = 0; i < G::IPW; ++i) {
+      dma16(rk, dst + (uint32_t)(i * 4096), row_off + ld_k);
+      dma16(rv, dst + (uint32_t)(kTile * 2 + i * 4096), row_off + ld_v);
+      row_off += (uint32_t)(4 * G::RPI) * rb;
     }
-  };
-  auto load_tile = [&](int t, TR& R) {
-    if (t < n_win_tiles) {
-      const uint32_t tb = (uint32_t)(jt0 + t * BN) * row_bytes;
-      load_rows(rs_k, rs_v, tb + k_loc, row_bytes, R);
-    } else {
-      const int base = (t - n_win_tiles) * BN;
-      const uint32_t tb = (uint32_t)base * (uint32_t)(D * 2);
-      load_rows(rs_kr, rs_vr, tb + kr_loc, (uint32_t)(D * 2), R);
-      R.pos = 0x7FFFFFFF;
-      if (tid < BN && base + tid < cnt) R.pos = prbase[base + tid];
-    }
+    if (!win && wv == 0)          // the tile's 64 positions (zeros past ret_count)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                   :: "s"(pos_base + (uint32_t)((t & 1) * BN * 4)), "v"((uint32_t)(row0 + lane) * 4u), "s"(rs_pos) : "memory");
   };
 
-  // LDS store addresses. The V tile stays row-major [key][d] without padding; its 64-byte chunks (32 columns)
-  // are XOR-swizzled with the key row so that the transposing operand loads (4 keys x 16 columns per 16 lanes)
-  // spread over all banks.  Rows of one pass differ by multiples of RPP, which leaves the swizzle term unchanged.
-  static_assert(G::RPP % 4 == 0, "row passes must preserve the swizzle phase");
-  const int k_st_off = k_row * KS + k_piece * 8;
-  const int v_st_off = BN * KS + k_row * VS + (((k_piece >> 2) ^ chunk_swizzle<D>(k_row)) << 5) + (k_piece & 3) * 8;
-  auto store_tile = [&](int t, const TR& R) {
-    bf16_t* buf = lds + (t & 1) * kBuf;
-#pragma unroll
-    for (int p = 0; p < G::KPASS; ++p) {
-      *reinterpret_cast<u32x4*>(buf + k_st_off + p * G::RPP * KS) = R.k[p];
-      *reinterpret_cast<u32x4*>(buf + v_st_off + p * G::RPP * VS) = R.v[p];
-    }
-    if (t >= n_win_tiles && wv == 0) pos_lds[t & 1][lane] = R.pos;   // the tile's 64 positions (INT_MAX past ret_count)
-  };
-
-  // operand load offsets inside a tile buffer
-  const int a_k_off = tile_row_of_mfma_row(ql) * KS + 8 * hb;                 // + 32*kb*KS + 16*ks
+  // operand load offsets inside a tile buffer (elements).  K: MFMA row ql carries tile row kr; its pieces 2*ks + hb.
+  const int k_row = tile_row_of_mfma_row(ql);
+  const int k_off0 = k_row * D + ((piece_swizzle<D>(k_row) ^ hb) << 3);         // ^ (16 * ks), + 32 * D * kb
   // V operand through the transposing LDS load: in each group of 16 lanes, lane j points at the four columns
   // d0 + 4*(j%4).. of key row kbase + j/4, and receives column d0 + j of the four keys kbase..kbase+3.
   const int tr_key = 8 * hb + ((lane & 15) >> 2);           // + 32*kb + 16*kk (+ 4 for the upper half)
   const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);  // + 32*db, inside one 64-byte chunk
   const int tr_swz = chunk_swizzle<D>(tr_key);                  // unchanged by adding multiples of 4 to the key
-  const int a_v_off = BN * KS + tr_key * VS + tr_col;
+  const int a_v_off = kTile + tr_key * D + tr_col;
 
   // ---- softmax state (per lane = per query; the two lane halves keep separate partial sums) ------
   float m_run[QB], l_part[QB];
@@ -232,16 +216,12 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   // mode: 0 = plain, 1 = window-edge mask (keys jt..), 2 = retained mask (positions in pos_lds).
   // The 64-key tile is consumed as two 32-key halves, each with its own softmax update, so that only one
   // 32x32 score block per query block is live at a time.
-  auto compute = [&](const int mode, const bf16_t* buf, const int* pos, int jt) {
-    const bf16_t* a_k = buf + a_k_off;
+  // `slots`: entries of a retained tile.
+  auto compute = [&](const int mode, const bf16_t* buf, const int* pos, int jt, int slots) {
     const bf16_t* a_v = buf + a_v_off;
-    // The tile is consumed as two 32-key blocks.  Program order puts the matrix work of one block next to the
-    // exponentials of the other (scores of block 1 beside the softmax of block 0, P.V of block 0 beside the
-    // softmax of block 1), because a wave issues in order: only MFMAs that sit between VALU instructions in
-    // the instruction stream run concurrently with them.
     auto load_k_ops = [&](int kb, bf16x8 (&a)[D / 16]) {
 #pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(a_k + 32 * kb * KS + 16 * ks);
+      for (int ks = 0; ks < D / 16; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(buf + (k_off0 ^ (16 * ks)) + 32 * D * kb);
     };
     auto score_block = [&](const bf16x8 (&a)[D / 16], f32x16 (&sc)[QB]) {
 #pragma unroll
@@ -280,7 +260,7 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
           for (int r8 = 0; r8 < 2; ++r8) {
             const int* pp = pos + 32 * kb + 16 * r8 + 8 * hb;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sc[8 * r8 + e] = (pp[e] <= lim) ? sc[8 * r8 + e] : -INFINITY;
+            for (int e = 0; e < 8; ++e) sc[8 * r8 + e] = (pp[e] <= lim && 32 * kb + 16 * r8 + 8 * hb + e < slots) ? sc[8 * r8 + e] : -INFINITY;
           }
         }
       }
@@ -358,9 +338,9 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     auto load_v_ops = [&](int kb, bf16x8 (&av)[D / 32][2]) {
 #pragma unroll
       for (int db = 0; db < D / 32; ++db) {
-        const bf16_t* ap = a_v + 32 * kb * VS + ((db ^ tr_swz) << 5);
-        av[db][0] = load_transposed(ap, VS);
-        av[db][1] = load_transposed(ap + 16 * VS, VS);
+        const bf16_t* ap = a_v + 32 * kb * D + ((db ^ tr_swz) << 5);
+        av[db][0] = load_transposed(ap, D);
+        av[db][1] = load_transposed(ap + 16 * D, D);
       }
     };
     auto pv_block = [&](const bf16x8 (&av)[D / 32][2], const bf16x8 (&pb)[QB][2]) {   // O^T += V^T P^T
@@ -372,39 +352,106 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
           o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[db][1], pb[qb][1], o[qb][db], 0, 0, 0);
         }
     };
-    // The value operands are requested ahead of the exponentials that hide their LDS latency (measured against
-    // requesting them next to their MFMAs: 2 % at D = 128, 1 % at D = 64).
-    constexpr bool kEarlyV = true;
-    f32x16 s0[QB], s1[QB];
-    bf16x8 p0[QB][2], p1[QB][2];
-    bf16x8 ak0[D / 16], ak1[D / 16];
-    load_k_ops(0, ak0);
-    load_k_ops(1, ak1);        // requested together with block 0's operands: their LDS latency passes under block 0
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * (D / 16), 0);   // all operand reads first
-    score_block(ak0, s0);
-    apply_mask(0, s0);
-    score_block(ak1, s1);
-    bf16x8 av0[D / 32][2], av1[D / 32][2];
-    if constexpr (kEarlyV) load_v_ops(0, av0);
-    softmax_block(0, s0, p0);
-    apply_mask(1, s1);
-    if constexpr (kEarlyV) load_v_ops(1, av1);
-    else load_v_ops(0, av0);
-    pv_block(av0, p0);
-    softmax_block(1, s1, p1);   // if it scales the accumulators, block 0's product (formed under the old m) is in them
-    if constexpr (!kEarlyV) load_v_ops(1, av1);
-    pv_block(av1, p1);
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      f32x16 s[QB];
+      bf16x8 p[QB][2], ak[D / 16], av[D / 32][2];
+      load_k_ops(kb, ak);
+      score_block(ak, s);
+      apply_mask(kb, s);
+      softmax_block(kb, s, p);
+      load_v_ops(kb, av);
+      pv_block(av, p);
+    }
   };
 
-  // ---- software pipeline: tile t is computed from LDS buffer t&1 while tile t+1 is being stored into the other
-  // buffer and tile t+2 is in flight from global memory --------------------------------------------------------
-  auto step = [&](int t, TR& R) {   // R holds tile t+1 on entry and tile t+2 on exit
-    __syncthreads();   // tile t is in LDS; everyone is done with tile t-1 (whose buffer is overwritten next)
-    if (t + 1 < n_tiles) store_tile(t + 1, R);
-    if (t + 2 < n_tiles) load_tile(t + 2, R);
+  // A tile that every row of the wave sees whole, once all rows have a reference value: the same products and exponentials
+  // without a branch in between, so that the instruction stream can interleave them.  A wave issues in order and a matrix
+  // instruction occupies the matrix pipe for 32 clocks after its issue: vector instructions placed behind it run in that
+  // time, those behind the last one of a row of matrix instructions do not.
+  auto compute_plain = [&](const bf16_t* buf) {
+    constexpr int NK = D / 16, ND = D / 32;
+    const bf16_t* a_v = buf + a_v_off;
+    auto k_op = [&](int kb, int ks) { return *reinterpret_cast<const bf16x8*>(buf + (k_off0 ^ (16 * ks)) + 32 * D * kb); };
+    auto v_op = [&](int kb, int db, int kk) { return load_transposed(a_v + 32 * kb * D + ((db ^ tr_swz) << 5) + 16 * kk * D, D); };
+    auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+    bf16x2 ones;
+    ones[0] = static_cast<bf16_t>(1.0f); ones[1] = static_cast<bf16_t>(1.0f);
+    // softmax of elements EPM*i .. of a block, behind its i-th matrix instruction: exponentials now, conversion and row sum
+    // of the elements of the step before
+    constexpr int EPM = 16 / NK;
+    float e[16], l0 = 0.f, l1 = 0.f;
+    auto exp_part = [&](int i, const f32x16& sc) {
+#pragma unroll
+      for (int r = EPM * i; r < EPM * (i + 1); ++r) {
+        e[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], scale_log2e, -m_run[0]));
+        asm volatile("" : "+v"(e[r]));      // here, not next to its first use
+      }
+    };
+    auto pin = [](bf16x8& x) {
+      u32x4 w = __builtin_bit_cast(u32x4, x);
+      asm volatile("" : "+v"(w));
+      x = __builtin_bit_cast(bf16x8, w);
+    };
+    auto pack_part = [&](int i, bf16x8 (&p)[2]) {
+#pragma unroll
+      for (int r = EPM * i; r < EPM * (i + 1); r += 2) {
+        bf16x2 x;
+        x[0] = static_cast<bf16_t>(e[r]); x[1] = static_cast<bf16_t>(e[r + 1]);
+        p[r / 8][r % 8] = x[0]; p[r / 8][r % 8 + 1] = x[1];
+        if (r % 4 == 0) l0 = __builtin_amdgcn_fdot2_f32_bf16(x, ones, l0, false);
+        else l1 = __builtin_amdgcn_fdot2_f32_bf16(x, ones, l1, false);
+      }
+    };
+    f32x16 s0, s1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { s0[r] = 0.f; s1[r] = 0.f; }
+    bf16x8 p0[2], p1[2], ka[NK], kb[NK], va[NK], vb[NK];     // value operands in the order (kk, db)
+#pragma unroll
+    for (int i = 0; i < NK; ++i) ka[i] = k_op(0, i);
+    fence();
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {                       // scores of block 0, reading block 1's keys
+      pin(ka[i]);
+      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qreg[0][i], s0, 0, 0, 0);
+      kb[i] = k_op(1, i);
+      fence();
+    }
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {                       // scores of block 1 / softmax of block 0 / values of block 0
+      pin(kb[i]);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[i], qreg[0][i], s1, 0, 0, 0);
+      va[i] = v_op(0, i % ND, i / ND);
+      exp_part(i, s0);
+      if (i > 0) pack_part(i - 1, p0);
+      fence();
+    }
+    pack_part(NK - 1, p0);
+    fence();
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {                       // value products of block 0 / softmax of block 1 / values of block 1
+      pin(va[i]);
+      o[0][i % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], p0[i / ND], o[0][i % ND], 0, 0, 0);
+      vb[i] = v_op(1, i % ND, i / ND);
+      exp_part(i, s1);
+      if (i > 0) pack_part(i - 1, p1);
+      fence();
+    }
+    pack_part(NK - 1, p1);
+    l_part[0] += l0 + l1;
+    fence();
+#pragma unroll
+    for (int i = 0; i < NK; ++i)
+      o[0][i % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[i], p1[i / ND], o[0][i % ND], 0, 0, 0);
+    fence();
+  };
+
+  // ---- tile t is computed from LDS buffer t&1 while tile t+1 is on its way into the other one ---------------------
+  auto step = [&](int t) {
+    if (t + 1 < n_tiles) load_tile(t + 1);      // everyone is done with tile t-1, whose buffer this is
     const bf16_t* buf = lds + (t & 1) * kBuf;
     // classify the tile for this wave: -1 skip, 0 every (query, key) pair valid, 1 window-edge mask, 2 retained mask
-    int mode = -1, jt = 0;
+    int mode = -1, jt = 0, slots = 0;
     if (r0 < n) {
       if (t < n_win_tiles) {
         jt = jt0 + t * BN;
@@ -414,23 +461,27 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
       } else {
         // every wave looks at the tile's positions itself (one LDS word per lane, two compares): an entry counts for
         // this wave once it has left the window of the wave's last row, and needs no mask once it has left the window
-        // of the first; the filler positions of a ragged last tile never do
-        const int pv = pos_lds[t & 1][lane];
+        // of the first; the slots past the last entry never do
+        slots = cnt - (t - n_win_tiles) * BN;
+        const int pv = lane < slots ? pos_lds[t & 1][lane] : 0x7FFFFFFF;
         if (__builtin_amdgcn_ballot_w64(pv <= r_hi - window) != 0ull)
           mode = __builtin_amdgcn_ballot_w64(pv > r0 - window) == 0ull ? 0 : 2;
       }
     }
     mode = __builtin_amdgcn_readfirstlane(mode);
-    if (mode >= 0) compute(mode, buf, pos_lds[t & 1], jt);
+    if (mode == 0 && all_have_m && !exact_pass) compute_plain(buf);
+    else if (mode >= 0) compute(mode, buf, pos_lds[t & 1], jt, slots);
+    wait_loads();
+    __syncthreads();   // tile t+1 is in LDS; everyone is done with tile t
   };
   if (tid == 0) redo_flag = 0;
 #pragma unroll 1
   for (int pass = 0; pass < 2; ++pass) {
-    TR regs;
-    load_tile(0, regs);
-    store_tile(0, regs);
-    if (n_tiles > 1) load_tile(1, regs);
-    for (int t = 0; t < n_tiles; ++t) step(t, regs);
+    load_tile(0);
+    wait_loads();
+    __syncthreads();
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) step(t);
     if (exact_pass) break;
     // did a row's reference value fall so far below its scores that its sums left the range?
     bool bad = false;
@@ -471,13 +522,14 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     // wave index is the head inside the group
     bf16_t* obase = out + ((int64_t)(lo_q + i0 - q_begin) * Hq + unit * HW) * D;
     const int64_t orow_stride = (int64_t)Hq * D;
+    constexpr int kRowsPerPass = kThreads / G::PPR;
 #pragma unroll
-    for (int p = 0; p < BM / G::RPP; ++p) {
-      const int row = p * G::RPP + k_row;
+    for (int p = 0; p < BM / kRowsPerPass; ++p) {
+      const int row = p * kRowsPerPass + tid / G::PPR;
       const int prow = HW == 1 ? row : row % (32 * QB), hd = HW == 1 ? 0 : row / (32 * QB);
       if (i0 + prow < n)
-        *reinterpret_cast<u32x4*>(obase + prow * orow_stride + hd * D + k_piece * 8) =
-            *reinterpret_cast<const u32x4*>(lds + row * G::OS + k_piece * 8);
+        *reinterpret_cast<u32x4*>(obase + prow * orow_stride + hd * D + (tid % G::PPR) * 8) =
+            *reinterpret_cast<const u32x4*>(lds + row * G::OS + (tid % G::PPR) * 8);
     }
   }
 }
