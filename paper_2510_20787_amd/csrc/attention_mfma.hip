@@ -463,14 +463,21 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
         // this wave once it has left the window of the wave's last row, and needs no mask once it has left the window
         // of the first; the slots past the last entry never do
         slots = cnt - (t - n_win_tiles) * BN;
-        const int pv = lane < slots ? pos_lds[t & 1][lane] : 0x7FFFFFFF;
+        int pv = pos_lds[t & 1][lane];
+        pv = lane < slots ? pv : 0x7FFFFFFF;
         if (__builtin_amdgcn_ballot_w64(pv <= r_hi - window) != 0ull)
           mode = __builtin_amdgcn_ballot_w64(pv > r0 - window) == 0ull ? 0 : 2;
       }
     }
     mode = __builtin_amdgcn_readfirstlane(mode);
-    if (mode == 0 && all_have_m && !exact_pass) compute_plain(buf);
-    else if (mode >= 0) compute(mode, buf, pos_lds[t & 1], jt, slots);
+    // Two steps in sequence rather than if / else: as an alternative of the plain body the other one kept the accumulators of
+    // before the tile alive across it, and every tile ended with waiting for its last products and copying them.
+    if (mode == 0 && all_have_m && !exact_pass) {
+      compute_plain(buf);
+      mode = -1;
+    }
+    asm volatile("" : "+s"(mode));
+    if (mode >= 0) compute(mode, buf, pos_lds[t & 1], jt, slots);
     wait_loads();
     __syncthreads();   // tile t+1 is in LDS; everyone is done with tile t
   };
@@ -489,7 +496,7 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     for (int qb = 0; qb < QB; ++qb) bad = bad || !(l_part[qb] <= kBig);
     if (__builtin_amdgcn_ballot_w64(bad) != 0ull && lane == 0) redo_flag = 1;
     __syncthreads();  // also: tile buffers are free
-    if (redo_flag == 0) break;
+    if (__builtin_amdgcn_readfirstlane(redo_flag) == 0) break;
     exact_pass = true;
     reset_rows();
   }
