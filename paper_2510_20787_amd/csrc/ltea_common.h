@@ -66,6 +66,18 @@ __device__ __forceinline__ int find_sequence(const int32_t* __restrict__ cu, int
   return lo;
 }
 
+// Inclusive sum over the wave on the cross-lane paths of the vector ALU (shifts inside the rows of 16, then the row totals
+// passed on): six dependent additions of a few clocks each, where six LDS permutes would cost about 100 each.
+__device__ __forceinline__ int wave_scan_add(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
 // Which sequence owns flat tile `flat`, when sequence i owns ceil(len_i / tile_len) consecutive tiles?  Called by
 // every lane of a wave with the same arguments (full exec).  The lengths are read 64 sequences at a time with one
 // vector load each for cu[i] and cu[i+1] and resolved with a wave prefix sum, so the search costs one trip to
@@ -79,23 +91,17 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ cu, int 
     const int ic = i < n_seqs ? i : n_seqs - 1;      // unconditional loads, inactive lanes count zero tiles
     const int a = cu[ic], b = cu[ic + 1];
     const int nt = i < n_seqs ? (b - a + tile_len - 1) / tile_len : 0;
-    int inc = nt;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int t = __shfl_up(inc, off, kWave);
-      if (lane >= off) inc += t;
-    }
-    const int total = __builtin_amdgcn_readfirstlane(__shfl(inc, kWave - 1, kWave));
+    const int inc = wave_scan_add(nt);
+    const int total = __builtin_amdgcn_readlane(inc, kWave - 1);
     if (flat < before + total) {
       const unsigned long long m = __builtin_amdgcn_ballot_w64(inc > flat - before);
       const int l = __builtin_ctzll(m);
       // the results are wave-uniform: hand them back in scalar registers so that everything derived from them
       // (loop bounds, buffer descriptors) stays scalar
       seq = s0 + l;
-      lo = __builtin_amdgcn_readfirstlane(__shfl(a, l, kWave));
-      len = __builtin_amdgcn_readfirstlane(__shfl(b, l, kWave)) - lo;
-      tile = flat - before -
-             __builtin_amdgcn_readfirstlane(__shfl(inc, l, kWave) - __shfl(nt, l, kWave));
+      lo = __builtin_amdgcn_readlane(a, l);
+      len = __builtin_amdgcn_readlane(b, l) - lo;
+      tile = flat - before - (__builtin_amdgcn_readlane(inc, l) - __builtin_amdgcn_readlane(nt, l));
       return true;
     }
     before += total;
@@ -119,21 +125,16 @@ __device__ __forceinline__ bool locate_tile_late_first(const int32_t* __restrict
       const int all = i < n_seqs ? (b - a + tile_len - 1) / tile_len : 0;
       const int early = all < first_late ? all : first_late;
       const int nt = part == 0 ? all - early : early;
-      int inc = nt;
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int t = __shfl_up(inc, off, kWave);
-        if (lane >= off) inc += t;
-      }
-      const int total = __builtin_amdgcn_readfirstlane(__shfl(inc, kWave - 1, kWave));
+      const int inc = wave_scan_add(nt);
+      const int total = __builtin_amdgcn_readlane(inc, kWave - 1);
       if (flat < total) {
         const unsigned long long m = __builtin_amdgcn_ballot_w64(inc > flat);
         const int l = __builtin_ctzll(m);
         seq = s0 + l;
-        lo = __builtin_amdgcn_readfirstlane(__shfl(a, l, kWave));
-        len = __builtin_amdgcn_readfirstlane(__shfl(b, l, kWave)) - lo;
-        const int within = flat - __builtin_amdgcn_readfirstlane(__shfl(inc, l, kWave) - __shfl(nt, l, kWave));
-        const int early_l = __builtin_amdgcn_readfirstlane(__shfl(early, l, kWave));
+        lo = __builtin_amdgcn_readlane(a, l);
+        len = __builtin_amdgcn_readlane(b, l) - lo;
+        const int within = flat - (__builtin_amdgcn_readlane(inc, l) - __builtin_amdgcn_readlane(nt, l));
+        const int early_l = __builtin_amdgcn_readlane(early, l);
         tile = part == 0 ? early_l + within : within;
         return true;
       }

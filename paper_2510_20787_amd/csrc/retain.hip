@@ -37,12 +37,7 @@ __device__ __forceinline__ float key_of_order_key(uint32_t u) {
 // `scratch` holds kSelWaves+1 ints of LDS. Contains two barriers.
 __device__ __forceinline__ int block_exclusive_scan(int val, int* scratch, int& total) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  int inc = val;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    int t = __shfl_up(inc, off, kWave);
-    if (lane >= off) inc += t;
-  }
+  const int inc = wave_scan_add(val);
   __syncthreads();  // protect scratch from the previous use
   if (lane == kWave - 1) scratch[wave] = inc;
   __syncthreads();
@@ -248,12 +243,7 @@ retain_kernel(const RetainArgs a) {
           cnt[i] = x.x + x.y + x.z + x.w + y.x + y.y + y.z + y.w;
           mine += cnt[i];
         }
-        int inc = mine;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-          const int t = __shfl_up(inc, off, kWave);
-          if (lane >= off) inc += t;
-        }
+        const int inc = wave_scan_add(mine);
         int running = inc - mine;   // elements with a larger digit than this lane's first
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
