@@ -128,7 +128,7 @@ size_t carve_train(const ltea_cfg& cfg, int n_seqs, int64_t total, int max_seqle
   float* win_score = reinterpret_cast<float*>(take(heads * cfg.window * 4));
   int32_t* n_seen = reinterpret_cast<int32_t*>(take((size_t)n_seqs * 4));
   int32_t* n_scored = reinterpret_cast<int32_t*>(take((size_t)n_seqs * 4));
-  float* d = reinterpret_cast<float*>(take((size_t)cfg.Hq * (size_t)total * 4));
+  float* d = reinterpret_cast<float*>(take((size_t)cfg.Hq * (size_t)total * 4 * (cfg.dtype == LTEA_BF16 ? 2 : 1)));
   float* fk = reinterpret_cast<float*>(take((size_t)train_far_chunks(n_seqs, cfg.Hkv) * heads * cap * cfg.D * 4));
   float* fv = reinterpret_cast<float*>(take((size_t)train_far_chunks(n_seqs, cfg.Hkv) * heads * cap * cfg.D * 4));
   if (far_dk) *far_dk = fk;

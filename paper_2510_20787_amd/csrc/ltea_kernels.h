@@ -163,7 +163,7 @@ hipError_t launch_cnn_backward(const ltea_cfg& cfg, const ltea_cnn& cnn, const v
 // ---- training-side backward --------------------------------------------------------------------------------
 // kept: the compact arrays the retention launcher leaves when run with budget = kept_capacity and a cap that never
 // binds (ascending kept out-of-window positions per (sequence, KV head) and their K / V rows).
-// delta: [Hq][total] fp32 scratch; dq/dk/dv contiguous [total][H][D] of cfg.dtype; dz [Hkv][total]; counts [n_seqs][Hkv].
+// delta: fp32 scratch, [Hq][total] (bf16 storage: [2][Hq][total]); dq/dk/dv contiguous [total][H][D] of cfg.dtype; dz [Hkv][total]; counts [n_seqs][Hkv].
 hipError_t launch_train_backward(const ltea_cfg& cfg, const void* q, int64_t q_st, int64_t q_sh, const void* k,
                                  const void* v, int64_t kv_st, int64_t kv_sh, const SeqView& sv, const void* out,
                                  const void* dout, const float* lse, const float* logits, const float* lambda,

@@ -26,16 +26,26 @@ template <int D> __device__ __forceinline__ int chunk_swizzle(int row) { return 
 // A operand from a row-major tile read transposed: eight consecutive tile rows of one column per lane, as two
 // transposing 64-bit LDS loads (rows +0..3, +4..7).  In each group of 16 lanes, lane j points at the four columns
 // c0 + 4*(j%4).. of tile row r0 + j/4 and receives column c0 + j of the four rows r0 .. r0+3.
-__device__ __forceinline__ bf16x8 load_transposed(const bf16_t* p, int row_stride) {
+__device__ __forceinline__ bf16x8 load_transposed_at(const bf16_t* p_lo, const bf16_t* p_hi) {
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef short s16x8 __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * row_stride));
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p_lo));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p_hi));
   s16x8 r;
   r[0] = lo[0]; r[1] = lo[1]; r[2] = lo[2]; r[3] = lo[3];
   r[4] = hi[0]; r[5] = hi[1]; r[6] = hi[2]; r[7] = hi[3];
   return __builtin_bit_cast(bf16x8, r);
+}
+__device__ __forceinline__ bf16x8 load_transposed(const bf16_t* p, int row_stride) {
+  return load_transposed_at(p, p + 4 * row_stride);
+}
+
+// Which 16-byte piece of its row a tile row's piece p is stored in (p ^ term) where one unpadded copy is read both row-wise
+// and transposed.  The 16 rows of a row read then lie in 16 different 16-byte bank groups, and the 64-byte chunks of four
+// consecutive rows in four different 64-byte groups.  Rows four apart differ in the lowest bit of the term.
+template <int D> __device__ __forceinline__ int both_ways_swizzle(int row) {
+  return D == 64 ? ((row & 2) << 1) | ((row >> 2) & 3) : ((row & 3) << 2) | ((row >> 2) & 3);
 }
 
 // Both lane halves (l, l^32) receive max / sum of the pair.

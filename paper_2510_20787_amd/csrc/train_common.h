@@ -27,7 +27,7 @@ struct TrainArgs {
   int max_seqlen;
   int far_chunks;                       // train_far_chunks(n_seqs, Hkv)
   const float *lse, *logits, *lambda;
-  float* delta;
+  float* delta;                         // [Hq][total]: <dO, O>; on the matrix-core path -<dO, O>, then [Hq][total] of -lse / scale
   float *far_dk, *far_dv;               // fp32 scratch of the matrix-core dK / dV path, far_chunks slices laid out like k_ret / v_ret
   void *dq, *dk, *dv;
   float* dz;

@@ -2,27 +2,36 @@
 // Section 3.1.2: the gradients that reach Q, K, V and, through the straight-through estimator, the retention scores).
 //
 // Three launches on the caller's stream:
-//   train_delta_mfma_kernel      delta = <dO, O> per (query, query head).
+//   train_delta_mfma_kernel      delta = <dO, O> and lse, scaled, per (query, query head).
 //   train_dq_far_mfma_kernel     two independent roles in one grid: the far pass of dK / dV (first, few and
 //                                long-running workgroups) and dQ (fills the compute units the far pass leaves idle).
 //   train_dkv_band_mfma_kernel   the band pass of dK / dV, which adds the far pass in, stores dK, dV and forms
 //                                d logit and the retention counts.
 //
-// dQ role: one workgroup = 128 consecutive queries of one (sequence, query head), 4 waves x 32 queries, walking the
-// same key tiles as the forward kernel (64-key tiles of K/V inside the window range, then 64-slot tiles of the
-// compacted candidates with the per-row mask "position <= i - window").  Per 32-key block and wave
-// (v_mfma_f32_32x32x16_bf16, a lane owns one query column):
+// dQ role: one workgroup = 128 consecutive queries of one (sequence, query head), 4 waves x 32 queries (or 32 queries of four
+// heads, one per wave, see dq_body), walking the same key tiles as the forward kernel (64-key tiles of K/V inside the window
+// range, then 64-slot tiles of the compacted candidates with the per-row mask "position <= i - window").  Per 32-key block
+// and wave (v_mfma_f32_32x32x16_bf16, a lane owns one query column):
 //   S^T[key, query]  = K . Q^T        A = K tile rows from LDS, B = Q fragment in registers
 //   dP^T[key, query] = V . dO^T       A = V tile rows from LDS, B = dO fragment in registers
-//   P^T = exp2(S^T c - lse), dS^T = P^T (dP^T - delta)      per-lane scalars lse, delta (no running maximum)
+//   P^T = exp2((S^T - lse / scale) c), dS^T = P^T (dP^T - delta)      no running maximum
 //   dQ^T[d, query]  += K^T . dS^T     A = K^T through the transposing LDS load, B = dS^T straight from registers
-// K is therefore staged twice per tile (padded rows for the row reads, swizzled unpadded rows for the transposing
-// reads), V once.  The dK / dV roles are the mirror image with a lane owning a key column (see dkv_body).
-// Two tile buffers and a register prefetch: one barrier per tile.  No floating-point atomics: the
-// partial sums of the far pass go to scratch slices that the band pass adds in a fixed order.
+// The two differences cost nothing: the products' accumulators start from -lse / scale and -delta.
+// The dK / dV roles are the mirror image with a lane owning a key column (see dkv_body).
+// What bounds them: the instruction stream of a wave, which issues in order.  Tiles come straight into LDS, one copy each,
+// swizzled so that the row reads and the transposing reads of it are both free of bank conflicts; a tile that every row of the
+// wave sees whole takes a body without branches in which each matrix instruction is followed by its share of the exponentials
+// (4.3 VALU per matrix instruction in dK / dV, 5 in dQ, from 10 to 12 when tiles went through registers, K / Q / dO were
+// stored twice and every block was a basic block of its own).  4 x 4096 tokens, 32 heads on 8, D = 64, window 768, an eighth
+// kept: dQ with the far pass 467 -> 363 us (378 with consecutive blocks of one head on the waves), band pass 359 -> 285 us.
+// Two tile buffers, one barrier per tile.  No floating-point atomics: the partial sums of the far pass go to scratch slices
+// that the band pass adds in a fixed order.
+#include <type_traits>
+
 #include "ltea_common.h"
 #include "ltea_kernels.h"
 #include "mfma_tiles.h"
+#include "score_dma.h"
 #include "train_common.h"
 
 namespace ltea {
@@ -33,47 +42,81 @@ constexpr int BM = 128;         // queries (or keys) per workgroup
 constexpr int kThreads = 256;
 
 template <int D> struct Geo {
-  static constexpr int KS = D + 8;       // padded row stride (elements) of tiles read row-wise
-  static constexpr int VS = D;           // unpadded, chunk-swizzled row stride of tiles read through the transposing load
-  static constexpr int PPR = D / 8;      // 16-byte pieces per row
-  static constexpr int RPP = kThreads / PPR;
-  static constexpr int KPASS = BN / RPP;
-  static constexpr int OS = D + 8;       // epilogue staging stride
-  static constexpr int kBufDq = 2 * BN * KS + BN * VS;        // K rows | K for transposed reads | V rows
-  static constexpr int kBufDkv = 2 * BN * KS + 2 * BN * VS;   // Q rows | Q transposed | dO rows | dO transposed
-  static constexpr int kBuf = kBufDkv;
+  static constexpr int PPR = D / 8;             // 16-byte pieces per row
+  static constexpr int RPP = kThreads / PPR;    // rows per epilogue pass
+  static constexpr int RPI = 64 / PPR;          // rows per wave load instruction
+  static constexpr int IPW = BN / RPI / 4;      // load instructions per wave, each of the two tiles of a step
+  static constexpr int OS = D + 8;              // epilogue staging stride
+  static constexpr int kTile = BN * D;          // elements of one tile; a buffer holds two (K and V, or Q and dO)
+  static constexpr int kBuf = 2 * kTile;
 };
 #define LTEA_GEO(D) \
   using G_ = Geo<D>; \
-  constexpr int KS = G_::KS, VS = G_::VS, PPR = G_::PPR, RPP = G_::RPP, KPASS = G_::KPASS, OS = G_::OS
+  constexpr int PPR = G_::PPR, RPP = G_::RPP, OS = G_::OS, kTile = G_::kTile, kBuf = G_::kBuf
 
-template <int D> struct TileRegs {
-  u32x4 a[Geo<D>::KPASS], b[Geo<D>::KPASS];
-  int pos;
+// Where a lane finds its operands in a tile (see both_ways_swizzle): row reads (A operand = tile rows) and transposing
+// reads (contraction over the tile rows) of the same copy.
+template <int D> struct Operands {
+  int row_off, tr_off;
+  __device__ __forceinline__ explicit Operands(int lane) {
+    const int ql = lane & 31, hb = lane >> 5;
+    const int m_row = tile_row_of_mfma_row(ql);
+    row_off = m_row * D + ((both_ways_swizzle<D>(m_row) ^ hb) << 3);
+    const int tr_row = 8 * hb + ((lane & 15) >> 2);
+    const int piece = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+    tr_off = tr_row * D + ((both_ways_swizzle<D>(tr_row) ^ piece) << 3) + 4 * (lane & 1);
+  }
+  // tile rows 32 * blk .., features 16 * ks ..
+  __device__ __forceinline__ bf16x8 rows(const bf16_t* t, int blk, int ks) const {
+    return *reinterpret_cast<const bf16x8*>(t + (row_off ^ (16 * ks)) + 32 * D * blk);
+  }
+  // features 32 * db .., contraction over tile rows 32 * blk + 16 * kk ..
+  __device__ __forceinline__ bf16x8 columns(const bf16_t* t, int blk, int kk, int db) const {
+    const bf16_t* p = t + (32 * blk + 16 * kk) * D;
+    return load_transposed_at(p + (tr_off ^ (32 * db)), p + 4 * D + (tr_off ^ 8 ^ (32 * db)));
+  }
 };
 
-template <int D>
+// f(0), f(1), .. f(N - 1) with the index as a constant (the compiler's own unrolling gives up on bodies of this size).
+template <int N, int I = 0, class F> __device__ __forceinline__ void static_for(const F& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+__device__ __forceinline__ void pin(bf16x8& x) {
+  u32x4 w = __builtin_bit_cast(u32x4, x);
+  asm volatile("" : "+v"(w));
+  x = __builtin_bit_cast(bf16x8, w);
+}
+
+// HW = query heads per workgroup.  1: the four waves take four consecutive blocks of 32 queries of one head.  4 (a multiple of
+// four query heads per KV head): the same 32 queries of four heads that share the KV head, so that all four waves see the
+// same window: the workgroup walks 96 positions less of it, and no wave waits at the barrier for another's masked tile.
+template <int D, int HW>
 __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int n_work, float scale_log2e, int block,
-                                        bf16_t* lds, int* pos_lds_base, int* pos_rng_base) {
+                                        bf16_t* lds, int* pos_lds_base) {
   LTEA_GEO(D);
-  constexpr int kK = 0, kKt = BN * KS, kV = BN * KS + BN * VS;
-  static_assert(G_::kBufDq >= BM * OS, "epilogue staging must fit in the tile buffer");
+  static_assert(2 * kBuf >= BM * OS, "epilogue staging must fit in the tile buffers");
 
   const int per_xcd = (n_work + 7) / 8;
   const int work = (block % 8) * per_xcd + block / 8;
   if (work >= n_work) return;
-  const int hq = work / tiles_upper;
+  constexpr int BMQ = BM / HW;               // query positions per workgroup
+  const int unit = work / tiles_upper;       // query head, or group of HW of them
   int tile, s, n, lo;
-  if (!locate_tile(A.cu, A.n_seqs, BM, work - hq * tiles_upper, s, tile, lo, n)) return;
+  if (!locate_tile(A.cu, A.n_seqs, BMQ, work - unit * tiles_upper, s, tile, lo, n)) return;
   const int Hq = A.Hq, Hkv = A.Hkv, window = A.window, budget = A.budget;
-  const int h = hq / (Hq / Hkv);
+  const int h = unit * HW / (Hq / Hkv);
   const int64_t head = (int64_t)s * Hkv + h;
-  const int i0 = tile * BM;
+  const int i0 = tile * BMQ;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ql = lane & 31, hb = lane >> 5;
-  const int r0 = i0 + 32 * wv;
+  const int hq = HW == 1 ? unit : unit * HW + wv;
+  const int r0 = i0 + (HW == 1 ? 32 * wv : 0);
   const int r_hi = r0 + 31;
 
   const bf16_t* q = static_cast<const bf16_t*>(A.q);
@@ -81,7 +124,7 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
   const bf16_t* v = static_cast<const bf16_t*>(A.v);
   const bf16_t* dout = static_cast<const bf16_t*>(A.dout);
 
-  // ---- per-lane query state: Q and dO fragments (B operands), lse (base-2 domain), delta ---------------------
+  // ---- per-lane query state: Q and dO fragments (B operands), -lse / scale and -delta --------------------------
   const int qi = r0 + ql;
   const int qc = qi < n ? qi : n - 1;
   bf16x8 qreg[D / 16], doreg[D / 16];
@@ -94,22 +137,11 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
       doreg[ks] = *reinterpret_cast<const bf16x8*>(dorow + 16 * ks + 8 * hb);
     }
   }
-  const float lse2 = A.lse[(int64_t)hq * A.total + lo + qc] * 1.4426950408889634f;
-  // delta = <dO, O> of the lane's query: each lane half holds half of the row
-  float dlt = 0.f;
-  {
-    const bf16_t* orow = static_cast<const bf16_t*>(A.out) + ((int64_t)(lo + qc) * Hq + hq) * D;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      const bf16x8 o8 = *reinterpret_cast<const bf16x8*>(orow + 16 * ks + 8 * hb);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dlt = fmaf(static_cast<float>(doreg[ks][e]), static_cast<float>(o8[e]), dlt);
-    }
-    dlt = pair_sum(dlt);
-  }
+  const int64_t stat = (int64_t)hq * A.total + lo + qc;
+  const float neg_dlt = A.delta[stat], neg_lse = A.delta[(int64_t)Hq * A.total + stat];
 
   // ---- tile schedule (as in the forward) ------------------------------------------------------------------
-  const int i_last = (i0 + BM < n ? i0 + BM : n) - 1;
+  const int i_last = (i0 + BMQ < n ? i0 + BMQ : n) - 1;
   const int jlo = i0 - window + 1 > 0 ? i0 - window + 1 : 0;
   const int jt0 = (jlo / BN) * BN;
   const int n_win_tiles = (i_last - jt0) / BN + 1;
@@ -120,79 +152,54 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
   const uint32_t row_bytes = (uint32_t)A.kv_st * 2u;
   const uint32_t win_bytes = (uint32_t)(n - 1) * row_bytes + (uint32_t)(D * 2);
   const uint32_t ret_bytes = (uint32_t)cnt * (uint32_t)(D * 2);
-  const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(k + (int64_t)lo * A.kv_st + (int64_t)h * A.kv_sh), 0, win_bytes, 0x00020000);
-  const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(v + (int64_t)lo * A.kv_st + (int64_t)h * A.kv_sh), 0, win_bytes, 0x00020000);
-  const auto rs_kr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(static_cast<const bf16_t*>(A.k_ret) + head * budget * D), 0, ret_bytes, 0x00020000);
-  const auto rs_vr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(static_cast<const bf16_t*>(A.v_ret) + head * budget * D), 0, ret_bytes, 0x00020000);
-  const int32_t* prbase = A.ret_pos + head * budget;
-  const int k_piece = tid % PPR, k_row = tid / PPR;
-  const uint32_t k_col = (uint32_t)k_piece * 16u;
-  const uint32_t k_loc = (uint32_t)k_row * row_bytes + k_col;
-  const uint32_t kr_loc = (uint32_t)k_row * (uint32_t)(D * 2) + k_col;
-
-  auto load_rows = [&](const auto& rk, const auto& rv, uint32_t b0, uint32_t rb, TileRegs<D>& R) {
+  const u32x4 rs_k = make_raw_rsrc(k + (int64_t)lo * A.kv_st + (int64_t)h * A.kv_sh, win_bytes);
+  const u32x4 rs_v = make_raw_rsrc(v + (int64_t)lo * A.kv_st + (int64_t)h * A.kv_sh, win_bytes);
+  const u32x4 rs_kr = make_raw_rsrc(static_cast<const bf16_t*>(A.k_ret) + head * budget * D, ret_bytes);
+  const u32x4 rs_vr = make_raw_rsrc(static_cast<const bf16_t*>(A.v_ret) + head * budget * D, ret_bytes);
+  const u32x4 rs_pos = make_raw_rsrc(A.ret_pos + head * budget, (uint32_t)cnt * 4u);
+  // global -> LDS: a wave instruction fills RPI rows (1 KB) of a tile, instruction wv + 4 * i; which piece a lane fetches
+  // makes the swizzle, whose term does not depend on i
+  const int ld_row = G_::RPI * wv + lane / PPR;
+  const uint32_t ld_col = (uint32_t)((lane % PPR) ^ both_ways_swizzle<D>(ld_row)) * 16u;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  const uint32_t pos_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)pos_lds_base;
+  auto load_tile = [&](int t) {
+    const bool win = t < n_win_tiles;
+    const int row0 = win ? jt0 + t * BN : (t - n_win_tiles) * BN;
+    const uint32_t rb = win ? row_bytes : (uint32_t)(D * 2);
+    const uint32_t dst = lds_base + (uint32_t)((t & 1) * kBuf * 2 + wv * 1024);
+    const u32x4 rk = win ? rs_k : rs_kr, rv = win ? rs_v : rs_vr;
+    uint32_t off = (uint32_t)(row0 + ld_row) * rb + ld_col;
 #pragma unroll
-    for (int p = 0; p < KPASS; ++p) {
-      R.a[p] = __builtin_amdgcn_raw_buffer_load_b128(rk, b0 + (uint32_t)(p * RPP) * rb, 0, 0);
-      R.b[p] = __builtin_amdgcn_raw_buffer_load_b128(rv, b0 + (uint32_t)(p * RPP) * rb, 0, 0);
+    for (int i = 0; i < G_::IPW; ++i) {
+      dma16(rk, dst + (uint32_t)(i * 4096), off);
+      dma16(rv, dst + (uint32_t)(kTile * 2 + i * 4096), off);
+      off += (uint32_t)(4 * G_::RPI) * rb;
     }
+    if (!win && wv == 0) dma4(rs_pos, pos_base + (uint32_t)((t & 1) * BN * 4), (uint32_t)(row0 + lane) * 4u);   // zeros past cnt
   };
-  auto load_tile = [&](int t, TileRegs<D>& R) {
-    if (t < n_win_tiles) {
-      load_rows(rs_k, rs_v, (uint32_t)(jt0 + t * BN) * row_bytes + k_loc, row_bytes, R);
-    } else {
-      const int base = (t - n_win_tiles) * BN;
-      load_rows(rs_kr, rs_vr, (uint32_t)base * (uint32_t)(D * 2) + kr_loc, (uint32_t)(D * 2), R);
-      R.pos = 0x7FFFFFFF;
-      if (tid < BN && base + tid < cnt) R.pos = prbase[base + tid];
-    }
-  };
-  static_assert(RPP % 4 == 0, "row passes must preserve the swizzle phase");
-  const int p_st_off = k_row * KS + k_piece * 8;
-  const int t_st_off = k_row * VS + (((k_piece >> 2) ^ chunk_swizzle<D>(k_row)) << 5) + (k_piece & 3) * 8;
-  auto store_tile = [&](int t, const TileRegs<D>& R) {
-    bf16_t* sb = lds + (t & 1) * G_::kBufDq;
-#pragma unroll
-    for (int p = 0; p < KPASS; ++p) {
-      *reinterpret_cast<u32x4*>(sb + kK + p_st_off + p * RPP * KS) = R.a[p];
-      *reinterpret_cast<u32x4*>(sb + kKt + t_st_off + p * RPP * VS) = R.a[p];
-      *reinterpret_cast<u32x4*>(sb + kV + p_st_off + p * RPP * KS) = R.b[p];
-    }
-    if (t >= n_win_tiles && wv == 0) {
-      pos_lds_base[(t & 1) * BN + lane] = R.pos;
-      const int mn = wave_min_i(R.pos);
-      const int mx = wave_max_i(R.pos == 0x7FFFFFFF ? (int)0x80000000 : R.pos);
-      if (lane == 0) { pos_rng_base[(t & 1) * 2] = mn; pos_rng_base[(t & 1) * 2 + 1] = mx; }
-    }
-  };
-  const bf16_t* tb = lds;            // tile buffer and position list of the tile being computed
-  const int* pos_lds = pos_lds_base;
+  const Operands<D> op(lane);
+  constexpr int NK = D / 16, ND = D / 32;
 
-  const int a_row_off = tile_row_of_mfma_row(ql) * KS + 8 * hb;        // + 32*kb*KS + 16*ks
-  const int tr_key = 8 * hb + ((lane & 15) >> 2);
-  const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const int tr_swz = chunk_swizzle<D>(tr_key);
-  const int a_tr_off = kKt + tr_key * VS + tr_col;
-
-  f32x16 acc[D / 32];
+  f32x16 acc[ND];
+  f32x16 neg_lse16, neg_dlt16;       // the products start from these: S - lse / scale and dP - delta come out of the pipe
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int r = 0; r < 16; ++r) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+    for (int db = 0; db < ND; ++db) acc[db][r] = 0.f;
+    neg_lse16[r] = neg_lse;
+    neg_dlt16[r] = neg_dlt;
+  }
 
-  // mode: 0 = every pair valid, 1 = window-edge mask, 2 = mask by the candidates' positions
-  auto compute = [&](const int mode, int jt) {
+  // mode: 1 = window-edge mask, 2 = mask by the candidates' positions (`slots`: entries of the tile)
+  auto compute = [&](const int mode, const bf16_t* tb, const int* pos, int jt, int slots) {
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-      f32x16 sc, dp;
+      f32x16 sc = neg_lse16, dp = neg_dlt16;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sc[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 ak = *reinterpret_cast<const bf16x8*>(tb + kK + a_row_off + 32 * kb * KS + 16 * ks);
-        const bf16x8 av = *reinterpret_cast<const bf16x8*>(tb + kV + a_row_off + 32 * kb * KS + 16 * ks);
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, qreg[ks], sc, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, doreg[ks], dp, 0, 0, 0);
+      for (int ks = 0; ks < NK; ++ks) {
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.rows(tb, kb, ks), qreg[ks], sc, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.rows(tb + kTile, kb, ks), doreg[ks], dp, 0, 0, 0);
       }
       // register r is local key 32*kb + 16*(r/8) + 8*hb + r%8
       if (mode == 1) {
@@ -208,65 +215,131 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
           const int c = 32 * kb + 16 * (r / 8) + (r % 8);
           sc[r] = ((unsigned)(c - c_lo) <= span) ? sc[r] : -INFINITY;
         }
-      } else if (mode == 2) {
+      } else {
         const int lim = qi - window;
 #pragma unroll
         for (int r8 = 0; r8 < 2; ++r8) {
-          const int* pp = pos_lds + 32 * kb + 16 * r8 + 8 * hb;
+          const int c0 = 32 * kb + 16 * r8 + 8 * hb;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) sc[8 * r8 + e] = (pp[e] <= lim) ? sc[8 * r8 + e] : -INFINITY;
+          for (int e = 0; e < 8; ++e) sc[8 * r8 + e] = (pos[c0 + e] <= lim && c0 + e < slots) ? sc[8 * r8 + e] : -INFINITY;
         }
       }
       bf16x8 pb[2];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float p = __builtin_amdgcn_exp2f(fmaf(sc[r], scale_log2e, -lse2));   // exp2(-inf) = 0 for masked pairs
-        pb[r / 8][r % 8] = static_cast<bf16_t>(p * (dp[r] - dlt));
+        const float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e);   // exp2(-inf) = 0 for masked pairs
+        pb[r / 8][r % 8] = static_cast<bf16_t>(p * dp[r]);
       }
 #pragma unroll
-      for (int db = 0; db < D / 32; ++db) {
-        const bf16_t* ap = tb + a_tr_off + 32 * kb * VS + ((db ^ tr_swz) << 5);
-        const bf16x8 a0 = load_transposed(ap, VS);
-        const bf16x8 a1 = load_transposed(ap + 16 * VS, VS);
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, pb[0], acc[db], 0, 0, 0);
-        acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, pb[1], acc[db], 0, 0, 0);
-      }
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int db = 0; db < ND; ++db)
+          acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.columns(tb, kb, kk, db), pb[kk], acc[db], 0, 0, 0);
     }
   };
 
-  // tile t is computed from buffer t & 1 while tile t+1 is stored into the other buffer and tile t+2 is in flight
-  TileRegs<D> regs;
-  load_tile(0, regs);
-  store_tile(0, regs);
-  if (n_tiles > 1) load_tile(1, regs);
+  // A tile that every row of the wave sees whole: 6 NK matrix instructions without a branch, the exponentials of one block
+  // behind the products of the other.  A wave issues in order and a matrix instruction holds the matrix pipe for 32 clocks
+  // after its issue; vector instructions and LDS reads placed behind it run in that time.
+  auto compute_plain = [&](const bf16_t* tb) {
+    auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+    auto operand = [&](int i) {          // of the tile's i-th matrix instruction
+      if (i < 4 * NK) return op.rows(tb + ((i & 1) ? kTile : 0), i / (2 * NK), (i % (2 * NK)) / 2);
+      const int j = i - 4 * NK;
+      return op.columns(tb, j / NK, (j % NK) / ND, j % ND);
+    };
+    constexpr int kAhead = 8;            // operands on their way from LDS
+    bf16x8 x[kAhead], p0[2], p1[2];
+    f32x16 s0 = neg_lse16, d0 = neg_dlt16, s1 = neg_lse16, d1 = neg_dlt16;
+    float e[16];
+    auto exps = [&](int i, int per, const f32x16& s, const f32x16& d) {
+#pragma unroll
+      for (int r = per * i; r < per * (i + 1); ++r) {
+        e[r] = __builtin_amdgcn_exp2f(s[r] * scale_log2e) * d[r];
+        asm volatile("" : "+v"(e[r]));      // here, not next to its first use
+      }
+    };
+    auto pack = [&](int i, int per, bf16x8 (&p)[2]) {
+#pragma unroll
+      for (int r = per * i; r < per * (i + 1); ++r) p[r / 8][r % 8] = static_cast<bf16_t>(e[r]);
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) x[i] = operand(i);
+    fence();
+    static_for<6 * NK>([&](auto index) {
+      constexpr int i = decltype(index)::value;
+      bf16x8& a = x[i % kAhead];
+      pin(a);
+      constexpr int j = i % (2 * NK), ks = j / 2;
+      if constexpr (i < 2 * NK) {                            // products of block 0
+        if (j & 1) d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, doreg[ks], d0, 0, 0, 0);
+        else s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[ks], s0, 0, 0, 0);
+      } else if constexpr (i < 4 * NK) {                     // products of block 1 / exponentials of block 0
+        if (j & 1) d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, doreg[ks], d1, 0, 0, 0);
+        else s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[ks], s1, 0, 0, 0);
+      } else if constexpr (i < 5 * NK) {                     // dQ of block 0 / exponentials of block 1
+        constexpr int m = i - 4 * NK;
+        acc[m % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p0[m / ND], acc[m % ND], 0, 0, 0);
+      } else {                                     // dQ of block 1
+        constexpr int m = i - 5 * NK;
+        acc[m % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p1[m / ND], acc[m % ND], 0, 0, 0);
+      }
+      if constexpr (i + kAhead < 6 * NK) a = operand(i + kAhead);
+      if constexpr (i >= 2 * NK && i < 4 * NK) {
+        constexpr int per = 8 / NK;
+        constexpr int m = i - 2 * NK;
+        exps(m, per, s0, d0);
+        if (m > 0) pack(m - 1, per, p0);
+        if (m == 2 * NK - 1) pack(m, per, p0);
+      } else if constexpr (i >= 4 * NK && i < 5 * NK) {
+        constexpr int per = 16 / NK;
+        constexpr int m = i - 4 * NK;
+        exps(m, per, s1, d1);
+        if (m > 0) pack(m - 1, per, p1);
+        if (m == NK - 1) pack(m, per, p1);
+      }
+      fence();
+    });
+  };
+
+  // tile t is computed from buffer t & 1 while tile t + 1 is on its way into the other one
+  load_tile(0);
+  wait_loads();
+  __syncthreads();
+#pragma unroll 1
   for (int t = 0; t < n_tiles; ++t) {
-    __syncthreads();                 // tile t is in LDS; everyone is done with tile t-1 (its buffer is written next)
-    if (t + 1 < n_tiles) store_tile(t + 1, regs);
-    if (t + 2 < n_tiles) load_tile(t + 2, regs);
-    tb = lds + (t & 1) * G_::kBufDq;
-    pos_lds = pos_lds_base + (t & 1) * BN;
-    int mode = -1, jt = 0;
+    if (t + 1 < n_tiles) load_tile(t + 1);
+    const bf16_t* tb = lds + (t & 1) * kBuf;
+    const int* pos = pos_lds_base + (t & 1) * BN;
+    int mode = -1, jt = 0, slots = 0;
     if (r0 < n) {
       if (t < n_win_tiles) {
         jt = jt0 + t * BN;
         if (!(jt > r_hi || jt + BN - 1 < r0 - window + 1))
           mode = ((jt + BN - 1 <= r0) && (jt >= r_hi - window + 1)) ? 0 : 1;
       } else {
-        const int pmin = pos_rng_base[(t & 1) * 2], pmax = pos_rng_base[(t & 1) * 2 + 1];
-        if (pmin <= r_hi - window) {
-          const bool full = (t - n_win_tiles + 1) * BN <= cnt;
-          mode = (full && pmax <= r0 - window) ? 0 : 2;
-        }
+        // an entry counts once it has left the window of the wave's last row and needs no mask once it has left the first's
+        slots = cnt - (t - n_win_tiles) * BN;
+        int pv = pos[lane];
+        pv = lane < slots ? pv : 0x7FFFFFFF;
+        if (__builtin_amdgcn_ballot_w64(pv <= r_hi - window) != 0ull)
+          mode = __builtin_amdgcn_ballot_w64(pv > r0 - window) == 0ull ? 0 : 2;
       }
     }
     mode = __builtin_amdgcn_readfirstlane(mode);
-    if (mode == 0) compute(0, jt);
-    else if (mode == 1) compute(1, jt);
-    else if (mode == 2) compute(2, jt);
+    // Two steps in sequence rather than if / else, so that the accumulators stay in place across the plain body.
+    if (mode == 0) {
+      compute_plain(tb);
+      mode = -1;
+    }
+    asm volatile("" : "+s"(mode));
+    if (mode == 1) compute(1, tb, pos, jt, slots);
+    else if (mode == 2) compute(2, tb, pos, jt, slots);
+    wait_loads();
+    __syncthreads();                 // tile t + 1 is in LDS; everyone is done with tile t
   }
 
   // ---- epilogue: dQ = scale * acc, staged through LDS, rows stored coalesced ---------------------------------
-  __syncthreads();
   {
     bf16_t* orow = lds + (32 * wv + ql) * OS + 4 * hb;
 #pragma unroll
@@ -281,24 +354,20 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
   }
   __syncthreads();
   {
-    bf16_t* obase = static_cast<bf16_t*>(A.dq) + ((int64_t)(lo + i0) * Hq + hq) * D;
+    const int k_piece = tid % PPR, k_row = tid / PPR;
+    bf16_t* obase = static_cast<bf16_t*>(A.dq) + ((int64_t)(lo + i0) * Hq + unit * HW) * D;
     const int64_t orow_stride = (int64_t)Hq * D;
 #pragma unroll
     for (int p = 0; p < BM / RPP; ++p) {
-      const int row = p * RPP + k_row;
-      if (i0 + row < n)
-        *reinterpret_cast<u32x4*>(obase + row * orow_stride + k_piece * 8) =
+      const int row = p * RPP + k_row, prow = HW == 1 ? row : row % 32, hd = HW == 1 ? 0 : row / 32;
+      if (i0 + prow < n)
+        *reinterpret_cast<u32x4*>(obase + prow * orow_stride + hd * D + k_piece * 8) =
             *reinterpret_cast<const u32x4*>(lds + row * OS + k_piece * 8);
     }
   }
 }
 
 
-
-template <int D> struct QTileRegs {
-  u32x4 a[Geo<D>::KPASS], b[Geo<D>::KPASS];
-  float stat;     // threads 0..63: lse (base-2 domain) of a query of the tile, threads 64..127: its delta
-};
 
 // train_dkv_mfma_kernel<FAR>: one workgroup = 128 keys of one (sequence, KV head), 4 waves x 32 keys; a lane owns one
 // key column.  It walks 64-query tiles of every query head of the group that can see its keys:
@@ -315,8 +384,7 @@ template <int D, bool FAR>
 __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, float scale_log2e, float* far_dk,
                                          float* far_dv, int block, bf16_t* lds, float* stat_base) {
   LTEA_GEO(D);
-  constexpr int kQ = 0, kQt = BN * KS, kO = BN * KS + BN * VS, kOt = 2 * BN * KS + BN * VS;
-  static_assert(G_::kBufDkv >= BM * OS, "epilogue staging must fit in the tile buffer");
+  static_assert(2 * kBuf >= BM * OS, "epilogue staging must fit in the tile buffers");
 
   const int Hq = A.Hq, Hkv = A.Hkv, window = A.window, cap = A.budget;
   const int G = Hq / Hkv;
@@ -414,119 +482,167 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
   const uint32_t q_row_bytes = (uint32_t)A.q_st * 2u, o_row_bytes = (uint32_t)(Hq * D) * 2u;
   const uint32_t q_bytes = (uint32_t)(n - 1) * q_row_bytes + (uint32_t)(D * 2);
   const uint32_t o_bytes = (uint32_t)(n - 1) * o_row_bytes + (uint32_t)(D * 2);
-  const int k_piece = tid % PPR, k_row = tid / PPR;
-  auto load_tile = [&](int it, QTileRegs<D>& R) {
+  const int ld_row = G_::RPI * wv + lane / PPR;        // global -> LDS as in the dQ role
+  const uint32_t ld_col = (uint32_t)((lane % PPR) ^ both_ways_swizzle<D>(ld_row)) * 16u;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  const uint32_t stat_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)stat_base;
+  auto load_tile = [&](int it) {
     const int g = it / n_qt, t = it - g * n_qt;
     const int hq = h * G + g;
     const int qt = (qt_first + t) * BN;
-    const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(q + (int64_t)lo * A.q_st + (int64_t)hq * A.q_sh), 0, q_bytes, 0x00020000);
-    const auto rs_o = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(dout + ((int64_t)lo * Hq + hq) * D), 0, o_bytes, 0x00020000);
+    const u32x4 rs_q = make_raw_rsrc(q + (int64_t)lo * A.q_st + (int64_t)hq * A.q_sh, q_bytes);
+    const u32x4 rs_o = make_raw_rsrc(dout + ((int64_t)lo * Hq + hq) * D, o_bytes);
+    const uint32_t dst = lds_base + (uint32_t)((it & 1) * kBuf * 2 + wv * 1024);
+    uint32_t q_off = (uint32_t)(qt + ld_row) * q_row_bytes + ld_col, o_off = (uint32_t)(qt + ld_row) * o_row_bytes + ld_col;
 #pragma unroll
-    for (int p = 0; p < KPASS; ++p) {
-      const uint32_t row = (uint32_t)(qt + k_row + p * RPP);
-      R.a[p] = __builtin_amdgcn_raw_buffer_load_b128(rs_q, row * q_row_bytes + (uint32_t)k_piece * 16u, 0, 0);
-      R.b[p] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, row * o_row_bytes + (uint32_t)k_piece * 16u, 0, 0);
+    for (int i = 0; i < G_::IPW; ++i) {
+      dma16(rs_q, dst + (uint32_t)(i * 4096), q_off);
+      dma16(rs_o, dst + (uint32_t)(kTile * 2 + i * 4096), o_off);
+      q_off += (uint32_t)(4 * G_::RPI) * q_row_bytes;
+      o_off += (uint32_t)(4 * G_::RPI) * o_row_bytes;
     }
-    if (tid < 2 * BN) {
-      const int qrow = qt + (tid & (BN - 1));
-      const int qc = qrow < n ? qrow : n - 1;
-      const int64_t idx = (int64_t)hq * A.total + lo + qc;
-      R.stat = tid < BN ? A.lse[idx] * 1.4426950408889634f : A.delta[idx];
+    if (wv < 2) {       // [-lse / scale of the 64 queries | their -delta], zeros past the sequence
+      const float* src = A.delta + (int64_t)(wv == 0 ? Hq : 0) * A.total + (int64_t)hq * A.total + lo;
+      dma4(make_raw_rsrc(src, (uint32_t)n * 4u), stat_lds + (uint32_t)(((it & 1) * 2 + wv) * BN * 4), (uint32_t)(qt + lane) * 4u);
     }
   };
-  static_assert(RPP % 4 == 0, "row passes must preserve the swizzle phase");
-  const int p_st_off = k_row * KS + k_piece * 8;
-  const int t_st_off = k_row * VS + (((k_piece >> 2) ^ chunk_swizzle<D>(k_row)) << 5) + (k_piece & 3) * 8;
-  auto store_tile = [&](int it, const QTileRegs<D>& R) {
-    bf16_t* sb = lds + (it & 1) * G_::kBufDkv;
-#pragma unroll
-    for (int p = 0; p < KPASS; ++p) {
-      *reinterpret_cast<u32x4*>(sb + kQ + p_st_off + p * RPP * KS) = R.a[p];
-      *reinterpret_cast<u32x4*>(sb + kQt + t_st_off + p * RPP * VS) = R.a[p];
-      *reinterpret_cast<u32x4*>(sb + kO + p_st_off + p * RPP * KS) = R.b[p];
-      *reinterpret_cast<u32x4*>(sb + kOt + t_st_off + p * RPP * VS) = R.b[p];
-    }
-    if (tid < 2 * BN) stat_base[(it & 1) * 2 * BN + tid] = R.stat;     // [lse of the 64 queries | their delta]
-  };
-  const bf16_t* tb = lds;            // tile buffer and row statistics of the tile being computed
-  const float *lse_lds = stat_base, *dlt_lds = stat_base + BN;
+  const Operands<D> op(lane);
+  constexpr int NK = D / 16, ND = D / 32;
 
-  const int a_row_off = tile_row_of_mfma_row(ql) * KS + 8 * hb;        // + 32*qb*KS + 16*ks
-  const int tr_row = 8 * hb + ((lane & 15) >> 2);
-  const int tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const int tr_swz = chunk_swizzle<D>(tr_row);
-  const int a_tr_off = tr_row * VS + tr_col;
-
-  f32x16 dva[D / 32], dka[D / 32];
+  f32x16 dva[ND], dka[ND];
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
+  for (int db = 0; db < ND; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dva[db][r] = 0.f; dka[db][r] = 0.f; }
 
-  auto compute = [&](const bool masked, int qt) {
+  // register r of a product is the tile's query 32*qb + 16*(r/8) + 8*hb + r%8; the products start from -lse / scale and -delta
+  auto start_values = [&](const float* st, int qb) {
+    f32x16 x;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const f32x4 y = *reinterpret_cast<const f32x4*>(st + 32 * qb + 16 * (r4 / 2) + 8 * hb + 4 * (r4 % 2));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[4 * r4 + e] = y[e];
+    }
+    return x;
+  };
+
+  auto compute_masked = [&](const bf16_t* tb, const float* st, int qt) {
 #pragma unroll 1
     for (int qb = 0; qb < 2; ++qb) {
-      f32x16 sc, dp;
+      f32x16 sc = start_values(st, qb), dp = start_values(st + BN, qb);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { sc[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 aq = *reinterpret_cast<const bf16x8*>(tb + kQ + a_row_off + 32 * qb * KS + 16 * ks);
-        const bf16x8 ao = *reinterpret_cast<const bf16x8*>(tb + kO + a_row_off + 32 * qb * KS + 16 * ks);
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq, kreg[ks], sc, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ao, vreg[ks], dp, 0, 0, 0);
+      for (int ks = 0; ks < NK; ++ks) {
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.rows(tb, qb, ks), kreg[ks], sc, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.rows(tb + kTile, qb, ks), vreg[ks], dp, 0, 0, 0);
       }
-      // register r is the tile's query 32*qb + 16*(r/8) + 8*hb + r%8
       bf16x8 pp[2], ps[2];
 #pragma unroll
-      for (int r8 = 0; r8 < 2; ++r8) {
-        const int row0 = 32 * qb + 16 * r8 + 8 * hb;
-        const f32x4 l0 = *reinterpret_cast<const f32x4*>(lse_lds + row0), l1 = *reinterpret_cast<const f32x4*>(lse_lds + row0 + 4);
-        const f32x4 d0 = *reinterpret_cast<const f32x4*>(dlt_lds + row0), d1 = *reinterpret_cast<const f32x4*>(dlt_lds + row0 + 4);
+      for (int r = 0; r < 16; ++r) {
+        const int row = 32 * qb + 16 * (r / 8) + 8 * hb + r % 8;
+        float p = __builtin_amdgcn_exp2f(sc[r] * scale_log2e);
+        p = ((unsigned)(qt + row - q_lo) < q_span) ? p : 0.f;
+        pp[r / 8][r % 8] = static_cast<bf16_t>(p);
+        ps[r / 8][r % 8] = static_cast<bf16_t>(p * dp[r]);
+      }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float l = e < 4 ? l0[e] : l1[e - 4];
-          const float dl = e < 4 ? d0[e] : d1[e - 4];
-          float p = __builtin_amdgcn_exp2f(fmaf(sc[8 * r8 + e], scale_log2e, -l));
-          if (masked) p = ((unsigned)(qt + row0 + e - q_lo) < q_span) ? p : 0.f;
-          pp[r8][e] = static_cast<bf16_t>(p);
-          ps[r8][e] = static_cast<bf16_t>(p * (dp[8 * r8 + e] - dl));
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int db = 0; db < ND; ++db) {
+          dva[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.columns(tb + kTile, qb, kk, db), pp[kk], dva[db], 0, 0, 0);
+          dka[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op.columns(tb, qb, kk, db), ps[kk], dka[db], 0, 0, 0);
         }
-      }
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db) {
-        const bf16_t* ao = tb + kOt + a_tr_off + 32 * qb * VS + ((db ^ tr_swz) << 5);
-        const bf16_t* aq = tb + kQt + a_tr_off + 32 * qb * VS + ((db ^ tr_swz) << 5);
-        const bf16x8 o0 = load_transposed(ao, VS), o1 = load_transposed(ao + 16 * VS, VS);
-        const bf16x8 q0 = load_transposed(aq, VS), q1 = load_transposed(aq + 16 * VS, VS);
-        dva[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o0, pp[0], dva[db], 0, 0, 0);
-        dva[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o1, pp[1], dva[db], 0, 0, 0);
-        dka[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0, ps[0], dka[db], 0, 0, 0);
-        dka[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q1, ps[1], dka[db], 0, 0, 0);
-      }
     }
   };
 
-  // tile `it` is computed from buffer it & 1 while the next one is stored into the other and the one after is in flight
-  QTileRegs<D> regs;
-  load_tile(0, regs);
-  store_tile(0, regs);
-  if (n_iter > 1) load_tile(1, regs);
+  // A tile that every key of the wave is seen by: 8 NK matrix instructions without a branch, arranged as in the dQ role.
+  auto compute_plain = [&](const bf16_t* tb, const float* st) {
+    auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+    auto operand = [&](int i) {          // of the tile's i-th matrix instruction
+      const int blk = i / (2 * NK) % 2, j = i % (2 * NK);
+      if (i < 4 * NK) return op.rows(tb + ((j & 1) ? kTile : 0), blk, j / 2);
+      return op.columns(tb + ((j & 1) ? 0 : kTile), blk, j / (2 * ND), j / 2 % ND);
+    };
+    constexpr int kAhead = 8;            // operands on their way from LDS
+    bf16x8 x[kAhead], p0[2], z0[2], p1[2], z1[2];
+    f32x16 s0 = start_values(st, 0), d0 = start_values(st + BN, 0), s1, d1;
+    float ep[16], ez[16];
+    constexpr int per = 8 / NK;     // elements behind each of 2 NK matrix instructions
+    auto exps = [&](int i, const f32x16& s, const f32x16& d) {
+#pragma unroll
+      for (int r = per * i; r < per * (i + 1); ++r) {
+        ep[r] = __builtin_amdgcn_exp2f(s[r] * scale_log2e);
+        ez[r] = ep[r] * d[r];
+        asm volatile("" : "+v"(ep[r]), "+v"(ez[r]));      // here, not next to their first use
+      }
+    };
+    auto pack = [&](int i, bf16x8 (&p)[2], bf16x8 (&z)[2]) {
+#pragma unroll
+      for (int r = per * i; r < per * (i + 1); ++r) {
+        p[r / 8][r % 8] = static_cast<bf16_t>(ep[r]);
+        z[r / 8][r % 8] = static_cast<bf16_t>(ez[r]);
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) x[i] = operand(i);
+    fence();
+    static_for<8 * NK>([&](auto index) {
+      constexpr int i = decltype(index)::value;
+      bf16x8& a = x[i % kAhead];
+      pin(a);
+      constexpr int j = i % (2 * NK), ks = j / 2, db = j / 2 % ND, kk = j / (2 * ND);
+      if constexpr (i < 2 * NK) {                            // products of block 0
+        if (j & 1) d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vreg[ks], d0, 0, 0, 0);
+        else s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kreg[ks], s0, 0, 0, 0);
+      } else if constexpr (i < 4 * NK) {                     // products of block 1 / exponentials of block 0
+        if (j & 1) d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, vreg[ks], d1, 0, 0, 0);
+        else s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, kreg[ks], s1, 0, 0, 0);
+      } else if constexpr (i < 6 * NK) {                     // dV, dK of block 0 / exponentials of block 1
+        if (j & 1) dka[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, z0[kk], dka[db], 0, 0, 0);
+        else dva[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p0[kk], dva[db], 0, 0, 0);
+      } else {                                     // dV, dK of block 1
+        if (j & 1) dka[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, z1[kk], dka[db], 0, 0, 0);
+        else dva[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, p1[kk], dva[db], 0, 0, 0);
+      }
+      if constexpr (i + kAhead < 8 * NK) a = operand(i + kAhead);
+      if (i == NK) { s1 = start_values(st, 1); d1 = start_values(st + BN, 1); }
+      if constexpr (i >= 2 * NK && i < 4 * NK) {
+        exps(j, s0, d0);
+        if (j > 0) pack(j - 1, p0, z0);
+        if (j == 2 * NK - 1) pack(j, p0, z0);
+      } else if constexpr (i >= 4 * NK && i < 6 * NK) {
+        exps(j, s1, d1);
+        if (j > 0) pack(j - 1, p1, z1);
+        if (j == 2 * NK - 1) pack(j, p1, z1);
+      }
+      fence();
+    });
+  };
+
+  // tile `it` is computed from buffer it & 1 while the next one is on its way into the other
+  load_tile(0);
+  wait_loads();
+  __syncthreads();
+#pragma unroll 1
   for (int it = 0; it < n_iter; ++it) {
-    __syncthreads();
-    if (it + 1 < n_iter) store_tile(it + 1, regs);
-    if (it + 2 < n_iter) load_tile(it + 2, regs);
-    tb = lds + (it & 1) * G_::kBufDkv;
-    lse_lds = stat_base + (it & 1) * 2 * BN;
-    dlt_lds = lse_lds + BN;
-    const int t = it % n_qt;
-    const int qt = (qt_first + t) * BN;
+    if (it + 1 < n_iter) load_tile(it + 1);
+    const bf16_t* tb = lds + (it & 1) * kBuf;
+    const float* st = stat_base + (it & 1) * 2 * BN;
+    const int qt = (qt_first + it % n_qt) * BN;
     // does any key of this wave see a query of the tile, and do all of them see all of it?
     const bool touches = q_span != 0u && q_lo < qt + BN && q_hi > qt;
     const bool covers = q_span != 0u && q_lo <= qt && q_hi >= qt + BN;
-    if (__builtin_amdgcn_ballot_w64(touches) == 0ull) continue;
-    if (__builtin_amdgcn_ballot_w64(!covers) == 0ull) compute(false, qt);
-    else compute(true, qt);
+    int mode = __builtin_amdgcn_ballot_w64(touches) == 0ull ? -1 : (__builtin_amdgcn_ballot_w64(!covers) == 0ull ? 0 : 1);
+    mode = __builtin_amdgcn_readfirstlane(mode);
+    // Two steps in sequence rather than if / else, so that the accumulators stay in place across the plain body.
+    if (mode == 0) {
+      compute_plain(tb, st);
+      mode = -1;
+    }
+    asm volatile("" : "+s"(mode));
+    if (mode == 1) compute_masked(tb, st, qt);
+    wait_loads();
+    __syncthreads();
   }
 
   // ---- epilogue: accumulator register r of block db is feature d = 32*db + 8*(r/4) + 4*hb + r%4 of the lane's key ---
@@ -614,6 +730,7 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
         *reinterpret_cast<bf16x4*>(orow + 32 * db + 8 * g4) = w4;
       }
     __syncthreads();
+    const int k_piece = tid % PPR, k_row = tid / PPR;
     bf16_t* obase = outs[which] + ((int64_t)(lo + j0) * Hkv + h) * D;
     const int64_t orow_stride = (int64_t)Hkv * D;
 #pragma unroll
@@ -626,25 +743,38 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
   }
 }
 
-// delta = <dO, O> per (query, query head), read by the dK / dV passes: eight lanes per 128-byte row.
+// -delta = -<dO, O> and -lse / scale per (query, query head), from which the products of the other kernels start.  One
+// workgroup = kDeltaTokens tokens of one head, heads fastest, PPR lanes per row: the results, [head][token], are written next
+// to each other and all of a lane's rows are in flight together.
+constexpr int kDeltaTokens = 128;
 template <int D>
 __global__ void __launch_bounds__(kThreads)
-train_delta_mfma_kernel(TrainArgs A) {
-  constexpr int PPR = Geo<D>::PPR;
-  const int64_t row = (int64_t)blockIdx.x * (kThreads / PPR) + threadIdx.x / PPR;
+train_delta_mfma_kernel(TrainArgs A, float inv_scale) {
+  constexpr int PPR = Geo<D>::PPR, RPP = Geo<D>::RPP, N = kDeltaTokens / RPP;
+  const int hq = (int)(blockIdx.x % (unsigned)A.Hq);
+  const int64_t tok0 = (int64_t)(blockIdx.x / (unsigned)A.Hq) * kDeltaTokens + threadIdx.x / PPR;
   const int piece = threadIdx.x % PPR;
-  const int64_t rows = A.total * A.Hq;
-  const int64_t rc = row < rows ? row : rows - 1;
-  const bf16x8 o8 = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(A.out) + rc * D + piece * 8);
-  const bf16x8 d8 = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(A.dout) + rc * D + piece * 8);
-  float acc = 0.f;
+  bf16x8 o8[N], d8[N];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc = fmaf(static_cast<float>(d8[e]), static_cast<float>(o8[e]), acc);
+  for (int i = 0; i < N; ++i) {
+    const int64_t tok = tok0 + i * RPP < A.total ? tok0 + i * RPP : A.total - 1;
+    const int64_t at = (tok * A.Hq + hq) * D + piece * 8;
+    o8[i] = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(A.out) + at);
+    d8[i] = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(A.dout) + at);
+  }
 #pragma unroll
-  for (int off = PPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-  if (piece == 0 && row < rows) {
-    const int64_t tok = row / A.Hq;
-    A.delta[(row - tok * A.Hq) * A.total + tok] = acc;
+  for (int i = 0; i < N; ++i) {
+    float acc = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = fmaf(static_cast<float>(d8[i][e]), static_cast<float>(o8[i][e]), acc);
+#pragma unroll
+    for (int off = PPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
+    const int64_t tok = tok0 + i * RPP;
+    if (piece == 0 && tok < A.total) {
+      const int64_t at = (int64_t)hq * A.total + tok;
+      A.delta[at] = -acc;
+      A.delta[(int64_t)A.Hq * A.total + at] = -A.lse[at] * inv_scale;
+    }
   }
 }
 
@@ -652,24 +782,23 @@ train_delta_mfma_kernel(TrainArgs A) {
 // the candidates of early positions face almost every later query), the others compute dQ and fill the compute
 // units that the far pass leaves idle.
 // (D = 128 needs more than 256 registers per lane for the dK / dV role: one wave per SIMD there.)
-template <int D>
+template <int D, int HW>
 __global__ void __launch_bounds__(kThreads, D == 64 ? 2 : 1)
 train_dq_far_mfma_kernel(TrainArgs A, int tiles_upper, int n_work, float scale_log2e, float* far_dk, float* far_dv,
                          int far_blocks) {
-  __shared__ __align__(16) bf16_t lds[2 * Geo<D>::kBuf];  // two tile buffers; the two roles lay their tiles out in them
-  __shared__ __align__(16) float stat_lds[4 * BN];
-  __shared__ int pos_rng[4];
+  __shared__ __align__(1024) bf16_t lds[2 * Geo<D>::kBuf];  // two tile buffers, for either role
+  __shared__ __align__(256) float stat_lds[4 * BN];
   if ((int)blockIdx.x < far_blocks)
     dkv_body<D, true>(A, 0, scale_log2e, far_dk, far_dv, (int)blockIdx.x, lds, stat_lds);
   else
-    dq_body<D>(A, tiles_upper, n_work, scale_log2e, (int)blockIdx.x - far_blocks, lds, reinterpret_cast<int*>(stat_lds), pos_rng);
+    dq_body<D, HW>(A, tiles_upper, n_work, scale_log2e, (int)blockIdx.x - far_blocks, lds, reinterpret_cast<int*>(stat_lds));
 }
 
 template <int D>
 __global__ void __launch_bounds__(kThreads, D == 64 ? 2 : 1)
 train_dkv_band_mfma_kernel(TrainArgs A, int tiles_upper, float scale_log2e, float* far_dk, float* far_dv) {
-  __shared__ __align__(16) bf16_t lds[2 * Geo<D>::kBufDkv];
-  __shared__ __align__(16) float stat_lds[4 * BN];
+  __shared__ __align__(1024) bf16_t lds[2 * Geo<D>::kBuf];
+  __shared__ __align__(256) float stat_lds[4 * BN];
   dkv_body<D, false>(A, tiles_upper, scale_log2e, far_dk, far_dv, (int)blockIdx.x, lds, stat_lds);
 }
 
@@ -689,23 +818,22 @@ bool train_mfma_supported(const TrainArgs& A, int D) {
 // delta, then [far pass of dK / dV | dQ] in one launch, then the band pass of dK / dV (which adds the far pass in).
 // far_dk / far_dv: fp32 scratch, [far_chunks][n_seqs * Hkv][budget][D] each (only rows below ret_count are touched).
 namespace {
-template <int D>
+template <int D, int HW>
 hipError_t run_mfma(const TrainArgs& A, hipStream_t stream) {
-  constexpr int PPR = Geo<D>::PPR;
   const float sl2 = A.scale * 1.4426950408889634f;
-  const int64_t rows = A.total * A.Hq;
-  hipLaunchKernelGGL(train_delta_mfma_kernel<D>, dim3((unsigned)((rows + kThreads / PPR - 1) / (kThreads / PPR))),
-                     dim3(kThreads), 0, stream, A);
+  const int64_t delta_blocks = (A.total + kDeltaTokens - 1) / kDeltaTokens * A.Hq;
+  hipLaunchKernelGGL(train_delta_mfma_kernel<D>, dim3((unsigned)delta_blocks), dim3(kThreads), 0, stream, A, 1.0f / A.scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int per_head = (A.max_seqlen + BM - 1) / BM;
   int64_t far_blocks = A.budget > 0 ? (int64_t)A.n_seqs * A.Hkv * per_head * A.far_chunks : 0;
   far_blocks = (far_blocks + 7) / 8 * 8;      // keeps the dQ role's workgroup-to-XCD pattern
   const int64_t tiles_upper = (A.total + BM - 1) / BM + A.n_seqs;
-  const int64_t n_work = tiles_upper * A.Hq;
+  const int64_t dq_tiles = (A.total + BM / HW - 1) / (BM / HW) + A.n_seqs;
+  const int64_t n_work = dq_tiles * (A.Hq / HW);
   const int64_t dq_blocks = (n_work + 7) / 8 * 8;
-  hipLaunchKernelGGL(train_dq_far_mfma_kernel<D>, dim3((unsigned)(far_blocks + dq_blocks)), dim3(kThreads), 0, stream, A,
-                     (int)tiles_upper, (int)n_work, sl2, A.far_dk, A.far_dv, (int)far_blocks);
+  hipLaunchKernelGGL((train_dq_far_mfma_kernel<D, HW>), dim3((unsigned)(far_blocks + dq_blocks)), dim3(kThreads), 0, stream, A,
+                     (int)dq_tiles, (int)n_work, sl2, A.far_dk, A.far_dv, (int)far_blocks);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(train_dkv_band_mfma_kernel<D>, dim3((unsigned)((tiles_upper * A.Hkv + 7) / 8 * 8)), dim3(kThreads), 0, stream, A,
@@ -715,7 +843,9 @@ hipError_t run_mfma(const TrainArgs& A, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_train_backward_mfma(const TrainArgs& A, int D, hipStream_t stream) {
-  return D == 64 ? run_mfma<64>(A, stream) : run_mfma<128>(A, stream);
+  const bool by_head = (A.Hq / A.Hkv) % 4 == 0;      // one query head per wave (see dq_body)
+  if (D == 64) return by_head ? run_mfma<64, 4>(A, stream) : run_mfma<64, 1>(A, stream);
+  return by_head ? run_mfma<128, 4>(A, stream) : run_mfma<128, 1>(A, stream);
 }
 
 }  // namespace ltea
