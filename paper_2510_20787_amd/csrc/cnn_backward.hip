@@ -8,13 +8,14 @@
 //   1. forward again, keeping the pre-activations y_l and the activations a_l = silu(y_l) of every layer
 //      (fp32 [Hkv][T][C_l] each); the features of layer 0 are copied to a dense fp32 array first unless the bf16
 //      kernels read k / v themselves;
-//   2. d y_L = dz * w_out * silu'(y_L);  d w_out = sum_t dz * silu(y_L),  d b_out = sum_t dz;
+//   2. d y_L = dz * w_out * silu'(y_L);  d w_out = sum_t dz * silu(y_L),  d b_out = sum_t dz   (the last layer's forward
+//      launch: neither its pre-activations nor its activations go to memory);
 //   3. for l = L .. 1:  d bias_l = sum_t d y_l;
 //                       d W_l[c][m][tap] = sum_t d y_l[t][c] * a_{l-1}[t + off(tap)][m]      (inside the sequence)
 //                       d a_{l-1}[t][m]  = sum_{tap, c} W_l[c][m][tap] * d y_l[t - off(tap)][c]
 //                       d y_{l-1} = d a_{l-1} * silu'(y_{l-1})        (l > 1)   or   dk, dv = d a_0   (l = 1).
-// Sums over tokens are taken in two stages: per chunk of kTokChunk (weights) or kColChunk (column sums) tokens into a
-// partial array, then over the chunks.
+// Sums over tokens are taken in two stages: per chunk of kTokChunk (weights) or TMC tokens (the column sums, by the
+// workgroup that computes the column) into a partial array, then over the chunks.
 #include <type_traits>
 
 #include "ltea_common.h"
@@ -26,36 +27,10 @@ namespace ltea {
 namespace {
 
 constexpr int kTokChunk = 512;   // tokens per partial of the weight products
-constexpr int kColChunk = 128;   // tokens per partial of the column sums
 
 __device__ __forceinline__ float silu_grad_f32(float y) {
   const float s = 1.0f / (1.0f + expf(-y));
   return s * (1.0f + y * (1.0f - s));
-}
-
-// seq_lo[t], seq_hi[t]: bounds of the sequence token t belongs to.
-__global__ void __launch_bounds__(256)
-token_bounds_kernel(const int32_t* __restrict__ cu, int n_seqs, int64_t total, int32_t* __restrict__ seq_lo,
-                    int32_t* __restrict__ seq_hi) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= total) return;
-  const int s = find_sequence(cu, n_seqs, t);
-  seq_lo[t] = cu[s];
-  seq_hi[t] = cu[s + 1];
-}
-
-// d y_L[h][t][c] = dz[h][t] * w_out[h][c] * silu'(y_L[h][t][c])
-template <typename T>
-__global__ void __launch_bounds__(256)
-out_proj_backward_kernel(const float* __restrict__ dz, const T* __restrict__ w_out, const float* __restrict__ pre, int C,
-                         int64_t total, float* __restrict__ dpre) {
-  const int h = blockIdx.y;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t tok = idx / C;
-  const int c = (int)(idx - tok * C);
-  if (tok >= total) return;
-  const int64_t i = ((int64_t)h * total + tok) * C + c;
-  dpre[i] = dz[(int64_t)h * total + tok] * to_f32(w_out[(int64_t)h * C + c]) * silu_grad_f32(pre[i]);
 }
 
 // Layer-0 input as a dense fp32 array: a0[h][t][m] = concat(key, value) features of token t, moved in 16-byte pieces of
@@ -79,25 +54,43 @@ features_kernel(const T* __restrict__ k, const T* __restrict__ v, int64_t stride
   for (int i = 0; i < EPP / 4; ++i) dst[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
 }
 
-// The weights of one layer as two fp32 panels per head: wf[h][tap][m][c] (contraction over the input channels m: the
-// forward) and wb[h][tap][c][m] (contraction over the output channels c: the backward towards the input);
-// wq and wqf, when given, are wb's and wf's order in the storage type (operands of the bf16 matrix instruction on
-// bf16 storage: the first layer's forward, and the products towards the input).
+// What the launches after it read besides the inputs, in one launch.  blockIdx.y < n_layers: the weights of that layer in
+// the orders its kernels contract over, those that are not null: fp32 wf[h][tap][m][c] (over the input channels m: the
+// forward) and wb[h][tap][c][m] (over the output channels c: towards the input), and the same two orders, wqf and wq, in the
+// storage type (operands of the bf16 matrix instruction).  blockIdx.y == n_layers: seq_lo[t], seq_hi[t], the bounds of the
+// sequence token t belongs to.
+struct LayerPanels { const void* w; float *wf, *wb; void *wq, *wqf; int cin, cout, ks; int64_t n; };
+struct PrepareArgs {
+  LayerPanels layer[LTEA_MAX_CNN_LAYERS];
+  int n_layers;
+  const int32_t* cu;
+  int n_seqs;
+  int64_t total;
+  int32_t *seq_lo, *seq_hi;
+};
 template <typename T>
 __global__ void __launch_bounds__(256)
-weight_panels_kernel(const T* __restrict__ W, int Cin, int Cout, int ks, int64_t n, float* __restrict__ wf,
-                     float* __restrict__ wb, T* __restrict__ wq, T* __restrict__ wqf) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;     // over [h][c][m][tap]
-  if (i >= n) return;
-  const int tap = (int)(i % ks);
-  const int m = (int)((i / ks) % Cin);
-  const int c = (int)((i / ((int64_t)ks * Cin)) % Cout);
-  const int64_t h = i / ((int64_t)ks * Cin * Cout);
-  const float w = to_f32(W[i]);
-  wf[((h * ks + tap) * Cin + m) * Cout + c] = w;
-  wb[((h * ks + tap) * Cout + c) * Cin + m] = w;
-  if (wq != nullptr) wq[((h * ks + tap) * Cout + c) * Cin + m] = W[i];     // wb's order in the storage type
-  if (wqf != nullptr) wqf[((h * ks + tap) * Cin + m) * Cout + c] = W[i];   // wf's order in the storage type
+prepare_kernel(const PrepareArgs A) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if ((int)blockIdx.y == A.n_layers) {
+    if (i >= A.total) return;
+    const int s = find_sequence(A.cu, A.n_seqs, i);
+    A.seq_lo[i] = A.cu[s];
+    A.seq_hi[i] = A.cu[s + 1];
+    return;
+  }
+  const LayerPanels& L = A.layer[blockIdx.y];
+  if (i >= L.n) return;                                          // over [h][c][m][tap]
+  const int tap = (int)(i % L.ks);
+  const int m = (int)((i / L.ks) % L.cin);
+  const int c = (int)((i / ((int64_t)L.ks * L.cin)) % L.cout);
+  const int64_t h = i / ((int64_t)L.ks * L.cin * L.cout);
+  const T w = static_cast<const T*>(L.w)[i];
+  const int64_t fwd = ((h * L.ks + tap) * L.cin + m) * L.cout + c, back = ((h * L.ks + tap) * L.cout + c) * L.cin + m;
+  if (L.wf != nullptr) L.wf[fwd] = to_f32(w);
+  if (L.wb != nullptr) L.wb[back] = to_f32(w);
+  if (L.wq != nullptr) static_cast<T*>(L.wq)[back] = w;
+  if (L.wqf != nullptr) static_cast<T*>(L.wqf)[fwd] = w;
 }
 
 // The fp32 products below run on v_mfma_f32_32x32x2_f32 (fp32 operands, two contraction steps per instruction: lane l
@@ -144,20 +137,117 @@ __device__ __forceinline__ float4 masked_quad(float4 v, unsigned mask4) {
   return make_float4(mask4 & 1u ? v.x : 0.f, mask4 & 2u ? v.y : 0.f, mask4 & 4u ? v.z : 0.f, mask4 & 8u ? v.w : 0.f);
 }
 
+// Sums over a workgroup's TMC tokens of NS values per output column, from the sums of a lane's own rows, in a fixed order:
+// the two lane halves, then the waves that share the columns (four; two when a row of waves is 64 columns wide).  The
+// result is in the threads tid < 64 (NARROW: 32), column tid.  All threads of the workgroup call it; red: LDS that is free.
+template <int NS, bool NARROW>
+__device__ __forceinline__ void tile_column_sums(float (&x)[NS], float* red, int wv, int lane) {
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    x[i] = pair_sum(x[i]);
+    if (lane < 32) red[i * 128 + wv * 32 + lane] = x[i];
+  }
+  __syncthreads();
+  if (wv == 0) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const float* r = red + i * 128 + lane;
+      x[i] = NARROW ? ((r[0] + r[32 * (lane < 32)]) + r[64 * (lane < 32)]) + r[96 * (lane < 32)] : r[0] + r[64];
+    }
+  }
+}
+
+// Of the last layer's forward launch: the output projection and its backward.  dz [Hkv][T], w_out [Hkv][C]; part_* get the
+// sums over the workgroup's tokens ([tile of TMC tokens][Hkv][C], part_bout [tile][Hkv]).
+template <typename T> struct OutProj {
+  const float* dz;            // null: not the last layer
+  const T* w_out;
+  float *part_b, *part_wout, *part_bout;
+};
+
+// From the pre-activations y of a lane's tokens of column n (valid: n_ok) to d y and the column's sums.
+template <int U, bool NARROW, typename T, class TokenOf>
+__device__ __forceinline__ void out_proj_backward(const OutProj<T>& P, const f32x16 (&acc)[U], float bv, int h, int Hkv, int n,
+                                                  int N, bool n_ok, int64_t total, const TokenOf& token_of, float* dpre,
+                                                  float* red, int wv, int lane) {
+  const float wo = n_ok ? to_f32(P.w_out[(int64_t)h * N + n]) : 0.f;
+  float sum[3] = {0.f, 0.f, 0.f};        // of d y, dz * silu(y), dz
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    float g[16];                         // all requested before the first is used
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t t = token_of(16 * u + r);
+      g[r] = P.dz[(int64_t)h * total + (t < total ? t : 0)];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t t = token_of(16 * u + r);
+      if (t >= total || !n_ok) continue;
+      const float y = acc[u][r] + bv;
+      const float den = 1.0f + expf(-y), s = 1.0f / den;
+      const float d = g[r] * wo * (s * (1.0f + y * (1.0f - s)));
+      sum[0] += d;
+      sum[1] += g[r] * (y / den);
+      sum[2] += g[r];
+      dpre[((int64_t)h * total + t) * N + n] = d;
+    }
+  }
+  tile_column_sums<3, NARROW>(sum, red, wv, lane);
+  const int col = (int)blockIdx.y * 64 + lane;
+  if (wv == 0 && lane < (NARROW ? 32 : 64) && col < N) {
+    const int64_t row = (int64_t)blockIdx.x * Hkv + h;
+    P.part_b[row * N + col] = sum[0];
+    P.part_wout[row * N + col] = sum[1];
+    if (col == 0) P.part_bout[row] = sum[2];
+  }
+}
+
+// d y of the layer below from d a (acc), and its column sums over the workgroup's tokens.
+template <int U, bool NARROW, class TokenOf>
+__device__ __forceinline__ void hidden_backward(const f32x16 (&acc)[U], int h, int Hkv, int n, int N, bool n_ok, int64_t total,
+                                                const TokenOf& token_of, const float* pre_prev, float* dpre, float* part_b,
+                                                float* red, int wv, int lane) {
+  float sum[1] = {0.f};
+  // per sub-tile, all of the lane's pre-activations are requested before the first is used
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    float pp[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t t = token_of(16 * u + r);
+      pp[r] = pre_prev[(t < total && n_ok) ? ((int64_t)h * total + t) * N + n : 0];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int64_t t = token_of(16 * u + r);
+      if (t >= total || !n_ok) continue;
+      const float d = acc[u][r] * silu_grad_f32(pp[r]);
+      sum[0] += d;
+      dpre[((int64_t)h * total + t) * N + n] = d;
+    }
+  }
+  tile_column_sums<1, NARROW>(sum, red, wv, lane);
+  const int col = (int)blockIdx.y * 64 + lane;
+  if (wv == 0 && lane < (NARROW ? 32 : 64) && col < N) part_b[((int64_t)blockIdx.x * Hkv + h) * N + col] = sum[0];
+}
+
 // out[t][n] = sum_tap sum_k in[t + sign * off(tap)][k] * wt[tap][k][n]   (rows outside t's sequence count as zero)
 // for one head, as a tiled fp32 product: TMC tokens x TN outputs per workgroup.  A stage brings one contraction slice
 // of KCC channels into LDS: the input rows of the tile plus the extra rows that a group of up to GT taps reaches
 // (at most HALO), and those taps' weight rows; every staged input row then serves all taps of the group.  Whether a
 // tap's row lies in the token's own sequence is decided where the operand is read.  What is done with the result:
-//   mode 0 (forward)          pre = out + bias, act = silu(pre)
-//   mode 1 (hidden backward)  dpre_out = out * silu'(pre_prev)
+//   mode 0 (forward)          pre = out + bias, act = silu(pre); the last layer: d pre (out0) and the output projection's sums
+//   mode 1 (hidden backward)  dpre_out = out * silu'(pre_prev), and its column sums over the tile's tokens (part_b)
 //   mode 2 (input backward)   dk / dv [T][Hkv][D] of the storage type (n < D: key part)
 template <typename T, bool VEC, bool NARROW>
 __global__ void __launch_bounds__(256, 4)
 conv_product_kernel(const float* __restrict__ in, const float* __restrict__ wt, int K, int N, int ks, int dil, int sign,
                     const int32_t* __restrict__ seq_lo, const int32_t* __restrict__ seq_hi, int64_t total, int Hkv,
                     int mode, const float* __restrict__ bias, const float* __restrict__ pre_prev,
-                    float* __restrict__ out0, float* __restrict__ out1, T* __restrict__ dk, T* __restrict__ dv, int D) {
+                    float* __restrict__ out0, float* __restrict__ out1, T* __restrict__ dk, T* __restrict__ dv, int D,
+                    const OutProj<T> proj, float* __restrict__ part_b) {
   __shared__ __align__(16) float a_s[A_ROWS][RSA];     // [staged input row][channel of the slice]
   __shared__ __align__(16) float b_s[GT * KCC][RSB];   // [tap of the group][channel of the slice][output]
   const int h = blockIdx.z;
@@ -276,6 +366,10 @@ conv_product_kernel(const float* __restrict__ in, const float* __restrict__ wt, 
   auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
   if (mode == 0) {
     const float bv = n_ok ? bias[(int64_t)h * N + n] : 0.f;
+    if (proj.dz != nullptr) {
+      out_proj_backward<U, NARROW>(proj, acc, bv, h, Hkv, n, N, n_ok, total, token_of, out0, &a_s[0][0], wv, lane);
+      return;
+    }
 #pragma unroll
     for (int ur = 0; ur < 16 * U; ++ur) {
       const int64_t t = token_of(ur);
@@ -286,22 +380,7 @@ conv_product_kernel(const float* __restrict__ in, const float* __restrict__ wt, 
       out1[o] = silu_f32(y);
     }
   } else if (mode == 1) {
-    // per sub-tile, all of the lane's pre-activations are requested before the first is used
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float pp[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t t = token_of(16 * u + r);
-        pp[r] = pre_prev[(t < total && n_ok) ? ((int64_t)h * total + t) * N + n : 0];
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t t = token_of(16 * u + r);
-        if (t >= total || !n_ok) continue;
-        out0[((int64_t)h * total + t) * N + n] = acc[u][r] * silu_grad_f32(pp[r]);
-      }
-    }
+    hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b, &a_s[0][0], wv, lane);
   } else {
     T* dst = n < D ? dk : dv;
     const int col = n < D ? n : n - D;
@@ -330,7 +409,7 @@ __global__ void __launch_bounds__(256, 4)
 conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int64_t stride_tok, int64_t stride_head,
                        const bf16_t* __restrict__ wq, int D, int N, int ks, int dil, const int32_t* __restrict__ seq_lo,
                        const int32_t* __restrict__ seq_hi, int64_t total, const float* __restrict__ bias,
-                       float* __restrict__ pre, float* __restrict__ act) {
+                       float* __restrict__ pre, float* __restrict__ act, int Hkv, const OutProj<bf16_t> proj) {
   __shared__ __align__(16) bf16_t a_s[A_ROWS][RSQ];       // [staged token row][channel of the slice]
   __shared__ __align__(16) bf16_t b_s[GT][TN][RSQ];       // [tap of the group][output][channel of the slice]
   const int K = 2 * D;
@@ -437,11 +516,17 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
   }
   // accumulator register r of lane half hb: token row 8*(r/4) + 4*hb + r%4 of the sub-tile, output column ql
   const int n = n0 + col0 + ql;
-  if (n >= N) return;
-  const float bv = bias[(int64_t)h * N + n];
+  const bool n_ok = n < N;
+  auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
+  const float bv = n_ok ? bias[(int64_t)h * N + n] : 0.f;
+  if (proj.dz != nullptr) {       // the only layer: pre receives d pre
+    out_proj_backward<U, NARROW>(proj, acc, bv, h, Hkv, n, N, n_ok, total, token_of, pre, reinterpret_cast<float*>(&a_s[0][0]), wv, lane);
+    return;
+  }
+  if (!n_ok) return;
 #pragma unroll
   for (int ur = 0; ur < 16 * U; ++ur) {
-    const int64_t t = t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4);
+    const int64_t t = token_of(ur);
     if (t >= total) continue;
     const int64_t o = ((int64_t)h * total + t) * N + n;
     const float y = acc[ur / 16][ur % 16] + bv;
@@ -464,7 +549,7 @@ __global__ void __launch_bounds__(256, 4)
 conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ wqf, int K, int N, int ks, int dil,
                       const int32_t* __restrict__ seq_lo, const int32_t* __restrict__ seq_hi, int64_t total, int Hkv,
                       int mode, const float* __restrict__ pre_prev, float* __restrict__ out0, bf16_t* __restrict__ dk,
-                      bf16_t* __restrict__ dv, int D) {
+                      bf16_t* __restrict__ dv, int D, float* __restrict__ part_b) {
   __shared__ __align__(16) bf16_t a_s[3][A_ROWS][RSS];    // [term of the split][staged token row][channel of the slice]
   __shared__ __align__(16) bf16_t b_s[GT][TN][RSS];       // [tap of the group][output][channel of the slice]
   const int h = blockIdx.z;
@@ -590,27 +675,15 @@ conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ w
   }
   // accumulator register r of lane half hb: token row 8*(r/4) + 4*hb + r%4 of the sub-tile, output column ql
   const int n = n0 + col0 + ql;
-  if (n >= N) return;
+  const bool n_ok = n < N;
   auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
   if (mode == 1) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float pp[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t t = token_of(16 * u + r);
-        pp[r] = pre_prev[t < total ? ((int64_t)h * total + t) * N + n : 0];
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t t = token_of(16 * u + r);
-        if (t < total) out0[((int64_t)h * total + t) * N + n] = acc[u][r] * silu_grad_f32(pp[r]);
-      }
-    }
+    hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b,
+                               reinterpret_cast<float*>(&a_s[0][0][0]), wv, lane);
   } else {
     bf16_t* dst = n < D ? dk : dv;
     const int col = n < D ? n : n - D;
-    if (dst != nullptr) {
+    if (dst != nullptr && n_ok) {
 #pragma unroll
       for (int ur = 0; ur < 16 * U; ++ur) {
         const int64_t t = token_of(ur);
@@ -890,55 +963,20 @@ chunk_sum_all_kernel(const SumSegs S) {
   seg.out[i] = acc;
 }
 
-// Column sums over the tokens: out[h][c] = sum_t x[h][t][c] (mode 0), sum_t dz[h][t] * x[h][t][c] (mode 1),
-// or, with C = 1, sum_t dz[h][t] (mode 2).  One workgroup per (h, tile of c_tile channels, c_tile a power of two
-// <= 64) and chunk of kColChunk tokens: 256 / c_tile token lanes each sum a strided share in order (neighbouring
-// threads read neighbouring channels of one token), then the lanes of a channel are added in lane order; the chunks
-// are added by chunk_sum_kernel.
-__global__ void __launch_bounds__(256)
-column_sum_kernel(const float* __restrict__ x, const float* __restrict__ dz, int C, int c_tile, int64_t total, int mode,
-                  int Hkv, float* __restrict__ partial) {
-  __shared__ float red[256];
-  const int h = blockIdx.y;
-  const int lanes = 256 / c_tile;
-  const int c = blockIdx.x * c_tile + (int)threadIdx.x % c_tile, tl = (int)threadIdx.x / c_tile;
-  float acc = 0.f;
-  if (c < C) {
-    const int64_t tb = (int64_t)blockIdx.z * kColChunk;
-    const int64_t te = tb + kColChunk < total ? tb + kColChunk : total;
-#pragma unroll 8
-    for (int64_t t = tb + tl; t < te; t += lanes) {
-      const float g = dz != nullptr ? dz[(int64_t)h * total + t] : 1.0f;
-      if (mode == 2) acc += g;
-      else {
-        const float xv = x[((int64_t)h * total + t) * C + c];
-        acc += mode == 1 ? g * xv : xv;
-      }
-    }
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  if (tl == 0 && c < C) {
-    float sum = 0.f;
-    for (int j = 0; j < lanes; ++j) sum += red[j * c_tile + (int)threadIdx.x];
-    partial[((int64_t)blockIdx.z * Hkv + h) * C + c] = sum;
-  }
-}
-
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct Layout {
   int32_t *seq_lo, *seq_hi;
   float* a0;                                  // [Hkv][T][2D] input features as fp32
-  float* pre[LTEA_MAX_CNN_LAYERS];            // [Hkv][T][C_l]
+  float* pre[LTEA_MAX_CNN_LAYERS];            // [Hkv][T][C_l], all but the last layer's
   float* act[LTEA_MAX_CNN_LAYERS];
   float* dpre[2];                             // [Hkv][T][widest layer], ping-pong
   float *wf[LTEA_MAX_CNN_LAYERS], *wb[LTEA_MAX_CNN_LAYERS];   // fp32 weight panels of every layer
   void* wq0;                                  // first layer's weights [Hkv][k][C_0][2D] in the storage type (bf16 only)
   void* wqf[LTEA_MAX_CNN_LAYERS];             // every layer's weights [Hkv][k][C_{l-1}][C_l] in the storage type (bf16 only)
   float* part_w[LTEA_MAX_CNN_LAYERS];         // [chunks][Hkv][C_l][C_{l-1}][k]: partial weight gradients
-  float* part_b[LTEA_MAX_CNN_LAYERS];         // [column chunks][Hkv][C_l]: partial bias gradients
-  float *part_wout, *part_bout;               // [column chunks][Hkv][C_L], [column chunks][Hkv]
+  float* part_b[LTEA_MAX_CNN_LAYERS];         // [tiles of TMC tokens][Hkv][C_l]: partial bias gradients
+  float *part_wout, *part_bout;               // [tiles of TMC tokens][Hkv][C_L], [tiles][Hkv]
   size_t bytes;
 };
 
@@ -954,8 +992,10 @@ Layout carve(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total, void* base
   int cin = 2 * cfg.D;
   for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) L.pre[l] = L.act[l] = nullptr;
   for (int l = 0; l < cnn.n_layers; ++l) {
-    L.pre[l] = reinterpret_cast<float*>(take(sizeof(float) * rows * cnn.c_out[l]));
-    L.act[l] = reinterpret_cast<float*>(take(sizeof(float) * rows * cnn.c_out[l]));
+    if (l < cnn.n_layers - 1) {
+      L.pre[l] = reinterpret_cast<float*>(take(sizeof(float) * rows * cnn.c_out[l]));
+      L.act[l] = reinterpret_cast<float*>(take(sizeof(float) * rows * cnn.c_out[l]));
+    }
     cmax = cnn.c_out[l] > cmax ? cnn.c_out[l] : cmax;
     cin = cnn.c_out[l];
   }
@@ -976,7 +1016,7 @@ Layout carve(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total, void* base
   }
   L.wq0 = cfg.dtype == LTEA_F32 ? nullptr : take(sizeof(bf16_t) * (size_t)cfg.Hkv * cnn.c_out[0] * 2 * cfg.D * cnn.kernel[0]);
   const size_t chunks = (size_t)((total + kTokChunk - 1) / kTokChunk);
-  const size_t col_chunks = (size_t)((total + kColChunk - 1) / kColChunk);
+  const size_t col_chunks = (size_t)((total + TMC - 1) / TMC);
   cin = 2 * cfg.D;
   for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) L.part_w[l] = L.part_b[l] = nullptr;
   for (int l = 0; l < cnn.n_layers; ++l) {
@@ -999,7 +1039,6 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
   const Layout L = carve(cfg, cnn, total, workspace);
   hipError_t e;
   const unsigned tok_tiles = (unsigned)((total + TMC - 1) / TMC);
-  auto blocks = [](int64_t n) { return dim3((unsigned)((n + 255) / 256)); };
   auto cin_of = [&](int l) { return l == 0 ? 2 * D : cnn.c_out[l - 1]; };
   auto in_of = [&](int l) -> const float* { return l == 0 ? L.a0 : L.act[l - 1]; };
   // rows of both operands in whole, 16-byte aligned quads: the vector-load instance
@@ -1008,51 +1047,55 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
     if (N <= 32) return vec ? conv_product_kernel<T, true, true> : conv_product_kernel<T, false, true>;
     return vec ? conv_product_kernel<T, true, false> : conv_product_kernel<T, false, false>;
   };
-  auto panels = [&](int l) {
-    const int64_t n = (int64_t)Hkv * cnn.c_out[l] * cin_of(l) * cnn.kernel[l];
-    hipLaunchKernelGGL(weight_panels_kernel<T>, blocks(n), dim3(256), 0, stream, static_cast<const T*>(cnn.w[l]), cin_of(l),
-                       cnn.c_out[l], cnn.kernel[l], n, L.wf[l], L.wb[l],
-                       l == 0 ? static_cast<T*>(L.wq0) : static_cast<T*>(nullptr), static_cast<T*>(L.wqf[l]));
-    return hipGetLastError();
-  };
-  hipLaunchKernelGGL(token_bounds_kernel, blocks(total), dim3(256), 0, stream, sv.cu_seqlens, sv.n_seqs, total, L.seq_lo,
-                     L.seq_hi);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // on bf16 storage, which of a layer's products take the bf16 kernels (the first layer's forward always does)
+  constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
+  auto back_on_bf16 = [&](int l) { return kBf16 && cnn.c_out[l] % 8 == 0 && cin_of(l) % 8 == 0; };
+  {
+    PrepareArgs P;
+    P.n_layers = nl; P.cu = sv.cu_seqlens; P.n_seqs = sv.n_seqs; P.total = total; P.seq_lo = L.seq_lo; P.seq_hi = L.seq_hi;
+    int64_t most = total;
+    for (int l = 0; l < nl; ++l) {
+      const int64_t n = (int64_t)Hkv * cnn.c_out[l] * cin_of(l) * cnn.kernel[l];
+      const bool first = kBf16 && l == 0;
+      P.layer[l] = LayerPanels{cnn.w[l], first ? nullptr : L.wf[l], back_on_bf16(l) ? nullptr : L.wb[l], first ? L.wq0 : nullptr,
+                               back_on_bf16(l) ? L.wqf[l] : nullptr, cin_of(l), cnn.c_out[l], cnn.kernel[l], n};
+      most = n > most ? n : most;
+    }
+    hipLaunchKernelGGL(prepare_kernel<T>, dim3((unsigned)((most + 255) / 256), (unsigned)(nl + 1)), dim3(256), 0, stream, P);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   // on bf16 storage the first layer's kernels read k / v themselves, unless its weight product takes the fp32 route
   if (!(std::is_same<T, bf16_t>::value && cnn.c_out[0] % 4 == 0)) {
     hipLaunchKernelGGL(features_kernel<T>, dim3((unsigned)((total * (2 * D / Elems<T>::N) + 255) / 256), (unsigned)Hkv), dim3(256),
                        0, stream, static_cast<const T*>(k), static_cast<const T*>(v), stride_tok, stride_head, D, total, L.a0);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // 1. forward, pre-activations and activations kept
+  // 1. forward, pre-activations and activations kept; 2. the output projection, in the last layer's launch
   for (int l = 0; l < nl; ++l) {
-    if ((e = panels(l)) != hipSuccess) return e;
     const int N = cnn.c_out[l];
+    const bool last = l == nl - 1;
+    const OutProj<T> proj = {last ? dz : nullptr, static_cast<const T*>(cnn.w_out), L.part_b[l], L.part_wout, L.part_bout};
+    float* const out0 = last ? L.dpre[0] : L.pre[l];
     if constexpr (std::is_same<T, bf16_t>::value) {
       if (l == 0) {     // both operands are bf16 values: the bf16 matrix instruction gives the fp32 result
         const dim3 grid(tok_tiles, (unsigned)((N + TN - 1) / TN), (unsigned)Hkv);
         hipLaunchKernelGGL(N <= 32 ? conv_first_bf16_kernel<true> : conv_first_bf16_kernel<false>, grid, dim3(256), 0, stream,
                            static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), stride_tok, stride_head,
                            static_cast<const bf16_t*>(L.wq0), D, N, cnn.kernel[0], cnn.dilation[0], L.seq_lo, L.seq_hi, total,
-                           cnn.bias[0], L.pre[0], L.act[0]);
+                           cnn.bias[0], out0, L.act[0], Hkv, proj);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         continue;
       }
     }
     hipLaunchKernelGGL(conv_product(cin_of(l), N), dim3(tok_tiles, (unsigned)((N + TN - 1) / TN), (unsigned)Hkv), dim3(256), 0,
                        stream, in_of(l), L.wf[l], cin_of(l), N, cnn.kernel[l], cnn.dilation[l], 1, L.seq_lo, L.seq_hi, total,
-                       Hkv, 0, cnn.bias[l], static_cast<const float*>(nullptr), L.pre[l], L.act[l], static_cast<T*>(nullptr),
-                       static_cast<T*>(nullptr), D);
+                       Hkv, 0, cnn.bias[l], static_cast<const float*>(nullptr), out0, L.act[l], static_cast<T*>(nullptr),
+                       static_cast<T*>(nullptr), D, proj, static_cast<float*>(nullptr));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // 2. output projection
   const int CL = cnn.c_out[nl - 1];
-  hipLaunchKernelGGL(out_proj_backward_kernel<T>, dim3((unsigned)((total * CL + 255) / 256), (unsigned)Hkv), dim3(256), 0,
-                     stream, dz, static_cast<const T*>(cnn.w_out), L.pre[nl - 1], CL, total, L.dpre[0]);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  auto c_tile_of = [](int C) { int t = 1; while (t < C && t < 64) t *= 2; return t; };
   const int chunks = (int)((total + kTokChunk - 1) / kTokChunk);
-  const int col_chunks = (int)((total + kColChunk - 1) / kColChunk);
+  const int col_chunks = (int)((total + TMC - 1) / TMC);
   // every sum's second stage runs in one launch at the end
   SumSegs sums;
   int n_sums = 0;
@@ -1061,21 +1104,14 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
     sums.s[n_sums++] = SumSeg{partial, out, n, n_chunks};
     n_sum_max = n > n_sum_max ? n : n_sum_max;
   };
-  auto column_sum = [&](const float* x, const float* dzp, int C, int mode, float* partial, float* out) {
-    const int ct = c_tile_of(C);
-    hipLaunchKernelGGL(column_sum_kernel, dim3((unsigned)((C + ct - 1) / ct), (unsigned)Hkv, (unsigned)col_chunks), dim3(256),
-                       0, stream, x, dzp, C, ct, total, mode, Hkv, partial);
-    second_stage(partial, out, (int64_t)Hkv * C, col_chunks);
-    return hipGetLastError();
-  };
-  if ((e = column_sum(L.act[nl - 1], dz, CL, 1, L.part_wout, g.w_out)) != hipSuccess) return e;
-  if ((e = column_sum(nullptr, dz, 1, 2, L.part_bout, g.b_out)) != hipSuccess) return e;
+  second_stage(L.part_wout, g.w_out, (int64_t)Hkv * CL, col_chunks);
+  second_stage(L.part_bout, g.b_out, Hkv, col_chunks);
+  for (int l = 0; l < nl; ++l) second_stage(L.part_b[l], g.bias[l], (int64_t)Hkv * cnn.c_out[l], col_chunks);
   // 3. layers in reverse
   int cur = 0;
   for (int l = nl - 1; l >= 0; --l) {
     const int Cout = cnn.c_out[l], Cin = cin_of(l), ks = cnn.kernel[l];
     const float* dpre = L.dpre[cur];
-    if ((e = column_sum(dpre, nullptr, Cout, 0, L.part_b[l], g.bias[l])) != hipSuccess) return e;
     // 32-wide halves of the 64 x 64 tile that a narrow layer would leave empty go to sharing the tokens instead
     const int wc = Cout <= 32 ? 1 : 2, wm = Cin <= 32 ? 1 : 2;
     const int tiles_m = (Cin + 32 * wm - 1) / (32 * wm), tiles_n = (Cout + 32 * wc - 1) / (32 * wc);
@@ -1103,12 +1139,13 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
       // towards the input: contraction over this layer's output channels, taps mirrored
       bool done = false;
       if constexpr (std::is_same<T, bf16_t>::value) {
-        if (Cout % 8 == 0 && Cin % 8 == 0) {   // bf16 weights, d y split into three bf16 terms
+        if (back_on_bf16(l)) {   // bf16 weights, d y split into three bf16 terms
           const dim3 grid(tok_tiles, (unsigned)((Cin + TN - 1) / TN), (unsigned)Hkv);
           hipLaunchKernelGGL(Cin <= 32 ? conv_back_bf16_kernel<true> : conv_back_bf16_kernel<false>, grid, dim3(256), 0, stream,
                              dpre, static_cast<const bf16_t*>(L.wqf[l]), Cout, Cin, ks, cnn.dilation[l], L.seq_lo, L.seq_hi,
                              total, Hkv, l > 0 ? 1 : 2, l > 0 ? L.pre[l - 1] : static_cast<const float*>(nullptr),
-                             L.dpre[cur ^ 1], static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), D);
+                             L.dpre[cur ^ 1], static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), D,
+                             l > 0 ? L.part_b[l - 1] : static_cast<float*>(nullptr));
           if ((e = hipGetLastError()) != hipSuccess) return e;
           done = true;
         }
@@ -1118,7 +1155,8 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
                          stream, dpre, L.wb[l], Cout, Cin, ks, cnn.dilation[l], -1, L.seq_lo, L.seq_hi, total, Hkv,
                          l > 0 ? 1 : 2, static_cast<const float*>(nullptr),
                          l > 0 ? L.pre[l - 1] : static_cast<const float*>(nullptr), L.dpre[cur ^ 1],
-                         static_cast<float*>(nullptr), static_cast<T*>(dk), static_cast<T*>(dv), D);
+                         static_cast<float*>(nullptr), static_cast<T*>(dk), static_cast<T*>(dv), D, OutProj<T>{},
+                         l > 0 ? L.part_b[l - 1] : static_cast<float*>(nullptr));
       if ((e = hipGetLastError()) != hipSuccess) return e;
       }
     }
