@@ -14,7 +14,7 @@
 //                       d W_l[c][m][tap] = sum_t d y_l[t][c] * a_{l-1}[t + off(tap)][m]      (inside the sequence)
 //                       d a_{l-1}[t][m]  = sum_{tap, c} W_l[c][m][tap] * d y_l[t - off(tap)][c]
 //                       d y_{l-1} = d a_{l-1} * silu'(y_{l-1})        (l > 1)   or   dk, dv = d a_0   (l = 1).
-// Sums over tokens are taken in two stages: per chunk of kTokChunk (weights) or TMC tokens (the column sums, by the
+// Sums over tokens are taken in two stages: per chunk (weights) or TMC tokens (the column sums, by the
 // workgroup that computes the column) into a partial array, then over the chunks.
 #include <type_traits>
 
@@ -26,7 +26,7 @@
 namespace ltea {
 namespace {
 
-constexpr int kTokChunk = 512;   // tokens per partial of the weight products
+constexpr int kTokChunk = 512;   // most tokens per partial of the weight products
 
 __device__ __forceinline__ float silu_grad_f32(float y) {
   const float s = 1.0f / (1.0f + expf(-y));
@@ -204,6 +204,27 @@ __device__ __forceinline__ void out_proj_backward(const OutProj<T>& P, const f32
   }
 }
 
+// What a forward launch does with its products: pre-activations and activations, or the output projection's backward.
+template <int U, bool NARROW, typename T, class TokenOf>
+__device__ __forceinline__ void forward_result(const OutProj<T>& P, const f32x16 (&acc)[U], const float* bias, int h, int Hkv, int n,
+                                               int N, bool n_ok, int64_t total, const TokenOf& token_of, float* out0, float* out1,
+                                               float* red, int wv, int lane) {
+  const float bv = n_ok ? bias[(int64_t)h * N + n] : 0.f;
+  if (P.dz != nullptr) {
+    out_proj_backward<U, NARROW>(P, acc, bv, h, Hkv, n, N, n_ok, total, token_of, out0, red, wv, lane);
+    return;
+  }
+#pragma unroll
+  for (int ur = 0; ur < 16 * U; ++ur) {
+    const int64_t t = token_of(ur);
+    if (t >= total || !n_ok) continue;
+    const int64_t o = ((int64_t)h * total + t) * N + n;
+    const float y = acc[ur / 16][ur % 16] + bv;
+    out0[o] = y;
+    out1[o] = silu_f32(y);
+  }
+}
+
 // d y of the layer below from d a (acc), and its column sums over the workgroup's tokens.
 template <int U, bool NARROW, class TokenOf>
 __device__ __forceinline__ void hidden_backward(const f32x16 (&acc)[U], int h, int Hkv, int n, int N, bool n_ok, int64_t total,
@@ -365,20 +386,7 @@ conv_product_kernel(const float* __restrict__ in, const float* __restrict__ wt, 
   const bool n_ok = n < N;
   auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
   if (mode == 0) {
-    const float bv = n_ok ? bias[(int64_t)h * N + n] : 0.f;
-    if (proj.dz != nullptr) {
-      out_proj_backward<U, NARROW>(proj, acc, bv, h, Hkv, n, N, n_ok, total, token_of, out0, &a_s[0][0], wv, lane);
-      return;
-    }
-#pragma unroll
-    for (int ur = 0; ur < 16 * U; ++ur) {
-      const int64_t t = token_of(ur);
-      if (t >= total || !n_ok) continue;
-      const int64_t o = ((int64_t)h * total + t) * N + n;
-      const float y = acc[ur / 16][ur % 16] + bv;
-      out0[o] = y;
-      out1[o] = silu_f32(y);
-    }
+    forward_result<U, NARROW>(proj, acc, bias, h, Hkv, n, N, n_ok, total, token_of, out0, out1, &a_s[0][0], wv, lane);
   } else if (mode == 1) {
     hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b, &a_s[0][0], wv, lane);
   } else {
@@ -518,38 +526,27 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
   const int n = n0 + col0 + ql;
   const bool n_ok = n < N;
   auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
-  const float bv = n_ok ? bias[(int64_t)h * N + n] : 0.f;
-  if (proj.dz != nullptr) {       // the only layer: pre receives d pre
-    out_proj_backward<U, NARROW>(proj, acc, bv, h, Hkv, n, N, n_ok, total, token_of, pre, reinterpret_cast<float*>(&a_s[0][0]), wv, lane);
-    return;
-  }
-  if (!n_ok) return;
-#pragma unroll
-  for (int ur = 0; ur < 16 * U; ++ur) {
-    const int64_t t = token_of(ur);
-    if (t >= total) continue;
-    const int64_t o = ((int64_t)h * total + t) * N + n;
-    const float y = acc[ur / 16][ur % 16] + bv;
-    pre[o] = y;
-    act[o] = silu_f32(y);
-  }
+  forward_result<U, NARROW>(proj, acc, bias, h, Hkv, n, N, n_ok, total, token_of, pre, act, reinterpret_cast<float*>(&a_s[0][0]), wv,
+                            lane);      // one layer only: pre receives d pre
 }
 
-// Towards the input on bf16 storage: out[t][m] = sum_tap sum_c d y[t - off(tap)][c] * W[c][m][tap].  The weights are
-// bf16 values; the fp32 d y is split into three bf16 terms (x = hi + mid + lo up to 2^-24 of x), whose products with
-// the weights are exact in fp32, so three bf16 matrix instructions give the fp32 product at about five times the fp32
+// The convs whose activations are fp32 on bf16 storage: out[t][n] = sum_tap sum_k in[t + sign * off(tap)][k] * W(tap, k, n),
+// sign = -1 towards the input, +1 the forward of the layers after the first.  The weights (w: [h][tap][n][k]) are bf16
+// values; the fp32 operand is split into three bf16 terms (x = hi + mid + lo up to 2^-24 of x), whose products with the
+// weights are exact in fp32, so three bf16 matrix instructions give the fp32 product at about five times the fp32
 // instruction's rate.  Tiling as conv_product_kernel, slices of KCS channels; used when K and N are multiples of 8.
-// mode 1: dpre_out = out * silu'(pre_prev);  mode 2: dk / dv [T][Hkv][D] (n < D: key part).
+// Modes as conv_product_kernel.
 constexpr int KCS = 16, RSS = KCS + 8;     // channels per slice; LDS row stride in elements
 constexpr int PSA = A_ROWS * (KCS / 4) / 256, PSB = (GT * TN * (KCS / 8) + 255) / 256;
 static_assert(A_ROWS * (KCS / 4) % 256 == 0, "whole quads per thread");
 
 template <bool NARROW>
 __global__ void __launch_bounds__(256, 4)
-conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ wqf, int K, int N, int ks, int dil,
-                      const int32_t* __restrict__ seq_lo, const int32_t* __restrict__ seq_hi, int64_t total, int Hkv,
-                      int mode, const float* __restrict__ pre_prev, float* __restrict__ out0, bf16_t* __restrict__ dk,
-                      bf16_t* __restrict__ dv, int D, float* __restrict__ part_b) {
+conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ w, int K, int N, int ks, int dil, int sign,
+                       const int32_t* __restrict__ seq_lo, const int32_t* __restrict__ seq_hi, int64_t total, int Hkv,
+                       int mode, const float* __restrict__ bias, const float* __restrict__ pre_prev, float* __restrict__ out0,
+                       float* __restrict__ out1, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int D,
+                       const OutProj<bf16_t> proj, float* __restrict__ part_b) {
   __shared__ __align__(16) bf16_t a_s[3][A_ROWS][RSS];    // [term of the split][staged token row][channel of the slice]
   __shared__ __align__(16) bf16_t b_s[GT][TN][RSS];       // [tap of the group][output][channel of the slice]
   const int h = blockIdx.z;
@@ -557,7 +554,7 @@ conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ w
   const int n0 = blockIdx.y * TN;
   const int tid = threadIdx.x;
   const float* in_h = in + (int64_t)h * total * K;
-  const bf16_t* w_h = wqf + (int64_t)h * ks * N * K;
+  const bf16_t* w_h = w + (int64_t)h * ks * N * K;
   const int half = (ks - 1) / 2;
   const int lane = tid & 63, wv = tid >> 6, ql = lane & 31, hb = lane >> 5;
   constexpr int U = NARROW ? 1 : 2;                       // wave roles as in conv_product_kernel
@@ -579,13 +576,12 @@ conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ w
   const int per_group = min(GT, 1 + HALO / dil);
   const int groups = (ks + per_group - 1) / per_group;
   const int slices = (K + KCS - 1) / KCS, stages = groups * slices;
-  // taps are mirrored: tap j of a group reads row t - (tap - half) * dil; the group's lowest row belongs to its last tap
   auto stage_taps = [&](int stage, int& tap0, int& ntap, int& k0, int& base_off) {
     const int g = stage / slices;
     k0 = (stage - g * slices) * KCS;
     tap0 = g * per_group;
     ntap = min(per_group, ks - tap0);
-    base_off = -(tap0 + ntap - 1 - half) * dil;
+    base_off = sign > 0 ? (tap0 - half) * dil : -(tap0 + ntap - 1 - half) * dil;
   };
   float4 ra[PSA];
   u32x4 rb[PSB];
@@ -651,7 +647,7 @@ conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ w
     stage_taps(stage, tap0, ntap, k0, base_off);
     if (stage + 1 < stages) fetch(stage + 1);
     for (int j = 0; j < ntap; ++j) {
-      const int off = -(tap0 + j - half) * dil;
+      const int off = sign * (tap0 + j - half) * dil;
       const int shift = off - base_off;
       bool valid[U];
 #pragma unroll
@@ -677,7 +673,10 @@ conv_back_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ w
   const int n = n0 + col0 + ql;
   const bool n_ok = n < N;
   auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
-  if (mode == 1) {
+  if (mode == 0) {
+    forward_result<U, NARROW>(proj, acc, bias, h, Hkv, n, N, n_ok, total, token_of, out0, out1, reinterpret_cast<float*>(&a_s[0][0][0]),
+                              wv, lane);
+  } else if (mode == 1) {
     hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b,
                                reinterpret_cast<float*>(&a_s[0][0][0]), wv, lane);
   } else {
@@ -701,7 +700,7 @@ template <int WC, int WM>
 __global__ void __launch_bounds__(256)
 weight_product_kernel(const float* __restrict__ act_in, const float* __restrict__ dpre, int Cin, int Cout, int ks, int dil,
                       const int32_t* __restrict__ seq_lo, const int32_t* __restrict__ seq_hi, int64_t total, int Hkv,
-                      int tiles_n, int tiles, int n_work, float* __restrict__ partial) {
+                      int tiles_n, int tiles, int n_work, int chunk_tokens, float* __restrict__ partial) {
   // [operand][token of the slice][channel ^ 32 * (token & 1)]: the two lane halves of an operand read take neighbouring
   // tokens, and the swap of the row halves on odd tokens puts them on different banks without padding the rows
   __shared__ float ab_s[2][KCW][64];
@@ -719,8 +718,8 @@ weight_product_kernel(const float* __restrict__ act_in, const float* __restrict_
   const int chunk = work / (tiles * Hkv * ks);
   const int tid = threadIdx.x;
   const int off = (tap - (ks - 1) / 2) * dil;
-  const int64_t tb = (int64_t)chunk * kTokChunk;
-  const int64_t te = tb + kTokChunk < total ? tb + kTokChunk : total;
+  const int64_t tb = (int64_t)chunk * chunk_tokens;
+  const int64_t te = tb + chunk_tokens < total ? tb + chunk_tokens : total;
   const float* a_h = act_in + (int64_t)h * total * Cin;
   const float* g_h = dpre + (int64_t)h * total * Cout;
   const int lane = tid & 63, wv = tid >> 6, ql = lane & 31, hb = lane >> 5;
@@ -728,7 +727,7 @@ weight_product_kernel(const float* __restrict__ act_in, const float* __restrict_
   // four, the S waves of a tile take every S-th pair of tokens of a slice and their sums are added in wave order.
   constexpr int S = 4 / (WC * WM);
   const int wq = wv % (WC * WM), sp = wv / (WC * WM), ci = wq / WM, mi = wq % WM;
-  for (int i = tid; i < kTokChunk; i += 256) {
+  for (int i = tid; i < chunk_tokens; i += 256) {
     const bool ok = tb + i < te;
     lo_s[i] = ok ? seq_lo[tb + i] : 0;
     hi_s[i] = ok ? seq_hi[tb + i] : 0;   // an empty range: rows past the chunk's end contribute nothing
@@ -800,140 +799,224 @@ weight_product_kernel(const float* __restrict__ act_in, const float* __restrict_
   }
 }
 
-// Stage 1 of d W_0 on bf16 storage: the input features are bf16 values, so with d y split into three bf16 terms (as in
-// conv_back_bf16_kernel) three bf16 matrix instructions give the fp32 product.  The contraction runs over the tokens,
-// i.e. over the rows of the staged [token][channel] tiles: both operands are fetched with transposing LDS loads
-// (eight consecutive tokens of one channel per lane).  Rows are 96 elements apart, which spreads the four rows a
-// 16-lane group reads over different banks.  Work order, wave roles and output as in weight_product_kernel with
-// WM = 2 (2 D >= 128 input channels); a 64-channel tile of input channels lies in the keys or in the values.
-constexpr int KCT = 64, RST = 96;            // tokens per slice, LDS row stride in elements
-template <int WC>
+// Stage 1 of d W_l on bf16 storage, for the channel counts that come in whole quads.  d y (fp32) is split into three bf16
+// terms as in conv_split_bf16_kernel.  X = bf16_t: the first layer, whose inputs are bf16 values, so three bf16 matrix
+// instructions give the fp32 product.  X = float: the layers after it; the activations are split too, and the six products of
+// terms down to 2^-16 of the largest are taken (the three others are below 2^-25 of it).
+// A workgroup takes one (head, chunk of tokens, tile of 32 WM input x 32 WC output channels) and a group of taps: d y is
+// loaded and split once for all of them, and the input rows that the taps reach are staged once and read at each tap's shift.
+// (A workgroup per tap spent its time on loading and splitting the same rows: 4 x 4096 tokens, paper stack, 49 us for the
+// first layer and, on fp32 instructions, 43 and 35 for the next two; 16 heads of D = 128, k = 5: 234 us.)
+// The contraction runs over the tokens, i.e. over the rows of the staged [token][channel] tiles: both operands are fetched
+// with transposing LDS loads (eight consecutive tokens of one channel per lane); the row strides put four consecutive rows'
+// 64 bytes on different banks.  Whether a tap's row lies in the token's own sequence: one bit per token of a slice in a
+// scalar mask, applied to the operand where any bit is clear.  Waves: WC x WM of them tile the output; where that takes fewer
+// than four, the S waves of a block take every S-th step of tokens and their sums are added in wave order.
+constexpr int KCT = 64, NTW = 4;             // tokens per slice; most taps per group
+template <class X, int WC, int WM> struct WeightTile {
+  static constexpr bool kSplit = std::is_same<X, float>::value;
+  static constexpr int S = 4 / (WC * WM), MT = 32 * WM, CT = 32 * WC, XT = kSplit ? 3 : 1;
+  static constexpr int kHalo = kSplit ? 16 : 64, XR = KCT + kHalo;
+  static constexpr int RSX = MT == 32 ? 32 : MT + 32, RSG = CT == 32 ? 32 : CT + 32;     // row strides in elements
+  static constexpr int EPX = kSplit ? 4 : 8;                                             // channels per loaded piece
+  static constexpr int PX = (XR * (MT / EPX) + 255) / 256, PG = KCT * (CT / 4) / 256;
+  static constexpr int kXElems = XT * XR * RSX, kElems = kXElems + 3 * KCT * RSG;
+  static_assert(kElems * 2 >= (S - 1) * WC * WM * 4096, "the waves' sums are exchanged in the tiles");
+};
+// Taps per group and groups, balanced.
+inline int weight_groups(int ks, int dil, bool split) {
+  const int reach = 1 + (split ? 16 : 64) / dil, most = reach < NTW ? reach : NTW;
+  return (ks + most - 1) / most;
+}
+
+// x = t0 + t1 + t2 in bf16 terms (t1, t2: exact residuals), four values packed per term.
+__device__ __forceinline__ void split_quad(float4 x, uint2 (&t)[3]) {
+  const float xs[4] = {x.x, x.y, x.z, x.w};
+  uint32_t b[3][4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const bf16_t b0 = from_f32<bf16_t>(xs[c]);
+    const float r1 = xs[c] - static_cast<float>(b0);
+    const bf16_t b1 = from_f32<bf16_t>(r1);
+    const float r2 = r1 - static_cast<float>(b1);
+    b[0][c] = (uint32_t)__builtin_bit_cast(uint16_t, b0);
+    b[1][c] = (uint32_t)__builtin_bit_cast(uint16_t, b1);
+    b[2][c] = (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(r2));
+  }
+#pragma unroll
+  for (int m = 0; m < 3; ++m) t[m] = make_uint2(b[m][0] | b[m][1] << 16, b[m][2] | b[m][3] << 16);
+}
+
+// Input channel m is x0's for m < split, else x1's channel m - split (the keys and the values; one array for X = float).
+template <class X, int WC, int WM>
 __global__ void __launch_bounds__(256)
-weight_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int64_t stride_tok, int64_t stride_head,
-                         const float* __restrict__ dpre, int D, int Cout, int ks, int dil,
-                         const int32_t* __restrict__ seq_lo, const int32_t* __restrict__ seq_hi, int64_t total, int Hkv,
-                         int tiles_n, int tiles, int n_work, float* __restrict__ partial) {
-  __shared__ __align__(16) bf16_t x_s[KCT][RST];          // features: [token of the slice][m]
-  __shared__ __align__(16) bf16_t g_s[3][KCT][RST];       // d y, term of the split: [token of the slice][c]
-  __shared__ int32_t lo_s[kTokChunk], hi_s[kTokChunk];
-  constexpr int WM = 2, S = 4 / (WC * WM);
-  const int Cin = 2 * D;
+weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int split, int64_t stride_tok, int64_t stride_head,
+                    const float* __restrict__ dpre, int Cin, int Cout, int ks, int dil, const int32_t* __restrict__ seq_lo,
+                    const int32_t* __restrict__ seq_hi, int64_t total, int Hkv, int tiles_n, int tiles, int groups, int n_work,
+                    int chunk_tokens, float* __restrict__ partial) {
+  using G = WeightTile<X, WC, WM>;
+  constexpr int S = G::S, MT = G::MT, CT = G::CT, RSX = G::RSX, RSG = G::RSG, EPX = G::EPX, XQ = MT / EPX, GQ = CT / 4;
+  __shared__ __align__(16) bf16_t lds[G::kElems];
+  bf16_t* const x_s = lds;                  // [term][staged row][channel]
+  bf16_t* const g_s = lds + G::kXElems;     // [term][token of the slice][channel]
+  // XCD-contiguous work order (tile, group, head, chunk): the tiles of one (head, chunk) read the same rows
   const int per_xcd = (n_work + 7) / 8;
   const int work = ((int)blockIdx.x % 8) * per_xcd + (int)blockIdx.x / 8;
   if (work >= n_work) return;
-  const int tile = work % tiles, head_tap = (work / tiles) % (Hkv * ks);
-  const int m0 = (tile / tiles_n) * 64, c0 = (tile % tiles_n) * (32 * WC);
-  const int h = head_tap / ks, tap = head_tap % ks;
-  const int chunk = work / (tiles * Hkv * ks);
-  const int tid = threadIdx.x;
-  const int off = (tap - (ks - 1) / 2) * dil;
-  const int64_t tb = (int64_t)chunk * kTokChunk;
-  const int64_t te = tb + kTokChunk < total ? tb + kTokChunk : total;
-  const int len = (int)(te - tb), tb32 = (int)tb;
-  const bf16_t* x_h = (m0 < D ? k + m0 : v + (m0 - D)) + (int64_t)h * stride_head;
-  const float* g_h = dpre + ((int64_t)h * total + tb) * Cout;
-  const int lane = tid & 63, wv = tid >> 6, hb = lane >> 5;
+  const int tile = work % tiles, head_group = (work / tiles) % (Hkv * groups);
+  const int m0 = (tile / tiles_n) * MT, c0 = (tile % tiles_n) * CT;
+  const int h = head_group / groups;
+  const int chunk = work / (tiles * Hkv * groups);
+  const int per = (ks + groups - 1) / groups, tap0 = (head_group % groups) * per, ntap = min(per, ks - tap0);
+  const int off0 = (tap0 - (ks - 1) / 2) * dil, rows = KCT + (ntap - 1) * dil;
+  const int tid = threadIdx.x, lane = tid & 63, hb = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wq = wv % (WC * WM), sp = wv / (WC * WM), ci = wq / WM, mi = wq % WM;
-  for (int i = tid; i < kTokChunk; i += 256) {
-    const bool ok = i < len;
-    lo_s[i] = ok ? seq_lo[tb + i] : 0;
-    hi_s[i] = ok ? seq_hi[tb + i] : 0;
-  }
-  __syncthreads();
-  f32x16 acc;
+  const int64_t tb = (int64_t)chunk * chunk_tokens;
+  const int64_t te = tb + chunk_tokens < total ? tb + chunk_tokens : total;
+  const int len = (int)(te - tb), tb32 = (int)tb, total32 = (int)total;
+  const float* g_h = dpre + ((int64_t)h * total + tb) * Cout;
+  const X* x0_h = x0 + (int64_t)h * stride_head;
+  const X* x1_h = x1 + (int64_t)h * stride_head;
+
+  f32x16 acc[NTW];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  // loader roles: features as 16-byte pieces (8 per token row), d y as quads of floats (16 per token row)
-  constexpr int PX = KCT * 8 / 256, PG = KCT * 16 / 256;
-  u32x4 rx[PX];
-  float4 rg[PG];
+  for (int j = 0; j < NTW; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  u32x4 rx[G::PX];
+  float4 rg[G::PG];
+  int lo, hi;                    // bounds of the sequence of the slice's token `lane`; empty past the chunk
   unsigned keep_x, keep_g;
-  auto fetch = [&](int i0) {
+  auto fetch = [&](int i0) {     // every load unconditional, from addresses inside the arrays
     keep_x = keep_g = 0u;
 #pragma unroll
-    for (int j = 0; j < PX; ++j) {
-      const int e = tid + 256 * j, i = i0 + e / 8, q = e % 8;
-      const bool t_ok = i < len;
-      const int ic = t_ok ? i : 0;
-      const int p = tb32 + ic + off;
-      const bool p_ok = t_ok & (p >= lo_s[ic]) & (p < hi_s[ic]);
-      rx[j] = *reinterpret_cast<const u32x4*>(x_h + (int64_t)(p_ok ? p : tb32) * stride_tok + 8 * q);
-      keep_x |= p_ok ? 1u << j : 0u;
+    for (int j = 0; j < G::PX; ++j) {
+      const int e = tid + 256 * j, m = m0 + EPX * (e % XQ);
+      const int p = tb32 + i0 + e / XQ + off0;
+      const bool ok = e / XQ < rows && p >= 0 && p < total32 && m < Cin;
+      const int mc = min(m, Cin - EPX);
+      const X* src = (mc < split ? x0_h + mc : x1_h + (mc - split)) + (int64_t)(ok ? p : 0) * stride_tok;
+      rx[j] = *reinterpret_cast<const u32x4*>(src);
+      keep_x |= ok ? 1u << j : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < PG; ++j) {
-      const int e = tid + 256 * j, i = i0 + e / 16, q = e % 16;
-      const bool ok = i < len && c0 + 4 * q < Cout && 4 * q < 32 * WC;                // Cout % 4 == 0: whole quads
-      rg[j] = *reinterpret_cast<const float4*>(g_h + (int64_t)(i < len ? i : 0) * Cout + min(c0 + 4 * q, Cout - 4));
-      keep_g |= ok ? 1u << j : 0u;
+    for (int j = 0; j < G::PG; ++j) {
+      const int e = tid + 256 * j, i = i0 + e / GQ, c = c0 + 4 * (e % GQ);
+      rg[j] = *reinterpret_cast<const float4*>(g_h + (int64_t)(i < len ? i : 0) * Cout + min(c, Cout - 4));
+      keep_g |= (i < len && c < Cout) ? 1u << j : 0u;
     }
-  };
-  auto masked_piece = [](u32x4 x, bool keep) {
-    asm volatile("" : "+v"(x));      // the loaded value is needed whatever the mask says: the load stays unconditional
-    return keep ? x : u32x4{0u, 0u, 0u, 0u};
+    const int t = i0 + lane < len ? tb32 + i0 + lane : tb32;
+    lo = seq_lo[t];
+    hi = seq_hi[t];
+    if (i0 + lane >= len) hi = lo;
   };
   // transposing loads: in each group of 16 lanes, lane j points at row j / 4, columns 4 * (j % 4) .. of its 16 columns
   const int tr_row = 8 * hb + ((lane & 15) >> 2), tr_col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const bf16_t* const g_op = g_s + tr_row * RSG + 32 * ci + tr_col;
+  const bf16_t* const x_op = x_s + tr_row * RSX + 32 * mi + tr_col;
   fetch(0);
   for (int i0 = 0; i0 < len; i0 += KCT) {
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < PX; ++j) {
+    for (int j = 0; j < G::PX; ++j) {
       const int e = tid + 256 * j;
-      *reinterpret_cast<u32x4*>(&x_s[e / 8][8 * (e % 8)]) = masked_piece(rx[j], keep_x >> j & 1u);
+      u32x4 x = rx[j];
+      asm volatile("" : "+v"(x));      // the loaded value is needed whatever the mask says: the load stays unconditional
+      if (!(keep_x >> j & 1u)) x = u32x4{0u, 0u, 0u, 0u};
+      bf16_t* dst = x_s + (e / XQ) * RSX + EPX * (e % XQ);
+      if (e < G::XR * XQ) {
+        if constexpr (G::kSplit) {
+          uint2 t[3];
+          split_quad(__builtin_bit_cast(float4, x), t);
+#pragma unroll
+          for (int m = 0; m < 3; ++m) *reinterpret_cast<uint2*>(dst + m * G::XR * RSX) = t[m];
+        } else {
+          *reinterpret_cast<u32x4*>(dst) = x;
+        }
+      }
     }
 #pragma unroll
-    for (int j = 0; j < PG; ++j) {
-      const int e = tid + 256 * j, row = e / 16, q = e % 16;
-      const float4 y = masked_quad(rg[j], (keep_g >> j & 1u) ? 0xFu : 0u);
-      const float ys[4] = {y.x, y.y, y.z, y.w};
-      uint32_t t[3][4];
+    for (int j = 0; j < G::PG; ++j) {
+      const int e = tid + 256 * j;
+      uint2 t[3];
+      split_quad(masked_quad(rg[j], (keep_g >> j & 1u) ? 0xFu : 0u), t);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const bf16_t b0 = from_f32<bf16_t>(ys[c]);
-        const float r1 = ys[c] - static_cast<float>(b0);        // exact
-        const bf16_t b1 = from_f32<bf16_t>(r1);
-        const float r2 = r1 - static_cast<float>(b1);            // exact
-        t[0][c] = (uint32_t)__builtin_bit_cast(uint16_t, b0);
-        t[1][c] = (uint32_t)__builtin_bit_cast(uint16_t, b1);
-        t[2][c] = (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(r2));
-      }
+      for (int m = 0; m < 3; ++m) *reinterpret_cast<uint2*>(g_s + (m * KCT + e / GQ) * RSG + 4 * (e % GQ)) = t[m];
+    }
+    uint64_t valid[NTW];           // bit i: token i of the slice has a row of its own sequence under the tap
 #pragma unroll
-      for (int m = 0; m < 3; ++m)
-        *reinterpret_cast<uint2*>(&g_s[m][row][4 * q]) = make_uint2(t[m][0] | t[m][1] << 16, t[m][2] | t[m][3] << 16);
+    for (int j = 0; j < NTW; ++j) {
+      const int p = tb32 + i0 + lane + off0 + j * dil;
+      valid[j] = __builtin_amdgcn_ballot_w64(p >= lo && p < hi);
     }
     __syncthreads();
     if (i0 + KCT < len) fetch(i0 + KCT);
 #pragma unroll
-    for (int st = sp; st < KCT / 16; st += S) {              // steps of 16 tokens, shared among the S waves of a tile
-      const bf16x8 b = load_transposed(&x_s[16 * st + tr_row][32 * mi + tr_col], RST);
+    for (int st = sp; st < KCT / 16; st += S) {              // steps of 16 tokens
+      bf16x8 a[3];
 #pragma unroll
-      for (int m = 2; m >= 0; --m)                           // smallest terms first
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_transposed(&g_s[m][16 * st + tr_row][32 * ci + tr_col], RST), b,
-                                                      acc, 0, 0, 0);
+      for (int m = 0; m < 3; ++m) a[m] = load_transposed(g_op + (m * KCT + 16 * st) * RSG, RSG);
+#pragma unroll
+      for (int j = 0; j < NTW; ++j) {
+        if (j >= ntap) break;
+        bf16x8 b[G::XT];
+#pragma unroll
+        for (int m = 0; m < G::XT; ++m) b[m] = load_transposed(x_op + (m * G::XR + 16 * st + j * dil) * RSX, RSX);
+        if (valid[j] != ~0ull) {
+          const uint32_t bits = (uint32_t)(valid[j] >> (16 * st)) >> (8 * hb);
+#pragma unroll
+          for (int m = 0; m < G::XT; ++m) {
+            u32x4 w = __builtin_bit_cast(u32x4, b[m]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              w[i] &= ((bits >> (2 * i) & 1u) ? 0xFFFFu : 0u) | ((bits >> (2 * i + 1) & 1u) ? 0xFFFF0000u : 0u);
+            b[m] = __builtin_bit_cast(bf16x8, w);
+          }
+        }
+        // smallest terms first
+        if constexpr (G::kSplit) {
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc[j], 0, 0, 0);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc[j], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int m = 2; m >= 0; --m) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[0], acc[j], 0, 0, 0);
+        }
+      }
     }
-  }
-  if constexpr (S > 1) {
-    float* red = reinterpret_cast<float*>(&g_s[0][0][0]);   // (S - 1) * WC * WM accumulator tiles of 1024 floats
-    __syncthreads();
-    if (sp > 0) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) red[((sp - 1) * WC * WM + wq) * 1024 + r * 64 + lane] = acc[r];
-    }
-    __syncthreads();
-    if (sp > 0) return;
-    for (int kk = 1; kk < S; ++kk)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] += red[((kk - 1) * WC * WM + wq) * 1024 + r * 64 + lane];
   }
   const int64_t per_head = (int64_t)Cout * Cin * ks;
   float* out = partial + ((int64_t)chunk * Hkv + h) * per_head;
   const int ql = lane & 31;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int c = c0 + 32 * ci + 8 * (r / 4) + 4 * hb + (r % 4);
-    const int m = m0 + 32 * mi + ql;
-    if (m < Cin && c < Cout) out[((int64_t)c * Cin + m) * ks + tap] = acc[r];
+  for (int j = 0; j < NTW; ++j) {
+    if (j >= ntap) break;
+    if constexpr (S > 1) {
+      float* red = reinterpret_cast<float*>(lds);       // (S - 1) * WC * WM accumulator tiles of 1024 floats
+      __syncthreads();
+      if (sp > 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[((sp - 1) * WC * WM + wq) * 1024 + r * 64 + lane] = acc[j][r];
+      }
+      __syncthreads();
+      if (sp == 0) {
+        for (int k = 1; k < S; ++k)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[j][r] += red[((k - 1) * WC * WM + wq) * 1024 + r * 64 + lane];
+      }
+    }
+    if (sp == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int c = c0 + 32 * ci + 8 * (r / 4) + 4 * hb + (r % 4);
+        const int m = m0 + 32 * mi + ql;
+        if (m < Cin && c < Cout) out[((int64_t)c * Cin + m) * ks + tap0 + j] = acc[j][r];
+      }
+    }
   }
 }
 
@@ -963,6 +1046,28 @@ chunk_sum_all_kernel(const SumSegs S) {
   seg.out[i] = acc;
 }
 
+// How a layer's weight product is cut: channel blocks per tile, tiles, tap groups and tokens per partial.
+struct WeightPlan { bool split; int wc, wm, tiles_n, tiles, groups, chunk, chunks; };
+WeightPlan weight_plan(const ltea_cfg& cfg, const ltea_cnn& cnn, int l, int64_t total) {
+  const int cin = l == 0 ? 2 * cfg.D : cnn.c_out[l - 1], cout = cnn.c_out[l], ks = cnn.kernel[l];
+  WeightPlan P;
+  P.split = cfg.dtype == LTEA_BF16 && cin % 4 == 0 && cout % 4 == 0;      // whole quads
+  // 32-wide halves of the 64 x 64 tile that a narrow layer would leave empty go to sharing the tokens instead, or (the
+  // first layer's inputs, 2 D >= 128 channels) to a tile of 128 input channels
+  P.wc = cout <= 32 ? 1 : 2;
+  P.wm = P.split && l == 0 ? 4 / P.wc : (cin <= 32 ? 1 : 2);
+  P.tiles_n = (cout + 32 * P.wc - 1) / (32 * P.wc);
+  P.tiles = ((cin + 32 * P.wm - 1) / (32 * P.wm)) * P.tiles_n;
+  P.groups = P.split ? weight_groups(ks, cnn.dilation[l], l > 0) : ks;
+  // A workgroup walks its chunk slice by slice, a memory round trip each, so a launch is as long as a chunk until the chip is
+  // full: chunks are halved while fewer than 512 workgroups (two per CU) would run.  Not below 128 tokens: a partial is as
+  // large as the weights, and each is written and read once.
+  P.chunk = kTokChunk;
+  while (P.chunk > 128 && (int64_t)P.tiles * cfg.Hkv * P.groups * ((total + P.chunk - 1) / P.chunk) < 512) P.chunk /= 2;
+  P.chunks = (int)((total + P.chunk - 1) / P.chunk);
+  return P;
+}
+
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct Layout {
@@ -972,7 +1077,7 @@ struct Layout {
   float* act[LTEA_MAX_CNN_LAYERS];
   float* dpre[2];                             // [Hkv][T][widest layer], ping-pong
   float *wf[LTEA_MAX_CNN_LAYERS], *wb[LTEA_MAX_CNN_LAYERS];   // fp32 weight panels of every layer
-  void* wq0;                                  // first layer's weights [Hkv][k][C_0][2D] in the storage type (bf16 only)
+  void* wq[LTEA_MAX_CNN_LAYERS];              // every layer's weights [Hkv][k][C_l][C_{l-1}] in the storage type (bf16 only)
   void* wqf[LTEA_MAX_CNN_LAYERS];             // every layer's weights [Hkv][k][C_{l-1}][C_l] in the storage type (bf16 only)
   float* part_w[LTEA_MAX_CNN_LAYERS];         // [chunks][Hkv][C_l][C_{l-1}][k]: partial weight gradients
   float* part_b[LTEA_MAX_CNN_LAYERS];         // [tiles of TMC tokens][Hkv][C_l]: partial bias gradients
@@ -1009,17 +1114,19 @@ Layout carve(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total, void* base
     cin = cnn.c_out[l];
   }
   cin = 2 * cfg.D;
-  for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) L.wqf[l] = nullptr;
+  for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) L.wq[l] = L.wqf[l] = nullptr;
   for (int l = 0; l < cnn.n_layers; ++l) {
-    if (cfg.dtype != LTEA_F32) L.wqf[l] = take(sizeof(bf16_t) * (size_t)cfg.Hkv * cnn.c_out[l] * cin * cnn.kernel[l]);
+    if (cfg.dtype != LTEA_F32) {
+      L.wq[l] = take(sizeof(bf16_t) * (size_t)cfg.Hkv * cnn.c_out[l] * cin * cnn.kernel[l]);
+      L.wqf[l] = take(sizeof(bf16_t) * (size_t)cfg.Hkv * cnn.c_out[l] * cin * cnn.kernel[l]);
+    }
     cin = cnn.c_out[l];
   }
-  L.wq0 = cfg.dtype == LTEA_F32 ? nullptr : take(sizeof(bf16_t) * (size_t)cfg.Hkv * cnn.c_out[0] * 2 * cfg.D * cnn.kernel[0]);
-  const size_t chunks = (size_t)((total + kTokChunk - 1) / kTokChunk);
   const size_t col_chunks = (size_t)((total + TMC - 1) / TMC);
   cin = 2 * cfg.D;
   for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) L.part_w[l] = L.part_b[l] = nullptr;
   for (int l = 0; l < cnn.n_layers; ++l) {
+    const size_t chunks = (size_t)weight_plan(cfg, cnn, l, total).chunks;
     L.part_w[l] = reinterpret_cast<float*>(take(sizeof(float) * chunks * cfg.Hkv * cnn.c_out[l] * cin * cnn.kernel[l]));
     L.part_b[l] = reinterpret_cast<float*>(take(sizeof(float) * col_chunks * cfg.Hkv * cnn.c_out[l]));
     cin = cnn.c_out[l];
@@ -1047,25 +1154,26 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
     if (N <= 32) return vec ? conv_product_kernel<T, true, true> : conv_product_kernel<T, false, true>;
     return vec ? conv_product_kernel<T, true, false> : conv_product_kernel<T, false, false>;
   };
-  // on bf16 storage, which of a layer's products take the bf16 kernels (the first layer's forward always does)
+  // on bf16 storage, the layers whose convs take the bf16 kernels, whole 16-byte pieces of both weight orders (the first
+  // layer's forward always does)
   constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
-  auto back_on_bf16 = [&](int l) { return kBf16 && cnn.c_out[l] % 8 == 0 && cin_of(l) % 8 == 0; };
+  auto on_bf16 = [&](int l) { return kBf16 && cnn.c_out[l] % 8 == 0 && cin_of(l) % 8 == 0; };
   {
     PrepareArgs P;
     P.n_layers = nl; P.cu = sv.cu_seqlens; P.n_seqs = sv.n_seqs; P.total = total; P.seq_lo = L.seq_lo; P.seq_hi = L.seq_hi;
     int64_t most = total;
     for (int l = 0; l < nl; ++l) {
       const int64_t n = (int64_t)Hkv * cnn.c_out[l] * cin_of(l) * cnn.kernel[l];
-      const bool first = kBf16 && l == 0;
-      P.layer[l] = LayerPanels{cnn.w[l], first ? nullptr : L.wf[l], back_on_bf16(l) ? nullptr : L.wb[l], first ? L.wq0 : nullptr,
-                               back_on_bf16(l) ? L.wqf[l] : nullptr, cin_of(l), cnn.c_out[l], cnn.kernel[l], n};
+      const bool fwd = on_bf16(l) || (kBf16 && l == 0), back = on_bf16(l);
+      P.layer[l] = LayerPanels{cnn.w[l], fwd ? nullptr : L.wf[l], back ? nullptr : L.wb[l], fwd ? L.wq[l] : nullptr,
+                               back ? L.wqf[l] : nullptr, cin_of(l), cnn.c_out[l], cnn.kernel[l], n};
       most = n > most ? n : most;
     }
     hipLaunchKernelGGL(prepare_kernel<T>, dim3((unsigned)((most + 255) / 256), (unsigned)(nl + 1)), dim3(256), 0, stream, P);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // on bf16 storage the first layer's kernels read k / v themselves, unless its weight product takes the fp32 route
-  if (!(std::is_same<T, bf16_t>::value && cnn.c_out[0] % 4 == 0)) {
+  if (!weight_plan(cfg, cnn, 0, total).split) {
     hipLaunchKernelGGL(features_kernel<T>, dim3((unsigned)((total * (2 * D / Elems<T>::N) + 255) / 256), (unsigned)Hkv), dim3(256),
                        0, stream, static_cast<const T*>(k), static_cast<const T*>(v), stride_tok, stride_head, D, total, L.a0);
   }
@@ -1081,8 +1189,17 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
         const dim3 grid(tok_tiles, (unsigned)((N + TN - 1) / TN), (unsigned)Hkv);
         hipLaunchKernelGGL(N <= 32 ? conv_first_bf16_kernel<true> : conv_first_bf16_kernel<false>, grid, dim3(256), 0, stream,
                            static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), stride_tok, stride_head,
-                           static_cast<const bf16_t*>(L.wq0), D, N, cnn.kernel[0], cnn.dilation[0], L.seq_lo, L.seq_hi, total,
+                           static_cast<const bf16_t*>(L.wq[0]), D, N, cnn.kernel[0], cnn.dilation[0], L.seq_lo, L.seq_hi, total,
                            cnn.bias[0], out0, L.act[0], Hkv, proj);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        continue;
+      }
+      if (on_bf16(l)) {
+        hipLaunchKernelGGL(N <= 32 ? conv_split_bf16_kernel<true> : conv_split_bf16_kernel<false>,
+                           dim3(tok_tiles, (unsigned)((N + TN - 1) / TN), (unsigned)Hkv), dim3(256), 0, stream, in_of(l),
+                           static_cast<const bf16_t*>(L.wq[l]), cin_of(l), N, cnn.kernel[l], cnn.dilation[l], 1, L.seq_lo, L.seq_hi,
+                           total, Hkv, 0, cnn.bias[l], static_cast<const float*>(nullptr), out0, L.act[l],
+                           static_cast<bf16_t*>(nullptr), static_cast<bf16_t*>(nullptr), D, proj, static_cast<float*>(nullptr));
         if ((e = hipGetLastError()) != hipSuccess) return e;
         continue;
       }
@@ -1094,7 +1211,6 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const int CL = cnn.c_out[nl - 1];
-  const int chunks = (int)((total + kTokChunk - 1) / kTokChunk);
   const int col_chunks = (int)((total + TMC - 1) / TMC);
   // every sum's second stage runs in one launch at the end
   SumSegs sums;
@@ -1112,39 +1228,48 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
   for (int l = nl - 1; l >= 0; --l) {
     const int Cout = cnn.c_out[l], Cin = cin_of(l), ks = cnn.kernel[l];
     const float* dpre = L.dpre[cur];
-    // 32-wide halves of the 64 x 64 tile that a narrow layer would leave empty go to sharing the tokens instead
-    const int wc = Cout <= 32 ? 1 : 2, wm = Cin <= 32 ? 1 : 2;
-    const int tiles_m = (Cin + 32 * wm - 1) / (32 * wm), tiles_n = (Cout + 32 * wc - 1) / (32 * wc);
-    auto weight_product = wc == 2 ? (wm == 2 ? weight_product_kernel<2, 2> : weight_product_kernel<2, 1>)
-                                  : (wm == 2 ? weight_product_kernel<1, 2> : weight_product_kernel<1, 1>);
-    const int64_t n_work = (int64_t)tiles_m * tiles_n * Hkv * ks * chunks;
+    const WeightPlan W = weight_plan(cfg, cnn, l, total);
+    const int64_t n_work = (int64_t)W.tiles * Hkv * W.groups * W.chunks;
     if (n_work > (int64_t)1 << 30) return hipErrorInvalidValue;
-    if constexpr (std::is_same<T, bf16_t>::value) {
-      if (l == 0 && Cout % 4 == 0) {   // bf16 features, d y split into three bf16 terms
-        hipLaunchKernelGGL(wc == 2 ? weight_first_bf16_kernel<2> : weight_first_bf16_kernel<1>, dim3((unsigned)((n_work + 7) / 8 * 8)),
-                           dim3(256), 0, stream, static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), stride_tok,
-                           stride_head, dpre, D, Cout, ks, cnn.dilation[0], L.seq_lo, L.seq_hi, total, Hkv, tiles_n,
-                           tiles_m * tiles_n, (int)n_work, L.part_w[0]);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        second_stage(L.part_w[0], g.w[0], (int64_t)Cout * Cin * ks * Hkv, chunks);
-        goto weights_done;
+    const dim3 wgrid((unsigned)((n_work + 7) / 8 * 8));
+    bool weights_done = false;
+    if constexpr (kBf16) {
+      if (W.split) {
+        auto launch = [&](auto kernel, auto x0, auto x1, int at, int64_t st, int64_t sh) {
+          hipLaunchKernelGGL(kernel, wgrid, dim3(256), 0, stream, x0, x1, at, st, sh, dpre, Cin, Cout, ks, cnn.dilation[l], L.seq_lo,
+                             L.seq_hi, total, Hkv, W.tiles_n, W.tiles, W.groups, (int)n_work, W.chunk, L.part_w[l]);
+        };
+        if (l == 0) {
+          const bf16_t *kp = static_cast<const bf16_t*>(k), *vp = static_cast<const bf16_t*>(v);
+          if (W.wc == 2) launch(weight_split_kernel<bf16_t, 2, 2>, kp, vp, D, stride_tok, stride_head);
+          else launch(weight_split_kernel<bf16_t, 1, 4>, kp, vp, D, stride_tok, stride_head);
+        } else {
+          auto kernel = W.wc == 2 ? (W.wm == 2 ? weight_split_kernel<float, 2, 2> : weight_split_kernel<float, 2, 1>)
+                                  : (W.wm == 2 ? weight_split_kernel<float, 1, 2> : weight_split_kernel<float, 1, 1>);
+          launch(kernel, in_of(l), in_of(l), Cin, (int64_t)Cin, total * Cin);
+        }
+        weights_done = true;
       }
     }
-    hipLaunchKernelGGL(weight_product, dim3((unsigned)((n_work + 7) / 8 * 8)), dim3(256), 0, stream, in_of(l), dpre, Cin, Cout,
-                       ks, cnn.dilation[l], L.seq_lo, L.seq_hi, total, Hkv, tiles_n, tiles_m * tiles_n, (int)n_work, L.part_w[l]);
+    if (!weights_done) {
+      auto weight_product = W.wc == 2 ? (W.wm == 2 ? weight_product_kernel<2, 2> : weight_product_kernel<2, 1>)
+                                      : (W.wm == 2 ? weight_product_kernel<1, 2> : weight_product_kernel<1, 1>);
+      hipLaunchKernelGGL(weight_product, wgrid, dim3(256), 0, stream, in_of(l), dpre, Cin, Cout, ks, cnn.dilation[l], L.seq_lo,
+                         L.seq_hi, total, Hkv, W.tiles_n, W.tiles, (int)n_work, W.chunk, L.part_w[l]);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    second_stage(L.part_w[l], g.w[l], (int64_t)Cout * Cin * ks * Hkv, chunks);
-  weights_done:
+    second_stage(L.part_w[l], g.w[l], (int64_t)Cout * Cin * ks * Hkv, W.chunks);
     if (l > 0 || dk != nullptr || dv != nullptr) {
       // towards the input: contraction over this layer's output channels, taps mirrored
       bool done = false;
       if constexpr (std::is_same<T, bf16_t>::value) {
-        if (back_on_bf16(l)) {   // bf16 weights, d y split into three bf16 terms
+        if (on_bf16(l)) {   // bf16 weights, d y split into three bf16 terms
           const dim3 grid(tok_tiles, (unsigned)((Cin + TN - 1) / TN), (unsigned)Hkv);
-          hipLaunchKernelGGL(Cin <= 32 ? conv_back_bf16_kernel<true> : conv_back_bf16_kernel<false>, grid, dim3(256), 0, stream,
-                             dpre, static_cast<const bf16_t*>(L.wqf[l]), Cout, Cin, ks, cnn.dilation[l], L.seq_lo, L.seq_hi,
-                             total, Hkv, l > 0 ? 1 : 2, l > 0 ? L.pre[l - 1] : static_cast<const float*>(nullptr),
-                             L.dpre[cur ^ 1], static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), D,
+          hipLaunchKernelGGL(Cin <= 32 ? conv_split_bf16_kernel<true> : conv_split_bf16_kernel<false>, grid, dim3(256), 0, stream,
+                             dpre, static_cast<const bf16_t*>(L.wqf[l]), Cout, Cin, ks, cnn.dilation[l], -1, L.seq_lo, L.seq_hi,
+                             total, Hkv, l > 0 ? 1 : 2, static_cast<const float*>(nullptr),
+                             l > 0 ? L.pre[l - 1] : static_cast<const float*>(nullptr), L.dpre[cur ^ 1], static_cast<float*>(nullptr),
+                             static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), D, OutProj<bf16_t>{},
                              l > 0 ? L.part_b[l - 1] : static_cast<float*>(nullptr));
           if ((e = hipGetLastError()) != hipSuccess) return e;
           done = true;

@@ -40,6 +40,7 @@ namespace {
 constexpr int BN = 64;          // keys (or queries) per tile
 constexpr int BM = 128;         // queries (or keys) per workgroup
 constexpr int kThreads = 256;
+constexpr int kStage = 2;       // tiles between two barriers
 
 template <int D> struct Geo {
   static constexpr int PPR = D / 8;             // 16-byte pieces per row
@@ -98,7 +99,7 @@ template <int D, int HW>
 __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int n_work, float scale_log2e, int block,
                                         bf16_t* lds, int* pos_lds_base) {
   LTEA_GEO(D);
-  static_assert(2 * kBuf >= BM * OS, "epilogue staging must fit in the tile buffers");
+  static_assert(2 * kStage * kBuf >= BM * OS, "epilogue staging must fit in the tile buffers");
 
   const int per_xcd = (n_work + 7) / 8;
   const int work = (block % 8) * per_xcd + block / 8;
@@ -167,7 +168,7 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
     const bool win = t < n_win_tiles;
     const int row0 = win ? jt0 + t * BN : (t - n_win_tiles) * BN;
     const uint32_t rb = win ? row_bytes : (uint32_t)(D * 2);
-    const uint32_t dst = lds_base + (uint32_t)((t & 1) * kBuf * 2 + wv * 1024);
+    const uint32_t dst = lds_base + (uint32_t)((t % (2 * kStage)) * kBuf * 2 + wv * 1024);
     const u32x4 rk = win ? rs_k : rs_kr, rv = win ? rs_v : rs_vr;
     uint32_t off = (uint32_t)(row0 + ld_row) * rb + ld_col;
 #pragma unroll
@@ -176,7 +177,7 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
       dma16(rv, dst + (uint32_t)(kTile * 2 + i * 4096), off);
       off += (uint32_t)(4 * G_::RPI) * rb;
     }
-    if (!win && wv == 0) dma4(rs_pos, pos_base + (uint32_t)((t & 1) * BN * 4), (uint32_t)(row0 + lane) * 4u);   // zeros past cnt
+    if (!win && wv == 0) dma4(rs_pos, pos_base + (uint32_t)((t % (2 * kStage)) * BN * 4), (uint32_t)(row0 + lane) * 4u);   // zeros past cnt
   };
   const Operands<D> op(lane);
   constexpr int NK = D / 16, ND = D / 32;
@@ -302,15 +303,20 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
     });
   };
 
-  // tile t is computed from buffer t & 1 while tile t + 1 is on its way into the other one
-  load_tile(0);
+  // a stage of tiles is computed while the next one is on its way into the other half of the buffers
+  auto load_stage = [&](int t0) {
+#pragma unroll
+    for (int t = t0; t < t0 + kStage; ++t)
+      if (t < n_tiles) load_tile(t);
+  };
+  load_stage(0);
   wait_loads();
   __syncthreads();
 #pragma unroll 1
   for (int t = 0; t < n_tiles; ++t) {
-    if (t + 1 < n_tiles) load_tile(t + 1);
-    const bf16_t* tb = lds + (t & 1) * kBuf;
-    const int* pos = pos_lds_base + (t & 1) * BN;
+    if (t % kStage == 0) load_stage(t + kStage);
+    const bf16_t* tb = lds + (t % (2 * kStage)) * kBuf;
+    const int* pos = pos_lds_base + (t % (2 * kStage)) * BN;
     int mode = -1, jt = 0, slots = 0;
     if (r0 < n) {
       if (t < n_win_tiles) {
@@ -335,8 +341,10 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
     asm volatile("" : "+s"(mode));
     if (mode == 1) compute(1, tb, pos, jt, slots);
     else if (mode == 2) compute(2, tb, pos, jt, slots);
-    wait_loads();
-    __syncthreads();                 // tile t + 1 is in LDS; everyone is done with tile t
+    if (t % kStage == kStage - 1 || t == n_tiles - 1) {
+      wait_loads();
+      __syncthreads();               // the next stage is in LDS; everyone is done with this one
+    }
   }
 
   // ---- epilogue: dQ = scale * acc, staged through LDS, rows stored coalesced ---------------------------------
@@ -384,7 +392,7 @@ template <int D, bool FAR>
 __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, float scale_log2e, float* far_dk,
                                          float* far_dv, int block, bf16_t* lds, float* stat_base) {
   LTEA_GEO(D);
-  static_assert(2 * kBuf >= BM * OS, "epilogue staging must fit in the tile buffers");
+  static_assert(2 * kStage * kBuf >= BM * OS, "epilogue staging must fit in the tile buffers");
 
   const int Hq = A.Hq, Hkv = A.Hkv, window = A.window, cap = A.budget;
   const int G = Hq / Hkv;
@@ -492,7 +500,7 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
     const int qt = (qt_first + t) * BN;
     const u32x4 rs_q = make_raw_rsrc(q + (int64_t)lo * A.q_st + (int64_t)hq * A.q_sh, q_bytes);
     const u32x4 rs_o = make_raw_rsrc(dout + ((int64_t)lo * Hq + hq) * D, o_bytes);
-    const uint32_t dst = lds_base + (uint32_t)((it & 1) * kBuf * 2 + wv * 1024);
+    const uint32_t dst = lds_base + (uint32_t)((it % (2 * kStage)) * kBuf * 2 + wv * 1024);
     uint32_t q_off = (uint32_t)(qt + ld_row) * q_row_bytes + ld_col, o_off = (uint32_t)(qt + ld_row) * o_row_bytes + ld_col;
 #pragma unroll
     for (int i = 0; i < G_::IPW; ++i) {
@@ -503,7 +511,7 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
     }
     if (wv < 2) {       // [-lse / scale of the 64 queries | their -delta], zeros past the sequence
       const float* src = A.delta + (int64_t)(wv == 0 ? Hq : 0) * A.total + (int64_t)hq * A.total + lo;
-      dma4(make_raw_rsrc(src, (uint32_t)n * 4u), stat_lds + (uint32_t)(((it & 1) * 2 + wv) * BN * 4), (uint32_t)(qt + lane) * 4u);
+      dma4(make_raw_rsrc(src, (uint32_t)n * 4u), stat_lds + (uint32_t)(((it % (2 * kStage)) * 2 + wv) * BN * 4), (uint32_t)(qt + lane) * 4u);
     }
   };
   const Operands<D> op(lane);
@@ -619,15 +627,20 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
     });
   };
 
-  // tile `it` is computed from buffer it & 1 while the next one is on its way into the other
-  load_tile(0);
+  // a stage of tiles is computed while the next one is on its way into the other half of the buffers
+  auto load_stage = [&](int it0) {
+#pragma unroll
+    for (int it = it0; it < it0 + kStage; ++it)
+      if (it < n_iter) load_tile(it);
+  };
+  load_stage(0);
   wait_loads();
   __syncthreads();
 #pragma unroll 1
   for (int it = 0; it < n_iter; ++it) {
-    if (it + 1 < n_iter) load_tile(it + 1);
-    const bf16_t* tb = lds + (it & 1) * kBuf;
-    const float* st = stat_base + (it & 1) * 2 * BN;
+    if (it % kStage == 0) load_stage(it + kStage);
+    const bf16_t* tb = lds + (it % (2 * kStage)) * kBuf;
+    const float* st = stat_base + (it % (2 * kStage)) * 2 * BN;
     const int qt = (qt_first + it % n_qt) * BN;
     // does any key of this wave see a query of the tile, and do all of them see all of it?
     const bool touches = q_span != 0u && q_lo < qt + BN && q_hi > qt;
@@ -641,8 +654,10 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
     }
     asm volatile("" : "+s"(mode));
     if (mode == 1) compute_masked(tb, st, qt);
-    wait_loads();
-    __syncthreads();
+    if (it % kStage == kStage - 1 || it == n_iter - 1) {
+      wait_loads();
+      __syncthreads();
+    }
   }
 
   // ---- epilogue: accumulator register r of block db is feature d = 32*db + 8*(r/4) + 4*hb + r%4 of the lane's key ---
@@ -786,8 +801,8 @@ template <int D, int HW>
 __global__ void __launch_bounds__(kThreads, D == 64 ? 2 : 1)
 train_dq_far_mfma_kernel(TrainArgs A, int tiles_upper, int n_work, float scale_log2e, float* far_dk, float* far_dv,
                          int far_blocks) {
-  __shared__ __align__(1024) bf16_t lds[2 * Geo<D>::kBuf];  // two tile buffers, for either role
-  __shared__ __align__(256) float stat_lds[4 * BN];
+  __shared__ __align__(1024) bf16_t lds[2 * kStage * Geo<D>::kBuf];  // for either role
+  __shared__ __align__(256) float stat_lds[4 * kStage * BN];
   if ((int)blockIdx.x < far_blocks)
     dkv_body<D, true>(A, 0, scale_log2e, far_dk, far_dv, (int)blockIdx.x, lds, stat_lds);
   else
@@ -797,8 +812,8 @@ train_dq_far_mfma_kernel(TrainArgs A, int tiles_upper, int n_work, float scale_l
 template <int D>
 __global__ void __launch_bounds__(kThreads, D == 64 ? 2 : 1)
 train_dkv_band_mfma_kernel(TrainArgs A, int tiles_upper, float scale_log2e, float* far_dk, float* far_dv) {
-  __shared__ __align__(1024) bf16_t lds[2 * Geo<D>::kBuf];
-  __shared__ __align__(256) float stat_lds[4 * BN];
+  __shared__ __align__(1024) bf16_t lds[2 * kStage * Geo<D>::kBuf];
+  __shared__ __align__(256) float stat_lds[4 * kStage * BN];
   dkv_body<D, false>(A, tiles_upper, scale_log2e, far_dk, far_dv, (int)blockIdx.x, lds, stat_lds);
 }
 
