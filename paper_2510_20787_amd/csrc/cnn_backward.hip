@@ -430,14 +430,13 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
   const int lane = tid & 63, wv = tid >> 6, ql = lane & 31, hb = lane >> 5;
   constexpr int U = NARROW ? 1 : 2;                       // wave roles as in conv_product_kernel
   const int row0 = NARROW ? 32 * wv : 64 * (wv >> 1), col0 = NARROW ? 0 : 32 * (wv & 1);
-  int64_t tok[U];
-  int lo[U], hi[U];
+  int tok32[U], lo[U], hi[U];      // token indices fit: the sequence bounds are int32
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    tok[u] = t0 + row0 + 32 * u + ql;
-    const bool ok = tok[u] < total;
-    lo[u] = ok ? seq_lo[tok[u]] : 0;
-    hi[u] = ok ? seq_hi[tok[u]] : 0;
+    tok32[u] = (int)t0 + row0 + 32 * u + ql;
+    const bool ok = tok32[u] < total;
+    lo[u] = ok ? seq_lo[tok32[u]] : 0;
+    hi[u] = ok ? seq_hi[tok32[u]] : 0;
   }
   f32x16 acc[U];
 #pragma unroll
@@ -503,9 +502,12 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
     for (int j = 0; j < ntap; ++j) {
       const int off = (tap0 + j - half) * dil;
       const int shift = off - base_off;
-      bool valid[U];
+      bool valid[U], inside[U];      // inside: the same for all tokens of the sub-tile (no sequence ends under it)
 #pragma unroll
-      for (int u = 0; u < U; ++u) valid[u] = tok[u] + off >= lo[u] && tok[u] + off < hi[u];
+      for (int u = 0; u < U; ++u) {
+        valid[u] = tok32[u] + off >= lo[u] && tok32[u] + off < hi[u];
+        inside[u] = __builtin_amdgcn_ballot_w64(!valid[u]) == 0ull;
+      }
       // lane half hb supplies channels 16 s + 8 hb .. + 7 of its row (tokens) / column (outputs) to step s
 #pragma unroll
       for (int sk = 0; sk < KCB / 16; ++sk) {
@@ -515,7 +517,7 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
         const u32x4 b = *reinterpret_cast<const u32x4*>(&b_s[j][col0 + ql][16 * sk + 8 * hb]);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          a[u] = masked_piece(a[u], valid[u]);
+          if (!inside[u]) a[u] = masked_piece(a[u], valid[u]);
           acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[u]), __builtin_bit_cast(bf16x8, b),
                                                           acc[u], 0, 0, 0);
         }
@@ -553,20 +555,19 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
   const int64_t t0 = (int64_t)blockIdx.x * TMC;
   const int n0 = blockIdx.y * TN;
   const int tid = threadIdx.x;
-  const float* in_h = in + (int64_t)h * total * K;
+  const float* in_t = in + ((int64_t)h * total + t0) * K;
   const bf16_t* w_h = w + (int64_t)h * ks * N * K;
   const int half = (ks - 1) / 2;
   const int lane = tid & 63, wv = tid >> 6, ql = lane & 31, hb = lane >> 5;
   constexpr int U = NARROW ? 1 : 2;                       // wave roles as in conv_product_kernel
   const int row0 = NARROW ? 32 * wv : 64 * (wv >> 1), col0 = NARROW ? 0 : 32 * (wv & 1);
-  int64_t tok[U];
-  int lo[U], hi[U];
+  int tok32[U], lo[U], hi[U];      // token indices fit: the sequence bounds are int32
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    tok[u] = t0 + row0 + 32 * u + ql;
-    const bool ok = tok[u] < total;
-    lo[u] = ok ? seq_lo[tok[u]] : 0;
-    hi[u] = ok ? seq_hi[tok[u]] : 0;
+    tok32[u] = (int)t0 + row0 + 32 * u + ql;
+    const bool ok = tok32[u] < total;
+    lo[u] = ok ? seq_lo[tok32[u]] : 0;
+    hi[u] = ok ? seq_hi[tok32[u]] : 0;
   }
   f32x16 acc[U];
 #pragma unroll
@@ -594,9 +595,9 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
 #pragma unroll
     for (int i = 0; i < PSA; ++i) {
       const int e = tid + 256 * i, row = e / (KCS / 4), q = e % (KCS / 4);
-      const int64_t p = t0 + row + base_off;
-      const bool ok = row < rows && p >= 0 && p < total && k0 + 4 * q < K;          // K % 4 == 0: whole quads
-      ra[i] = *reinterpret_cast<const float4*>(in_h + (ok ? p : 0) * K + min(k0 + 4 * q, K - 4));
+      const int p = row + base_off;                                                 // from the tile's first token
+      const bool ok = row < rows && (int)t0 + p >= 0 && (int)t0 + p < (int)total && k0 + 4 * q < K;   // K % 4 == 0: whole quads
+      ra[i] = *reinterpret_cast<const float4*>(in_t + (ok ? p * K : 0) + min(k0 + 4 * q, K - 4));
       keep_a |= ok ? 1u << i : 0u;
     }
 #pragma unroll
@@ -604,7 +605,7 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
       const int e = tid + 256 * i, jn = e / (KCS / 8), q = e % (KCS / 8);
       const int j = jn / TN, n = jn % TN;
       const bool ok = e < GT * TN * (KCS / 8) && j < ntap && n0 + n < N && k0 + 8 * q < K;   // K % 8 == 0: whole pieces
-      rb[i] = *reinterpret_cast<const u32x4*>(w_h + (ok ? ((int64_t)(tap0 + j) * N + n0 + n) * K : 0) + min(k0 + 8 * q, K - 8));
+      rb[i] = *reinterpret_cast<const u32x4*>(w_h + (ok ? ((tap0 + j) * N + n0 + n) * K : 0) + min(k0 + 8 * q, K - 8));
       keep_b |= ok ? 1u << i : 0u;
     }
   };
@@ -649,9 +650,12 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
     for (int j = 0; j < ntap; ++j) {
       const int off = sign * (tap0 + j - half) * dil;
       const int shift = off - base_off;
-      bool valid[U];
+      bool valid[U], inside[U];      // inside: the same for all tokens of the sub-tile (no sequence ends under it)
 #pragma unroll
-      for (int u = 0; u < U; ++u) valid[u] = tok[u] + off >= lo[u] && tok[u] + off < hi[u];
+      for (int u = 0; u < U; ++u) {
+        valid[u] = tok32[u] + off >= lo[u] && tok32[u] + off < hi[u];
+        inside[u] = __builtin_amdgcn_ballot_w64(!valid[u]) == 0ull;
+      }
       // lane half hb supplies channels 8 hb .. 8 hb + 7 of its row (tokens) / column (outputs)
       u32x4 a[3][U];
 #pragma unroll
@@ -663,7 +667,7 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
       for (int m = 2; m >= 0; --m)        // smallest terms first
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          a[m][u] = masked_piece(a[m][u], valid[u]);
+          if (!inside[u]) a[m][u] = masked_piece(a[m][u], valid[u]);
           acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[m][u]), __builtin_bit_cast(bf16x8, b),
                                                           acc[u], 0, 0, 0);
         }
@@ -680,13 +684,25 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
     hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b,
                                reinterpret_cast<float*>(&a_s[0][0][0]), wv, lane);
   } else {
-    bf16_t* dst = n < D ? dk : dv;
-    const int col = n < D ? n : n - D;
-    if (dst != nullptr && n_ok) {
+    // N = 2 D and D is a multiple of TN: the workgroup's columns are all keys' or all values'
+    bf16_t* const dst = n0 < D ? dk : dv;
+    const int first = n0 < D ? n0 : n0 - D;
+    if (dst != nullptr && !NARROW) {      // rows through LDS, 16 bytes per lane
+      constexpr int RSO = TN + 8;
+      static_assert(sizeof(a_s) >= TMC * RSO * sizeof(bf16_t), "the tile fits the staging rows");
+      bf16_t* const o_s = &a_s[0][0][0];
+      __syncthreads();
 #pragma unroll
-      for (int ur = 0; ur < 16 * U; ++ur) {
-        const int64_t t = token_of(ur);
-        if (t < total) dst[(t * Hkv + h) * D + col] = from_f32<bf16_t>(acc[ur / 16][ur % 16]);
+      for (int ur = 0; ur < 16 * U; ++ur)
+        o_s[(row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4)) * RSO + col0 + ql] = from_f32<bf16_t>(acc[ur / 16][ur % 16]);
+      __syncthreads();
+      const int rows_left = (int)(total - t0 < TMC ? total - t0 : TMC);
+      bf16_t* const o_t = dst + (t0 * Hkv + h) * D + first;
+#pragma unroll
+      for (int i = 0; i < TMC * (TN / 8) / 256; ++i) {
+        const int e = tid + 256 * i, row = e / (TN / 8), q = e % (TN / 8);
+        if (row < rows_left)
+          *reinterpret_cast<u32x4*>(o_t + (int64_t)row * Hkv * D + 8 * q) = *reinterpret_cast<const u32x4*>(o_s + row * RSO + 8 * q);
       }
     }
   }
