@@ -367,7 +367,7 @@ def bench_decode(args):
                 algorithmic_bytes_per_step=bytes_per_step, lazy=lazy,
                 roofline=dict(bound="hbm", kernel="decode step (all launches)", achieved=gbs, peak=PEAK_HBM_GBS,
                               unit="GB/s", frac=gbs / PEAK_HBM_GBS,
-                              traffic=measured_traffic("decode_bf16", "decode_main_kernel")))
+                              traffic=measured_traffic("decode_bf16", "decode_step_kernel")))
 
 
 def bench_train(args):
