@@ -110,8 +110,9 @@ int do_attention(const ltea_cfg& cfg, const void* q, int64_t qst, int64_t qsh, c
 
 // Saved state of a training forward, carved from the caller's workspace: an uncapped cache (compact arrays with
 // max_seqlen rows per head), the delta scratch of the backward, then the scoring kernels' own workspace.
+// most: room for any number of sequences up to this one, which may take more slices (what the size query reports).
 size_t carve_train(const ltea_cfg& cfg, int n_seqs, int64_t total, int max_seqlen, void* base, ltea_cache* c,
-                   float** delta, float** far_dk = nullptr, float** far_dv = nullptr) {
+                   float** delta, float** far_dk = nullptr, float** far_dv = nullptr, bool most = false) {
   const size_t esz = (size_t)elem_size(cfg.dtype);
   const size_t heads = (size_t)n_seqs * cfg.Hkv;
   const size_t cap = (size_t)(max_seqlen > 1 ? max_seqlen : 1);
@@ -129,8 +130,9 @@ size_t carve_train(const ltea_cfg& cfg, int n_seqs, int64_t total, int max_seqle
   int32_t* n_seen = reinterpret_cast<int32_t*>(take((size_t)n_seqs * 4));
   int32_t* n_scored = reinterpret_cast<int32_t*>(take((size_t)n_seqs * 4));
   float* d = reinterpret_cast<float*>(take((size_t)cfg.Hq * (size_t)total * 4 * (cfg.dtype == LTEA_BF16 ? 2 : 1)));
-  float* fk = reinterpret_cast<float*>(take((size_t)train_far_chunks(n_seqs, cfg.Hkv) * heads * cap * cfg.D * 4));
-  float* fv = reinterpret_cast<float*>(take((size_t)train_far_chunks(n_seqs, cfg.Hkv) * heads * cap * cfg.D * 4));
+  const size_t slices = most ? train_far_slices_most(n_seqs, cfg.Hkv) : (size_t)train_far_chunks(n_seqs, cfg.Hkv) * heads;
+  float* fk = reinterpret_cast<float*>(take(slices * cap * cfg.D * 4));
+  float* fv = reinterpret_cast<float*>(take(slices * cap * cfg.D * 4));
   if (far_dk) *far_dk = fk;
   if (far_dv) *far_dv = fv;
   if (c) *c = ltea_cache{k_win, v_win, win_score, k_ret, v_ret, ret_score, ret_pos, ret_count, n_seen, n_scored};
@@ -185,9 +187,10 @@ size_t ltea_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_
   return bytes;
 }
 
-static size_t decode_scored_workspace(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_seqs) {
+// What scoring packed receptive-field windows takes besides the step's own workspace.
+static size_t decode_windows_workspace(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_seqs) {
   const int rho = cnn_rho(cnn);
-  return align_up(decode_workspace(*cfg, n_seqs), 256) + align_up(decode_windows_layout(*cfg, rho, n_seqs, nullptr, nullptr), 256) +
+  return align_up(decode_windows_layout(*cfg, rho, n_seqs, nullptr, nullptr), 256) +
          score_workspace(*cfg, *cnn, (int64_t)n_seqs * (2 * rho + 1));
 }
 
@@ -195,11 +198,11 @@ size_t ltea_decode_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int
   if (check_cfg(cfg) != LTEA_OK || n_seqs < 0) return 0;
   if (cnn && check_cnn(cfg, cnn) != LTEA_OK) return 0;
   // CNNs that the step's own launch cannot hold are scored through the prefill kernels
-  const size_t step = align_up(decode_workspace(*cfg, n_seqs), 256);
+  const size_t step = align_up(decode_workspace_most(*cfg, n_seqs), 256);
   if (!cnn) return step;
   // the size for a stack stays above the minimum, which callers compare it with
   if (decode_scores_inside(*cfg, *cnn)) return step + (cnn->n_layers > 1 ? 256 : 0);
-  return decode_scored_workspace(cfg, cnn, n_seqs);
+  return step + decode_windows_workspace(cfg, cnn, n_seqs);
 }
 
 int ltea_score(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* k, const void* v, int64_t stride_tok,
@@ -444,7 +447,9 @@ int ltea_decode_step_static(const ltea_cfg* cfg, const ltea_cnn* cnn, const void
   if (st != LTEA_OK) return st;
   if (n_seqs < 0) return LTEA_EINVAL;
   // beyond the fixed scratch: refused here, before anything is looked up or launched
-  if (ltea_decode_workspace_bytes(cfg, cnn, n_seqs) > (size_t)LTEA_STATIC_SCRATCH_BYTES) return LTEA_EWORKSPACE;
+  const size_t need = align_up(decode_workspace(*cfg, n_seqs), 256) +
+                      (decode_scores_inside(*cfg, *cnn) ? 0 : decode_windows_workspace(cfg, cnn, n_seqs));
+  if (need > (size_t)LTEA_STATIC_SCRATCH_BYTES) return LTEA_EWORKSPACE;
   if (n_seqs == 0) return ltea_decode_step(cfg, cnn, q, k, v, out, cache, 0, nullptr, 0, stream);
   if (!q || !k || !v || !out || !cache) return LTEA_EINVAL;     // before the device is asked for the array's address
   hipError_t e = hipSuccess;
@@ -457,7 +462,7 @@ int ltea_decode_step_static(const ltea_cfg* cfg, const ltea_cnn* cnn, const void
 
 size_t ltea_decode_feat_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int32_t n_seqs) {
   if (check_cfg(cfg) != LTEA_OK || check_cnn(cfg, cnn) != LTEA_OK || n_seqs < 0) return 0;
-  return decode_scored_workspace(cfg, cnn, n_seqs);
+  return align_up(decode_workspace_most(*cfg, n_seqs), 256) + decode_windows_workspace(cfg, cnn, n_seqs);
 }
 
 int ltea_decode_step_feat(const ltea_cfg* cfg, const ltea_cnn* cnn, const ltea_rope* rope, const void* q, const void* k,
@@ -554,7 +559,7 @@ size_t ltea_train_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int3
   if (check_cfg(cfg) != LTEA_OK || (cnn && check_cnn(cfg, cnn) != LTEA_OK) || n_seqs < 0 || total_tokens < 0 ||
       max_seqlen < 0)
     return 0;
-  return carve_train(*cfg, n_seqs, total_tokens, max_seqlen, nullptr, nullptr, nullptr) +
+  return carve_train(*cfg, n_seqs, total_tokens, max_seqlen, nullptr, nullptr, nullptr, nullptr, nullptr, true) +
          (cnn ? score_workspace(*cfg, *cnn, total_tokens) : 0);
 }
 
@@ -628,7 +633,7 @@ int ltea_train_backward(const ltea_cfg* cfg, const void* q, int64_t q_stride_tok
 
 size_t ltea_cnn_backward_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int64_t total_tokens) {
   if (check_cfg(cfg) != LTEA_OK || check_cnn(cfg, cnn) != LTEA_OK || total_tokens < 0) return 0;
-  return align_up(cnn_backward_workspace(*cfg, *cnn, total_tokens), 256);
+  return align_up(cnn_backward_workspace_most(*cfg, *cnn, total_tokens), 256);
 }
 
 int ltea_cnn_backward(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* k_feat, const void* v, int64_t stride_tok,

@@ -1083,6 +1083,15 @@ WeightPlan weight_plan(const ltea_cfg& cfg, const ltea_cnn& cnn, int l, int64_t 
   P.chunks = (int)((total + P.chunk - 1) / P.chunk);
   return P;
 }
+// The most partials that any total up to this one takes (a shorter one may be cut finer): with W workgroups per partial and
+// n = ceil(512 / W), fewer than n chunks are halved, so a finer cut never exceeds 2 (n - 1) of them.
+int64_t most_chunks(const ltea_cfg& cfg, const ltea_cnn& cnn, int l, int64_t total) {
+  const WeightPlan P = weight_plan(cfg, cnn, l, total);
+  const int64_t w = (int64_t)P.tiles * cfg.Hkv * P.groups, finer = 2 * ((512 + w - 1) / w - 1);
+  const int64_t shortest = (total + 127) / 128, longest = (total + kTokChunk - 1) / kTokChunk;
+  const int64_t most = shortest < finer ? shortest : finer;
+  return most > longest ? most : longest;
+}
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
@@ -1101,7 +1110,8 @@ struct Layout {
   size_t bytes;
 };
 
-Layout carve(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total, void* base) {
+// most: room for every total up to this one (what the size query reports), else for exactly this one.
+Layout carve(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total, void* base, bool most = false) {
   Layout L;
   uintptr_t p = reinterpret_cast<uintptr_t>(base);   // integer arithmetic: a size query carves from a null base
   auto take = [&](size_t bytes) { char* r = reinterpret_cast<char*>(p); p += up256(bytes); return r; };
@@ -1142,7 +1152,7 @@ Layout carve(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total, void* base
   cin = 2 * cfg.D;
   for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) L.part_w[l] = L.part_b[l] = nullptr;
   for (int l = 0; l < cnn.n_layers; ++l) {
-    const size_t chunks = (size_t)weight_plan(cfg, cnn, l, total).chunks;
+    const size_t chunks = (size_t)(most ? most_chunks(cfg, cnn, l, total) : weight_plan(cfg, cnn, l, total).chunks);
     L.part_w[l] = reinterpret_cast<float*>(take(sizeof(float) * chunks * cfg.Hkv * cnn.c_out[l] * cin * cnn.kernel[l]));
     L.part_b[l] = reinterpret_cast<float*>(take(sizeof(float) * col_chunks * cfg.Hkv * cnn.c_out[l]));
     cin = cnn.c_out[l];
@@ -1311,6 +1321,9 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
 
 size_t cnn_backward_workspace(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total_tokens) {
   return carve(cfg, cnn, total_tokens, nullptr).bytes;
+}
+size_t cnn_backward_workspace_most(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total_tokens) {
+  return carve(cfg, cnn, total_tokens, nullptr, true).bytes;
 }
 
 hipError_t launch_cnn_backward(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v,

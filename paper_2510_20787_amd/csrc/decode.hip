@@ -70,17 +70,31 @@ hipError_t launch_step(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const S
 // measured, in us per lazy step, 25 / 15.3 / 12.7 / 11.8 (one sequence of 16 heads x 1536 rows of D = 128), 46 / 16.9 / 16.1
 // / 16.2 (32 heads x 3072 rows), 13.9 / 13.8 / 12.8 / 12.1 (8 heads x 1280 rows of D = 64); more workgroups than CUs gained
 // nothing (16 sequences of the latter: 15.9 -> 18.1).
+namespace {
+int64_t shares_by_rows(const ltea_cfg& cfg) {
+  const int64_t n = ((int64_t)cfg.window + cfg.budget) * 2 * cfg.D * (cfg.dtype == LTEA_F32 ? 4 : 2) / (64 * 1024);
+  return n < 1 ? 1 : n > 64 ? 64 : n;
+}
+size_t workspace_of(const ltea_cfg& cfg, int n_seqs, int64_t shares /* of all sequences, per KV head */) {
+  return ((size_t)shares * cfg.Hq * (cfg.D + 2) + (size_t)n_seqs * cfg.Hkv) * sizeof(float) +
+         ((size_t)n_seqs + (size_t)n_seqs * cfg.Hkv) * sizeof(int32_t);
+}
+}  // namespace
+
 int decode_num_splits(const ltea_cfg& cfg, int n_seqs) {
-  const int64_t heads = (int64_t)n_seqs * cfg.Hkv;
-  const int64_t bytes = ((int64_t)cfg.window + cfg.budget) * 2 * cfg.D * (cfg.dtype == LTEA_F32 ? 4 : 2);
-  int64_t n = bytes / (64 * 1024);
-  if (heads > 0 && n > 256 / heads) n = 256 / heads;
-  return n < 1 ? 1 : n > 64 ? 64 : (int)n;
+  const int64_t heads = (int64_t)n_seqs * cfg.Hkv, n = shares_by_rows(cfg);
+  const int64_t by_cus = heads > 0 ? 256 / heads : n;
+  return by_cus < 1 ? 1 : (int)(n < by_cus ? n : by_cus);
 }
 
 size_t decode_workspace(const ltea_cfg& cfg, int n_seqs) {
-  return (partial_floats(cfg, n_seqs, decode_num_splits(cfg, n_seqs)) + (size_t)n_seqs * cfg.Hkv) * sizeof(float) +
-         ((size_t)n_seqs + (size_t)n_seqs * cfg.Hkv) * sizeof(int32_t);
+  return workspace_of(cfg, n_seqs, (int64_t)n_seqs * decode_num_splits(cfg, n_seqs));
+}
+
+size_t decode_workspace_most(const ltea_cfg& cfg, int n_seqs) {
+  const int64_t shared = n_seqs * shares_by_rows(cfg), by_cus = 256 / cfg.Hkv;
+  const int64_t most = shared < by_cus ? shared : by_cus;
+  return workspace_of(cfg, n_seqs, most > n_seqs ? most : n_seqs);
 }
 
 // The documented bound on the CNN, for two generations of activation rows of the whole receptive field (the launch keeps

@@ -125,7 +125,10 @@ hipError_t launch_append_build(const ltea_cfg& cfg, const void* k_new, const voi
 
 // ---- (d) decode step -------------------------------------------------------------------------------
 int decode_num_splits(const ltea_cfg& cfg, int n_seqs);
+// What a step of n_seqs sequences needs, and the most that one of up to n_seqs needs (a smaller batch may share out its
+// heads' rows): what the size queries report, so that a buffer for the largest batch serves the smaller ones.
 size_t decode_workspace(const ltea_cfg& cfg, int n_seqs);
+size_t decode_workspace_most(const ltea_cfg& cfg, int n_seqs);
 // Whether the step's launch itself can run this CNN (its activation rows fit LDS beside the stream).
 bool decode_scores_inside(const ltea_cfg& cfg, const ltea_cnn& cnn);
 // rope, k_feat, status (all optional): rotary models, whose ring keys are rotated back for the scoring.
@@ -156,6 +159,7 @@ hipError_t launch_decode_step_lazy(const ltea_cfg& cfg, const void* q, const voi
 
 // ---- backward of the scoring CNN (cnn_backward.hip) ---------------------------------------------------------
 size_t cnn_backward_workspace(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total_tokens);
+size_t cnn_backward_workspace_most(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total_tokens);   // of any total up to it
 hipError_t launch_cnn_backward(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v,
                                int64_t stride_tok, int64_t stride_head, const SeqView& sv, const float* dz,
                                const ltea_cnn_grad& grad, void* dk, void* dv, void* workspace, hipStream_t stream);

@@ -13,6 +13,11 @@ inline int train_far_chunks(int n_seqs, int Hkv) {
   long c = heads > 0 ? (256 + heads - 1) / heads : 1;
   return (int)(c < 1 ? 1 : (c > kTrainFarChunksMax ? kTrainFarChunksMax : c));
 }
+// The most slices (chunks x heads) of any number of sequences up to n_seqs: h ceil(256 / h) <= 255 + h.
+inline size_t train_far_slices_most(int n_seqs, int Hkv) {
+  const size_t heads = (size_t)n_seqs * (size_t)Hkv;
+  return heads * kTrainFarChunksMax < 255 + heads ? heads * kTrainFarChunksMax : 255 + heads;
+}
 
 struct TrainArgs {
   const void *q, *k, *v, *out, *dout;

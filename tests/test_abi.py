@@ -381,3 +381,26 @@ def test_cnn_prepare_argument_errors():
     assert L.ltea_cnn_prepare(C.byref(cfg), C.byref(cnn), None, need, None) == B.LTEA_EWORKSPACE
     assert L.ltea_cnn_prepare(C.byref(cfg), C.byref(cnn), 0x1000, need - 1, None) == B.LTEA_EWORKSPACE
     assert L.ltea_cnn_prepare(C.byref(good_cfg(dtype="f32")), C.byref(cnn), None, 0, None) == B.LTEA_OK   # nothing to prepare
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("Hq,Hkv,D,window,budget,kernel,dilation,c_out", [
+    (32, 8, 64, 768, 512, (3, 3, 3), (2, 2, 2), (64, 32, 16)), (16, 16, 128, 1024, 512, (5,), (1,), (32,)),
+    (64, 1, 64, 2048, 1024, (7,), (1,), (32,)), (6, 3, 128, 300, 33, (3, 5), (1, 2), (20, 12)),
+    (2, 2, 64, 512, 100, (63,), (1,), (16,)),
+])
+def test_workspace_sizes_never_fall(dtype, Hq, Hkv, D, window, budget, kernel, dilation, c_out):
+    """A buffer sized for the largest batch serves every smaller one: no size query falls as its token or sequence count
+    rises, although the kernels cut small problems into more shares."""
+    L, cfg, cnn = B.lib(), good_cfg(Hq=Hq, Hkv=Hkv, D=D, window=window, budget=budget, dtype=dtype), fake_cnn(kernel, dilation, c_out)
+    cfg, cnn = C.byref(cfg), C.byref(cnn)
+    tokens = sorted({*range(1, 700), *(k + d for k in range(512, 70000, 512) for d in (-1, 0, 1))})
+    for size in (lambda n: L.ltea_cnn_backward_workspace_bytes(cfg, cnn, n), lambda n: L.ltea_workspace_bytes(cfg, cnn, 1, n, n),
+                 lambda n: L.ltea_append_workspace_bytes(cfg, cnn, 1, n, n), lambda n: L.ltea_train_workspace_bytes(cfg, cnn, 1, n, n)):
+        sizes = [size(n) for n in tokens]
+        assert sizes == sorted(sizes)
+    for size in (lambda n: L.ltea_decode_workspace_bytes(cfg, None, n), lambda n: L.ltea_decode_workspace_bytes(cfg, cnn, n),
+                 lambda n: L.ltea_decode_feat_workspace_bytes(cfg, cnn, n), lambda n: L.ltea_rescore_workspace_bytes(cfg, cnn, n),
+                 lambda n: L.ltea_append_workspace_bytes(cfg, cnn, n, 5000, 5000), lambda n: L.ltea_train_workspace_bytes(cfg, cnn, n, 5000, 5000)):
+        sizes = [size(n) for n in range(1, 600)]
+        assert sizes == sorted(sizes)
