@@ -69,10 +69,13 @@ hipError_t launch_step(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const S
 // A CU alone streams about 64 KB per us, handing shares over costs about 5 us: one share per 1 MB / 256 KB / 128 KB / 64 KB
 // measured, in us per lazy step, 25 / 15.3 / 12.7 / 11.8 (one sequence of 16 heads x 1536 rows of D = 128), 46 / 16.9 / 16.1
 // / 16.2 (32 heads x 3072 rows), 13.9 / 13.8 / 12.8 / 12.1 (8 heads x 1280 rows of D = 64); more workgroups than CUs gained
-// nothing (16 sequences of the latter: 15.9 -> 18.1).
+// nothing (16 sequences of the latter: 15.9 -> 18.1).  At least 128 rows per share: fp32 rows of D = 128 are 1 KB, and records for
+// twice the shares would not fit the fixed scratch of ltea_decode_step_static where a group has 64 query heads and more.
 namespace {
 int64_t shares_by_rows(const ltea_cfg& cfg) {
-  const int64_t n = ((int64_t)cfg.window + cfg.budget) * 2 * cfg.D * (cfg.dtype == LTEA_F32 ? 4 : 2) / (64 * 1024);
+  const int64_t rows = (int64_t)cfg.window + cfg.budget, bytes = rows * 2 * cfg.D * (cfg.dtype == LTEA_F32 ? 4 : 2);
+  const int64_t by_bytes = bytes / (64 * 1024), by_rows = (rows + 127) / 128;
+  const int64_t n = by_bytes < by_rows ? by_bytes : by_rows;
   return n < 1 ? 1 : n > 64 ? 64 : n;
 }
 size_t workspace_of(const ltea_cfg& cfg, int n_seqs, int64_t shares /* of all sequences, per KV head */) {

@@ -404,3 +404,20 @@ def test_workspace_sizes_never_fall(dtype, Hq, Hkv, D, window, budget, kernel, d
                  lambda n: L.ltea_append_workspace_bytes(cfg, cnn, n, 5000, 5000), lambda n: L.ltea_train_workspace_bytes(cfg, cnn, n, 5000, 5000)):
         sizes = [size(n) for n in range(1, 600)]
         assert sizes == sorted(sizes)
+
+
+def test_static_decode_accepts_what_fits_its_scratch():
+    """fp32 rows of D = 128 are 1 KB: sharing them out by bytes alone made more records than the fixed scratch holds for wide
+    groups whose 128-row shares fit (13 sequences of 64 query heads on one, 1536 rows).  The missing q is looked at after the
+    scratch check, so nothing is launched."""
+    L = B.lib()
+    cache = B.ltea_cache()
+    for name, _ in cache._fields_:
+        setattr(cache, name, 0x1000)
+    accepts = lambda G, Hkv, n, cnn: L.ltea_decode_step_static(
+        C.byref(good_cfg(Hq=Hkv * G, Hkv=Hkv, D=128, window=1024, budget=512, dtype="f32")), C.byref(cnn), None, 0x1000, 0x1000,
+        0x1000, C.byref(cache), n, None) == B.LTEA_EINVAL
+    deep = fake_cnn((3, 3, 3), (2, 2, 2), (64, 32, 16))
+    for G, Hkv, n, cnn in ((64, 1, 13, fake_cnn((63,))), (128, 1, 8, fake_cnn()), (64, 2, 8, deep), (64, 8, 2, deep), (128, 8, 1, deep)):
+        assert accepts(G, Hkv, n, cnn), (G, Hkv, n)
+    assert not accepts(128, 8, 32, deep)
