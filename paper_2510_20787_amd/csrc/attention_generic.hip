@@ -108,45 +108,75 @@ attention_fp32_kernel(const T* __restrict__ q, int64_t q_st, int64_t q_sh, const
     }
   };
 
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run, l_run;
   f32x4 o[DV];
+  // The matrix product multiplies every row of a block by its probability, and 0 * V of a masked pair is not zero when V is
+  // not finite.  Sums that end up not finite are therefore formed again (exact) from the pairs whose probability is not zero,
+  // one by one.  At the end of the walk: finite inputs, the case that is timed, pay one comparison.
+  auto walk = [&](const bool exact) {
+    m_run = -INFINITY;
+    l_run = 0.f;
 #pragma unroll
-  for (int e = 0; e < DV; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  Rows cur;
-  if (wave < n_blocks) load(wave, cur);
-  for (int blk = wave; blk < n_blocks; blk += kWaves) {
-    Rows nxt = cur;
-    if (blk + kWaves < n_blocks) load(blk + kWaves, nxt);
-    f32x4 sc = {0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < DV; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Rows cur;
+    if (wave < n_blocks) load(wave, cur);
+    for (int blk = wave; blk < n_blocks; blk += kWaves) {
+      Rows nxt = cur;
+      if (blk + kWaves < n_blocks) load(blk + kWaves, nxt);
+      f32x4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < DK; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[i], qf[i], sc, 0, 0, 0);
-    const bool win = blk < n_win;
-    float mx = -INFINITY;
+      for (int i = 0; i < DK; ++i) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[i], qf[i], sc, 0, 0, 0);
+      const bool win = blk < n_win;
+      float mx = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int j = cur.pos[r];
-      const bool valid = win ? (j <= qi && j > qi - window) : j <= qi - window;
-      sc[r] = valid ? sc[r] * scale : -INFINITY;
-      mx = fmaxf(mx, sc[r]);
+      for (int r = 0; r < 4; ++r) {
+        const int j = cur.pos[r];
+        const bool valid = win ? (j <= qi && j > qi - window) : j <= qi - window;
+        sc[r] = valid ? sc[r] * scale : -INFINITY;
+        mx = fmaxf(mx, sc[r]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+      const float m_new = fmaxf(m_run, mx);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;        // nothing visible so far: every factor below is 0
+      const float alpha = expf(m_run - m_use);
+      float p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = expf(sc[r] - m_use);
+      l_run = l_run * alpha + ((p[0] + p[1]) + (p[2] + p[3]));     // this lane's keys; the lane groups meet at the end
+      m_run = m_new;
+#pragma unroll
+      for (int e = 0; e < DV; ++e) o[e] *= alpha;
+      if (!exact) {
+#pragma unroll
+        for (int e = 0; e < DV; ++e)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.v[r][e], p[r], o[e], 0, 0, 0);
+      } else {
+        const int base = win ? jlo + blk * kBlock : (blk - n_win) * kBlock, last = win ? n - 1 : cnt - 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          for (int kg = 0; kg < 4; ++kg) {
+            const float pk = __shfl(p[r], 16 * kg + ql, kWave);
+            const int row = base + 4 * kg + r, rv = row < last ? row : last;
+            const T* vp = (win ? vb + rv * kv_st : vrb + (int64_t)rv * D) + DV * 4 * g;
+            if (pk == 0.f) continue;
+#pragma unroll
+            for (int e = 0; e < DV; ++e)
+#pragma unroll
+              for (int r2 = 0; r2 < 4; ++r2) o[e][r2] = fmaf(pk, to_f32(vp[DV * r2 + e]), o[e][r2]);
+          }
+      }
+      cur = nxt;
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-    const float m_new = fmaxf(m_run, mx);
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;          // nothing visible so far: every factor below is 0
-    const float alpha = expf(m_run - m_use);
-    float p[4];
+  };
+  walk(false);
+  bool finite = true;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) p[r] = expf(sc[r] - m_use);
-    l_run = l_run * alpha + ((p[0] + p[1]) + (p[2] + p[3]));       // this lane's keys; the lane groups meet at the end
-    m_run = m_new;
+  for (int e = 0; e < DV; ++e)
 #pragma unroll
-    for (int e = 0; e < DV; ++e) {
-      o[e] *= alpha;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.v[r][e], p[r], o[e], 0, 0, 0);
-    }
-    cur = nxt;
-  }
+    for (int r = 0; r < 4; ++r) finite = finite && fabsf(o[e][r]) < INFINITY;
+  if (__builtin_amdgcn_ballot_w64(!finite) != 0ull) walk(true);
 
   // ---- merge of the waves: register r of o[e] is head dimension DV * (4*g + r) + e of query ql -----------------
   l_run += __shfl_xor(l_run, 16, kWave);

@@ -1,0 +1,52 @@
+"""Values at which a matrix product differs from the sum it stands for: rows that are masked but not finite, sums that cancel to
+the last bits of their terms, infinite operands of split products."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ltea_oracle as orc
+from paper_2510_20787_amd import binding as B
+from paper_2510_20787_amd import workloads as wl
+from tests.gpu_util import DeviceWorkload, dev, to_np
+from tests.helpers import oracle_cfg
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,lens", [(64, 2, 2, [150, 33]), (128, 4, 2, [97])])
+def test_fp32_attention_keeps_masked_values_out(D, Hq, Hkv, lens):
+    """NaN and infinities in the values of tokens that are not kept: the queries that see such a token get what the sum gives,
+    all others (earlier ones in the same blocks of 16, later ones past its window) the result without it, at the fp32 bar."""
+    window, budget = 40, 12
+    w = wl.make_prefill("masked_values", 61 + D, "f32", lens, Hq, Hkv, D, window, budget, 1, 0.0, cnn_kernel=(3,), cnn_channels=(16,))
+    cfg = oracle_cfg(w)
+    d = DeviceWorkload(w)
+    cache = d.new_cache()
+    B.ltea_prefill(d.cfg, d.cnn, d.q, d.k, d.v, d.cu, d.max_seqlen, cache)
+    v = w.v.copy()
+    kept = [[sorted(cache.ret_pos[s, h, :int(cache.ret_count[s, h])].tolist()) for h in range(Hkv)] for s in range(w.n_seqs)]
+    for s, n in enumerate(lens):
+        lo = int(w.cu_seqlens[s])
+        for h in range(Hkv):
+            free = [j for j in range(n) if j not in kept[s][h]]
+            v[lo + free[len(free) // 4], h] = np.nan
+            v[lo + free[len(free) // 2], h] = np.inf
+            v[lo + n - 1, h, 3:] = -np.inf                # the newest token, one of its row's columns finite
+            v[lo + n - 1, h, :3] = 1.0
+    out = to_np(B.ltea_sparse_attention(d.cfg, d.q, d.k, dev(v, "f32"), d.cu, d.max_seqlen, cache))
+    seen_bad = seen_good = 0
+    with np.errstate(invalid="ignore"):
+        for s, n in enumerate(lens):
+            lo = int(w.cu_seqlens[s])
+            vs = v[lo:lo + n].astype(np.float64)
+            for h in range(Hkv):      # compact rows hold the clean values; kept tokens were not poisoned
+                for j in kept[s][h]:
+                    vs[j, h] = w.v[lo + j, h]
+            ref = orc.sparse_attention_sequence(w.q[lo:lo + n], w.k[lo:lo + n], vs, cfg, [np.asarray(x, np.int64) for x in kept[s]])
+            got = out[lo:lo + n]
+            fine = np.isfinite(ref)
+            assert np.array_equal(np.isnan(ref), np.isnan(got)) and np.array_equal(ref[~fine & ~np.isnan(ref)], got[~fine & ~np.isnan(ref)])
+            assert np.max(np.abs(got[fine] - ref[fine])) <= 1e-5
+            seen_bad += int((~fine).sum())
+            seen_good += int(fine.sum())
+    assert seen_bad > 0 and seen_good > 0
