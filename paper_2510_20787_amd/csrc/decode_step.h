@@ -723,8 +723,9 @@ decode_finish_kernel(CacheDev C, StepParams P, const T* __restrict__ k_new, cons
 //                                holds 8 columns of one row), Q as the B operand (heads past the group are zeros)
 //   O^T[d, head] += V^T . P^T    V rows pass through 32 rows of LDS of the wave's own (no barrier: a wave's LDS operations
 //                                are in order) and come back transposed (ds_read_b64_tr_b16); P goes from the
-//                                accumulator registers of S^T into the B operand, as a bf16 hi + lo pair in two MFMAs, so
-//                                that the probabilities keep 16 bits of mantissa
+//                                accumulator registers of S^T into the B operand as three bf16 terms whose sum is the fp32
+//                                probability exactly (8 bits of mantissa each), an MFMA per term: products with bf16
+//                                values are exact, so O is what fp32 multiply-adds give
 // In the accumulators a lane owns one head (lane % 16) and four rows per tile, so the softmax state is per lane.  The next
 // 32 rows are in flight from memory during this block.  Bound: HBM.  With fp32 VALU products instead (one row per 8
 // lanes, four heads) the paper's layer at B = 32 took 22.9 us for 84 MB of rows: the unpacking, the four dot products and
@@ -961,7 +962,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
         m_run = m_new;
         l_run *= alpha;
-        bf16x8 hi, lo;
+        bf16x8 hi, mid, lo;                // p = hi + mid + lo, exactly
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -969,7 +970,9 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
             const float p = __builtin_amdgcn_exp2f(sc[j][r] - m_use);
             l_run += p;
             hi[4 * j + r] = static_cast<bf16_t>(p);
-            lo[4 * j + r] = static_cast<bf16_t>(p - to_f32(hi[4 * j + r]));
+            const float rest = p - to_f32(hi[4 * j + r]);
+            mid[4 * j + r] = static_cast<bf16_t>(rest);
+            lo[4 * j + r] = static_cast<bf16_t>(rest - to_f32(mid[4 * j + r]));
           }
 #pragma unroll
         for (int d = 0; d < MS::DT; ++d) {
@@ -978,6 +981,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
           const bf16x8 av = __builtin_bit_cast(bf16x8, u32x4{a0[0], a0[1], a1[0], a1[1]});
           o[d] *= alpha;
           o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, hi, o[d], 0, 0, 0);
+          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, mid, o[d], 0, 0, 0);
           o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, lo, o[d], 0, 0, 0);
         }
       }

@@ -50,3 +50,46 @@ def test_fp32_attention_keeps_masked_values_out(D, Hq, Hkv, lens):
             seen_bad += int((~fine).sum())
             seen_good += int(fine.sum())
     assert seen_bad > 0 and seen_good > 0
+
+
+def few_rows_cache(cfg, D, scores, values, scale):
+    """A fresh cache of one (sequence, KV head) whose first rows have these attention scores (query = e_0) and values."""
+    cache = B.alloc_cache(cfg, 1)
+    n = len(scores) - 1
+    cache.k_win[0, 0, :n, 0] = torch.tensor(scores[:n] / scale).to(torch.bfloat16)
+    cache.v_win[0, 0, :n] = torch.from_numpy(values[:n]).to("cuda", torch.bfloat16)
+    cache.n_seen.fill_(n)
+    cache.n_scored.fill_(max(0, n - 1))
+    q = torch.zeros((1, cfg.Hq, D), dtype=torch.bfloat16, device="cuda")
+    q[:, :, 0] = 1
+    k = torch.zeros((1, 1, D), dtype=torch.bfloat16, device="cuda")
+    k[0, 0, 0] = float(scores[n] / scale)
+    return cache, q, k, torch.from_numpy(values[n:n + 1][None]).to("cuda", torch.bfloat16)
+
+
+@pytest.mark.parametrize("D,Hq", [(64, 1), (64, 4), (128, 8)])
+def test_decode_probabilities_keep_32_bits(D, Hq):
+    """Three rows whose weighted sum cancels down to 2^-18 of its terms: the values are bf16 numbers chosen, row by row, to take off
+    what the earlier rows leave.  A probability off by 2^-18 would leave nothing of the result; fp32 probabilities (relative error
+    2^-23 from the exponential) leave it 2^-4.  The bar is four times that."""
+    cfg = B.make_cfg(Hq, 1, D, 16, 4, 0, dtype="bf16")
+    scale = D ** -0.5
+    rng = np.random.default_rng(D + Hq)
+    bf = lambda x: wl.to_storage(np.asarray(x, np.float32), "bf16").astype(np.float64)
+    cnn = B.upload_cnn((3,), (1,), [np.zeros((1, 16, 2 * D, 3), np.float32)], [np.zeros((1, 16), np.float32)],
+                       np.zeros((1, 16), np.float32), np.zeros(1, np.float32), "bf16")
+    rel = []
+    for _ in range(12):
+        scores = np.concatenate([[0.0], -rng.uniform(0.1, 0.9, 2)])
+        scores = bf(scores / scale) * scale
+        p = np.exp(scores)
+        v = np.zeros((3, D))
+        v[1] = bf(rng.uniform(0.5, 1.5, D))
+        v[0] = -bf(p[1] * v[1])
+        v[2] = -bf((v[0] + p[1] * v[1]) / p[2])
+        ref = (p @ v) / p.sum()
+        cache, q, k, vn = few_rows_cache(cfg, D, scores, v.astype(np.float32), scale)
+        out = to_np(B.ltea_decode_step(cfg, cnn, q, k, vn, cache))[0]
+        for hq in range(Hq):
+            rel.append(np.linalg.norm(out[hq] - ref) / np.linalg.norm(ref))
+    assert max(rel) <= 2.0 ** -2, rel
