@@ -720,13 +720,17 @@ decode_finish_kernel(CacheDev C, StepParams P, const T* __restrict__ k_new, cons
 // ---- streaming for grouped queries (bf16): up to 16 query heads of a KV group per pass, on MFMA --------------------------
 // One wave takes 32 ring slots or 32 compact slots at a time, every W-th block of the workgroup's share:
 //   S^T[row, head] = K . Q^T     v_mfma_f32_16x16x32_bf16, K rows straight from global memory into the A operand (a lane
-//                                holds 8 columns of one row), Q as the B operand (heads past the group are zeros)
+//                                holds 8 columns of one row), Q as the B operand (unused columns are zeros)
 //   O^T[d, head] += V^T . P^T    V rows pass through 32 rows of LDS of the wave's own (no barrier: a wave's LDS operations
 //                                are in order) and come back transposed (ds_read_b64_tr_b16); P goes from the
 //                                accumulator registers of S^T into the B operand as three bf16 terms whose sum is the fp32
-//                                probability exactly (8 bits of mantissa each), an MFMA per term: products with bf16
-//                                values are exact, so O is what fp32 multiply-adds give
-// In the accumulators a lane owns one head (lane % 16) and four rows per tile, so the softmax state is per lane.  The next
+//                                probability exactly (8 bits of mantissa each): products with bf16 values are exact, so O is
+//                                what fp32 multiply-adds give
+// Groups of up to 5 query heads (GT = 5) use the columns that they leave empty for the terms: column 5 * term + head of one
+// MFMA, every lane working out the probability of its head and keeping its column's term of it.  Wider groups (GT = 16) take
+// an MFMA per term.  Paper's layer (4 query heads per KV head), 32 sequences, in us per lazy step: 19.5 with two terms in two
+// MFMAs (16 bits), 23.4 with three in three, 20.1 with three in one.
+// In the accumulators a lane owns one column (lane % 16) and four rows per tile, so the softmax state is per lane.  The next
 // 32 rows are in flight from memory during this block.  Bound: HBM.  With fp32 VALU products instead (one row per 8
 // lanes, four heads) the paper's layer at B = 32 took 22.9 us for 84 MB of rows: the unpacking, the four dot products and
 // their shuffles were as much VALU time as the rows' flight; the same launch on MFMA 18.3 us.
@@ -749,16 +753,16 @@ __device__ __forceinline__ u32x2 read_transposed4(const bf16_t* p) {
 
 // GT = query heads of a KV group handled per pass over the rows: every K/V row is loaded once per pass and used for GT
 // queries, so grouped-query configurations do not re-stream the cache once per query head.  1, 2 or 4 on the VALU (fp32
-// storage, and bf16 with one query head per KV head); 0: up to 16 on MFMA (bf16).
+// storage, and bf16 with one query head per KV head); up to 5 or up to 16 on MFMA (bf16).
 // W = waves per workgroup.  SK = scoring compiled into this instance: 3, 5 or 7 the batched single-layer role of that kernel
 // size, kDeepRole the one for stacks, kPerHead one (sequence, KV head) per workgroup, 0 none: one instance holding all
 // would carry the largest one's registers.
 template <typename T, int D, int GT, int W, int SK>
-__global__ void __launch_bounds__(W * kWave, GT == 0 && D == 128 ? 2 : 4)
+__global__ void __launch_bounds__(W * kWave, GT >= 5 && D == 128 ? 2 : 4)
 decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q, const T* __restrict__ k_new,
                    const T* __restrict__ v_new, Handover H, T* __restrict__ out) {
   constexpr int NT = W * kWave;
-  constexpr int kHeads = GT == 0 ? 16 : 1;   // heads merged at once
+  constexpr int kHeads = GT >= 5 ? 16 : 1;   // columns merged at once
   extern __shared__ __align__(16) float dyn_lds[];  // per-head scoring: two generations of activation rows
   __shared__ float red_m[W][kHeads], red_l[W][kHeads];
   // merge of the waves; before that the wave-private V tiles of the MFMA stream; the batched scoring roles' scratch
@@ -850,7 +854,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
     }
   };
 
-  if constexpr (GT == 0) {
+  if constexpr (GT >= 5) {
     using MS = MfmaStream<D>;
     static_assert(sizeof(scratch) >= W * MS::kTile * sizeof(bf16_t), "the V tiles of the four waves");
     const int kg = lane >> 4, c16 = lane & 15;
@@ -905,12 +909,16 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
           if (MS::RPI * i + v_row == special) R.v[i] = *reinterpret_cast<const u32x4*>(vs + 8 * v_piece);
       }
     };
+    // this lane's column: a head of the pass and (GT = 5) which term of its probabilities
+    constexpr bool kTermColumns = GT == 5;
+    const int term = kTermColumns ? c16 / 5 : 0, col_head = kTermColumns ? c16 % 5 : c16;
+    const float from_second = term > 0 ? 1.f : 0.f, from_third = term > 1 ? 1.f : 0.f;
     bf16x8 qf[MS::QK];
     auto load_queries = [&](int g0) {
 #pragma unroll
       for (int i = 0; i < MS::QK; ++i) {
-        const bool real = g0 + c16 < G;
-        u32x4 x = *reinterpret_cast<const u32x4*>(q + ((int64_t)b * P.Hq + h * G + (real ? g0 + c16 : 0)) * D + 32 * i + 8 * kg);
+        const bool real = g0 + col_head < G && term < 3;
+        u32x4 x = *reinterpret_cast<const u32x4*>(q + ((int64_t)b * P.Hq + h * G + (real ? g0 + col_head : 0)) * D + 32 * i + 8 * kg);
         if (!real) x = u32x4{0u, 0u, 0u, 0u};
         qf[i] = __builtin_bit_cast(bf16x8, x);
       }
@@ -922,74 +930,130 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
     load_queries(0);
     if (early) load(first, cur);
     decide(blk_end > ring_blocks);
-    for (int g0 = 0; g0 < G; g0 += 16) {
-      const int heads_here = G - g0 < 16 ? G - g0 : 16;
+    for (int g0 = 0; g0 < G; g0 += GT) {
+      const int heads_here = G - g0 < GT ? G - g0 : GT;
       if (g0 > 0) load_queries(g0);
       if (first < blk_end && !(early && g0 == 0)) load(first, cur);
-      float m_run = -INFINITY, l_run = 0.f;
+      float m_run, l_run;
       f32x4 o[MS::DT];
+      auto value_operand = [&](int d) {
+        const u32x2 a0 = read_transposed4(v_src + ((d ^ MS::swz(tr_row)) << 4));
+        const u32x2 a1 = read_transposed4(v_src + 16 * D + ((d ^ MS::swz(tr_row)) << 4));
+        return __builtin_bit_cast(bf16x8, u32x4{a0[0], a0[1], a1[0], a1[1]});
+      };
+      auto walk = [&](auto all_terms) {
+        m_run = -INFINITY;
+        l_run = 0.f;
 #pragma unroll
-      for (int d = 0; d < MS::DT; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int blk = first; blk < blk_end; blk += W) {
-        f32x4 sc[2];
+        for (int d = 0; d < MS::DT; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int blk = first; blk < blk_end; blk += W) {
+          f32x4 sc[2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int j = 0; j < 2; ++j) {
+            sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int i = 0; i < MS::QK; ++i)
-            sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.k[j][i]), qf[i], sc[j], 0, 0, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < MS::NV; ++i) {
-          const int r = MS::RPI * i + v_row;
-          *reinterpret_cast<u32x4*>(vt + r * D + (((v_piece >> 1) ^ MS::swz(r)) << 4) + (v_piece & 1) * 8) = cur.v[i];
-        }
-        if (blk + W < blk_end) load(blk + W, cur);
-        bool ring;
-        int row0, n_live;
-        where(blk, ring, row0, n_live);
-        float m_new = m_run;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            sc[j][r] = 16 * j + 4 * kg + r < n_live ? sc[j][r] * scale2 : -INFINITY;
-            m_new = fmaxf(m_new, sc[j][r]);
-          }
-        m_new = fmaxf(m_new, __shfl_xor(m_new, 16, kWave));
-        m_new = fmaxf(m_new, __shfl_xor(m_new, 32, kWave));
-        const float m_use = m_new == -INFINITY ? 0.f : m_new;    // nothing live yet: every factor below is 0
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
-        m_run = m_new;
-        l_run *= alpha;
-        bf16x8 hi, mid, lo;                // p = hi + mid + lo, exactly
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float p = __builtin_amdgcn_exp2f(sc[j][r] - m_use);
-            l_run += p;
-            hi[4 * j + r] = static_cast<bf16_t>(p);
-            const float rest = p - to_f32(hi[4 * j + r]);
-            mid[4 * j + r] = static_cast<bf16_t>(rest);
-            lo[4 * j + r] = static_cast<bf16_t>(rest - to_f32(mid[4 * j + r]));
+            for (int i = 0; i < MS::QK; ++i)
+              sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur.k[j][i]), qf[i], sc[j], 0, 0, 0);
           }
 #pragma unroll
-        for (int d = 0; d < MS::DT; ++d) {
-          const u32x2 a0 = read_transposed4(v_src + ((d ^ MS::swz(tr_row)) << 4));
-          const u32x2 a1 = read_transposed4(v_src + 16 * D + ((d ^ MS::swz(tr_row)) << 4));
-          const bf16x8 av = __builtin_bit_cast(bf16x8, u32x4{a0[0], a0[1], a1[0], a1[1]});
-          o[d] *= alpha;
-          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, hi, o[d], 0, 0, 0);
-          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, mid, o[d], 0, 0, 0);
-          o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, lo, o[d], 0, 0, 0);
+          for (int i = 0; i < MS::NV; ++i) {
+            const int r = MS::RPI * i + v_row;
+            *reinterpret_cast<u32x4*>(vt + r * D + (((v_piece >> 1) ^ MS::swz(r)) << 4) + (v_piece & 1) * 8) = cur.v[i];
+          }
+          if (blk + W < blk_end) load(blk + W, cur);
+          bool ring;
+          int row0, n_live;
+          where(blk, ring, row0, n_live);
+          float m_new = m_run;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              sc[j][r] = 16 * j + 4 * kg + r < n_live ? sc[j][r] * scale2 : -INFINITY;
+              m_new = fmaxf(m_new, sc[j][r]);
+            }
+          m_new = fmaxf(m_new, __shfl_xor(m_new, 16, kWave));
+          m_new = fmaxf(m_new, __shfl_xor(m_new, 32, kWave));
+          const float m_use = m_new == -INFINITY ? 0.f : m_new;    // nothing live yet: every factor below is 0
+          const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
+          m_run = m_new;
+          l_run *= alpha;
+          if constexpr (kTermColumns) {
+            // p = top + middle + rest, cut to 8 bits each: the lane's term is what the ones above it leave, cut in turn
+            auto top = [](float x) { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); };
+            u32x4 cut;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int r = 0; r < 4; r += 2) {
+                uint32_t x[2];
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                  const float p = __builtin_amdgcn_exp2f(sc[j][r + e] - m_use);
+                  l_run += p;
+                  const float y = fmaf(-from_second, top(p), p);
+                  x[e] = __float_as_uint(fmaf(-from_third, top(y), y));
+                }
+                cut[2 * j + r / 2] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302u);    // upper halves
+              }
+            const bf16x8 pt = __builtin_bit_cast(bf16x8, cut);
+#pragma unroll
+            for (int d = 0; d < MS::DT; ++d) {
+              o[d] *= alpha;
+              o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(value_operand(d), pt, o[d], 0, 0, 0);
+            }
+          } else {
+            bf16x8 hi, mid, lo;                // p = hi + mid + lo, exactly
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float p = __builtin_amdgcn_exp2f(sc[j][r] - m_use);
+                l_run += p;
+                hi[4 * j + r] = static_cast<bf16_t>(p);
+                const float rest = p - to_f32(hi[4 * j + r]);
+                mid[4 * j + r] = static_cast<bf16_t>(rest);
+                lo[4 * j + r] = static_cast<bf16_t>(rest - to_f32(mid[4 * j + r]));
+              }
+#pragma unroll
+            for (int d = 0; d < MS::DT; ++d) {
+              const bf16x8 av = value_operand(d);
+              o[d] *= alpha;
+              o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, hi, o[d], 0, 0, 0);
+              if constexpr (decltype(all_terms)::value) {
+                o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, mid, o[d], 0, 0, 0);
+                o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, lo, o[d], 0, 0, 0);
+              }
+            }
+          }
+        }
+      };
+      walk(std::true_type{});
+      // An infinite value times the lower terms of a probability, zero or of either sign, is not the infinity that the
+      // probability itself makes of it: such sums are what the leading terms give.
+      if constexpr (!kTermColumns) {
+        bool finite = true;
+#pragma unroll
+        for (int d = 0; d < MS::DT; ++d)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) finite = finite && fabsf(o[d][r]) < INFINITY;
+        if (__builtin_amdgcn_ballot_w64(!finite) != 0ull) {
+          f32x4 all[MS::DT];
+#pragma unroll
+          for (int d = 0; d < MS::DT; ++d) all[d] = o[d];
+          load(first, cur);
+          walk(std::false_type{});
+#pragma unroll
+          for (int d = 0; d < MS::DT; ++d)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[d][r] = fabsf(all[d][r]) < INFINITY ? all[d][r] : o[d][r];
         }
       }
-      // merge of the waves, fixed order; register r of o[d] is column 16*d + 4*kg + r of head g0 + c16
+      // merge of the waves, fixed order; register r of o[d] is head dimension 16*d + 4*kg + r of column c16
       l_run += __shfl_xor(l_run, 16, kWave);
       l_run += __shfl_xor(l_run, 32, kWave);
       __syncthreads();      // every wave is done with its V tile
-      if (c16 < heads_here) {
+      if (col_head < heads_here && term < 3) {
         if (kg == 0) { red_m[wave][c16] = m_run; red_l[wave][c16] = l_run; }
 #pragma unroll
         for (int d = 0; d < MS::DT; ++d) *reinterpret_cast<f32x4*>((scratch + (wave * kHeads + c16) * D) + 16 * d + 4 * kg) = o[d];
@@ -1006,7 +1070,12 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
           for (int w = 0; w < W; ++w) {
             const float f = __builtin_amdgcn_exp2f(red_m[w][g] - M);
             L = fmaf(red_l[w][g], f, L);
-            A = fmaf(scratch[(w * kHeads + g) * D + d], f, A);
+            float a = scratch[(w * kHeads + g) * D + d];
+            if constexpr (kTermColumns) {
+              const float lower = scratch[(w * kHeads + 5 + g) * D + d] + scratch[(w * kHeads + 10 + g) * D + d];
+              a = fabsf(a) < INFINITY ? a + lower : a;
+            }
+            A = fmaf(a, f, A);
           }
         }
         put_row(h * G + g0 + g, d, M * 0.6931471805599453f, L, A);
@@ -1276,7 +1345,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   auto launch = [&](auto gt, auto waves) {
     if (role == 0) return launch_sk(gt, waves, std::integral_constant<int, 0>{});
     if constexpr (sizeof(T) == 2) {
-      if constexpr (D == 64 && decltype(gt)::value == 0) {
+      if constexpr (D == 64 && decltype(gt)::value >= 5) {
         if (role == kDeepRole) return launch_sk(gt, waves, std::integral_constant<int, kDeepRole>{});
       }
       if (role == 3) return launch_sk(gt, waves, std::integral_constant<int, 3>{});
@@ -1286,7 +1355,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
     launch_sk(gt, waves, std::integral_constant<int, kPerHead>{});
   };
   auto launch_gt = [&](auto gt) {
-    constexpr bool kWide = decltype(gt)::value == 0 && D == 128;
+    constexpr bool kWide = decltype(gt)::value >= 5 && D == 128;
     const int w = step_waves(heads * P.nsplit + P.n_score_blocks, kWide);
     if constexpr (sizeof(T) == 2) {
       if (w == 8) return launch(gt, std::integral_constant<int, 8>{});
@@ -1295,7 +1364,8 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   };
   if constexpr (sizeof(T) == 2) {
     // one query head leaves 15 of the 16 matrix columns idle and streams as fast on the VALU
-    if (G > 1) launch_gt(std::integral_constant<int, 0>{});
+    if (G > 5) launch_gt(std::integral_constant<int, 16>{});
+    else if (G > 1) launch_gt(std::integral_constant<int, 5>{});
     else launch_gt(std::integral_constant<int, 1>{});
   } else {
     if (G % 4 == 0) launch_gt(std::integral_constant<int, 4>{});

@@ -93,3 +93,31 @@ def test_decode_probabilities_keep_32_bits(D, Hq):
         for hq in range(Hq):
             rel.append(np.linalg.norm(out[hq] - ref) / np.linalg.norm(ref))
     assert max(rel) <= 2.0 ** -2, rel
+
+
+@pytest.mark.parametrize("D,Hq", [(64, 1), (64, 4), (128, 20)])
+def test_decode_infinite_values(D, Hq):
+    """A visible infinite value makes its column infinite (NaN where two of them cancel, or where it is NaN itself) and leaves the
+    other columns alone, at the bf16 bar.  Scores as drawn, so that the probabilities' lower terms have either sign."""
+    cfg = B.make_cfg(Hq, 1, D, 64, 4, 0, dtype="bf16")
+    scale = D ** -0.5
+    rng = np.random.default_rng(7 * D + Hq)
+    bf = lambda x: wl.to_storage(np.asarray(x, np.float32), "bf16").astype(np.float64)
+    cnn = B.upload_cnn((3,), (1,), [np.zeros((1, 16, 2 * D, 3), np.float32)], [np.zeros((1, 16), np.float32)],
+                       np.zeros((1, 16), np.float32), np.zeros(1, np.float32), "bf16")
+    n = 50
+    scores = bf(rng.uniform(-2, 0, n) / scale) * scale
+    p = np.exp(scores)
+    v = bf(rng.standard_normal((n, D)))
+    for c in range(40):
+        v[rng.integers(n), c] = np.inf if c % 2 else -np.inf
+    v[3, 10], v[30, 10] = np.inf, -np.inf
+    v[17, 11] = np.nan
+    with np.errstate(invalid="ignore"):
+        ref = (p[:, None] * v).sum(0) / p.sum()
+    cache, q, k, vn = few_rows_cache(cfg, D, scores, v.astype(np.float32), scale)
+    out = to_np(B.ltea_decode_step(cfg, cnn, q, k, vn, cache))[0].astype(np.float64)
+    fine = np.isfinite(ref)
+    for hq in range(Hq):
+        assert np.array_equal(np.isnan(out[hq]), np.isnan(ref)) and np.array_equal(out[hq][np.isinf(ref)], ref[np.isinf(ref)])
+        assert np.max(np.abs(out[hq][fine] - ref[fine])) <= 2e-2 * np.max(np.abs(ref[fine]))
