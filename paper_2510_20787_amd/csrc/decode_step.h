@@ -443,18 +443,20 @@ __device__ __forceinline__ void score_new_tokens_mfma(const CnnDev& cnn, const S
 // Workgroup = (KV head, 8 sequences).  The logit of position t - rho depends on 2*L + 1 input positions, dilation apart,
 // 2*L - 1 outputs of the first layer, and so on down to one: those are the rows, (sequence, position) pairs, of small
 // GEMMs on v_mfma_f32_16x16x32_bf16, a wave per 16 output channels (and row tile where a layer has fewer channels).
-// Inputs are staged in LDS once (rotated back there for rotary models); activations stay in LDS as bf16 hi + lo pairs,
-// each multiplied in its own MFMA, as in the prefill kernels.  A lane's weights of 8 input channels and 3 taps are 24
+// Inputs are staged in LDS once (rotated back there for rotary models); activations stay in LDS as three bf16 terms whose sum
+// is the fp32 activation exactly, each multiplied in its own MFMA: the arithmetic of the per-head scoring.  A lane's weights of 8 input channels and 3 taps are 24
 // consecutive elements of its channel's row.
 // Bound: latency (n_seen -> rows and weights -> three short layers), hidden under the streaming.  The windows of the
 // whole batch packed in the main launch and scored by the prefill kernel in a launch of its own took 9-12 us of the step, and scoring each (sequence, head) in the workgroup that streams it 14 us of a 20 us step: a dozen
 // dependent trips to memory in front of the stream, or, requested ahead, more registers than the stream leaves.
 constexpr int kDeepSeqs = 8;
+constexpr float kMaxBf16 = 3.3895314e38f;                    // above: infinity in bf16
 constexpr int kDeepMaxCh = 64;                              // output channels per layer
 constexpr int kDeepXS = 2 * 64 + 8, kDeepAS = kDeepMaxCh + 8;   // row strides: 16-byte reads of 16 rows cover all banks
 constexpr int kDeepOffB = kDeepSeqs * 7 * kDeepXS * 2;      // region A: inputs, later layer 2's output; region B: layer 1's
-constexpr int kDeepLds = kDeepOffB + 2 * kDeepSeqs * 5 * kDeepAS * 2;
-static_assert(2 * kDeepSeqs * 3 * kDeepAS * 2 <= kDeepOffB, "layer 2's output fits region A");
+constexpr int kDeepTerms = 3;                               // of an activation
+constexpr int kDeepLds = kDeepOffB + kDeepTerms * kDeepSeqs * 5 * kDeepAS * 2;
+static_assert(kDeepTerms * kDeepSeqs * 3 * kDeepAS * 2 <= kDeepOffB, "layer 2's output fits region A");
 
 template <int CH> struct DeepWeights { u32x4 w[CH][3]; };   // [32-channel chunk][tap], as B operands
 
@@ -532,9 +534,9 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
   }
   if (out_of_tables && P.status != nullptr) atomicOr(P.status, LTEA_ROPE_RANGE);
 
-  // one layer: rows of n_in positions per sequence in `src` (hi, and lo lo_off elements behind it; 0: no lo part) to
-  // n_in - 2 positions per sequence in `dst` (hi, lo) or, from the last layer, fp32 rows of kDeepMaxCh
-  auto layer = [&](int l, const auto& W, int chunks, int rows_in, const bf16_t* src, int stride, int lo_off, unsigned char* dst,
+  // one layer: rows of n_in positions per sequence in `src` (the terms term_off elements apart; 0: one term) to
+  // n_in - 2 positions per sequence in `dst` (three terms) or, from the last layer, fp32 rows of kDeepMaxCh
+  auto layer = [&](int l, const auto& W, int chunks, int rows_in, const bf16_t* src, int stride, int term_off, unsigned char* dst,
                    bool last) {
     constexpr int kCh = sizeof(W.w) / sizeof(W.w[0]);
     const int nc = cnn.c_out[l] / 16, ct = wv % nc, rows_out = rows_in - 2, n_rows = kDeepSeqs * rows_out;
@@ -553,8 +555,11 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
           const bf16_t* ap = a + tap * stride + 32 * ch;
           const bf16x8 w = __builtin_bit_cast(bf16x8, W.w[ch][tap]);
           acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap), w, acc, 0, 0, 0);
-          if (lo_off != 0)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap + lo_off), w, acc, 0, 0, 0);
+          if (term_off != 0) {
+#pragma unroll
+            for (int u = 1; u < kDeepTerms; ++u)
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap + u * term_off), w, acc, 0, 0, 0);
+          }
         }
       }
 #pragma unroll
@@ -570,8 +575,12 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
           reinterpret_cast<float*>(dst)[so * kDeepMaxCh + 16 * ct + col] = val;
         } else {
           bf16_t* d = reinterpret_cast<bf16_t*>(dst) + ro * kDeepAS + 16 * ct + col;
-          d[0] = static_cast<bf16_t>(val);
-          d[n_rows * kDeepAS] = static_cast<bf16_t>(val - to_f32(d[0]));
+          const bf16_t t0 = static_cast<bf16_t>(val);
+          const float r1 = fabsf(val) <= kMaxBf16 ? val - to_f32(t0) : 0.f;     // infinite: no lower terms
+          const bf16_t t1 = static_cast<bf16_t>(r1);
+          d[0] = t0;
+          d[n_rows * kDeepAS] = t1;
+          d[2 * n_rows * kDeepAS] = static_cast<bf16_t>(r1 - to_f32(t1));
         }
       }
     }

@@ -121,3 +121,32 @@ def test_decode_infinite_values(D, Hq):
     for hq in range(Hq):
         assert np.array_equal(np.isnan(out[hq]), np.isnan(ref)) and np.array_equal(out[hq][np.isinf(ref)], ref[np.isinf(ref)])
         assert np.max(np.abs(out[hq][fine] - ref[fine])) <= 2e-2 * np.max(np.abs(ref[fine]))
+
+
+@pytest.mark.parametrize("kernel,channels,dilation", [((3, 3, 3), (64, 32, 16), (2, 2, 2)), ((3, 3), (32, 64), (3, 3))])
+def test_stack_scoring_role_keeps_32_bits(kernel, channels, dilation):
+    """Logits that the decode step finalises for a stack, eleven sequences (a second, partly filled group of eight): activations
+    rounded to 16 bits would be off by about 2^-18 of the logits (3.6e-6 measured for the prefill kernels, which do that), fp32
+    arithmetic by a few 2^-24.  Bar 2^-20."""
+    Bn, Hq, Hkv, D, window = 11, 4, 2, 64, 40
+    rng = np.random.default_rng(len(kernel))
+    c = wl.make_cnn(rng, "bf16", Hkv, D, kernel, channels, dilation, 0.1)
+    rho = c.rho
+    cfg = B.make_cfg(Hq, Hkv, D, window, 8, 0, dtype="bf16")
+    cnn = B.upload_cnn(c.kernel, c.dilation, c.w, c.bias, c.w_out, c.b_out, "bf16")
+    ocnn = orc.cnn_from_arrays(c.kernel, c.dilation, c.w, c.bias, c.w_out, c.b_out)
+    seen = rng.integers(rho, window, Bn)
+    rows = [wl.to_storage(rng.standard_normal((Bn, window, Hkv, D), dtype=np.float32), "bf16") for _ in range(2)]
+    cache = B.alloc_cache(cfg, Bn)
+    for s in range(Bn):
+        cache.k_win[s, :, :seen[s]] = dev(rows[0][s, :seen[s]].transpose(1, 0, 2), "bf16")
+        cache.v_win[s, :, :seen[s]] = dev(rows[1][s, :seen[s]].transpose(1, 0, 2), "bf16")
+    cache.n_seen.copy_(torch.from_numpy(seen.astype(np.int32)))
+    cache.n_scored.copy_(torch.from_numpy((seen - rho).astype(np.int32)))
+    at = np.arange(Bn)
+    q = dev(rng.standard_normal((Bn, Hq, D), dtype=np.float32), "bf16")
+    ws = torch.empty(int(B.lib().ltea_decode_workspace_bytes(B.C.byref(cfg), None, Bn)), dtype=torch.uint8, device="cuda")
+    B.ltea_decode_step(cfg, cnn, q, dev(rows[0][at, seen], "bf16"), dev(rows[1][at, seen], "bf16"), cache, workspace=ws)
+    got = np.stack([to_np(cache.win_score)[s, :, (seen[s] - rho) % window] for s in range(Bn)]).astype(np.float64)
+    ref = np.stack([orc.score_sequence(rows[0][s, :seen[s] + 1], rows[1][s, :seen[s] + 1], ocnn)[:, seen[s] - rho] for s in range(Bn)])
+    assert np.linalg.norm(got - ref) <= 2.0 ** -20 * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
