@@ -532,6 +532,39 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
                             lane);      // one layer only: pre receives d pre
 }
 
+// x = t0 + t1 + t2 in bf16 terms (t1, t2: exact residuals), four values packed per term.  Values beyond bf16's largest would
+// leave inf - inf: their first term is cut instead of rounded, and an infinity is 1 and 0 in front of itself, so that the
+// products that are taken with another split value (third by first, first by third) make the infinity that the value would.
+constexpr float kMaxBf16 = 3.3895314e38f;
+__device__ __forceinline__ void split_quad(float4 x, uint2 (&t)[3]) {
+  const float xs[4] = {x.x, x.y, x.z, x.w};
+  uint32_t b[3][4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const bf16_t b0 = from_f32<bf16_t>(xs[c]);
+    const float r1 = xs[c] - static_cast<float>(b0);
+    const bf16_t b1 = from_f32<bf16_t>(r1);
+    const float r2 = r1 - static_cast<float>(b1);
+    b[0][c] = (uint32_t)__builtin_bit_cast(uint16_t, b0);
+    b[1][c] = (uint32_t)__builtin_bit_cast(uint16_t, b1);
+    b[2][c] = (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(r2));
+  }
+  if (fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) > kMaxBf16) {
+    auto bits = [](float y) { return (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(y)); };
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (!(fabsf(xs[c]) > kMaxBf16)) continue;
+      const bool infinite = fabsf(xs[c]) == INFINITY;
+      const float top = __uint_as_float(__float_as_uint(xs[c]) & 0xFFFF0000u);
+      b[0][c] = infinite ? bits(copysignf(1.f, xs[c])) : bits(top);
+      b[1][c] = infinite ? 0u : bits(xs[c] - top);
+      b[2][c] = infinite ? bits(xs[c]) : bits((xs[c] - top) - __uint_as_float(bits(xs[c] - top) << 16));
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 3; ++m) t[m] = make_uint2(b[m][0] | b[m][1] << 16, b[m][2] | b[m][3] << 16);
+}
+
 // The convs whose activations are fp32 on bf16 storage: out[t][n] = sum_tap sum_k in[t + sign * off(tap)][k] * W(tap, k, n),
 // sign = -1 towards the input, +1 the forward of the layers after the first.  The weights (w: [h][tap][n][k]) are bf16
 // values; the fp32 operand is split into three bf16 terms (x = hi + mid + lo up to 2^-24 of x), whose products with the
@@ -613,29 +646,16 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
     asm volatile("" : "+v"(x));      // the loaded value is needed whatever the mask says: the load stays unconditional
     return keep ? x : u32x4{0u, 0u, 0u, 0u};
   };
-  auto bits = [](float x) { return (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(x)); };
   fetch(0);
   for (int stage = 0; stage < stages; ++stage) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PSA; ++i) {
       const int e = tid + 256 * i, row = e / (KCS / 4), q = e % (KCS / 4);
-      const float4 x = masked_quad(ra[i], (keep_a >> i & 1u) ? 0xFu : 0u);
-      const float xs[4] = {x.x, x.y, x.z, x.w};
-      uint32_t t[3][4];
+      uint2 t[3];
+      split_quad(masked_quad(ra[i], (keep_a >> i & 1u) ? 0xFu : 0u), t);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const bf16_t b0 = from_f32<bf16_t>(xs[c]);
-        const float r1 = xs[c] - static_cast<float>(b0);       // exact
-        const bf16_t b1 = from_f32<bf16_t>(r1);
-        const float r2 = r1 - static_cast<float>(b1);           // exact
-        t[0][c] = (uint32_t)__builtin_bit_cast(uint16_t, b0);
-        t[1][c] = (uint32_t)__builtin_bit_cast(uint16_t, b1);
-        t[2][c] = bits(r2);
-      }
-#pragma unroll
-      for (int m = 0; m < 3; ++m)
-        *reinterpret_cast<uint2*>(&a_s[m][row][4 * q]) = make_uint2(t[m][0] | t[m][1] << 16, t[m][2] | t[m][3] << 16);
+      for (int m = 0; m < 3; ++m) *reinterpret_cast<uint2*>(&a_s[m][row][4 * q]) = t[m];
     }
 #pragma unroll
     for (int i = 0; i < PSB; ++i) {
@@ -843,24 +863,6 @@ template <class X, int WC, int WM> struct WeightTile {
 inline int weight_groups(int ks, int dil, bool split) {
   const int reach = 1 + (split ? 16 : 64) / dil, most = reach < NTW ? reach : NTW;
   return (ks + most - 1) / most;
-}
-
-// x = t0 + t1 + t2 in bf16 terms (t1, t2: exact residuals), four values packed per term.
-__device__ __forceinline__ void split_quad(float4 x, uint2 (&t)[3]) {
-  const float xs[4] = {x.x, x.y, x.z, x.w};
-  uint32_t b[3][4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const bf16_t b0 = from_f32<bf16_t>(xs[c]);
-    const float r1 = xs[c] - static_cast<float>(b0);
-    const bf16_t b1 = from_f32<bf16_t>(r1);
-    const float r2 = r1 - static_cast<float>(b1);
-    b[0][c] = (uint32_t)__builtin_bit_cast(uint16_t, b0);
-    b[1][c] = (uint32_t)__builtin_bit_cast(uint16_t, b1);
-    b[2][c] = (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(r2));
-  }
-#pragma unroll
-  for (int m = 0; m < 3; ++m) t[m] = make_uint2(b[m][0] | b[m][1] << 16, b[m][2] | b[m][3] << 16);
 }
 
 // Input channel m is x0's for m < split, else x1's channel m - split (the keys and the values; one array for X = float).

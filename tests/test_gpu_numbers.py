@@ -150,3 +150,35 @@ def test_stack_scoring_role_keeps_32_bits(kernel, channels, dilation):
     got = np.stack([to_np(cache.win_score)[s, :, (seen[s] - rho) % window] for s in range(Bn)]).astype(np.float64)
     ref = np.stack([orc.score_sequence(rows[0][s, :seen[s] + 1], rows[1][s, :seen[s] + 1], ocnn)[:, seen[s] - rho] for s in range(Bn)])
     assert np.linalg.norm(got - ref) <= 2.0 ** -20 * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("kernel,channels", [((5,), (32,)), ((3, 3), (32, 16))])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_cnn_backward_with_infinite_gradients(dtype, kernel, channels):
+    """An infinite d logit (an overflown loss) reaches the gradients as the sums make it: infinite where all its products have one
+    sign, NaN where they have not, nothing elsewhere.  Weights of one sign, so that both occur."""
+    lens, Hkv, D = [90, 140], 2, 64
+    w = wl.make_prefill("infinite_dz", 5 + len(kernel), dtype, lens, Hkv, Hkv, D, 32, 4, 0, 0.0, cnn_kernel=kernel,
+                        cnn_channels=channels, w_std=0.1)
+    for l in range(len(kernel)):
+        w.cnn.w[l] = np.abs(w.cnn.w[l])
+    w.cnn.w_out = np.abs(w.cnn.w_out)
+    cnn = orc.cnn_from_arrays(w.cnn.kernel, w.cnn.dilation, w.cnn.w, w.cnn.bias, w.cnn.w_out, w.cnn.b_out)
+    rng = np.random.default_rng(3)
+    dz = rng.standard_normal((Hkv, w.total_tokens), dtype=np.float32)
+    dz[0, 40] = np.inf
+    dz[1, 200] = -np.inf
+    d = DeviceWorkload(w)
+    got = B.ltea_cnn_backward(d.cfg, d.cnn, d.k, d.v, d.cu, d.max_seqlen, torch.from_numpy(dz).cuda())
+    with np.errstate(invalid="ignore"):
+        ref = orc.score_backward(w.k, w.v, cnn, w.cu_seqlens, dz.astype(np.float64))
+    flat = lambda r: [y for x in r for y in (x if isinstance(x, (list, tuple)) else [x])]
+    infinite = 0
+    for g, r in zip(flat(got), flat(ref)):
+        g = to_np(g).astype(np.float64)
+        assert np.array_equal(np.isnan(g), np.isnan(r)) and np.array_equal(g[np.isinf(r)], r[np.isinf(r)])
+        infinite += int(np.isinf(r).sum())
+        fine = np.isfinite(r)
+        if fine.any():
+            assert np.max(np.abs(g[fine] - r[fine])) <= 2e-2 * np.max(np.abs(r[fine]))
+    assert infinite > 0
