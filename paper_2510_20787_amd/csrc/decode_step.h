@@ -51,7 +51,10 @@ constexpr int kPerHead = 1, kDeepRole = 9;   // scoring roles besides the kernel
 
 struct CnnDev {
   int n_layers;
-  int kernel[LTEA_MAX_CNN_LAYERS], dilation[LTEA_MAX_CNN_LAYERS], c_out[LTEA_MAX_CNN_LAYERS];   // dilation in units of P.unit
+  int kernel[LTEA_MAX_CNN_LAYERS], c_out[LTEA_MAX_CNN_LAYERS];
+  // Per-head scoring: the outputs of a layer that a logit depends on are `unit` positions apart (the greatest common divisor of
+  // the dilations after it); dilation and row_step (from one such output to the next) are in rows of the layer's input.
+  int unit[LTEA_MAX_CNN_LAYERS], dilation[LTEA_MAX_CNN_LAYERS], row_step[LTEA_MAX_CNN_LAYERS];
   const void* w[LTEA_MAX_CNN_LAYERS];
   const float* bias[LTEA_MAX_CNN_LAYERS];
   const void* w_out;
@@ -195,12 +198,13 @@ __device__ __forceinline__ void put_logit(const CacheDev& C, const StepParams& P
 constexpr int kRoleThreads = 256, kRoleWaves = 4;   // the batched scoring roles; a launch's further waves leave at once
 
 // ---- scoring, one (sequence, KV head) per workgroup: any CNN, fp32 arithmetic ------------------------------------
-// One layer over the rows in LDS: KS taps, `dil` rows apart, RR output rows per pass.  A thread owns one (output channel,
-// every lpc-th run of 8 input channels); a run's weights are 8*KS consecutive elements of the channel's row ([channel][tap]
-// order), the runs of a channel meet in a shuffle reduction.
-template <typename T, int KS, int RR, int NT>
-__device__ __forceinline__ void conv_rows(const T* __restrict__ W, const float* __restrict__ bias, int cin, int cout,
-                                          const float* cur, float* nxt, int row_f, int out_rows, int first_pos, int unit) {
+// One layer over the rows in LDS: KS taps, `dil` rows apart, RR output rows, `step` rows apart, per pass (DENSE: both 1,
+// neighbouring outputs share their rows).  A thread owns one (output channel, every lpc-th run of 8 input channels); a run's weights are 8*KS
+// consecutive elements of the channel's row ([channel][tap] order), the runs of a channel meet in a shuffle reduction.
+template <typename T, int KS, int RR, bool DENSE, int NT>
+__device__ __forceinline__ void conv_rows(const T* __restrict__ W, const float* __restrict__ bias, int cin, int cout, int dil,
+                                          int step, const float* cur, float* nxt, int row_f, int out_rows, int first_pos,
+                                          int unit) {
   const int tid = threadIdx.x, n_runs = cin / 8;
   int lpc = n_runs < kWave ? n_runs : kWave;                    // lanes per channel: a power of two
   lpc = 1 << (31 - __clz(lpc));
@@ -223,19 +227,31 @@ __device__ __forceinline__ void conv_rows(const T* __restrict__ W, const float* 
           else return __uint_as_float(f & 1 ? raw[f / 8][f % 8 / 2] & 0xFFFF0000u : raw[f / 8][f % 8 / 2] << 16);
         };
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+        for (int half = 0; half < 2; ++half) {
+          auto x_of = [&](int row) { return *reinterpret_cast<const f32x4*>(cur + row * row_f + 8 * run + 4 * half); };
+          if constexpr (DENSE) {
 #pragma unroll
-          for (int i = 0; i < RR + KS - 1; ++i) {               // input row r0 + i is tap i - r of output r0 + r
-            const int row = r0 + i < out_rows + KS - 1 ? r0 + i : r0;   // past the last: not used by a stored output
-            const f32x4 x = *reinterpret_cast<const f32x4*>(cur + row * row_f + 8 * run + 4 * half);
+            for (int i = 0; i < RR + KS - 1; ++i) {             // input row r0 + i is tap i - r of output r0 + r
+              const f32x4 x = x_of(r0 + i < out_rows + KS - 1 ? r0 + i : r0);   // past the last: not used by a stored output
 #pragma unroll
-            for (int r = 0; r < RR; ++r) {
-              const int tap = i - r;
-              if (tap < 0 || tap >= KS) continue;
+              for (int r = 0; r < RR; ++r) {
+                const int tap = i - r;
+                if (tap < 0 || tap >= KS) continue;
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[r] = fmaf(x[e], weight((4 * half + e) * KS + tap), acc[r]);
+                for (int e = 0; e < 4; ++e) acc[r] = fmaf(x[e], weight((4 * half + e) * KS + tap), acc[r]);
+              }
             }
+          } else {
+#pragma unroll
+            for (int r = 0; r < RR; ++r)
+#pragma unroll
+              for (int tap = 0; tap < KS; ++tap) {
+                const f32x4 x = x_of((r0 + r < out_rows ? r0 + r : r0) * step + tap * dil);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[r] = fmaf(x[e], weight((4 * half + e) * KS + tap), acc[r]);
+              }
           }
+        }
       }
 #pragma unroll
       for (int r = 0; r < RR; ++r)
@@ -250,23 +266,117 @@ __device__ __forceinline__ void conv_rows(const T* __restrict__ W, const float* 
   }
 }
 
-// The same for any layer, one thread per output.
-template <typename T, int NT>
+// The same for any kernel size and channel count: a thread owns one (output channel, every lpc-th piece of EPP consecutive
+// elements of its row), several pieces in flight.
+template <typename T, int EPP, int NT>
 __device__ __forceinline__ void conv_rows_any(const T* __restrict__ W, const float* __restrict__ bias, int cin, int cout, int ks,
-                                              int dil, const float* cur, float* nxt, int row_f, int out_rows, int first_pos,
+                                              int dil, int step, const float* cur, float* nxt, int row_f, int out_rows, int first_pos,
                                               int unit) {
-  for (int idx = threadIdx.x; idx < out_rows * cout; idx += NT) {
-    const int r = idx / cout, c = idx - r * cout;
-    float acc = bias[c];
-    for (int m = 0; m < cin; ++m)
-      for (int tap = 0; tap < ks; ++tap) acc = fmaf(cur[(r + tap * dil) * row_f + m], to_f32(W[((int64_t)c * cin + m) * ks + tap]), acc);
-    nxt[r * row_f + c] = first_pos + r * unit >= 0 ? silu_f32(acc) : 0.f;
+  constexpr int kAhead = EPP == 1 ? 8 : 4, RR = 4;
+  const int tid = threadIdx.x, n_pieces = cin * ks / EPP;
+  int lpc = n_pieces < kWave ? n_pieces : kWave;
+  lpc = 1 << (31 - __clz(lpc));
+  while (lpc > 1 && lpc * cout > NT) lpc >>= 1;
+  const int sub = tid & (lpc - 1), c_step = NT / lpc;
+  const int ch_step = lpc * EPP / ks, tap_step = lpc * EPP % ks;
+  for (int c0 = 0; c0 < cout; c0 += c_step) {
+    const int c = c0 + tid / lpc;
+    const T* wr = W + (int64_t)(c < cout ? c : 0) * cin * ks;
+    for (int r0 = 0; r0 < out_rows; r0 += RR) {
+      float acc[RR];
+#pragma unroll
+      for (int r = 0; r < RR; ++r) acc[r] = 0.f;
+      int m0 = sub * EPP / ks, tap0 = sub * EPP % ks;       // input channel and tap of a piece's first element
+      for (int p0 = sub; p0 < n_pieces; p0 += kAhead * lpc) {
+        float w[kAhead][EPP];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int p = p0 + u * lpc < n_pieces ? p0 + u * lpc : p0;
+          if constexpr (EPP == 1) w[u][0] = to_f32(wr[p]);
+          else Piece<T>::load(wr + (int64_t)p * EPP, w[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          if (p0 + u * lpc < n_pieces) {
+            int m = m0, tap = tap0;
+#pragma unroll
+            for (int e = 0; e < EPP; ++e) {
+              const float* x = cur + (r0 * step + tap * dil) * row_f + m;
+#pragma unroll
+              for (int r = 0; r < RR; ++r)
+                if (r0 + r < out_rows) acc[r] = fmaf(x[r * step * row_f], w[u][e], acc[r]);
+              if (++tap == ks) { tap = 0; ++m; }
+            }
+          }
+          m0 += ch_step;
+          tap0 += tap_step;
+          if (tap0 >= ks) { tap0 -= ks; ++m0; }
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < RR; ++r)
+        for (int off = lpc / 2; off > 0; off >>= 1) acc[r] += __shfl_xor(acc[r], off, kWave);
+      if (sub == 0 && c < cout) {
+#pragma unroll
+        for (int r = 0; r < RR; ++r)
+          if (r0 + r < out_rows) nxt[(r0 + r) * row_f + c] = first_pos + (r0 + r) * unit >= 0 ? silu_f32(acc[r] + bias[c]) : 0.f;
+      }
+    }
   }
 }
 
-// Logit of position t - rho of one (sequence, KV head): any CNN.  The
-// rows of layer l are positions `unit` apart around t - rho; `lds` holds two generations of 2*rho/unit + 1 rows.
-// Bound: latency, a trip to memory per layer.
+// A single layer: with its inputs staged in the order of a weight row, [channel][tap], an output is one dot product.  A thread
+// owns one (output channel, every lpc-th piece of EPP consecutive elements), eight pieces in flight.  k = 9, 128 -> 32 channels,
+// one sequence of the paper's other sizes: a step took 102 us with one thread per output and a load per multiply-add, 11.3 in
+// this form.
+template <typename T, int EPP, int NT>
+__device__ __forceinline__ void conv_flat(const T* __restrict__ W, const float* __restrict__ bias, int n_el, int cout,
+                                          const float* x, float* out) {
+  constexpr int kAhead = 8;
+  const int tid = threadIdx.x, n_pieces = n_el / EPP;
+  int lpc = n_pieces < kWave ? n_pieces : kWave;
+  lpc = 1 << (31 - __clz(lpc));
+  while (lpc > 1 && lpc * cout > NT) lpc >>= 1;
+  const int sub = tid & (lpc - 1);
+  for (int c0 = 0; c0 < cout; c0 += NT / lpc) {
+    const int c = c0 + tid / lpc;
+    const T* wr = W + (int64_t)(c < cout ? c : 0) * n_el;
+    float acc[2] = {0.f, 0.f};
+    for (int p0 = sub; p0 < n_pieces; p0 += kAhead * lpc) {
+      float w[kAhead][EPP];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int p = p0 + u * lpc < n_pieces ? p0 + u * lpc : p0;
+        if constexpr (EPP == 1) w[u][0] = to_f32(wr[p]);
+        else Piece<T>::load(wr + (int64_t)p * EPP, w[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (p0 + u * lpc >= n_pieces) break;
+        const float* xp = x + (p0 + u * lpc) * EPP;
+        if constexpr (EPP == 1) {
+          acc[u & 1] = fmaf(xp[0], w[u][0], acc[u & 1]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < EPP; e += 4) {
+            const f32x4 y = *reinterpret_cast<const f32x4*>(xp + e);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[u & 1] = fmaf(y[i], w[u][e + i], acc[u & 1]);
+          }
+        }
+      }
+    }
+    float a = acc[0] + acc[1];
+    for (int off = lpc / 2; off > 0; off >>= 1) a += __shfl_xor(a, off, kWave);
+    if (sub == 0 && c < cout) out[c] = silu_f32(a + bias[c]);
+  }
+}
+
+// Logit of position t - rho of one (sequence, KV head): any CNN.  The inputs are rows of positions `unit` apart around t - rho;
+// `lds` holds two generations of 2*rho/unit + 1 rows.  Of every layer only the rows that the layers after it read are formed (3 + 3
+// + 3 taps with dilations 1, 2, 4: 7, 3 and 1 of them instead of 13, 9 and 1; a step of 128 sequences of 8 KV heads 176 -> 74 us,
+// of one sequence 47 -> 16, taps more than a row apart one thread per output before).
+// Bound: latency, a trip to memory per layer; from some 2000 (sequence, head) pairs on the weights' trips from L2.
 template <typename T, int NT>
 __device__ __forceinline__ void score_token(const CnnDev& cnn, const StepParams& P, const CacheDev& C, const T* __restrict__ k_new,
                                             const T* __restrict__ v_new, int64_t head, int h, int t, float* lds, float* ws_logit) {
@@ -298,25 +408,44 @@ __device__ __forceinline__ void score_token(const CnnDev& cnn, const StepParams&
     }
     float x[EPP];
     Piece<T>::unpack(raw, x);
+    if (cnn.n_layers == 1) {
 #pragma unroll
-    for (int i = 0; i < EPP; i += 4) *reinterpret_cast<f32x4*>(cur + r * row_f + m + i) = f32x4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+      for (int i = 0; i < EPP; ++i) cur[(m + i) * rows0 + r] = x[i];      // the order of a weight row
+    } else {
+#pragma unroll
+      for (int i = 0; i < EPP; i += 4) *reinterpret_cast<f32x4*>(cur + r * row_f + m + i) = f32x4{x[i], x[i + 1], x[i + 2], x[i + 3]};
+    }
   }
   if (out_of_tables && P.status != nullptr) atomicOr(P.status, LTEA_ROPE_RANGE);
   __syncthreads();
   int rows = rows0, cin = 2 * D;
   for (int l = 0; l < cnn.n_layers; ++l) {
-    const int ks = cnn.kernel[l], dil = cnn.dilation[l], cout = cnn.c_out[l];
-    const int out_rows = rows - dil * (ks - 1);
-    const int first_pos = t - rho - (out_rows - 1) / 2 * unit;
+    const int ks = cnn.kernel[l], dil = cnn.dilation[l], step = cnn.row_step[l], cout = cnn.c_out[l], apart = cnn.unit[l];
+    const int out_rows = (rows - 1 - dil * (ks - 1)) / step + 1;
+    const int first_pos = t - rho - (out_rows - 1) / 2 * apart;
     const T* W = static_cast<const T*>(cnn.w[l]) + (int64_t)h * cout * cin * ks;
     const float* bias = cnn.bias[l] + h * cout;
-    // whole runs, 16-byte aligned, taps on adjacent rows
-    const bool runs = cin % 8 == 0 && (dil == 1 || ks == 1) && (reinterpret_cast<uintptr_t>(W) & 15u) == 0;
-    if (runs && ks == 1) conv_rows<T, 1, 1, NT>(W, bias, cin, cout, cur, nxt, row_f, out_rows, first_pos, unit);
-    else if (runs && ks == 3) conv_rows<T, 3, 5, NT>(W, bias, cin, cout, cur, nxt, row_f, out_rows, first_pos, unit);
-    else if (runs && ks == 5) conv_rows<T, 5, 1, NT>(W, bias, cin, cout, cur, nxt, row_f, out_rows, first_pos, unit);
-    else if (runs && ks == 7) conv_rows<T, 7, 1, NT>(W, bias, cin, cout, cur, nxt, row_f, out_rows, first_pos, unit);
-    else conv_rows_any<T, NT>(W, bias, cin, cout, ks, dil, cur, nxt, row_f, out_rows, first_pos, unit);
+    // whole runs, 16-byte aligned
+    const bool aligned = (reinterpret_cast<uintptr_t>(W) & 15u) == 0, runs = cin % 8 == 0 && aligned;
+    const bool dense = dil == 1 && step == 1;
+    if (cnn.n_layers == 1) {
+      if (aligned) conv_flat<T, EPP, NT>(W, bias, cin * ks, cout, cur, nxt);       // 2 D channels: whole pieces
+      else conv_flat<T, 1, NT>(W, bias, cin * ks, cout, cur, nxt);
+    } else if (runs && ks == 1) {
+      conv_rows<T, 1, 1, false, NT>(W, bias, cin, cout, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    } else if (runs && ks == 3 && dense && out_rows <= 5) {
+      conv_rows<T, 3, 5, true, NT>(W, bias, cin, cout, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    } else if (runs && ks == 3) {
+      conv_rows<T, 3, 4, false, NT>(W, bias, cin, cout, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    } else if (runs && ks == 5) {
+      conv_rows<T, 5, 1, false, NT>(W, bias, cin, cout, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    } else if (runs && ks == 7) {
+      conv_rows<T, 7, 1, false, NT>(W, bias, cin, cout, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    } else if (aligned && cin * ks % EPP == 0) {
+      conv_rows_any<T, EPP, NT>(W, bias, cin, cout, ks, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    } else {
+      conv_rows_any<T, 1, NT>(W, bias, cin, cout, ks, dil, step, cur, nxt, row_f, out_rows, first_pos, apart);
+    }
     __syncthreads();
     float* tmp = cur; cur = nxt; nxt = tmp;
     rows = out_rows; cin = cout;
@@ -1261,15 +1390,23 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   }
 }
 
-// Positions between the rows that a logit depends on: the greatest common divisor of the dilations.
-int receptive_unit(const ltea_cnn& cnn) {
+// Positions between the rows that a logit depends on, of the input of layer `first`: the greatest common divisor of the
+// dilations from there on (1 where no layer reaches further than its own row).
+int receptive_unit(const ltea_cnn& cnn, int first) {
   int g = 0;
-  for (int l = 0; l < cnn.n_layers; ++l) {
+  for (int l = first; l < cnn.n_layers; ++l) {
     int a = cnn.kernel[l] > 1 ? cnn.dilation[l] : 0, b = g;
     while (a != 0) { const int r = b % a; b = a; a = r; }
     g = b;
   }
   return g > 0 ? g : 1;
+}
+
+// Whether a logit depends on one output of layer l alone: no later layer reaches past its own row.
+bool last_reach(const ltea_cnn& cnn, int l) {
+  for (int m = l + 1; m < cnn.n_layers; ++m)
+    if (cnn.kernel[m] > 1) return false;
+  return true;
 }
 
 // Stacks that the deep scoring role takes (see score_new_tokens_deep); its weight loads are 16-byte pieces of the rows.
@@ -1308,7 +1445,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   P.tau = cfg.tau_logit;
   P.scale = cfg.softmax_scale > 0.f ? cfg.softmax_scale : 1.0f / sqrtf((float)cfg.D);
   P.lazy = cnn_or_null == nullptr ? 1 : 0;
-  P.unit = receptive_unit(cnn);
+  P.unit = receptive_unit(cnn, 0);
   P.lds_row_floats = lds_row_floats(cfg, cnn);
   P.status = in.status;
   P.rope = rope_dev(in.rope);
@@ -1320,7 +1457,10 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   for (int l = 0; l < LTEA_MAX_CNN_LAYERS; ++l) {
     const bool on = l < cnn.n_layers;
     cd.kernel[l] = on ? cnn.kernel[l] : 1;
-    cd.dilation[l] = on && cnn.kernel[l] > 1 ? cnn.dilation[l] / P.unit : 1;
+    const int in_unit = receptive_unit(cnn, l), out_unit = receptive_unit(cnn, l + 1);
+    cd.unit[l] = last_reach(cnn, l) ? in_unit : out_unit;      // a single row has no spacing
+    cd.row_step[l] = cd.unit[l] / in_unit;
+    cd.dilation[l] = on && cnn.kernel[l] > 1 ? cnn.dilation[l] / in_unit : 1;
     cd.c_out[l] = on ? cnn.c_out[l] : 0;
     cd.w[l] = on ? cnn.w[l] : nullptr;
     cd.bias[l] = on ? cnn.bias[l] : nullptr;
@@ -1340,7 +1480,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   H.t = reinterpret_cast<int32_t*>(H.logit + heads);
   H.dst = H.t + n_seqs;
   const int G = cfg.Hq / cfg.Hkv;
-  const int role = !scores ? 0 : G > 1 && deep_role(cfg, cnn) ? kDeepRole : single_layer_role(cfg, cnn) != 0 ? single_layer_role(cfg, cnn) : kPerHead;
+  const int role = !scores ? 0 : deep_role(cfg, cnn) ? kDeepRole : single_layer_role(cfg, cnn) != 0 ? single_layer_role(cfg, cnn) : kPerHead;
   P.seq_arrivals = scores ? 2 * cfg.Hkv : cfg.Hkv;
   const int per_group = role == kDeepRole ? kDeepSeqs : role == kPerHead ? 1 : kSingleSeqs;
   P.n_score_blocks = role == 0 ? 0 : cfg.Hkv * ((n_seqs + per_group - 1) / per_group);
@@ -1354,7 +1494,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   auto launch = [&](auto gt, auto waves) {
     if (role == 0) return launch_sk(gt, waves, std::integral_constant<int, 0>{});
     if constexpr (sizeof(T) == 2) {
-      if constexpr (D == 64 && decltype(gt)::value >= 5) {
+      if constexpr (D == 64) {
         if (role == kDeepRole) return launch_sk(gt, waves, std::integral_constant<int, kDeepRole>{});
       }
       if (role == 3) return launch_sk(gt, waves, std::integral_constant<int, 3>{});
