@@ -1506,9 +1506,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn* cnn_or_null, const StepInput
   auto launch_gt = [&](auto gt) {
     constexpr bool kWide = decltype(gt)::value >= 5 && D == 128;
     const int w = step_waves(heads * P.nsplit + P.n_score_blocks, kWide);
-    if constexpr (sizeof(T) == 2) {
-      if (w == 8) return launch(gt, std::integral_constant<int, 8>{});
-    }
+    if (w == 8) return launch(gt, std::integral_constant<int, 8>{});
     launch(gt, std::integral_constant<int, 4>{});
   };
   if constexpr (sizeof(T) == 2) {
