@@ -107,6 +107,12 @@ __device__ __forceinline__ void arrive_sequence(const CacheDev& C, const StepPar
   if (!P.lazy) C.n_scored[b] = t + 1 > P.rho ? t + 1 - P.rho : 0;
 }
 
+// Whether a key in the receptive field of position t - rho that is rotated back lies past the rotary tables: the newest one does.
+__device__ __forceinline__ bool past_tables(const StepParams& P, int t) {
+  if (P.rope.cos == nullptr) return false;
+  return P.kf_new == nullptr ? t >= P.rope.n_pos : P.rho > 0 && t - 1 >= P.rope.n_pos;
+}
+
 // exp used by the softmax: library expf for fp32 storage (1e-5 tolerance), hardware exp2 path for bf16.
 template <typename T> __device__ __forceinline__ float soft_exp(float x);
 template <> __device__ __forceinline__ float soft_exp<float>(float x) { return expf(x); }
@@ -388,7 +394,6 @@ __device__ __forceinline__ void score_token(const CnnDev& cnn, const StepParams&
   // layer-0 features (keys then values), one 16-byte piece per thread per pass
   constexpr int EPP = Piece<T>::N;
   const int ppr = 2 * D / EPP;
-  bool out_of_tables = false;
   for (int idx = tid; idx < rows0 * ppr; idx += NT) {
     const int r = idx / ppr, m = (idx - r * ppr) * EPP;
     const int p = t - 2 * rho + r * unit;
@@ -401,10 +406,7 @@ __device__ __forceinline__ void score_token(const CnnDev& cnn, const StepParams&
       const bool ready = p == t && P.kf_new != nullptr;         // the key as the CNN wants it
       if (!is_v && ready) row = static_cast<const T*>(P.kf_new) + head * D;
       raw = *reinterpret_cast<const u32x4*>(row + mm);
-      if (!is_v && !ready && P.rope.cos != nullptr && mm < P.rope.rot_dim) {
-        if (p >= P.rope.n_pos) out_of_tables = true;
-        else raw = unrotate_piece<T>(P.rope, p, mm, raw, row);
-      }
+      if (!is_v && !ready && P.rope.cos != nullptr && p < P.rope.n_pos) raw = unrotate_piece<T>(P.rope, p, mm, raw, row);
     }
     float x[EPP];
     Piece<T>::unpack(raw, x);
@@ -416,7 +418,6 @@ __device__ __forceinline__ void score_token(const CnnDev& cnn, const StepParams&
       for (int i = 0; i < EPP; i += 4) *reinterpret_cast<f32x4*>(cur + r * row_f + m + i) = f32x4{x[i], x[i + 1], x[i + 2], x[i + 3]};
     }
   }
-  if (out_of_tables && P.status != nullptr) atomicOr(P.status, LTEA_ROPE_RANGE);
   __syncthreads();
   int rows = rows0, cin = 2 * D;
   for (int l = 0; l < cnn.n_layers; ++l) {
@@ -526,10 +527,7 @@ __device__ __forceinline__ void score_new_tokens_mfma(const CnnDev& cnn, const S
       }
       araw[tap] = *reinterpret_cast<const u32x4*>(rowp + col);
       if constexpr (ROT) {
-        if (rotate) {
-          if (p >= P.rope.n_pos) { if (P.status != nullptr) atomicOr(P.status, LTEA_ROPE_RANGE); }
-          else araw[tap] = unrotate_piece<bf16_t>(P.rope, p, col, araw[tap], rowp);
-        }
+        if (rotate && p < P.rope.n_pos) araw[tap] = unrotate_piece<bf16_t>(P.rope, p, col, araw[tap], rowp);
       }
       if (!p_ok) araw[tap] = u32x4{0u, 0u, 0u, 0u};
     }
@@ -634,7 +632,6 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
   __syncthreads();
   // ---- inputs: row (sequence, i) is position t - rho + (i - L) * dil; 8 key pieces, 8 value pieces ----
   bf16_t* xs = reinterpret_cast<bf16_t*>(lds);
-  bool out_of_tables = false;
   constexpr int kPerThread = (kDeepSeqs * 7 * 16 + kRoleThreads - 1) / kRoleThreads;    // requested together
   u32x4 piece[kPerThread];
 #pragma unroll
@@ -650,10 +647,7 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
       const bool rotated = !is_v && P.rope.cos != nullptr, ready = p == t && P.kf_new != nullptr;
       if (rotated && ready) row = static_cast<const bf16_t*>(P.kf_new) + head * D;
       piece[u] = reinterpret_cast<const u32x4*>(row)[pc & 7];
-      if (rotated && !ready && pc * 8 < P.rope.rot_dim) {
-        if (p >= P.rope.n_pos) out_of_tables = true;
-        else piece[u] = unrotate_piece<bf16_t>(P.rope, p, pc * 8, piece[u], row);
-      }
+      if (rotated && !ready && p < P.rope.n_pos) piece[u] = unrotate_piece<bf16_t>(P.rope, p, pc * 8, piece[u], row);
     }
   }
 #pragma unroll
@@ -661,7 +655,6 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
     const int idx = tid + u * kRoleThreads;
     if (idx < kDeepSeqs * n_in * 16) *reinterpret_cast<u32x4*>(xs + (idx >> 4) * kDeepXS + (idx & 15) * 8) = piece[u];
   }
-  if (out_of_tables && P.status != nullptr) atomicOr(P.status, LTEA_ROPE_RANGE);
 
   // one layer: rows of n_in positions per sequence in `src` (the terms term_off elements apart; 0: one term) to
   // n_in - 2 positions per sequence in `dst` (three terms) or, from the last layer, fp32 rows of kDeepMaxCh
@@ -932,10 +925,11 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
         else
           score_new_tokens_mfma<D, SK, false>(cnn, P, C, k_new, v_new, h, first_seq, scratch, H.logit);
       }
+      const int b = first_seq + (int)threadIdx.x;
+      const bool mine = (int)threadIdx.x < n_seqs && b < P.B;
+      const int t = mine ? C.n_seen[b] : 0;
+      if (mine && P.status != nullptr && past_tables(P, t)) atomicOr(P.status, LTEA_ROPE_RANGE);
       if (P.fused) {
-        const int b = first_seq + (int)threadIdx.x;
-        const bool mine = (int)threadIdx.x < n_seqs && b < P.B;
-        const int t = mine ? C.n_seen[b] : 0;
         __syncthreads();                        // every wave has read the counters
         if (mine) arrive_sequence(C, P, b, t);
       }

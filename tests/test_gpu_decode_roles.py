@@ -1,6 +1,6 @@
 """Eager decode steps by what scores inside them: the stack role, the single-layer role and the per-head scoring with each of its
 forms (single layers of any kernel, unequal dilations, odd channel counts, weights that are not 16-byte aligned), more sequences
-than a scoring workgroup takes; rotary models with either pairing, with and without unrotated keys; and the
+than a scoring workgroup takes; rotary models with either pairing, with and without unrotated keys, past their tables; and the
 finishing launch of caches with more than 127 KV heads.  Oracle: the eager step, or for rotary models a lazy step and a batched
 scoring after every step."""
 import numpy as np
@@ -125,6 +125,21 @@ def test_rotary_stack_role(cnn, interleaved, give_k_feat, rot_dim):
         if not give_k_feat:
             compare_sets(cache, states, w, t)
     assert int(status.item()) == 0
+
+
+@pytest.mark.parametrize("cnn", [STACK, ((5,), (32,), (1,)), ((3, 3), (32, 16), (1, 2))])
+def test_positions_past_the_rotary_tables(cnn):
+    """The status bit is set once a ring key that has to be rotated back lies past the tables, and not before; the incoming key,
+    given as it was before the rotation, needs none."""
+    w, d, cache, _ = prefilled("bf16", [40, 20], 4, 2, 64, 32, 8, cnn, seed=17)
+    cos, sin = wl.rope_tables(42, 64, 100.0)
+    rope = B.upload_rope(cos, sin, False)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for t, past in ((40, 0), (41, 0), (42, 0), (43, B.LTEA_ROPE_RANGE)):      # keys of positions below t come from the ring
+        q, k, v = wl.decode_inputs(w.seed, t, "bf16", 2, 4, 2, 64)
+        B.ltea_decode_step_feat(d.cfg, d.cnn, dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), cache, rope=rope, k_feat=dev(k, "bf16"),
+                                status=status)
+        assert int(status.item()) == past, t
 
 
 @pytest.mark.parametrize("cnn", [STACK, ((5,), (32,), (1,))])
