@@ -45,7 +45,7 @@ __device__ __forceinline__ void load_run(const bf16_t* p, bool vec, int left, fl
 // operands are in flight together, and the four waves' partial sums meet once in LDS.
 // Bound: latency (one trip to memory, 8*ks matrix instructions per wave).  512 tokens x 2 heads, k = 5, 128 -> 16
 // channels: 77 us with one thread per output reading both operands from memory inside its chain, 18.7 us staged through
-// LDS tap by tap, 5 us in this form (projection included, a launch of 4 us before).
+// LDS tap by tap, 6.4 us in this form (projection included, a launch of 4 us before).
 // KS: kernel size compiled in (1, 3, 5, 7), 0: any.
 // act_in == null: input features are concat(K row, V row) of the token (2*D channels, keys first), else
 // [Hkv][T][Cin] fp32.  Tap t reads position j + (t - (ks-1)/2) * dil of the same sequence; outside -> 0 (zero padding
@@ -184,13 +184,19 @@ out_proj_kernel(const float* __restrict__ act, const T* __restrict__ w_out, cons
   logits[(int64_t)h * total + tok] = acc;
 }
 
+// Floats of one activation array, in whole 256-byte pieces: rows of a multiple of kRun channels then start on 16-byte
+// boundaries in both arrays, as the vector loads of the next layer assume.
+size_t activation_floats(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total) {
+  int cmax = 0;
+  for (int l = 0; l < cnn.n_layers; ++l) cmax = cnn.c_out[l] > cmax ? cnn.c_out[l] : cmax;
+  return ((size_t)cfg.Hkv * (size_t)total * (size_t)cmax + 63) / 64 * 64;
+}
+
 template <typename T>
 hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v, int64_t stride_tok,
                int64_t stride_head, const SeqView& sv, float* logits, void* workspace, hipStream_t stream) {
   const int64_t total = sv.total_tokens;
-  int cmax = 0;
-  for (int l = 0; l < cnn.n_layers; ++l) cmax = cnn.c_out[l] > cmax ? cnn.c_out[l] : cmax;
-  float* buf[2] = {static_cast<float*>(workspace), static_cast<float*>(workspace) + (int64_t)cfg.Hkv * total * cmax};
+  float* buf[2] = {static_cast<float*>(workspace), static_cast<float*>(workspace) + activation_floats(cfg, cnn, total)};
   int cin = 2 * cfg.D;
   const float* act_in = nullptr;
   for (int l = 0; l < cnn.n_layers; ++l) {
@@ -233,9 +239,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
 }  // namespace
 
 size_t score_generic_workspace(const ltea_cfg& cfg, const ltea_cnn& cnn, int64_t total_tokens) {
-  int cmax = 0;
-  for (int l = 0; l < cnn.n_layers; ++l) cmax = cnn.c_out[l] > cmax ? cnn.c_out[l] : cmax;
-  const size_t one = (size_t)cfg.Hkv * (size_t)total_tokens * (size_t)cmax * sizeof(float);
+  const size_t one = activation_floats(cfg, cnn, total_tokens) * sizeof(float);
   return cnn.n_layers > 1 ? 2 * one : one;
 }
 

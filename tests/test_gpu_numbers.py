@@ -182,3 +182,14 @@ def test_cnn_backward_with_infinite_gradients(dtype, kernel, channels):
         if fine.any():
             assert np.max(np.abs(g[fine] - r[fine])) <= 2e-2 * np.max(np.abs(r[fine]))
     assert infinite > 0
+
+
+@pytest.mark.parametrize("dtype,channels", [("f32", (17, 16, 8)), ("f32", (5, 8, 24)), ("bf16", (17, 16, 8))])
+def test_layered_scoring_with_odd_activation_arrays(dtype, channels):
+    """Hidden layers of widths whose arrays have an odd number of floats (one head, 77 tokens): the second array and the rows in
+    it still start where the next layer's vector loads need them."""
+    w = wl.make_prefill("odd_arrays", 71, dtype, [60, 17], 1, 1, 64, 20, 4, 0, 0.0, cnn_kernel=(3, 3, 3), cnn_channels=channels, w_std=0.1)
+    d = DeviceWorkload(w)
+    z = to_np(B.ltea_score(d.cfg, d.cnn, d.k, d.v, d.cu, d.max_seqlen))
+    ref = orc.score(w.k, w.v, orc.cnn_from_arrays(w.cnn.kernel, w.cnn.dilation, w.cnn.w, w.cnn.bias, w.cnn.w_out, w.cnn.b_out), w.cu_seqlens)
+    assert np.all(np.abs(z - ref) <= 1e-5 * np.maximum(1.0, np.abs(ref)))
