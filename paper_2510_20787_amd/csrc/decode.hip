@@ -101,9 +101,9 @@ size_t decode_workspace_most(const ltea_cfg& cfg, int n_seqs) {
 }
 
 // The documented bound on the CNN, for two generations of activation rows of the whole receptive field (the launch keeps
-// only every unit-th row of them in LDS, beside the step's own 64 KB).
+// only every unit-th row of them in LDS, in whole quads, beside the step's own 64 KB).
 bool decode_scores_inside(const ltea_cfg& cfg, const ltea_cnn& cnn) {
-  return (size_t)2 * (2 * cnn_rho(&cnn) + 1) * lds_row_floats(cfg, cnn) * sizeof(float) <= 48 * 1024;
+  return (size_t)2 * (2 * cnn_rho(&cnn) + 1) * widest_row(cfg, cnn) * sizeof(float) <= 48 * 1024;
 }
 
 hipError_t launch_decode_step(const ltea_cfg& cfg, const ltea_cnn& cnn, const ltea_rope* rope, const void* q, const void* k,

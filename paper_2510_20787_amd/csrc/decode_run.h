@@ -21,11 +21,12 @@ inline size_t partial_floats(const ltea_cfg& cfg, int n_seqs, int nsplit) {
   return (size_t)n_seqs * cfg.Hq * nsplit * (cfg.D + 2);
 }
 
-inline int lds_row_floats(const ltea_cfg& cfg, const ltea_cnn& cnn) {
+inline int widest_row(const ltea_cfg& cfg, const ltea_cnn& cnn) {
   int row_floats = 2 * cfg.D;
   for (int l = 0; l < cnn.n_layers; ++l) row_floats = cnn.c_out[l] > row_floats ? cnn.c_out[l] : row_floats;
-  return (row_floats + 3) / 4 * 4;
+  return row_floats;
 }
+inline int lds_row_floats(const ltea_cfg& cfg, const ltea_cnn& cnn) { return (widest_row(cfg, cnn) + 3) / 4 * 4; }
 
 // The step for one storage type and head size.  cnn_or_null == null: the lazy step; given_logits: scored windows of
 // [Hkv][given_total] (see launch_decode_step_scored).

@@ -421,3 +421,12 @@ def test_static_decode_accepts_what_fits_its_scratch():
     for G, Hkv, n, cnn in ((64, 1, 13, fake_cnn((63,))), (128, 1, 8, fake_cnn()), (64, 2, 8, deep), (64, 8, 2, deep), (128, 8, 1, deep)):
         assert accepts(G, Hkv, n, cnn), (G, Hkv, n)
     assert not accepts(128, 8, 32, deep)
+
+
+def test_decode_scores_inside_up_to_48_kb_of_rows():
+    """The documented bound, 2 * (2 * rho + 1) * max(2 * D, widest layer) floats: 877 channels with k = 7 are 49 112 bytes and need
+    no more than the minimal workspace, 878 channels are 49 168 and need the packed windows."""
+    L, cfg = B.lib(), good_cfg(window=64)
+    size = lambda cnn: L.ltea_decode_workspace_bytes(C.byref(cfg), C.byref(cnn) if cnn else None, 3)
+    assert size(fake_cnn((7,), (1,), (877,))) == size(None)
+    assert size(fake_cnn((7,), (1,), (878,))) > size(None)
