@@ -199,10 +199,7 @@ size_t ltea_decode_workspace_bytes(const ltea_cfg* cfg, const ltea_cnn* cnn, int
   if (cnn && check_cnn(cfg, cnn) != LTEA_OK) return 0;
   // CNNs that the step's own launch cannot hold are scored through the prefill kernels
   const size_t step = align_up(decode_workspace_most(*cfg, n_seqs), 256);
-  if (!cnn) return step;
-  // the size for a stack stays above the minimum, which callers compare it with
-  if (decode_scores_inside(*cfg, *cnn)) return step + (cnn->n_layers > 1 ? 256 : 0);
-  return step + decode_windows_workspace(cfg, cnn, n_seqs);
+  return !cnn || decode_scores_inside(*cfg, *cnn) ? step : step + decode_windows_workspace(cfg, cnn, n_seqs);
 }
 
 int ltea_score(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* k, const void* v, int64_t stride_tok,
@@ -414,7 +411,7 @@ int ltea_decode_step(const ltea_cfg* cfg, const ltea_cnn* cnn, const void* q, co
 }
 
 // ---- the decode step for callers that cannot allocate ----------------------------------------------------------
-// Its scratch (split partials, finalised logits, step indices: everything ltea_decode_step carves from a caller
+// Its scratch (the records that the shares of a head hand over: everything ltea_decode_step carves from a caller
 // workspace) lives in a file-scope device array.  Host code never passes the array's name to a kernel: the name is a
 // host-side stand-in, the device address comes from hipGetSymbolAddress, looked up once per device (each GPU holds
 // its own copy at its own address) with that device current, and kept.
@@ -455,8 +452,7 @@ int ltea_decode_step_static(const ltea_cfg* cfg, const ltea_cnn* cnn, const void
   hipError_t e = hipSuccess;
   void* ws = static_scratch(&e);
   if (ws == nullptr) return LTEA_EHIP;
-  // nothing in the scratch has to start at zero: every part is written by the step's first launch before its
-  // second launch reads it
+  // nothing in the scratch has to start at zero: a step reads only what it has written there itself
   return ltea_decode_step(cfg, cnn, q, k, v, out, cache, n_seqs, ws, (size_t)LTEA_STATIC_SCRATCH_BYTES, stream);
 }
 

@@ -395,21 +395,24 @@ def test_decode_from_empty_cache(dtype, D):
         compare_state(cache, states, w, t)
 
 
-@pytest.mark.parametrize("small_ws", [False, True])
-def test_decode_deep_cnn_both_scoring_paths(small_ws):
-    """Multi-layer bf16 CNN from an empty cache (so the first 2*rho steps have receptive fields cut by the sequence
-    start): with the full workspace the packed-window path scores, with the minimal one the per-head path does;
-    both must agree with the oracle."""
+@pytest.mark.parametrize("kernel,channels,dilation,inside", [
+    ((3, 3, 3), (64, 32, 16), (2, 2, 2), True),        # the role for stacks: several sequences per workgroup, matrix products
+    ((3, 3, 3), (64, 32, 16), (1, 2, 3), True),        # unequal dilations: one (sequence, head) per workgroup
+    ((7, 7, 7), (64, 32, 16), (2, 2, 4), False),       # rows that do not fit LDS: windows packed for the prefill kernels
+])
+def test_decode_deep_cnn_from_empty(kernel, channels, dilation, inside):
+    """Multi-layer bf16 CNNs from an empty cache (so the first 2*rho steps have receptive fields cut by the sequence start), one
+    for each way a step scores them, with the smallest workspace that serves it: what the step reports without a CNN where it
+    scores inside its own launch."""
     n, B_ = 60, 3
-    w = wl.make_prefill("deep_from_empty", 78, "bf16", [n] * B_, 4, 2, 64, 32, 10, 2, 0.0, cnn_kernel=(3, 3, 3),
-                        cnn_channels=(64, 32, 16), cnn_dilation=(2, 2, 2), w_std=0.1)
+    w = wl.make_prefill("deep_from_empty", 78, "bf16", [n] * B_, 4, 2, 64, 50, 10, 2, 0.0, cnn_kernel=kernel,
+                        cnn_channels=channels, cnn_dilation=dilation, w_std=0.1 if inside else 0.05)
     cfg, cnn = oracle_cfg(w), oracle_cnn(w.cnn)
     d = DeviceWorkload(w)
     cache = d.new_cache()
-    full = B.ltea_decode_workspace_bytes(d.cfg, d.cnn, B_)
-    minimal = int(B.lib().ltea_decode_workspace_bytes(B.C.byref(d.cfg), None, B_))
-    assert minimal < full
-    ws = torch.empty(minimal if small_ws else full, dtype=torch.uint8, device="cuda")
+    need = B.ltea_decode_workspace_bytes(d.cfg, d.cnn, B_)
+    assert (need == B.ltea_decode_workspace_bytes(d.cfg, None, B_)) == inside
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     states = [orc.empty_state(cfg) for _ in range(B_)]
     q3 = w.q.reshape(B_, n, w.Hq, 64); k3 = w.k.reshape(B_, n, w.Hkv, 64); v3 = w.v.reshape(B_, n, w.Hkv, 64)
     for t in range(n):
