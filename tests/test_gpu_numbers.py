@@ -193,3 +193,21 @@ def test_layered_scoring_with_odd_activation_arrays(dtype, channels):
     z = to_np(B.ltea_score(d.cfg, d.cnn, d.k, d.v, d.cu, d.max_seqlen))
     ref = orc.score(w.k, w.v, orc.cnn_from_arrays(w.cnn.kernel, w.cnn.dilation, w.cnn.w, w.cnn.bias, w.cnn.w_out, w.cnn.b_out), w.cu_seqlens)
     assert np.all(np.abs(z - ref) <= 1e-5 * np.maximum(1.0, np.abs(ref)))
+
+
+def test_attention_backward_with_a_vanishing_scale():
+    """softmax_scale = 1e-39: every visible pair has the same probability, and lse / scale does not fit fp32."""
+    n, Hq, Hkv, D, window = 100, 4, 1, 64, 24
+    w = wl.make_prefill("flat", 8, "bf16", [n], Hq, Hkv, D, window, 1, 0, 0.0, cnn_kernel=(3,), cnn_channels=(16,))
+    d = DeviceWorkload(w)
+    d.cfg.softmax_scale = 1e-39
+    z = torch.full((Hkv, n), -1.0, device="cuda")            # nothing is kept
+    out, lse, _, ws = B.ltea_train_forward(d.cfg, None, d.q, d.k, d.v, d.cu, n, logits=z, rho=1)
+    rng = np.random.default_rng(2)
+    dout = wl.to_storage(rng.standard_normal((n, Hq, D), dtype=np.float32), "bf16")
+    dv = to_np(B.ltea_train_backward(d.cfg, d.q, d.k, d.v, d.cu, n, out, dev(dout, "bf16"), lse, z, torch.zeros(Hkv, device="cuda"), ws)[2])
+    i, j = np.arange(n)[:, None], np.arange(n)[None]
+    P = ((j <= i) & (j > i - window)).astype(np.float64)
+    P /= P.sum(1, keepdims=True)
+    ref = np.einsum("ij,ihd->jd", P, dout.astype(np.float64))
+    assert np.max(np.abs(dv[:, 0] - ref)) <= 2e-2 * np.max(np.abs(ref))
