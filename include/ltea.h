@@ -119,7 +119,9 @@ const char *ltea_strerror(int status);
  * ltea_prefill need for these sizes (0 is a valid answer).  Returns 0 on
  * invalid arguments as well; the entry points report those themselves.
  * Every workspace pointer of this library, here and below, must be 256-byte
- * aligned (device allocations are); a misaligned one is LTEA_EINVAL. */
+ * aligned (device allocations are); a misaligned one is LTEA_EINVAL.  No
+ * workspace query falls as its number of tokens or sequences rises: a buffer
+ * for the largest call serves every smaller one. */
 size_t ltea_workspace_bytes(const ltea_cfg *cfg, const ltea_cnn *cnn, int32_t n_seqs, int64_t total_tokens,
                             int32_t max_seqlen);
 
@@ -219,7 +221,7 @@ int ltea_decode_step(const ltea_cfg *cfg, const ltea_cnn *cnn, const void *q, co
  * streams or threads) race.  Nothing is carried from one call to the next.  Calls no hipMalloc, hipFree or other
  * allocating routine; the first call on a device looks the array's device address up once.
  * Returns LTEA_EWORKSPACE, before anything is launched, when ltea_decode_workspace_bytes(cfg, cnn, n_seqs) exceeds
- * LTEA_STATIC_SCRATCH_BYTES (decode_bf16's 64 sequences x 16 heads x D = 128 need about 2.2 MB). */
+ * LTEA_STATIC_SCRATCH_BYTES (decode_bf16's 64 sequences x 16 heads x D = 128 need about 0.54 MB). */
 #define LTEA_STATIC_SCRATCH_BYTES (8u << 20)
 int ltea_decode_step_static(const ltea_cfg *cfg, const ltea_cnn *cnn, const void *q, const void *k, const void *v,
                             void *out, const ltea_cache *cache, int32_t n_seqs, void *stream);

@@ -11,7 +11,7 @@
 // In the accumulator layout a lane owns one query, so the softmax state is per lane; rows go from global memory to
 // registers, one block ahead.  Small problems are what this path sees, so the bound is latency: a tile of window 64 +
 // budget 32 is two blocks per wave.  512 tokens x 2 heads (D = 64): 29 us with one wave per query and scalar row loads,
-// 7 us in this form.
+// 7 us in this form (a whole prefill 18.2 us, 18.5 with the test for sums that are not finite).
 #include "ltea_common.h"
 #include "ltea_kernels.h"
 

@@ -838,7 +838,9 @@ weight_product_kernel(const float* __restrict__ act_in, const float* __restrict_
 // Stage 1 of d W_l on bf16 storage, for the channel counts that come in whole quads.  d y (fp32) is split into three bf16
 // terms as in conv_split_bf16_kernel.  X = bf16_t: the first layer, whose inputs are bf16 values, so three bf16 matrix
 // instructions give the fp32 product.  X = float: the layers after it; the activations are split too, and the six products of
-// terms down to 2^-16 of the largest are taken (the three others are below 2^-25 of it).
+// terms down to 2^-16 of the largest are taken (the three others are below 2^-25 of it).  Not the fp32 instruction's result to
+// the last bit; relative error of the three layers' weight gradients against 64 bits (2 x 1500 tokens, paper stack): 3.3e-7,
+// 3.6e-7 and 3.6e-7 on fp32 instructions, 2.4e-7, 2.6e-7 and 2.6e-7 in this form.
 // A workgroup takes one (head, chunk of tokens, tile of 32 WM input x 32 WC output channels) and a group of taps: d y is
 // loaded and split once for all of them, and the input rows that the taps reach are staged once and read at each tap's shift.
 // (A workgroup per tap spent its time on loading and splitting the same rows: 4 x 4096 tokens, paper stack, 49 us for the

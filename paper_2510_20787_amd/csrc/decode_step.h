@@ -25,10 +25,10 @@
 // anybody: no fences, which write back a whole L2 each, and no spinning.
 //
 // Measured on the paper's layer (32 query heads on 8, D = 64, 1280 rows): separate streaming, scoring and finishing
-// launches took 28.6 us per eager step of one sequence and 48.3 us for 32 of a rotary model, this launch 12.9 and 23.0 us;
-// a lazy step of 32: 29.8 and 19.8 us.  Handing shares over costs about 5 us at the end (stores, count, records, each a trip
+// launches took 28.6 us per eager step of one sequence and 48.3 us for 32 of a rotary model, this launch 12.3 and 23.3 us;
+// a lazy step of 32: 29.8 and 20.1 us.  Handing shares over costs about 5 us at the end (stores, count, records, each a trip
 // past the L2), which is why a head is one workgroup when the heads alone fill the chip and shared out when its rows are
-// long.  Caches that do not fit the counting (no budget, or a budget of 2^16 and more, or over 127 KV heads) or whose logit
+// long.  (With the finishing as a launch of its own for every cache, and nothing counted, 14.7, 25.8 and 22.4 us.)  Caches that do not fit the counting (no budget, or a budget of 2^16 and more, or over 127 KV heads) or whose logit
 // is final at once (rho = 0: the scoring would write the ring slot whose old logit the eviction reads) run the finishing as
 // a launch of its own, decode_finish_kernel.
 //
@@ -574,8 +574,9 @@ __device__ __forceinline__ void score_new_tokens_mfma(const CnnDev& cnn, const S
 // is the fp32 activation exactly, each multiplied in its own MFMA: the arithmetic of the per-head scoring.  A lane's weights of 8 input channels and 3 taps are 24
 // consecutive elements of its channel's row.
 // Bound: latency (n_seen -> rows and weights -> three short layers), hidden under the streaming.  The windows of the
-// whole batch packed in the main launch and scored by the prefill kernel in a launch of its own took 9-12 us of the step, and scoring each (sequence, head) in the workgroup that streams it 14 us of a 20 us step: a dozen
-// dependent trips to memory in front of the stream, or, requested ahead, more registers than the stream leaves.
+// whole batch packed in the main launch and scored by the prefill kernel in a launch of its own took 9-12 us of the step, and
+// scoring each (sequence, head) in the workgroup that streams it 14 us of a 20 us step: a dozen dependent trips to memory in
+// front of the stream, or, requested ahead, more registers than the stream leaves.
 constexpr int kDeepSeqs = 8;
 constexpr float kMaxBf16 = 3.3895314e38f;                    // above: infinity in bf16
 constexpr int kDeepMaxCh = 64;                              // output channels per layer

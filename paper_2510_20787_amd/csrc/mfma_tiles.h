@@ -1,15 +1,14 @@
 // Pieces shared by the bf16 MFMA attention kernels (forward and training backward): how 32x32x16 operands are laid
-// out in LDS tiles and fetched from them, and the two-lane / wave reductions those kernels use.
+// out in LDS tiles and fetched from them, and the two-lane reductions those kernels use.
 //
 // Conventions (v_mfma_f32_32x32x16_bf16, wave64; lane = 32*hb + c):
 //   * a lane owns accumulator column c; its 16 registers are rows 8*(r/4) + 4*hb + r%4 of the product;
-//   * tiles whose rows feed the A operand row-wise are stored padded (row stride D + 8 elements) and MFMA row m is
-//     made to carry tile row tile_row_of_mfma_row(m), so that accumulator register r of lane half hb belongs to tile
-//     row 16*(r/8) + 8*hb + r%8: a lane's eight values per MFMA are then eight consecutive tile rows, which is the
-//     order the second product consumes them in as its B operand;
-//   * tiles that feed the A operand transposed (contraction over tile rows) stay row-major and unpadded; their
-//     64-byte chunks are XOR-swizzled with the row so that the transposing loads and the staging stores spread over
-//     all banks.
+//   * tiles are row-major and unpadded, as direct global-to-LDS loads leave them; which 16-byte piece of a row a lane
+//     fetches is XOR-swizzled with the row, so that the reads below spread over all banks: row reads (the rows feed the A
+//     operand), transposing reads (contraction over the tile rows), or both of one copy;
+//   * where the rows feed the A operand, MFMA row m is made to carry tile row tile_row_of_mfma_row(m), so that accumulator
+//     register r of lane half hb belongs to tile row 16*(r/8) + 8*hb + r%8: a lane's eight values per MFMA are then eight
+//     consecutive tile rows, which is the order the second product consumes them in as its B operand.
 #pragma once
 #include "ltea_common.h"
 
@@ -56,16 +55,6 @@ __device__ __forceinline__ float pair_max(float x) {
 __device__ __forceinline__ float pair_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ int wave_min_i(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) { const int y = __shfl_xor(x, off, kWave); x = y < x ? y : x; }
-  return x;
-}
-__device__ __forceinline__ int wave_max_i(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) { const int y = __shfl_xor(x, off, kWave); x = y > x ? y : x; }
-  return x;
 }
 
 }  // namespace ltea
