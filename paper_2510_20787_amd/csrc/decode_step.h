@@ -28,7 +28,8 @@
 // launches took 28.6 us per eager step of one sequence and 48.3 us for 32 of a rotary model, this launch 12.3 and 23.3 us;
 // a lazy step of 32: 29.8 and 20.1 us.  Handing shares over costs about 5 us at the end (stores, count, records, each a trip
 // past the L2), which is why a head is one workgroup when the heads alone fill the chip and shared out when its rows are
-// long.  (With the finishing as a launch of its own for every cache, and nothing counted, 14.7, 25.8 and 22.4 us.)  Caches that do not fit the counting (no budget, or a budget of 2^16 and more, or over 127 KV heads) or whose logit
+// long.  With the finishing as a launch of its own for every cache, and nothing counted: 14.7, 25.8 and 22.4 us.  Caches that do
+// not fit the counting (no budget, or a budget of 2^16 and more, or over 127 KV heads) or whose logit
 // is final at once (rho = 0: the scoring would write the ring slot whose old logit the eviction reads) run the finishing as
 // a launch of its own, decode_finish_kernel.
 //
