@@ -438,7 +438,7 @@ def bench_train(args):
     return dict(workload="paper_stack_bf16 without the cap (training): B=4 x n=4096, Hq=32 on Hkv=8, D=64, window=768, "
                          f"output biases shifted so that every head keeps {share:.3f} of its tokens (measured {kept_frac:.3f})", forward_ms=fwd_ms, backward_ms=bwd_ms,
                 cnn_backward_ms=cnn_bwd_ms, tokens_per_s=w.total_tokens / ((fwd_ms + bwd_ms) * 1e-3), pairs=pairs,
-                roofline=dict(bound="mfma", kernel="train_dq_mfma_kernel + train_dkv_mfma_kernel (both passes)",
+                roofline=dict(bound="mfma", kernel="train_dq_far_mfma_kernel + train_dkv_band_mfma_kernel",
                               achieved=tf, peak=PEAK_BF16_TFLOPS, unit="TFLOP/s", frac=tf / PEAK_BF16_TFLOPS, traffic=None,
                               note="algorithmic flops = 10 D per (query, key) pair (S, dP, dV, dK, dQ); the two kernels "
                                    "each recompute S and dP, so they issue 14 D"))

@@ -220,8 +220,9 @@ int ltea_decode_step(const ltea_cfg *cfg, const ltea_cnn *cnn, const void *q, co
  * reentrant: every call on a GPU shares that GPU's array, and calls that overlap in time on one GPU (different
  * streams or threads) race.  Nothing is carried from one call to the next.  Calls no hipMalloc, hipFree or other
  * allocating routine; the first call on a device looks the array's device address up once.
- * Returns LTEA_EWORKSPACE, before anything is launched, when ltea_decode_workspace_bytes(cfg, cnn, n_seqs) exceeds
- * LTEA_STATIC_SCRATCH_BYTES (decode_bf16's 64 sequences x 16 heads x D = 128 need about 0.54 MB). */
+ * Returns LTEA_EWORKSPACE, before anything is launched, when the call needs more than LTEA_STATIC_SCRATCH_BYTES
+ * (decode_bf16's 64 sequences x 16 heads x D = 128 need about 0.54 MB).  It never does where
+ * ltea_decode_workspace_bytes(cfg, cnn, n_seqs), which covers every smaller batch too, does not exceed it. */
 #define LTEA_STATIC_SCRATCH_BYTES (8u << 20)
 int ltea_decode_step_static(const ltea_cfg *cfg, const ltea_cnn *cnn, const void *q, const void *k, const void *v,
                             void *out, const ltea_cache *cache, int32_t n_seqs, void *stream);
