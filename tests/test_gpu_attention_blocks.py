@@ -1,0 +1,66 @@
+"""Block schedule of the bf16 prefill attention: window lower edges and diagonals at every offset from the 32-key blocks,
+compact segments whose positions are in no order, that end inside a block, that nobody or only some rows see, and that are
+longer than the positions kept in LDS.  Against the fp64 oracle, at the output tolerance of the other attention tests."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ltea_oracle as orc
+from paper_2510_20787_amd import binding as B
+from paper_2510_20787_amd import workloads as wl
+from .gpu_util import DeviceWorkload, dev, to_np, OUT_TOL
+
+pytestmark = pytest.mark.gpu
+
+
+def run(D, G, window, budget, lens, keep_of, shuffle, seed):
+    rng = np.random.default_rng(seed)
+    w = wl.make_prefill("blocks", seed, "bf16", lens, 2 * G, 2, D, window, budget, qkv_scale=1.0)
+    d = DeviceWorkload(w)
+    cache = d.new_cache()
+    for t in (cache.k_ret, cache.v_ret):
+        t.fill_(float("nan"))                   # slots past the last entry are never used
+    kq, vq = to_np(d.k), to_np(d.v)
+    keep = {}
+    for s, n in enumerate(lens):
+        lo = int(w.cu_seqlens[s])
+        for h in range(w.Hkv):
+            p = np.asarray(keep_of(n, h, rng), np.int64)[:budget]
+            keep[s, h] = np.sort(p)
+            if shuffle:
+                p = rng.permutation(p)
+            m = len(p)
+            cache.ret_count[s, h] = m
+            cache.ret_pos[s, h, :m] = torch.from_numpy(p.astype(np.int32))
+            cache.k_ret[s, h, :m] = dev(kq[lo + p, h], "bf16")
+            cache.v_ret[s, h, :m] = dev(vq[lo + p, h], "bf16")
+    out = to_np(B.ltea_sparse_attention(d.cfg, d.q, d.k, d.v, d.cu, d.max_seqlen, cache))
+    cfg = orc.OracleCfg(w.Hq, w.Hkv, w.D, window, budget, 0, 0.0)
+    for s, n in enumerate(lens):
+        lo = int(w.cu_seqlens[s])
+        ref = orc.sparse_attention_sequence(w.q[lo:lo + n], w.k[lo:lo + n], w.v[lo:lo + n], cfg, [keep[s, h] for h in range(w.Hkv)])
+        err = np.abs(out[lo:lo + n] - ref).max()
+        assert err <= OUT_TOL["bf16"] * min(1.0, np.abs(ref).max()), f"sequence {s}: {err}"
+
+
+@pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 1), (128, 4)])
+@pytest.mark.parametrize("window", [1, 17, 31, 32, 33, 63, 64, 65, 96, 127, 200])
+def test_window_edges(D, G, window):
+    """Sequences that end at, before and after block and tile ends; two compact blocks, the second one cut short."""
+    run(D, G, window, 40, [1, 31, 33, 129, 290], lambda n, h, rng: np.arange(h, n, 5 + h), False, window)
+
+
+@pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 1)])
+@pytest.mark.parametrize("budget", [1, 31, 32, 33, 95, 128, 300])
+@pytest.mark.parametrize("shuffle", [False, True])
+def test_compact_segments(D, G, budget, shuffle):
+    """Odd and even numbers of window and compact blocks; entries in ascending order, as a prefill leaves them, or in none, as
+    after decode steps; one head that keeps nothing."""
+    run(D, G, 64, budget, [420, 97, 230], lambda n, h, rng: [] if h == 1 and n == 230 else rng.permutation(n)[:2 * n // 3], shuffle, budget)
+
+
+@pytest.mark.parametrize("D,G", [(64, 1), (128, 4)])
+@pytest.mark.parametrize("shuffle", [False, True])
+def test_segments_longer_than_lds(D, G, shuffle):
+    """More than 2048 and more than 4096 entries: the later blocks are classified from memory, 64 at a time."""
+    run(D, G, 33, 4500, [4700], lambda n, h, rng: np.sort(rng.permutation(n)[:4400 - 2100 * h]), shuffle, 3)
