@@ -28,6 +28,9 @@
 // (4.3 VALU per matrix instruction in dK / dV, 5 in dQ, from 10 to 12 when tiles went through registers, K / Q / dO were
 // stored twice and every block was a basic block of its own).  4 x 4096 tokens, 32 heads on 8, D = 64, window 768, an eighth
 // kept: dQ with the far pass 467 -> 363 us (378 with consecutive blocks of one head on the waves), band pass 359 -> 285 us.
+// Candidates that no row of a dQ workgroup sees (half of them on average, all of them later positions) are neither loaded nor
+// waited for, and a masked tile leaves out a block of 32 that nobody of the wave sees (in either role): the whole training
+// step of that layer 1026 -> 1012 us, both forms in turn on one box, with the same results.
 // Two tile buffers, one barrier per tile.  No floating-point atomics: the partial sums of the far pass go to scratch slices
 // that the band pass adds in a fixed order.
 #include <type_traits>
@@ -151,8 +154,7 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
   const int jt0 = (jlo / BN) * BN;
   const int n_win_tiles = (i_last - jt0) / BN + 1;
   const int cnt = (budget > 0 && i_last - window >= 0) ? A.ret_count[head] : 0;
-  const int n_ret_tiles = (cnt + BN - 1) / BN;
-  const int n_tiles = n_win_tiles + n_ret_tiles;
+  int n_tiles = n_win_tiles + (cnt + BN - 1) / BN;
 
   const uint32_t row_bytes = (uint32_t)A.kv_st * 2u;
   const uint32_t win_bytes = (uint32_t)(n - 1) * row_bytes + (uint32_t)(D * 2);
@@ -196,10 +198,12 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
     neg_dlt16[r] = neg_dlt;
   }
 
-  // mode: 1 = window-edge mask, 2 = mask by the candidates' positions (`slots`: entries of the tile)
-  auto compute = [&](const int mode, const bf16_t* tb, const int* pos, int jt, int slots) {
+  // mode: 1 = window-edge mask, 2 = mask by the candidates' positions (`slots`: entries of the tile); bit kb of `live`: some
+  // row of the wave sees a key of block kb
+  auto compute = [&](const int mode, const int live, const bf16_t* tb, const int* pos, int jt, int slots) {
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
+      if ((live >> kb & 1) == 0) continue;
       f32x16 sc = neg_lse16, dp = neg_dlt16;
 #pragma unroll
       for (int ks = 0; ks < NK; ++ks) {
@@ -314,6 +318,23 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
       if (t < n_tiles) load_tile(t);
   };
   load_stage(0);
+  // Under the flight of the first tiles: how many candidates have left the window of the last row (positions ascend, 64 of them
+  // looked at per step).  The later ones are neither loaded nor waited for: half of them on average.
+  {
+    const int* rp = A.ret_pos + head * budget;
+    const int lim = i_last - window;
+    int seen = 0, left = cnt;
+    while (left > 0) {
+      const int step = (left + 63) / 64;
+      const bool le = lane * step < left && rp[seen + lane * step] <= lim;
+      const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(le));
+      if (c == 0) break;
+      const int end = seen + left;
+      seen += (c - 1) * step + 1;
+      left = step - 1 < end - seen ? step - 1 : end - seen;
+    }
+    n_tiles = n_win_tiles + (__builtin_amdgcn_readfirstlane(seen) + BN - 1) / BN;
+  }
   wait_loads();
   __syncthreads();
 #pragma unroll 1
@@ -321,30 +342,34 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
     if (t % kStage == 0) load_stage(t + kStage);
     const bf16_t* tb = lds + (t % (2 * kStage)) * kBuf;
     const int* pos = pos_lds_base + (t % (2 * kStage)) * BN;
-    int mode = -1, jt = 0, slots = 0;
+    int mode = -1, live = 0, jt = 0, slots = 0;
     if (r0 < n) {
       if (t < n_win_tiles) {
         jt = jt0 + t * BN;
         if (!(jt > r_hi || jt + BN - 1 < r0 - window + 1))
           mode = ((jt + BN - 1 <= r0) && (jt >= r_hi - window + 1)) ? 0 : 1;
+        live = (jt + 31 >= r0 - window + 1 ? 1 : 0) | (jt + 32 <= r_hi ? 2 : 0);      // of a tile that is not -1
       } else {
         // an entry counts once it has left the window of the wave's last row and needs no mask once it has left the first's
         slots = cnt - (t - n_win_tiles) * BN;
         int pv = pos[lane];
         pv = lane < slots ? pv : 0x7FFFFFFF;
-        if (__builtin_amdgcn_ballot_w64(pv <= r_hi - window) != 0ull)
+        const uint64_t some = __builtin_amdgcn_ballot_w64(pv <= r_hi - window);
+        live = ((uint32_t)some != 0u ? 1 : 0) | ((uint32_t)(some >> 32) != 0u ? 2 : 0);
+        if (some != 0ull)
           mode = __builtin_amdgcn_ballot_w64(pv > r0 - window) == 0ull ? 0 : 2;
       }
     }
     mode = __builtin_amdgcn_readfirstlane(mode);
+    live = __builtin_amdgcn_readfirstlane(live);
     // Two steps in sequence rather than if / else, so that the accumulators stay in place across the plain body.
     if (mode == 0) {
       compute_plain(tb);
       mode = -1;
     }
     asm volatile("" : "+s"(mode));
-    if (mode == 1) compute(1, tb, pos, jt, slots);
-    else if (mode == 2) compute(2, tb, pos, jt, slots);
+    if (mode == 1) compute(1, live, tb, pos, jt, slots);
+    else if (mode == 2) compute(2, live, tb, pos, jt, slots);
     if (t % kStage == kStage - 1 || t == n_tiles - 1) {
       wait_loads();
       __syncthreads();               // the next stage is in LDS; everyone is done with this one
@@ -542,6 +567,8 @@ __device__ __forceinline__ void dkv_body(const TrainArgs& A, int tiles_upper, fl
   auto compute_masked = [&](const bf16_t* tb, const float* st, int qt) {
 #pragma unroll 1
     for (int qb = 0; qb < 2; ++qb) {
+      // no key of the wave sees a query of the block
+      if (__builtin_amdgcn_ballot_w64(q_span != 0u && q_lo < qt + 32 * qb + 32 && q_hi > qt + 32 * qb) == 0ull) continue;
       f32x16 sc = start_values(st, qb), dp = start_values(st + BN, qb);
 #pragma unroll
       for (int ks = 0; ks < NK; ++ks) {
