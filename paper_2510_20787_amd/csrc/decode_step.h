@@ -946,12 +946,52 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const int split = work % nsplit;
   const int64_t head = work / nsplit;
   const int b = (int)(head / Hkv), h = (int)(head - (int64_t)b * Hkv);
-  const int t = C.n_seen[b];
+  int t = C.n_seen[b];
   const T* kw = static_cast<const T*>(C.k_win) + head * window * D;
   const T* vw = static_cast<const T*>(C.v_win) + head * window * D;
   const int G = P.Hq / Hkv;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+  // Matrix stream of a step without scoring workgroups (lazy scoring, logits given): a wave's first block of 32 ring slots is
+  // requested before n_seen has come, whatever it holds;
+  // settle() takes out what is not there yet.  One trip to memory less: 756 lazy steps of 32 sequences of the paper's layer
+  // 15 182 -> 14 562 us.  Beside scoring workgroups, which the same memory serves first, the order bought nothing (22.9 -> 23.2
+  // us per rotary step of 32).
+  constexpr bool kBlind = GT >= 5 && SK == 0;
+  using MS = MfmaStream<D>;
+  typename MS::Rows cur;
+  // V: this lane's row of an instruction and its 16-byte piece
+  const int kg = lane >> 4, c16 = lane & 15, v_row = lane / (D / 8), v_piece = lane % (D / 8);
+  const uint32_t k_off = (uint32_t)(c16 * D + 8 * kg) * 2u, v_off = (uint32_t)(v_row * D + 8 * v_piece) * 2u;
+  // shares are whole blocks of 32 ring slots or 32 compact slots
+  const int ring_blocks = (window + 31) / 32, all_blocks = ring_blocks + (budget + 31) / 32;
+  const int blk_chunk = (all_blocks + nsplit - 1) / nsplit, blk_begin = split * blk_chunk;
+  const int blk_end = blk_begin + blk_chunk < all_blocks ? blk_begin + blk_chunk : all_blocks;
+  const int first = blk_begin + wave;
+  const bool early = GT >= 5 && first < blk_end && first < ring_blocks;
+  // 32 rows from ks, vs on, the first `n_rows` of them real (the others read as zeros)
+  auto load_rows = [&](const T* ks, const T* vs, int n_rows, typename MS::Rows& R) {
+    const uint32_t bytes = (uint32_t)n_rows * (uint32_t)(D * 2);
+    const auto rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(ks), 0, bytes, 0x00020000);
+    const auto rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(vs), 0, bytes, 0x00020000);
+    constexpr int kNonTemporal = 2;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < MS::QK; ++i)
+        R.k[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off + (uint32_t)(16 * j * D + 32 * i) * 2u, 0, kNonTemporal);
+#pragma unroll
+    for (int i = 0; i < MS::NV; ++i)
+      R.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off + (uint32_t)(MS::RPI * i * D) * 2u, 0, kNonTemporal);
+  };
+  if constexpr (kBlind) {
+    if (early) {
+      const int64_t row0 = 32 * first;
+      load_rows(kw + row0 * D, vw + row0 * D, window - 32 * first < 32 ? window - 32 * first : 32, cur);
+    }
+    asm volatile("" : "+s"(t));       // waited for here, behind the requests
+  }
   const T* kr = static_cast<const T*>(C.k_ret) + head * budget * D;
   const T* vr = static_cast<const T*>(C.v_ret) + head * budget * D;
   const T* kn = k_new + head * D;
@@ -993,21 +1033,12 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   };
 
   if constexpr (GT >= 5) {
-    using MS = MfmaStream<D>;
     static_assert(sizeof(scratch) >= W * MS::kTile * sizeof(bf16_t), "the V tiles of the four waves");
-    const int kg = lane >> 4, c16 = lane & 15;
     bf16_t* vt = reinterpret_cast<bf16_t*>(scratch) + wave * MS::kTile;
     const float scale2 = P.scale * 1.4426950408889634f;
-    // V: this lane's row of an instruction and its 16-byte piece
-    const int v_row = lane / (D / 8), v_piece = lane % (D / 8);
     // V^T operand: 16 lanes point at a 4-row x 16-column block; rows 4*kg.. of either half
     const int tr_row = 4 * kg + (c16 >> 2);
     const bf16_t* v_src = vt + tr_row * D + 4 * (lane & 3);
-    const uint32_t k_off = (uint32_t)(c16 * D + 8 * kg) * 2u, v_off = (uint32_t)(v_row * D + 8 * v_piece) * 2u;
-    // shares are whole blocks of 32 ring slots or 32 compact slots
-    const int ring_blocks = (window + 31) / 32, all_blocks = ring_blocks + (budget + 31) / 32;
-    const int blk_chunk = (all_blocks + nsplit - 1) / nsplit, blk_begin = split * blk_chunk;
-    const int blk_end = blk_begin + blk_chunk < all_blocks ? blk_begin + blk_chunk : all_blocks;
     // rows of block `blk`: ring or compact slots row0 .., `n_live` of them real (the others read as zeros)
     auto where = [&](int blk, bool& ring, int& row0, int& n_live) {
       ring = blk < ring_blocks;
@@ -1015,23 +1046,8 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       const int left = (ring ? n_valid : cnt) - row0;
       n_live = left < 0 ? 0 : (left < 32 ? left : 32);
     };
-    auto load = [&](int blk, typename MS::Rows& R) {
-      bool ring;
-      int row0, n_live;
-      where(blk, ring, row0, n_live);
-      const uint32_t bytes = (uint32_t)n_live * (uint32_t)(D * 2);
-      const auto rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>((ring ? kw : kr) + (int64_t)row0 * D), 0, bytes, 0x00020000);
-      const auto rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>((ring ? vw : vr) + (int64_t)row0 * D), 0, bytes, 0x00020000);
-      constexpr int kNonTemporal = 2;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < MS::QK; ++i)
-          R.k[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off + (uint32_t)(16 * j * D + 32 * i) * 2u, 0, kNonTemporal);
-#pragma unroll
-      for (int i = 0; i < MS::NV; ++i)
-        R.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off + (uint32_t)(MS::RPI * i * D) * 2u, 0, kNonTemporal);
-      // the one row whose contents after this step are somewhere else: the incoming token's, or the evicted one's
+    // the one row whose contents after this step are somewhere else: the incoming token's, or the evicted one's
+    auto replace = [&](bool ring, int row0, typename MS::Rows& R) {
       const int special = (ring ? slot : dst) - row0;      // dst = -1: none
       if (special >= 0 && special < 32 && (ring || dst >= 0)) {
         const T* ks = ring ? kn : k_evicted;
@@ -1047,6 +1063,25 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
           if (MS::RPI * i + v_row == special) R.v[i] = *reinterpret_cast<const u32x4*>(vs + 8 * v_piece);
       }
     };
+    auto load = [&](int blk, typename MS::Rows& R) {
+      bool ring;
+      int row0, n_live;
+      where(blk, ring, row0, n_live);
+      load_rows((ring ? kw : kr) + (int64_t)row0 * D, (ring ? vw : vr) + (int64_t)row0 * D, n_live, R);
+      replace(ring, row0, R);
+    };
+    // the block requested before n_seen was known: V rows past the newest token count as zeros (scores are masked)
+    auto settle = [&]() {
+      bool ring;
+      int row0, n_live;
+      where(first, ring, row0, n_live);
+      if (n_live < 32) {
+#pragma unroll
+        for (int i = 0; i < MS::NV; ++i)
+          if (MS::RPI * i + v_row >= n_live) cur.v[i] = u32x4{0u, 0u, 0u, 0u};
+      }
+      replace(ring, row0, cur);
+    };
     // this lane's column: a head of the pass and (GT = 5) which term of its probabilities
     constexpr bool kTermColumns = GT == 5;
     const int term = kTermColumns ? c16 / 5 : 0, col_head = kTermColumns ? c16 % 5 : c16;
@@ -1061,12 +1096,12 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
         qf[i] = __builtin_bit_cast(bf16x8, x);
       }
     };
-    typename MS::Rows cur;
-    const int first = blk_begin + wave;
-    // ring blocks do not wait for the eviction decision
-    const bool early = first < blk_end && first < ring_blocks;
     load_queries(0);
-    if (early) load(first, cur);
+    // ring blocks do not wait for the eviction decision
+    if (early) {
+      if constexpr (kBlind) settle();
+      else load(first, cur);
+    }
     decide(blk_end > ring_blocks);
     for (int g0 = 0; g0 < G; g0 += GT) {
       const int heads_here = G - g0 < GT ? G - g0 : GT;
