@@ -42,6 +42,7 @@
 // at D = 64 (half the operand reads, but 47 registers spilled: 192 us against 162).
 #include <type_traits>
 
+#include "attention_blocks.h"
 #include "ltea_common.h"
 #include "ltea_kernels.h"
 #include "mfma_tiles.h"
@@ -51,7 +52,6 @@ namespace ltea {
 namespace {
 
 constexpr int BN = 64;   // keys per tile: two blocks
-constexpr int BK = 32;   // keys per block
 constexpr int kThreads = 256;
 constexpr int kPosLds = 2048;   // positions of the compact segment kept in LDS (longer segments: the rest is read where needed)
 constexpr float kBig = 1.8446744e19f;  // 2^64: a row sum above this (or not a number) sends the workgroup through its tiles again
@@ -70,8 +70,6 @@ template <int D> struct Geo {
 // Which 16-byte piece of its row a K tile row keeps at slot p (p ^ term): the row reads of 16 consecutive lanes (16 rows at
 // one piece) then cover all 64 banks.
 template <int D> __device__ __forceinline__ int piece_swizzle(int row) { return D == 64 ? ((row >> 1) & 7) : (row & 15); }
-
-enum : int { kSkip = 0, kPlain = 1, kMasked = 2 };
 
 // HW = query heads per workgroup.  1: the four waves take four consecutive blocks of 32 query positions of one head.
 // 4 (grouped-query shapes with a multiple of four query heads per KV head): the four waves take the SAME 32
@@ -141,15 +139,8 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   const int ql = lane & 31, hb = lane >> 5;
   const int hq = HW == 1 ? unit : unit * HW + wv;                 // this wave's query head
   const int r0 = i0 + (HW == 1 ? 32 * wv : 0);               // first query row of this wave
-  const int r_hi = r0 + 31;        // last query row of this wave
-
-  // ---- block schedule -----------------------------------------------------------------------------------
-  // Block i < n_win: keys j_low + 32 * i ..+31, up to the diagonal; block n_win + b: compact slots 32 * b ..+31.
-  const int i_last = (i0 + BMQ < n ? i0 + BMQ : n) - 1;          // last real query row of the workgroup
-  const int j_first = i0 - window + 1 > 0 ? i0 - window + 1 : 0;
-  const int j_diag = i0 + ((i_last - i0) & ~(BK - 1));            // the block of the last real query row
-  const int n_win = (j_diag - j_first + BK - 1) / BK + 1;
-  const int j_low = j_diag - BK * (n_win - 1);                    // may lie before the sequence's start
+  BlockSchedule plan(i0, BMQ, n, window, r0);
+  const int i_last = plan.i_last, j_low = plan.j_low, n_win = plan.n_win, first_hi = plan.first_hi;
 
   // ---- per-thread load addressing: buffer loads with 32-bit byte offsets; rows outside the sequence (or past ret_count in
   // the compact segment) are out of the descriptor's range and read as zeros ------------------------------------------
@@ -168,7 +159,6 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   const uint32_t ld_k = (uint32_t)(ld_slot ^ piece_swizzle<D>(ld_row)) * 16u;
   const uint32_t ld_v = (uint32_t)((((ld_slot >> 2) ^ chunk_swizzle<D>(ld_row)) << 2) | (ld_slot & 3)) * 16u;
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
-  int n_blocks = n_win;        // grows once the positions of the compact segment are known
   auto load_rows = [&](u32x4 rk, u32x4 rv, uint32_t dst, uint32_t off, uint32_t step, const int from, const int to) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = from; x < to; ++x) {
@@ -215,11 +205,8 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   };
 
   // ---- which blocks of the compact segment does this wave see? --------------------------------------------------
-  // Bit b of `ret_any`: some entry of a block has left the window of the wave's last row; of `ret_all`: every slot of it holds
-  // an entry that has left the window of its first row.  The first 64 blocks' positions are in LDS (slots past the last
-  // entry as 2^31 - 1); of a longer segment the bits describe the 64 blocks that are being read.
-  unsigned long long ret_any = 0, ret_all = 0;
-  const int lim_hi = r0 < n ? r_hi - window : -1, lim_lo = r0 - window;
+  // The first 64 blocks' positions are in LDS (slots past the last entry as 2^31 - 1); of a longer segment the bits describe
+  // the 64 blocks that are being read.
   auto note_blocks = [&](int n_entries) __attribute__((always_inline)) -> int {      // returns the blocks up to the last one that the workgroup sees
     // lane b looks at block b: 16-byte pieces in an order that spreads 16 lanes over all banks
     int lowest = 0x7FFFFFFF, highest = 0;
@@ -230,47 +217,24 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
       highest = max(max(highest, x.x), max(max(x.y, x.z), x.w));
     }
     const bool there = BK * lane < n_entries;
-    ret_any = __builtin_amdgcn_ballot_w64(there && lowest <= lim_hi);
-    ret_all = __builtin_amdgcn_ballot_w64(there && highest <= lim_lo);
-    const unsigned long long wg = __builtin_amdgcn_ballot_w64(there && lowest <= i_last - window);
+    plan.ret_any = __builtin_amdgcn_ballot_w64(there && plan.some_row_sees(lowest));
+    plan.ret_all = __builtin_amdgcn_ballot_w64(there && plan.every_row_sees(highest));
+    const unsigned long long wg = __builtin_amdgcn_ballot_w64(there && plan.workgroup_sees(lowest));
     return wg == 0 ? 0 : 64 - __builtin_clzll(wg);
   };
   auto far_blocks = [&](int b0) __attribute__((always_inline)) {          // blocks b0 .. b0 + 63 of a segment that LDS does not hold
-    ret_any = ret_all = 0;
+    plan.ret_any = plan.ret_all = 0;
 #pragma unroll 1
     for (int b = b0; b < b0 + 64 && BK * b < cnt; ++b) {
       const int slot = BK * b + ql;
       const int pos = slot < cnt ? head_pos[slot] : 0x7FFFFFFF;
-      if (__builtin_amdgcn_ballot_w64(pos <= lim_hi) != 0ull) ret_any |= 1ull << (b - b0);
-      if (__builtin_amdgcn_ballot_w64(pos > lim_lo) == 0ull) ret_all |= 1ull << (b - b0);
+      if (__builtin_amdgcn_ballot_w64(plan.some_row_sees(pos)) != 0ull) plan.ret_any |= 1ull << (b - b0);
+      if (__builtin_amdgcn_ballot_w64(!plan.every_row_sees(pos)) == 0ull) plan.ret_all |= 1ull << (b - b0);
     }
   };
-  // Window blocks that some row of this wave sees, [w_from, w_to), and that every row sees whole, [p_from, p_to).
-  const int first = r0 - window + 1 > 0 ? r0 - window + 1 : 0, first_hi = r_hi - window + 1 > 0 ? r_hi - window + 1 : 0;
-  const int w_from = first > j_low ? (first - j_low) / BK : 0, w_to = r0 >= n ? 0 : r_hi < j_diag ? (r_hi - j_low) / BK + 1 : n_win;
-  const int p_from = first_hi > j_low ? (first_hi - j_low + BK - 1) / BK : 0, p_to = (r0 - j_low) / BK;
-  auto classify = [&](int i) __attribute__((always_inline)) -> int {
-    if (i < n_win) return i < w_from || i >= w_to ? kSkip : i >= p_from && i < p_to ? kPlain : kMasked;
-    if (i >= n_blocks) return kSkip;
+  auto note_far = [&](int i) __attribute__((always_inline)) {        // before a block is classified
     const int b = i - n_win;
-    if (b >= kPosLds / BK && (b & 63) == 0) far_blocks(b);
-    if (((ret_any >> (b & 63)) & 1) == 0) return kSkip;
-    return ((ret_all >> (b & 63)) & 1) != 0 ? kPlain : kMasked;
-  };
-  // The first block after i that the wave does not see, and the first one from i on that needs a mask.
-  auto end_of_seen = [&](int i) __attribute__((always_inline)) -> int {
-    if (i < n_win && w_to < n_win) return w_to;
-    const int b = i < n_win ? 0 : (i - n_win) & 63;
-    const unsigned long long gone = ~(ret_any >> b);
-    return (i < n_win ? n_win : i) + (gone == 0 ? 64 - b : __builtin_ctzll(gone));
-  };
-  auto next_masked = [&](int i) __attribute__((always_inline)) -> int {
-    if (i < n_win) {
-      if (i < p_from || i >= p_to) return i;
-      return p_to;                        // the diagonal
-    }
-    const unsigned long long part = ~(ret_all >> ((i - n_win) & 63));
-    return part == 0 ? 0x7FFFFFFF : i + __builtin_ctzll(part);
+    if (b >= kPosLds / BK && (b & 63) == 0 && i < plan.n_blocks) far_blocks(b);
   };
 
   // ---- softmax state (per lane = per query; the two lane halves keep separate partial sums) ------
@@ -326,7 +290,7 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
 #pragma unroll
         for (int r = 0; r < 16; ++r) x[r] = (16 * (r / 8) + r % 8 >= c_lo) ? x[r] : -INFINITY;
       }
-    } else if (((ret_all >> ((i - n_win) & 63)) & 1) == 0) {
+    } else if (((plan.ret_all >> ((i - n_win) & 63)) & 1) == 0) {
       const int b = i - n_win, slot0 = BK * b + 8 * hb;
       int pos[16];
       if (b < kPosLds / BK) {
@@ -489,12 +453,12 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     wait_loads();
     __syncthreads();
     // up to which block does some row of the workgroup see an entry?  (segments longer than what LDS holds: all of them)
-    n_blocks = n_win;
+    plan.n_blocks = n_win;
     if (cnt > 0) {
       const int seen = note_blocks(cnt);
-      n_blocks = n_win + (cnt > kPosLds ? (cnt + BK - 1) / BK : seen);
+      plan.n_blocks = n_win + (cnt > kPosLds ? (cnt + BK - 1) / BK : seen);
     }
-    const int n_tiles = (n_blocks + 1) >> 1;
+    const int n_tiles = plan.n_tiles();
     reset_rows();
     auto tile_done = [&]() __attribute__((always_inline)) {
       wait_loads();
@@ -503,9 +467,13 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
 #pragma unroll 1
     for (int t = 0; t < n_tiles;) {
       // tiles from t on of which the wave sees both blocks
-      int t_end = all_have_m && !exact_pass && classify(2 * t) != kSkip ? end_of_seen(2 * t) >> 1 : t;
+      int t_end = t;
+      if (all_have_m && !exact_pass) {
+        note_far(2 * t);
+        t_end = plan.end_of_whole(t);
+      }
       t_end = __builtin_amdgcn_readfirstlane(t_end);
-      int masked_at = __builtin_amdgcn_readfirstlane(next_masked(2 * t));
+      int masked_at = __builtin_amdgcn_readfirstlane(plan.next_masked(2 * t));
       if (t < t_end) {
 #pragma unroll 1
         do {
@@ -533,7 +501,7 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
             tile_interleaved(t & 1, std::true_type{}, t);
             tile_done();
             ++t;
-            masked_at = __builtin_amdgcn_readfirstlane(next_masked(2 * t));
+            masked_at = __builtin_amdgcn_readfirstlane(plan.next_masked(2 * t));
           }
         } while (t < t_end);
       }
@@ -541,8 +509,10 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
       if (t < n_tiles && (t_end <= t)) {
         if (t + 1 < n_tiles) load_tile(t + 1);
 #pragma unroll 1
-        for (int i = 2 * t; i < 2 * t + 2; ++i)
-          if (__builtin_amdgcn_readfirstlane(classify(i)) != kSkip) block_general(i);
+        for (int i = 2 * t; i < 2 * t + 2; ++i) {
+          note_far(i);
+          if (__builtin_amdgcn_readfirstlane(plan.classify(i)) != kSkip) block_general(i);
+        }
         tile_done();
         ++t;
       }

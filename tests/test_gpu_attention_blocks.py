@@ -64,3 +64,13 @@ def test_compact_segments(D, G, budget, shuffle):
 def test_segments_longer_than_lds(D, G, shuffle):
     """More than 2048 and more than 4096 entries: the later blocks are classified from memory, 64 at a time."""
     run(D, G, 33, 4500, [4700], lambda n, h, rng: np.sort(rng.permutation(n)[:4400 - 2100 * h]), shuffle, 3)
+
+
+@pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 1), (128, 4)])
+@pytest.mark.parametrize("n,window,runs", [(277, 96, 3), (330, 97, 2), (421, 64, 4), (161, 128, 3)])
+def test_late_entries_in_interleaved_runs(D, G, n, window, runs):
+    """The segment's last blocks hold only positions behind the window of rows past the sequence's end: no wave may take them
+    (the others would not load and wait for those tiles)."""
+    late = np.arange(n - window, n)
+    order = np.concatenate([late[r::runs] for r in range(runs)])
+    run(D, G, window, window, [n, n - 32], lambda m, h, rng: order[order < m], False, runs)
