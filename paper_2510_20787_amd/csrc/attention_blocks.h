@@ -41,8 +41,8 @@ struct BlockSchedule {
     p_from = first_hi > j_low ? (first_hi - j_low + BK - 1) / BK : 0;
     p_to = (r0 - j_low) / BK;
     // Rows past the sequence's end see nothing: a wave that counted what they would see took tiles that the other waves do not
-    // load and wait for.
-    lim_hi = r0 < n ? (r_hi < i_last ? r_hi : i_last) - window : -1;
+    // load and wait for.  (Below every position: the kept entries of a continued prefill have negative ones.)
+    lim_hi = r0 < n ? (r_hi < i_last ? r_hi : i_last) - window : -0x7FFFFFFF - 1;
     lim_lo = r0 - window;
   }
 

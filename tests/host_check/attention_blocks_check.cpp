@@ -1,7 +1,8 @@
 // Walks the block schedule of the bf16 prefill attention (csrc/attention_blocks.h) on the host, the way the kernel's four waves
 // do, over random sequences, windows and compact segments in any order.  Checks that all waves pass the same tiles (each one
-// waits for the others at every tile), that every (row, key) pair of the set formula is computed exactly once, and that a block
-// taken without a mask has none to apply.  Prints "0 failures" and exits with 0 if all hold.
+// waits for the others at every tile), that every (row, key) pair of the set formula is computed exactly once, that a block
+// taken without a mask has none to apply, and that a wave without a row computes nothing.  Prints "0 failures" and exits with 0
+// if all hold.
 #include <cstdio>
 #include <cstdint>
 #include <algorithm>
@@ -52,7 +53,7 @@ static void workgroup(int n, int window, int i0, int rows, const Segment& seg, c
     std::vector<std::vector<int>> key(32, std::vector<int>(n, 0)), slot(32, std::vector<int>(cnt, 0));
     auto visit = [&](int i) {
       const int kind = p.classify(i);
-      if (kind == kSkip) { ++bad; return; }
+      if (kind == kSkip || r0 >= n) { ++bad; return; }      // a wave without a row has nothing to compute
       for (int r = 0; r < 32; ++r)
         for (int e = 0; e < BK; ++e) {
           const int row = r0 + r;

@@ -36,6 +36,9 @@ CASES = {
     "d64_deep": ([600, 333], 8, 2, 64, 96, 40, 4, 0.0, (3, 3, 3), (64, 32, 16), (2, 2, 2), [0.1, 0.7]),
     "d64_topb": ([640], 2, 2, 64, 64, 33, 0, -np.inf, (5,), (32,), None, [0.3, 0.31]),
     "d64_budget0": ([300, 200], 2, 2, 64, 64, 0, 3, 0.0, (5,), (16,), None, [0.5]),
+    # a chunk of 33 on one head per workgroup: two of the four waves have no row, and all kept entries lie in their past
+    "d64_chunk33": ([400], 4, 4, 64, 64, 96, 0, -np.inf, (5,), (32,), None, [367 / 400]),
+    "d128_chunk33": ([433], 2, 2, 128, 96, 130, 0, -np.inf, (5,), (32,), None, [400 / 433]),
 }
 
 
