@@ -4,6 +4,9 @@
 // Block i < n_win holds the keys j_low + 32 * i ..+31, up to the diagonal; block n_win + b the compact slots 32 * b ..+31.  Two
 // blocks are a tile, which all waves of the workgroup load together and wait for together: every wave passes the same
 // n_tiles() tiles, whatever it sees of them.
+//
+// What is known of the compact segment (its positions in LDS, the bits below) are the blocks base .. next_base() - 1, 64 of them
+// (63 at first where n_win is odd, so that a tile's blocks are known together).  A longer segment is walked group by group.
 #pragma once
 
 namespace ltea {
@@ -16,13 +19,14 @@ struct BlockSchedule {
   // of the workgroup
   int window = 0, i_last = 0;        // last query row that exists
   int j_low = 0, n_win = 0;          // j_low may lie before the sequence's start
-  int n_blocks = 0;                  // n_win, and the compact blocks up to the last one that some row sees
+  int base = 0;                      // first compact block of the group
+  int n_blocks = 0;                  // n_win, and the compact blocks up to the last one of the group that some row sees
   // of the wave
   int r0 = 0, r_hi = 0, first_hi = 0;     // first and last row, the last one's first key
   int w_from = 0, w_to = 0, p_from = 0, p_to = 0;   // window blocks that some row sees, and that every row sees whole
   int lim_hi = 0, lim_lo = 0;        // positions that the last and the first row have behind their window
-  // Bit b of `ret_any`: some entry of compact block b has left the window of the wave's last row; of `ret_all`: every slot of it
-  // holds an entry that has left the window of its first row.  Of a segment of more than 64 blocks: of the 64 blocks around b.
+  // Bit b of `ret_any`: some entry of compact block base + b has left the window of the wave's last row; of `ret_all`: every slot
+  // of it holds an entry that has left the window of its first row.
   unsigned long long ret_any = 0, ret_all = 0;
 
   // The workgroup owns the query rows i0 .. i0 + rows - 1 of a sequence of n, the wave the 32 rows from first_row on.
@@ -47,6 +51,8 @@ struct BlockSchedule {
   }
 
   [[gnu::always_inline]] constexpr int n_tiles() const { return (n_blocks + 1) >> 1; }
+  [[gnu::always_inline]] constexpr int first_tile() const { return base == 0 ? 0 : (n_win + base) >> 1; }     // of the group
+  [[gnu::always_inline]] constexpr int next_base() const { return ((n_win + base + 64) & ~1) - n_win; }
 
   // What a compact block of which `lowest` and `highest` are the positions (a slot past the last entry: 2^31 - 1) is to the wave
   // and to the workgroup.
@@ -54,13 +60,13 @@ struct BlockSchedule {
   [[gnu::always_inline]] constexpr bool every_row_sees(int highest) const { return highest <= lim_lo; }
   [[gnu::always_inline]] constexpr bool workgroup_sees(int lowest) const { return lowest <= i_last - window; }
 
-  // (of a compact block: the bits have to describe it)
+  // (a compact block has to be of the group)
   [[gnu::always_inline]] constexpr int classify(int i) const {
     if (i < n_win) return i < w_from || i >= w_to ? kSkip : i >= p_from && i < p_to ? kPlain : kMasked;
     if (i >= n_blocks) return kSkip;
-    const int b = i - n_win;
-    if (((ret_any >> (b & 63)) & 1) == 0) return kSkip;
-    return ((ret_all >> (b & 63)) & 1) != 0 ? kPlain : kMasked;
+    const int b = i - n_win - base;
+    if (((ret_any >> b) & 1) == 0) return kSkip;
+    return ((ret_all >> b) & 1) != 0 ? kPlain : kMasked;
   }
 
   // The tile after the last one of those from t on of which the wave sees both blocks; t if it does not see both of t's.
@@ -69,7 +75,7 @@ struct BlockSchedule {
     if (classify(i) == kSkip) return t;
     int end = w_to;                                  // the first block that the wave does not see
     if (i >= n_win || w_to >= n_win) {
-      const int b = i < n_win ? 0 : (i - n_win) & 63;
+      const int b = i < n_win ? 0 : i - n_win - base;
       const unsigned long long gone = ~(ret_any >> b);
       end = (i < n_win ? n_win : i) + (gone == 0 ? 64 - b : __builtin_ctzll(gone));
       end = end < n_blocks ? end : n_blocks;
@@ -80,7 +86,7 @@ struct BlockSchedule {
   // The first block from i on that needs a mask.
   [[gnu::always_inline]] constexpr int next_masked(int i) const {
     if (i < n_win) return i < p_from || i >= p_to ? i : p_to;      // p_to: the diagonal
-    const unsigned long long part = ~(ret_all >> ((i - n_win) & 63));
+    const unsigned long long part = ~(ret_all >> ((i - n_win - base) & 63));
     return part == 0 ? 0x7FFFFFFF : i + __builtin_ctzll(part);
   }
 };

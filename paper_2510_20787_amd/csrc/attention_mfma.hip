@@ -53,7 +53,7 @@ namespace {
 
 constexpr int BN = 64;   // keys per tile: two blocks
 constexpr int kThreads = 256;
-constexpr int kPosLds = 2048;   // positions of the compact segment kept in LDS (longer segments: the rest is read where needed)
+constexpr int kPosLds = 64 * BK;   // positions of the compact segment kept in LDS (longer segments: group by group)
 constexpr float kBig = 1.8446744e19f;  // 2^64: a row sum above this (or not a number) sends the workgroup through its tiles again
 
 template <int D> struct Geo {
@@ -205,10 +205,18 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   };
 
   // ---- which blocks of the compact segment does this wave see? --------------------------------------------------
-  // The first 64 blocks' positions are in LDS (slots past the last entry as 2^31 - 1); of a longer segment the bits describe
-  // the 64 blocks that are being read.
-  auto note_blocks = [&](int n_entries) __attribute__((always_inline)) -> int {      // returns the blocks up to the last one that the workgroup sees
-    // lane b looks at block b: 16-byte pieces in an order that spreads 16 lanes over all banks
+  // The group's positions are in LDS (slots past the last entry as 2^31 - 1): 64 blocks.  A longer segment is walked in groups
+  // of them: its positions arrive with the group's first tile, and a group that nobody sees costs that one wait.  (Positions
+  // read where they were needed, a block at a time, were slower than a load of them with every tile: 2 x 8192 tokens, 16 heads
+  // of D = 64 on 4000 entries 228 us with every tile, 292 block by block, 196 in groups; 32768 tokens, 8 heads on 31000 entries
+  // 1398, 2079 and 1194 us.)
+  auto load_positions = [&]() __attribute__((always_inline)) {
+    const int from = BK * plan.base, left = cnt - from, n_lds = left < kPosLds ? (left + BK - 1) & ~(BK - 1) : kPosLds;
+#pragma unroll 2
+    for (int i = tid; i < n_lds; i += kThreads) pos_lds[i] = i < left ? head_pos[from + i] : 0x7FFFFFFF;
+  };
+  auto note_blocks = [&]() __attribute__((always_inline)) {
+    // lane b looks at block base + b: 16-byte pieces in an order that spreads 16 lanes over all banks
     int lowest = 0x7FFFFFFF, highest = 0;
 #pragma unroll 2
     for (int c = 0; c < 8; ++c) {
@@ -216,25 +224,12 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
       lowest = min(min(lowest, x.x), min(min(x.y, x.z), x.w));
       highest = max(max(highest, x.x), max(max(x.y, x.z), x.w));
     }
-    const bool there = BK * lane < n_entries;
+    const int b = plan.base + lane;
+    const bool there = BK * b < cnt && b < plan.next_base();
     plan.ret_any = __builtin_amdgcn_ballot_w64(there && plan.some_row_sees(lowest));
     plan.ret_all = __builtin_amdgcn_ballot_w64(there && plan.every_row_sees(highest));
     const unsigned long long wg = __builtin_amdgcn_ballot_w64(there && plan.workgroup_sees(lowest));
-    return wg == 0 ? 0 : 64 - __builtin_clzll(wg);
-  };
-  auto far_blocks = [&](int b0) __attribute__((always_inline)) {          // blocks b0 .. b0 + 63 of a segment that LDS does not hold
-    plan.ret_any = plan.ret_all = 0;
-#pragma unroll 1
-    for (int b = b0; b < b0 + 64 && BK * b < cnt; ++b) {
-      const int slot = BK * b + ql;
-      const int pos = slot < cnt ? head_pos[slot] : 0x7FFFFFFF;
-      if (__builtin_amdgcn_ballot_w64(plan.some_row_sees(pos)) != 0ull) plan.ret_any |= 1ull << (b - b0);
-      if (__builtin_amdgcn_ballot_w64(!plan.every_row_sees(pos)) == 0ull) plan.ret_all |= 1ull << (b - b0);
-    }
-  };
-  auto note_far = [&](int i) __attribute__((always_inline)) {        // before a block is classified
-    const int b = i - n_win;
-    if (b >= kPosLds / BK && (b & 63) == 0 && i < plan.n_blocks) far_blocks(b);
+    plan.n_blocks = n_win + plan.base + (wg == 0 ? 0 : 64 - __builtin_clzll(wg));
   };
 
   // ---- softmax state (per lane = per query; the two lane halves keep separate partial sums) ------
@@ -290,21 +285,10 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
 #pragma unroll
         for (int r = 0; r < 16; ++r) x[r] = (16 * (r / 8) + r % 8 >= c_lo) ? x[r] : -INFINITY;
       }
-    } else if (((plan.ret_all >> ((i - n_win) & 63)) & 1) == 0) {
-      const int b = i - n_win, slot0 = BK * b + 8 * hb;
-      int pos[16];
-      if (b < kPosLds / BK) {
+    } else if (((plan.ret_all >> (i - n_win - plan.base)) & 1) == 0) {
+      const int* pos = pos_lds + BK * (i - n_win - plan.base) + 8 * hb;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) pos[r] = pos_lds[slot0 + 16 * (r / 8) + r % 8];
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int slot = slot0 + 16 * (r / 8) + r % 8;
-          pos[r] = slot < cnt ? head_pos[slot] : 0x7FFFFFFF;
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) x[r] = pos[r] <= r0 + ql - window ? x[r] : -INFINITY;
+      for (int r = 0; r < 16; ++r) x[r] = pos[16 * (r / 8) + r % 8] <= r0 + ql - window ? x[r] : -INFINITY;
     }
   };
   // The reference value m of a row (probabilities are exp2(score - m)) only has to keep the exponentials in range,
@@ -438,41 +422,31 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
   };
 
   if (tid == 0) redo_flag = 0;
-#pragma unroll 1
-  for (int pass = 0; pass < 2; ++pass) {
-    if (n_win >= 2) load_tile(0);      // of the window only: does not wait for the count of the compact segment's entries
-    if (pass == 0) {
-      cnt = __builtin_amdgcn_readfirstlane(budget > 0 && i_last - window >= 0 ? ret_count[head] : 0);
-      rs_kr = make_raw_rsrc(k_ret + head * budget * D, (uint32_t)cnt * (uint32_t)(D * 2));
-      rs_vr = make_raw_rsrc(v_ret + head * budget * D, (uint32_t)cnt * (uint32_t)(D * 2));
-      const int n_lds = cnt < kPosLds ? (cnt + BK - 1) & ~(BK - 1) : kPosLds;
-#pragma unroll 2
-      for (int i = tid; i < n_lds; i += kThreads) pos_lds[i] = i < cnt ? head_pos[i] : 0x7FFFFFFF;
-    }
-    if (n_win < 2) load_tile(0);
+  if (n_win >= 2) load_tile(0);      // of the window only: does not wait for the count of the compact segment's entries
+  cnt = __builtin_amdgcn_readfirstlane(budget > 0 && i_last - window >= 0 ? ret_count[head] : 0);
+  rs_kr = make_raw_rsrc(k_ret + head * budget * D, (uint32_t)cnt * (uint32_t)(D * 2));
+  rs_vr = make_raw_rsrc(v_ret + head * budget * D, (uint32_t)cnt * (uint32_t)(D * 2));
+  load_positions();
+  if (n_win < 2) load_tile(0);
+  reset_rows();
+  auto tile_done = [&]() __attribute__((always_inline)) {
     wait_loads();
-    __syncthreads();
-    // up to which block does some row of the workgroup see an entry?  (segments longer than what LDS holds: all of them)
-    plan.n_blocks = n_win;
-    if (cnt > 0) {
-      const int seen = note_blocks(cnt);
-      plan.n_blocks = n_win + (cnt > kPosLds ? (cnt + BK - 1) / BK : seen);
-    }
-    const int n_tiles = plan.n_tiles();
-    reset_rows();
-    auto tile_done = [&]() __attribute__((always_inline)) {
-      wait_loads();
-      __syncthreads();   // tile t + 1 is in LDS; everyone is done with tile t
-    };
+    __syncthreads();   // tile t + 1 is in LDS; everyone is done with tile t
+  };
+  // One loop over the groups and the repeated pass, with one place that starts a group: what the prologue needs (counts, base
+  // addresses) then does not live through the tiles.  No register is spilled; with the prologue inside a loop over the passes 15
+  // to 25 scalar registers were, and a workgroup waited for one argument more (4 x 4096 tokens, 16 heads of D = 64, window
+  // 96, nothing kept: 37.8 -> 35.2 us).
 #pragma unroll 1
-    for (int t = 0; t < n_tiles;) {
+  while (true) {       // window and first group of the compact segment, further groups of it; perhaps all of it once more
+    tile_done();       // the group's first tile and its positions
+    plan.n_blocks = n_win;
+    if (cnt > 0) note_blocks();
+    const int n_tiles = plan.n_tiles();
+#pragma unroll 1
+    for (int t = plan.first_tile(); t < n_tiles;) {
       // tiles from t on of which the wave sees both blocks
-      int t_end = t;
-      if (all_have_m && !exact_pass) {
-        note_far(2 * t);
-        t_end = plan.end_of_whole(t);
-      }
-      t_end = __builtin_amdgcn_readfirstlane(t_end);
+      const int t_end = __builtin_amdgcn_readfirstlane(all_have_m && !exact_pass ? plan.end_of_whole(t) : t);
       int masked_at = __builtin_amdgcn_readfirstlane(plan.next_masked(2 * t));
       if (t < t_end) {
 #pragma unroll 1
@@ -509,22 +483,27 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
       if (t < n_tiles && (t_end <= t)) {
         if (t + 1 < n_tiles) load_tile(t + 1);
 #pragma unroll 1
-        for (int i = 2 * t; i < 2 * t + 2; ++i) {
-          note_far(i);
+        for (int i = 2 * t; i < 2 * t + 2; ++i)
           if (__builtin_amdgcn_readfirstlane(plan.classify(i)) != kSkip) block_general(i);
-        }
         tile_done();
         ++t;
       }
     }
-    wait_loads();
-    if (exact_pass) break;
-    // did a row's reference value fall so far below its scores that its sums left the range?
-    bool bad = !(l_part <= kBig) || !(l_mat[0] <= kBig) || !(l_mat[1] <= kBig);
-    if (__builtin_amdgcn_ballot_w64(bad) != 0ull && lane == 0) redo_flag = 1;
-    __syncthreads();  // also: tile buffers are free
-    if (__builtin_amdgcn_readfirstlane(redo_flag) == 0) break;
-    exact_pass = true;
+    plan.base = plan.next_base();
+    if (BK * plan.base >= cnt) {
+      if (exact_pass) break;
+      // did a row's reference value fall so far below its scores that its sums left the range?
+      const bool bad = !(l_part <= kBig) || !(l_mat[0] <= kBig) || !(l_mat[1] <= kBig);
+      if (__builtin_amdgcn_ballot_w64(bad) != 0ull && lane == 0) redo_flag = 1;
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(redo_flag) == 0) break;
+      exact_pass = true;
+      plan.base = 0;
+      reset_rows();
+    }
+    __syncthreads();   // everyone is done with the tile buffers and has looked at the positions
+    load_tile(plan.first_tile());
+    load_positions();
   }
 
   // ---- epilogue: normalise, stage through LDS, store rows coalesced -------------------------------------------

@@ -28,17 +28,17 @@ static int highest_or(const Segment& s, int b, bool lowest) {
   return v;
 }
 
-// The wave's bits of 64 blocks from `base` on; returns the blocks up to the last one that the workgroup sees.
-static int note(BlockSchedule& p, const Segment& s, int base) {
+// The wave's bits of the group, and its last block that the workgroup sees.
+static void note(BlockSchedule& p, const Segment& s) {
   int seen = 0;
   p.ret_any = p.ret_all = 0;
-  for (int b = base; b < base + 64 && BK * b < (int)s.pos.size(); ++b) {
+  for (int b = p.base; b < p.base + 64 && b < p.next_base() && BK * b < (int)s.pos.size(); ++b) {
     const int low = highest_or(s, b, true), high = std::max(0, highest_or(s, b, false));
-    if (p.some_row_sees(low)) p.ret_any |= 1ull << (b - base);
-    if (p.every_row_sees(high)) p.ret_all |= 1ull << (b - base);
-    if (p.workgroup_sees(low)) seen = b - base + 1;
+    if (p.some_row_sees(low)) p.ret_any |= 1ull << (b - p.base);
+    if (p.every_row_sees(high)) p.ret_all |= 1ull << (b - p.base);
+    if (p.workgroup_sees(low)) seen = b - p.base + 1;
   }
-  return seen;
+  p.n_blocks = p.n_win + p.base + seen;
 }
 
 static void workgroup(int n, int window, int i0, int rows, const Segment& seg, const char* what) {
@@ -70,31 +70,29 @@ static void workgroup(int n, int window, int i0, int rows, const Segment& seg, c
           }
         }
     };
-    const int seen = note(p, seg, 0);
-    p.n_blocks = p.n_win + (cnt > 64 * BK ? (cnt + BK - 1) / BK : seen);
-    const int n_tiles = p.n_tiles();
-    auto note_far = [&](int i) {
-      const int b = i - p.n_win;
-      if (b >= 64 && (b & 63) == 0 && i < p.n_blocks) note(p, seg, b);
-    };
     int settled_at = pick(2, 5), visited = 0, passed = 0;      // blocks by themselves before the reference values are settled
-    for (int t = 0; t < n_tiles;) {
-      int end = t;
-      if (visited >= settled_at) { note_far(2 * t); end = p.end_of_whole(t); }
-      if (end > n_tiles) ++bad;
-      for (; t < end; ++t, ++passed) {
-        const int masked_at = p.next_masked(2 * t);
-        for (int i = 2 * t; i < 2 * t + 2; ++i) {
-          if (i < masked_at && p.classify(i) != kPlain) ++bad;
-          visit(i);
+    while (true) {
+      note(p, seg);
+      const int n_tiles = p.n_tiles();
+      if (p.next_base() - p.base > 64 || n_tiles > std::max((p.n_win + p.next_base()) / 2, p.first_tile())) ++bad;
+      for (int t = p.first_tile(); t < n_tiles;) {
+        const int end = visited >= settled_at ? p.end_of_whole(t) : t;
+        if (end > n_tiles) ++bad;
+        for (; t < end; ++t, ++passed) {
+          const int masked_at = p.next_masked(2 * t);
+          for (int i = 2 * t; i < 2 * t + 2; ++i) {
+            if (i < masked_at && p.classify(i) != kPlain) ++bad;
+            visit(i);
+          }
         }
+        if (t >= n_tiles) break;
+        for (int i = 2 * t; i < 2 * t + 2; ++i)
+          if (p.classify(i) != kSkip) { visit(i); ++visited; }
+        ++t, ++passed;
       }
-      if (t >= n_tiles) break;
-      for (int i = 2 * t; i < 2 * t + 2; ++i) {
-        note_far(i);
-        if (p.classify(i) != kSkip) { visit(i); ++visited; }
-      }
-      ++t, ++passed;
+      const int next = p.next_base();
+      if (BK * next >= cnt) break;
+      p.base = next;
     }
     tiles_of[wave] = passed;
     for (int r = 0; r < 32 && r0 + r < n; ++r) {

@@ -74,3 +74,12 @@ def test_late_entries_in_interleaved_runs(D, G, n, window, runs):
     late = np.arange(n - window, n)
     order = np.concatenate([late[r::runs] for r in range(runs)])
     run(D, G, window, window, [n, n - 32], lambda m, h, rng: order[order < m], False, runs)
+
+
+@pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 1)])
+@pytest.mark.parametrize("entries", [2015, 2016, 2017, 2048, 2049, 4064, 4097])
+def test_groups_of_64_blocks(D, G, entries):
+    """Segments around the end of a group of 64 blocks (63 where the window takes an odd number), ascending and with the
+    earliest positions in the last group, so that a group that nobody sees comes before one that all rows see."""
+    late_first = lambda n: np.concatenate([np.arange(n // 2, n), np.arange(n // 2)])[-entries:]
+    run(D, G, 40 + entries % 64, entries, [4200], lambda n, h, rng: np.arange(entries) if h == 0 else late_first(n), False, 5)
