@@ -304,9 +304,12 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     const float m_new = fmaxf(m_run, mx * scale_log2e);
     // nothing visible so far and nothing now: m stays -inf, and the factor must not become exp2(nan)
     const float a = (m_new == m_run) ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+    const bool none = m_run == -INFINITY;
     m_run = m_new;
     l_part *= a;
-    if (__builtin_amdgcn_ballot_w64(a != 1.0f) != 0ull) {
+    // A row that has seen nothing has nothing to scale: the first block waits for no accumulator.  (With two blocks to settle the
+    // reference, short windows felt each of these passes: 4 x 4096 tokens, 16 heads of D = 128, window 16 55.6 -> 54.4 us.)
+    if (__builtin_amdgcn_ballot_w64(a != 1.0f && !none) != 0ull) {
 #pragma unroll
       for (int db = 0; db < ND; ++db)
 #pragma unroll
@@ -434,9 +437,9 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     __syncthreads();   // tile t + 1 is in LDS; everyone is done with tile t
   };
   // One loop over the groups and the repeated pass, with one place that starts a group: what the prologue needs (counts, base
-  // addresses) then does not live through the tiles.  No register is spilled; with the prologue inside a loop over the passes 15
-  // to 25 scalar registers were, and a workgroup waited for one argument more (4 x 4096 tokens, 16 heads of D = 64, window
-  // 96, nothing kept: 37.8 -> 35.2 us).
+  // addresses) then does not live through the tiles.  No vector register and at most two scalar ones (at D = 128) are spilled; with
+  // the prologue inside a loop over the passes 15 to 25 were, and a workgroup waited for one argument more (4 x 4096 tokens, 16
+  // heads of D = 64, window 96, nothing kept: 37.8 -> 35.2 us).
 #pragma unroll 1
   while (true) {       // window and first group of the compact segment, further groups of it; perhaps all of it once more
     tile_done();       // the group's first tile and its positions
