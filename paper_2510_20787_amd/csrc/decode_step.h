@@ -899,10 +899,11 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   extern __shared__ __align__(16) float dyn_lds[];  // per-head scoring: two generations of activation rows
   __shared__ float red_m[W][kHeads], red_l[W][kHeads];
   // merge of the waves; before that the wave-private V tiles of the MFMA stream; the batched scoring roles' scratch.  The 16
-  // columns of the MFMA stream write theirs side by side: four words between the rows of a group of up to five heads spread
-  // them over all 64 banks (rows of D words meet in 4 of them; 32 sequences of the paper's layer, us per step: 23.3 -> 22.9, and
-  // 756 lazy steps with their scoring 15 431 -> 15 182).
-  constexpr int kRow = GT == 5 ? D + 4 : D;
+  // columns of the MFMA stream write theirs side by side: four words between the rows spread them over all 64 banks (rows of D
+  // words meet in 4 of them).  Groups of up to five heads: lazy steps of 32 sequences of the paper's layer 19.1 -> 18.9 us, of a
+  // layer with D = 128 37.7 -> 36.9; 8 heads: 26.7 -> 25.8 at D = 128, 18.0 -> 17.6 at D = 64; 16 heads: 20.7 -> 18.8 (8 sequences,
+  // D = 128), 16.4 -> 15.7 (32, D = 64).
+  constexpr int kRow = GT >= 5 ? D + 4 : D;
   constexpr int kMerge = W * kHeads * kRow, kRole = SK == kDeepRole ? kDeepLds / 4 : SK > 1 ? 2048 : 0;
   __shared__ __align__(16) float scratch[kMerge > kRole ? kMerge : kRole];
   __shared__ unsigned long long red64[W];
