@@ -955,10 +955,10 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
   // Matrix stream of a step without scoring workgroups (lazy scoring, logits given): a wave's first block of 32 ring slots is
-  // requested before n_seen has come, whatever it holds;
-  // settle() takes out what is not there yet.  One trip to memory less: 756 lazy steps of 32 sequences of the paper's layer
-  // 15 182 -> 14 562 us.  Beside scoring workgroups, which the same memory serves first, the order bought nothing (22.9 -> 23.2
-  // us per rotary step of 32).
+  // requested before n_seen has come, whatever it holds; settle() takes out what is not there yet.  One trip to memory less:
+  // 756 lazy steps of 32 sequences of the paper's layer 15 182 -> 14 562 us.  Steps with scoring workgroups keep the order: on
+  // groups of four they took 11.2 -> 11.5 us with it (one sequence, one layer of k = 5), 12.2 -> 12.2 (one, the paper's stack),
+  // 14.5 -> 14.9 (8, the stack), 20.9 -> 21.0 (32, the stack); only D = 128 gained (32 sequences, 8 heads: 30.3 -> 29.9).
   constexpr bool kBlind = GT >= 5 && SK == 0;
   using MS = MfmaStream<D>;
   typename MS::Rows cur;
