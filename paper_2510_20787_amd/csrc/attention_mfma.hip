@@ -30,16 +30,21 @@
 // blocks plus one, two of them masked; tiles of 64 keys on a fixed grid cost up to three blocks more, and blocks of the
 // segment that lie in the future of all rows (half of them on average) were loaded and waited for.  Window blocks go in
 // ascending order: neighbouring workgroups, which start one after the other, then meet in the L2 (from the diagonal down
-// three times as many bytes came from beyond it).
+// 4.0 GB instead of 1.4 came from beyond it for 32768 tokens x 32 heads of D = 128).
 //
-// What bounds it: at D = 128 the power that the matrix instructions draw (a loop of them on normally distributed operands
-// runs at 1.66 GHz and 1.53 PFLOP/s, on zeros at 2.39 GHz and 2.2), at D = 64 the issue of a wave's instructions (a matrix
-// instruction holds it for 16 clocks of its 32, an exponential for 8, others for 4) and the start of a workgroup (about 6000
-// of 40000 clocks: sequence, count, positions, first tile).  Kernel time on one box, tiles on the fixed grid -> this form:
-// 32768 tokens x 32 heads of D = 128 1425 -> 1304 us; 4 x 4096 tokens, 32 query heads on 8 of D = 64 191 -> 167 us, 16 heads
-// of D = 64 76 -> 70 us; 777 tokens, 32 on 8 heads 17.7 -> 15.3 us.  Tried and not kept: the products of one block beside the
-// scores of the next across tiles (same speed, and every first and last block of a wave runs by itself); 64 queries per wave
-// at D = 64 (half the operand reads, but 47 registers spilled: 192 us against 162).
+// What bounds it: at D = 128 the clock that power leaves (1.80 GHz of 2.4, as for a bare loop of matrix instructions on normally
+// distributed operands, which reaches 1.84 PFLOP/s there and 2.45 on zeros) and a matrix pipe that is busy in 58 % of those
+// clocks; at D = 64 the issue of a wave's instructions (a matrix instruction holds it for 16 clocks of its 32, an exponential
+// for 8, others for 4) and the start of a workgroup (7000 to 8000 of 44000 to 51000 clocks: sequence, count, positions, first
+// tile).  Kernel time, tiles on the fixed grid and this form in turn on one box:
+// 32768 tokens x 32 heads of D = 128 1435 -> 1298 us; 4 x 4096 tokens, 32 query heads on 8 of D = 64 166 -> 151 us, 16 heads
+// of D = 64 67.9 -> 63.3 us; 777 tokens, 32 on 8 heads 16.0 -> 13.5 us.  Windows of up to 64 keys on one head per workgroup lose:
+// a wave's few blocks then run by themselves, and the first two settle the reference values (4 x 4096 tokens, 16 heads, 64 kept:
+// D = 64, window 16 36.7 -> 38.7 us, window 64 37.0 -> 38.3; D = 128, window 48 67.0 -> 68.5, window 16 67.7 -> 63.9).
+// Tried and not kept: the products of one block beside the scores of the next across tiles (same speed, and every first and
+// last block of a wave runs by itself); 64 queries per wave at D = 64 (half the operand reads, but 47 registers spilled: 192 us
+// against 162); blocks that run by themselves with all their operands requested ahead (windows of up to 128 keys 1 to 2 %
+// slower).
 #include <type_traits>
 
 #include "attention_blocks.h"

@@ -9,8 +9,9 @@
 //                                d logit and the retention counts.
 //
 // dQ role: one workgroup = 128 consecutive queries of one (sequence, query head), 4 waves x 32 queries (or 32 queries of four
-// heads, one per wave, see dq_body), walking the same key tiles as the forward kernel (64-key tiles of K/V inside the window
-// range, then 64-slot tiles of the compacted candidates with the per-row mask "position <= i - window").  Per 32-key block
+// heads, one per wave, see dq_body), walking 64-key tiles of K/V on a fixed grid inside the window range, then 64-slot tiles of
+// the compacted candidates with the per-row mask "position <= i - window" (the forward kernel has since gone over to blocks of
+// 32 keys aligned to the query rows, with masked tiles interleaved like plain ones; this one has not).  Per 32-key block
 // and wave (v_mfma_f32_32x32x16_bf16, a lane owns one query column):
 //   S^T[key, query]  = K . Q^T        A = K tile rows from LDS, B = Q fragment in registers
 //   dP^T[key, query] = V . dO^T       A = V tile rows from LDS, B = dO fragment in registers
@@ -148,7 +149,7 @@ __device__ __forceinline__ void dq_body(const TrainArgs& A, int tiles_upper, int
   const int64_t stat = (int64_t)hq * A.total + lo + qc;
   const float neg_dlt = A.delta[stat], neg_lse = A.delta[(int64_t)Hq * A.total + stat];
 
-  // ---- tile schedule (as in the forward) ------------------------------------------------------------------
+  // ---- tile schedule: 64-key tiles from the multiple of 64 at or before the window's first key ------------------
   const int i_last = (i0 + BMQ < n ? i0 + BMQ : n) - 1;
   const int jlo = i0 - window + 1 > 0 ? i0 - window + 1 : 0;
   const int jt0 = (jlo / BN) * BN;

@@ -251,9 +251,9 @@ def test_sparse_attention_uniform_keep(dtype, D, G):
 
 @pytest.mark.parametrize("D,G", [(64, 1), (64, 4), (128, 1), (128, 4)])
 def test_sparse_attention_scores_far_above_the_first_block(D, G):
-    """Keys that grow 64-fold later in the sequence: a row's later scores exceed the maximum of the first block it
+    """Keys that grow 64-fold later in the sequence: a row's later scores exceed the maximum of the first blocks it
     sees by hundreds of binary orders, more than the exponent range covers.  The MFMA kernel keeps the reference
-    value of a row from that first block; such rows must come out right all the same (it runs the workgroup's
+    value of a row from its first two blocks; such rows must come out right all the same (it runs the workgroup's
     tiles again with the running maximum).  Softmax rows are then nearly one-hot, so the output is the value row of
     the best key."""
     lens = [700, 333, 64]
