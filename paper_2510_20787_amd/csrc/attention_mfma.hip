@@ -39,8 +39,10 @@
 // tile).  Kernel time, tiles on the fixed grid and this form in turn on one box:
 // 32768 tokens x 32 heads of D = 128 1435 -> 1298 us; 4 x 4096 tokens, 32 query heads on 8 of D = 64 166 -> 151 us, 16 heads
 // of D = 64 67.9 -> 63.3 us; 777 tokens, 32 on 8 heads 16.0 -> 13.5 us.  Windows of up to 64 keys on one head per workgroup lose:
-// a wave's few blocks then run by themselves, and the first two settle the reference values (4 x 4096 tokens, 16 heads, 64 kept:
-// D = 64, window 16 36.7 -> 38.7 us, window 64 37.0 -> 38.3; D = 128, window 48 67.0 -> 68.5, window 16 67.7 -> 63.9).
+// a wave's few blocks then run by themselves, the operands of the second waiting for the first (4 x 4096 tokens, 16 heads, 64
+// kept: D = 64, window 16 36.7 -> 38.7 us, window 64 37.0 -> 38.3; D = 128, window 48 67.0 -> 68.5, window 16 67.7 -> 63.9).
+// Neither one block for the reference values (38.7 -> 38.8 us at window 16) nor an even number of window blocks (38.2 there, but
+// 151 -> 152 us for the 4 x 4096 tokens above and 13.6 -> 14.9 for the 777) changes that.
 // Tried and not kept: the products of one block beside the scores of the next across tiles (same speed, and every first and
 // last block of a wave runs by itself); 64 queries per wave at D = 64 (half the operand reads, but 47 registers spilled: 192 us
 // against 162); blocks that run by themselves with all their operands requested ahead (windows of up to 128 keys 1 to 2 %
@@ -312,8 +314,8 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     const bool none = m_run == -INFINITY;
     m_run = m_new;
     l_part *= a;
-    // A row that has seen nothing has nothing to scale: the first block waits for no accumulator.  (With two blocks to settle the
-    // reference, short windows felt each of these passes: 4 x 4096 tokens, 16 heads of D = 128, window 16 55.6 -> 54.4 us.)
+    // A row that has seen nothing has nothing to scale: the first block waits for no accumulator.  (Short
+    // windows feel it: 4 x 4096 tokens, 16 heads of D = 128, window 16 55.6 -> 54.4 us.)
     if (__builtin_amdgcn_ballot_w64(a != 1.0f && !none) != 0ull) {
 #pragma unroll
       for (int db = 0; db < ND; ++db)
