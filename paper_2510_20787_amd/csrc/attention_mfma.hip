@@ -314,8 +314,8 @@ attention_mfma_kernel(const bf16_t* __restrict__ q, int64_t q_st, int64_t q_sh, 
     const bool none = m_run == -INFINITY;
     m_run = m_new;
     l_part *= a;
-    // A row that has seen nothing has nothing to scale: the first block waits for no accumulator.  (Short
-    // windows feel it: 4 x 4096 tokens, 16 heads of D = 128, window 16 55.6 -> 54.4 us.)
+    // A row that has seen nothing has nothing to scale: the first block waits for no accumulator.  (Short windows feel it: 4 x 4096
+    // tokens, 16 heads of D = 128, window 16 55.6 -> 54.4 us.)
     if (__builtin_amdgcn_ballot_w64(a != 1.0f && !none) != 0ull) {
 #pragma unroll
       for (int db = 0; db < ND; ++db)
