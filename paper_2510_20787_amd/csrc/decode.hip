@@ -101,7 +101,7 @@ size_t decode_workspace_most(const ltea_cfg& cfg, int n_seqs) {
 }
 
 // The documented bound on the CNN, for two generations of activation rows of the whole receptive field (the launch keeps
-// only every unit-th row of them in LDS, in whole quads, beside the step's own 64 KB).
+// only every unit-th row of them in LDS, in whole quads, beside the step's own 69 KB at most).
 bool decode_scores_inside(const ltea_cfg& cfg, const ltea_cnn& cnn) {
   return (size_t)2 * (2 * cnn_rho(&cnn) + 1) * widest_row(cfg, cnn) * sizeof(float) <= 48 * 1024;
 }
