@@ -11,28 +11,42 @@
 //   score_weight_panels_kernel  re-lays the weights [Hkv][C][2D][k] once per call as tap-major panels
 //                               [Hkv][k][32][2D] (channels zero-padded to 32) in the workspace, so that the main
 //                               kernel can fetch a panel with coalesced 16-byte loads;
-//   score_mfma_kernel           one workgroup = 4 consecutive 128-token tiles of one (sequence, KV head).  Input
-//                               channels are processed in chunks of 128 (D = 64: keys and values together;
-//                               D = 128: keys, then values): all taps' weight panels of the chunk are staged in
-//                               LDS once and reused for the four tiles (one accumulator set per tile); each
-//                               tile's rows with their halo of half*dil rows (zeros outside the sequence) are
-//                               fetched into registers while the previous tile is being multiplied and then
-//                               stored to LDS in 16-byte pieces.  Rows are padded by 16 bytes, which makes the
-//                               16-lane groups of every ds_read_b128 hit 64 distinct banks.
+//   score_mfma_kernel           one workgroup = up to 8 consecutive tiles of one (sequence, KV head), 32 tokens per wave in
+//                               a tile.  The weights of 128 input channels (D = 64: all; D = 128: the keys', then the
+//                               values') lie in LDS while all its tiles pass, one accumulator per tile, so they are
+//                               brought there once or twice per workgroup.  A stage is 64 channels of a tile's rows with
+//                               their halo of half*dil rows (zeros outside the sequence): it is multiplied out of one of
+//                               two LDS buffers while the next one is stored into the other and the two after that are
+//                               on their way to registers.  One barrier per stage; operand reads run three matrix
+//                               instructions ahead of their use.
+//
+// What bounds it: the rows' way from memory, 64 channels (128 bytes) out of every token's 2 D Hkv: without the products of all
+// but one tap it takes 194 of 231 us (16 sequences of 1024 to 16384 tokens, 16 heads of D = 128, k = 5) and 125 of 150 (32768
+// tokens, 32 heads, k = 7), 5.5 and 4.3 TB/s where a linear read reaches 6.6.  Rows of all 128 bytes of a channel half at once
+// give 4 % of that, an order of heads that keeps an XCD's neighbouring nothing, non-temporal loads 2 % here and minus 15 % on
+// 4 x 4096 tokens (32.2 -> 37.2 us: the attention's and the next call's rows then come from HBM).  What was slow before, with
+// 128-token tiles of 128 channels in one buffer: at k = 7 one workgroup per CU, in lockstep through load, store and products
+// (the matrix pipe busy for 57 of 197 us).  Before -> now, us per call: the two shapes above 259 -> 231 and 199 -> 150, 2048
+// tokens x 32 heads, k = 7 22.4 -> 14.5, 512 x 16, k = 5 17.4 -> 11, 4 x 4096 x 16, k = 5 32.9 -> 31.9, D = 64, k = 7 30.0 -> 25.2.
+// Tried: the weights beside every stage instead of resident (240 and 154 us); direct global-to-LDS rows of 32 channels,
+// five stages deep, shared or private to the waves (274, 290 and 148, 150 us: pieces of 64 bytes).
+#include <type_traits>
+
 #include "ltea_common.h"
 #include "ltea_kernels.h"
+#include "score_dma.h"
 
 namespace ltea {
 namespace {
 
-constexpr int TM = 128;       // tokens per workgroup
-constexpr int kThreads = 256;
 constexpr int CP = 32;        // channels padded to one MFMA tile
-constexpr int CH = 128;       // input channels per chunk
-constexpr int XS = CH + 8;    // LDS row stride (elements) of the token tile and of the weight panel
-constexpr int NT = 4;         // consecutive token tiles per workgroup (weights staged once for all of them)
+constexpr int HC = 128;       // input channels whose weights are in LDS at a time
+constexpr int SC = 64;        // input channels per stage: token rows of 128 bytes, all of them keys' or all values'
 constexpr int kMaxRho = 4;    // largest half receptive field the token tile is sized for
-constexpr int kTileRows = TM + 2 * kMaxRho;   // LDS rows of the token tile
+constexpr int kMaxTaps = 2 * kMaxRho + 1;
+constexpr int kMaxGroup = 8;  // tiles per workgroup
+constexpr int stage_bytes(int waves) { return (32 * waves + 2 * kMaxRho) * SC * 2; }   // 32 tokens per wave and the halo
+constexpr int kTapB = CP * HC * 2;                 // one tap's weights of HC channels
 
 // panels[h][tap][c][m] = W[h][c][m][tap] for c < C, 0 for C <= c < 32
 __global__ void __launch_bounds__(256)
@@ -48,131 +62,181 @@ score_weight_panels_kernel(const uint16_t* __restrict__ W, uint16_t* __restrict_
   panels[idx] = c < C ? W[((h * C + c) * C2 + m) * ks + tap] : (uint16_t)0;
 }
 
-template <int D>
-__global__ void __launch_bounds__(kThreads)
+// KS: the kernel size, 0: any up to kMaxTaps.  NW: waves; four where two workgroups share a CU's LDS (k <= 5: 76 KB each; one hides
+// the start of the other: 265 -> 231 us on the ragged shape above), eight where one fills it.
+template <int D, int KS, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
 score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int64_t st, int64_t sh,
                   const bf16_t* __restrict__ panels, const float* __restrict__ bias,
-                  const bf16_t* __restrict__ w_out, const float* __restrict__ b_out, int C, int ks, int dil,
-                  const int32_t* __restrict__ cu, int n_seqs, int groups_upper, int64_t total,
-                  float* __restrict__ logits) {
-  constexpr int C2 = 2 * D;        // input channels
-  constexpr int NCH = C2 / CH;     // chunks
-  constexpr int PPR = CH / 8;      // 16-byte pieces per chunk row (16)
-  constexpr int RPP = kThreads / PPR;   // token rows per staging pass (16)
-  constexpr int XREG = (TM + 2 * kMaxRho + RPP - 1) / RPP;   // staging passes (registers) per tile
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int half = (ks - 1) / 2, rho = half * dil;
-  const int tile_rows = TM + 2 * rho;              // rows of the token tile actually used (at most kTileRows)
-  bf16_t* x_lds = reinterpret_cast<bf16_t*>(smem);
-  bf16_t* w_lds = x_lds + (size_t)tile_rows * XS;  // ks panels of CP x XS (all taps of the current chunk)
+                  const bf16_t* __restrict__ w_out, const float* __restrict__ b_out, int C, int any_ks, int dil,
+                  const int32_t* __restrict__ cu, int n_seqs, int Hkv, int64_t total, float* __restrict__ logits,
+                  int group_tiles) {
+  constexpr int kThreads = 64 * NW, TM = 32 * NW, kStageB = stage_bytes(NW);
+  constexpr int C2 = 2 * D, NH = C2 / HC, SPT = HC / SC;      // input channels, passes over the tiles, stages per tile and pass
+  extern __shared__ __align__(1024) unsigned char smem[];
+  const int ks = KS > 0 ? KS : any_ks;
+  const int rho = (ks - 1) / 2 * dil;
+  unsigned char* const w_lds = smem;                          // [tap][channel] rows of HC inputs
+  unsigned char* const x_lds = smem + ks * kTapB;             // two stages of token rows
+  float* const out_lds = reinterpret_cast<float*>(x_lds + 2 * kStageB);     // bias, output projection
 
-  const int h = blockIdx.y;
-  int grp, s, n, lo32;
-  if (!locate_tile(cu, n_seqs, NT * TM, blockIdx.x, s, grp, lo32, n)) return;
-  const int64_t lo = lo32;
-  const int g0 = grp * NT * TM;                      // first token of this workgroup's NT tiles
-  int n_tiles = (n - g0 + TM - 1) / TM;
-  n_tiles = n_tiles < NT ? n_tiles : NT;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, ql = lane & 31, hb = lane >> 5;
+  // heads fastest: workgroups that run together read neighbouring pieces of the same rows, and where the heads are a multiple
+  // of the 8 XCDs an XCD sees the weights of its own heads only
+  const int h = (int)(blockIdx.x % (unsigned)Hkv);
+  const int tid = threadIdx.x, lane = tid & 63, ql = lane & 31, hb = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  const bf16_t* ph = panels + (int64_t)h * ks * CP * C2;
-  // all taps' panels of one chunk -> LDS: 512 coalesced 16-byte pieces per tap, two per thread, no conditions
-  auto stage_panels = [&](int chunk) {
-    const int pm = (tid % (CH / 8)) * 8, c0 = tid / (CH / 8);           // channels c0 and c0 + 16
-    const bf16_t* src = ph + (int64_t)c0 * C2 + chunk * CH + pm;
-    bf16_t* dst = w_lds + (size_t)c0 * XS + pm;
-    for (int tap0 = 0; tap0 < ks; tap0 += 4) {
-      u32x4 w[4][2];
+  // weights of one half: 16 pieces of 16 bytes per row, piece p of row c to place p ^ (c & 15)
+  const int w_row = tid >> 4, w_piece = tid & 15;
+  constexpr int kWRows = kThreads / 16, kWTaps = KS > 0 ? KS : kMaxTaps;            // rows per pass
+  const bf16_t* const w_src = panels + ((int64_t)h * ks * CP + w_row) * C2 + w_piece * 8;
+  unsigned char* const w_dst = w_lds + w_row * (HC * 2) + ((w_piece ^ (w_row & 15)) << 4);
+  u32x4 wreg[kWTaps][CP / kWRows];
+  auto load_weights = [&](int half) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int tap = tap0 + u < ks ? tap0 + u : ks - 1;                // clamp: the extra copies are harmless
-        w[u][0] = *reinterpret_cast<const u32x4*>(src + (int64_t)tap * CP * C2);
-        w[u][1] = *reinterpret_cast<const u32x4*>(src + (int64_t)tap * CP * C2 + 16 * C2);
-      }
+    for (int i = 0; i < kWTaps; ++i)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int tap = tap0 + u < ks ? tap0 + u : ks - 1;
-        *reinterpret_cast<u32x4*>(dst + (size_t)tap * CP * XS) = w[u][0];
-        *reinterpret_cast<u32x4*>(dst + (size_t)tap * CP * XS + 16 * XS) = w[u][1];
-      }
-    }
+      for (int j = 0; j < CP / kWRows; ++j)
+        wreg[i][j] = *reinterpret_cast<const u32x4*>(w_src + ((int64_t)(KS > 0 || i < ks ? i : 0) * CP + j * kWRows) * C2 + half * HC);
   };
-  // Token tile of one chunk with halo: global -> registers (issued early), registers -> LDS (after the MFMAs).
-  // Buffer loads: rows before the sequence start or past its end are outside the descriptor and read as zeros,
-  // so the loads carry no conditions and are issued back to back.  For D = 64 a chunk row is 8 key pieces followed
-  // by 8 value pieces; waves 0-1 fetch the key halves and waves 2-3 the value halves (one descriptor per wave).
-  constexpr int HT = D == 64 ? kThreads / 2 : kThreads;   // threads cooperating on one tensor's part of the rows
-  constexpr int PPH = D == 64 ? 8 : 16;                   // 16-byte pieces of that part per row
-  const int t_in = tid % HT, piece = t_in % PPH, r_in = t_in / PPH;   // 16 rows per pass either way
-  const bool v_wave = D == 64 && __builtin_amdgcn_readfirstlane(tid / HT) == 1;
-  // The descriptors start at the first row this workgroup reads (the sequence start for the first group, whose
-  // halo rows then wrap to huge offsets) and end at the last one or at the sequence end, so that 32-bit byte
-  // offsets only ever span one group of tiles however long the sequence is.
+  auto store_weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < kWTaps; ++i)
+#pragma unroll
+      for (int j = 0; j < CP / kWRows; ++j)
+        if (KS > 0 || i < ks) *reinterpret_cast<u32x4*>(w_dst + i * kTapB + j * kWRows * (HC * 2)) = wreg[i][j];
+  };
+  load_weights(0);
+  if (tid < CP) {
+    const int c = tid < C ? tid : C - 1;         // unconditional loads, then select
+    const float b_ld = bias[h * C + c], w_ld = to_f32(w_out[h * C + c]);
+    out_lds[tid] = tid < C ? b_ld : 0.f;
+    out_lds[CP + tid] = tid < C ? w_ld : 0.f;
+  }
+  const float bo = b_out[h];
+  int grp, s, n, lo32;
+  if (!locate_tile(cu, n_seqs, group_tiles * TM, (int)(blockIdx.x / (unsigned)Hkv), s, grp, lo32, n)) return;
+  const int64_t lo = lo32;
+  const int g0 = grp * group_tiles * TM;         // first token of this workgroup's tiles
+  const int n_tiles = min((n - g0 + TM - 1) / TM, group_tiles);
+
+  // Rows before the sequence start or past its end are outside the descriptors and arrive as zeros.  The descriptors start at
+  // the first row this workgroup reads (the sequence start for the first group, whose halo rows then wrap to huge offsets)
+  // and end at the last one or at the sequence end, so that 32-bit byte offsets only ever span one group of tiles.
   const uint32_t row_bytes = (uint32_t)st * 2u;
   const int base_row = g0 > 0 ? g0 - rho : 0;
-  const int rows_here = n - base_row < NT * TM + 2 * kMaxRho ? n - base_row : NT * TM + 2 * kMaxRho;
+  const int rows_here = min(n - base_row, n_tiles * TM + 2 * rho);
   const uint32_t seq_bytes = (uint32_t)(rows_here - 1) * row_bytes + (uint32_t)(D * 2);
   const int64_t base_el = (lo + base_row) * st + (int64_t)h * sh;
   const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(k + base_el), 0, seq_bytes, 0x00020000);
   const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(v + base_el), 0, seq_bytes, 0x00020000);
-  const int lds_col = (v_wave ? D : 0) + piece * 8;
-  u32x4 xreg[XREG];
-  auto load_tokens = [&](int chunk, int tile) {
-    const bool is_v = D == 64 ? v_wave : chunk == 1;
-    const int j0 = g0 + tile * TM;
-    const uint32_t off0 = (uint32_t)(j0 - rho + r_in - base_row) * row_bytes + (uint32_t)piece * 16u;   // wraps for rows < 0
+  // A thread brings one 16-byte piece of every kPassRows-th row.  Piece p of row r goes to place p ^ ((r >> 1) & 7), so that the operand
+  // reads of 16 consecutive rows at one piece cover all 64 banks.
+  constexpr int kPassRows = kThreads / 8, kPasses = TM / kPassRows;
+  const int piece = tid & 7, r_in = tid >> 3;
+  const uint32_t off0 = (uint32_t)(g0 - rho + r_in - base_row) * row_bytes + (uint32_t)piece * 16u;   // wraps for rows < 0
+  const bool halo = r_in < 2 * rho;
+  unsigned char* const x_dst = x_lds + r_in * (SC * 2) + ((piece ^ ((r_in >> 1) & 7)) << 4);
+  u32x4 xreg[2][kPasses + 1];
+  int ld_sub = 0, ld_tile = 0, ld_half = 0;      // the next stage to request
+  auto request = [&](u32x4 (&x)[kPasses + 1]) __attribute__((always_inline)) {
+    const int ch = ld_half * HC + ld_sub * SC;
+    const bool is_v = ch >= D;
+    const uint32_t off = off0 + (uint32_t)(ld_tile * TM) * row_bytes + (uint32_t)((is_v ? ch - D : ch) * 2);
 #pragma unroll
-    for (int i = 0; i < XREG; ++i) {
-      const uint32_t off = off0 + (uint32_t)(i * RPP) * row_bytes;
-      xreg[i] = is_v ? __builtin_amdgcn_raw_buffer_load_b128(rs_v, off, 0, 0)
-                     : __builtin_amdgcn_raw_buffer_load_b128(rs_k, off, 0, 0);
+    for (int i = 0; i <= kPasses; ++i) {
+      const uint32_t at = i < kPasses || halo ? off + (uint32_t)(kPassRows * i) * row_bytes : 0xFFFFFFF0u;
+      x[i] = is_v ? __builtin_amdgcn_raw_buffer_load_b128(rs_v, at, 0, 0) : __builtin_amdgcn_raw_buffer_load_b128(rs_k, at, 0, 0);
+    }
+    if (++ld_sub == SPT) {
+      ld_sub = 0;
+      if (++ld_tile == n_tiles) { ld_tile = 0; ++ld_half; }
     }
   };
-  auto store_tokens = [&]() {
+  auto deposit = [&](const u32x4 (&x)[kPasses + 1], int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < XREG; ++i)
-      if (r_in + i * RPP < tile_rows)   // the token tile ends where the weight panels begin
-        *reinterpret_cast<u32x4*>(&x_lds[(r_in + i * RPP) * XS + lds_col]) = xreg[i];
+    for (int i = 0; i < kPasses; ++i) *reinterpret_cast<u32x4*>(x_dst + buf * kStageB + i * (kPassRows * SC * 2)) = x[i];
+    if (halo) *reinterpret_cast<u32x4*>(x_dst + buf * kStageB + kPasses * (kPassRows * SC * 2)) = x[kPasses];
   };
+  const int n_stages = NH * n_tiles * SPT;
 
-  f32x16 acc[NT];
+  f32x16 acc[kMaxGroup];
 #pragma unroll
-  for (int t = 0; t < NT; ++t)
+  for (int t = 0; t < kMaxGroup; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
 
-  load_tokens(0, 0);
-  for (int chunk = 0; chunk < NCH; ++chunk) {
-    __syncthreads();                 // previous chunk's panels and token tile are no longer read
-    stage_panels(chunk);
+  // operands of one stage: steps of 16 channels of one tap, read kAhead steps before their products
+  constexpr int NS = SC / 16, kAhead = 3, kOps = 4;
+  static_assert(NS == kOps, "a step's operands have the place of its channels");
+  const unsigned char* const a_base = w_lds + ql * (HC * 2);                  // channel ql
+  const int a_swz = ((ql & 15) ^ hb) << 4;
+  bf16x8 a_op[kOps], b_op[kOps];
+  struct TapRow { const unsigned char* row; int swz; };
+  auto multiply = [&](f32x16& sum, int sub) __attribute__((always_inline)) {
+    auto tap_row = [&](int tap) __attribute__((always_inline)) {
+      int row = 32 * wv + ql + tap * dil;
+      asm volatile("" : "+v"(row));      // worked out here: kept for all taps these addresses are many registers
+      return TapRow{x_lds + sub * kStageB + row * (SC * 2), (((row >> 1) & 7) ^ hb) << 4};
+    };
+    auto read_step = [&](const TapRow& at, int tap, int mc) __attribute__((always_inline)) {
+      a_op[mc] = *reinterpret_cast<const bf16x8*>(a_base + tap * kTapB + (a_swz ^ (SC * 2 * sub + 32 * mc)));
+      b_op[mc] = *reinterpret_cast<const bf16x8*>(at.row + (at.swz ^ (32 * mc)));
+    };
+    TapRow at = tap_row(0);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      if (t < n_tiles) {             // uniform
-        if (t > 0) __syncthreads();  // previous tile's rows are no longer read
-        store_tokens();
-        __syncthreads();
-        // prefetch the next token tile (next tile of this chunk, or first tile of the next chunk)
-        if (t + 1 < n_tiles) load_tokens(chunk, t + 1);
-        else if (chunk + 1 < NCH) load_tokens(chunk + 1, 0);
-        for (int tap = 0; tap < ks; ++tap) {
-          const bf16_t* a_row = w_lds + (size_t)(tap * CP + ql) * XS + 8 * hb;                // channel ql
-          const bf16_t* b_row = x_lds + (size_t)(32 * wv + ql + tap * dil) * XS + 8 * hb;     // token, shifted
+    for (int mc = 0; mc < kAhead; ++mc) read_step(at, 0, mc);
+    auto one_tap = [&](int tap) __attribute__((always_inline)) {
+      const int next = tap + 1 < ks ? tap + 1 : tap;
 #pragma unroll
-          for (int mc = 0; mc < CH / 16; ++mc) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(a_row + 16 * mc);
-            const bf16x8 b = *reinterpret_cast<const bf16x8*>(b_row + 16 * mc);
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[t], 0, 0, 0);
-          }
-          // Issue order inside one tap: operand reads run three MFMAs ahead of their use, so that LDS latency is
-          // covered by matrix work instead of being waited for before every MFMA.
-          __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+      for (int mc = 0; mc < NS; ++mc) {
+        if (mc + kAhead == NS) at = tap_row(next);
+        const int to = (mc + kAhead) % NS;
+        if (mc + kAhead < NS) read_step(at, tap, to);
+        else if (KS == 0 || tap + 1 < KS) read_step(at, next, to);
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_op[mc], b_op[mc], sum, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    if constexpr (KS > 0) {
 #pragma unroll
-          for (int i = 0; i < CH / 16 - 3; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          }
-          __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
-        }
+      for (int tap = 0; tap < KS; ++tap) one_tap(tap);
+    } else {
+#pragma unroll 1
+      for (int tap = 0; tap < ks; ++tap) one_tap(tap);
+    }
+  };
+
+  // Stage s: its rows are in buffer s & 1; those of s + 1 go to the other one, s + 2 and s + 3 are on their way.
+  static_assert(SPT == 2, "a stage's buffer and registers are those of its part of the tile");
+  request(xreg[0]);
+  request(xreg[1]);
+  deposit(xreg[0], 0);
+  if (n_stages > 2) request(xreg[0]);
+  store_weights();
+  __syncthreads();
+  int at = 0;
+  auto stage = [&](f32x16& sum, auto sub) __attribute__((always_inline)) {
+    constexpr int S = decltype(sub)::value;
+    if (at + 1 < n_stages) deposit(xreg[S ^ 1], S ^ 1);
+    if (at + 3 < n_stages) request(xreg[S ^ 1]);
+    __builtin_amdgcn_sched_barrier(0);      // the requests leave before the products
+    multiply(sum, S);
+    __syncthreads();
+    ++at;
+  };
+#pragma unroll
+  for (int half = 0; half < NH; ++half) {
+    if (half > 0) {          // the other channels' weights; everyone is done with the ones before
+      load_weights(half);
+      store_weights();
+      __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < kMaxGroup; ++t) {
+      if (t < n_tiles) {     // uniform
+        stage(acc[t], std::integral_constant<int, 0>{});
+        stage(acc[t], std::integral_constant<int, 1>{});
       }
     }
   }
@@ -181,16 +245,11 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   float bs[16], wo[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int c = 8 * (r / 4) + 4 * hb + (r % 4);
-    const int cc = c < C ? c : C - 1;            // unconditional loads (no branch per element), then select
-    const float b_ld = bias[h * C + cc];
-    const float w_ld = to_f32(w_out[h * C + cc]);
-    bs[r] = c < C ? b_ld : 0.f;
-    wo[r] = c < C ? w_ld : 0.f;
+    bs[r] = out_lds[8 * (r / 4) + 4 * hb + (r % 4)];
+    wo[r] = out_lds[CP + 8 * (r / 4) + 4 * hb + (r % 4)];
   }
-  const float bo = b_out[h];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
+  for (int t = 0; t < kMaxGroup; ++t) {
     if (t < n_tiles) {
       float z = 0.f;
 #pragma unroll
@@ -205,11 +264,7 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   }
 }
 
-// Token tile sized by the actual reach: 79.4 KB for kernel 5 / dilation 1, so that two workgroups share a CU.
-size_t lds_bytes(int ks, int dil) {
-  const int rho = (ks - 1) / 2 * dil;
-  return ((size_t)(TM + 2 * rho) + (size_t)ks * CP) * XS * sizeof(uint16_t);
-}
+size_t lds_bytes(int ks, int waves) { return (size_t)ks * kTapB + (size_t)2 * stage_bytes(waves) + 2 * CP * sizeof(float); }
 
 template <int D>
 hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v, int64_t st, int64_t sh,
@@ -226,17 +281,27 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
     panels = workspace;
   }
   if (score_reg_supported(cfg, cnn)) return launch_score_reg(cfg, cnn, k, v, st, sh, sv, logits, panels, stream);
-  const size_t lds = lds_bytes(ks, cnn.dilation[0]);
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_mfma_kernel<D>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  const int64_t groups_upper = (sv.total_tokens + NT * TM - 1) / (NT * TM) + sv.n_seqs;
-  hipLaunchKernelGGL(score_mfma_kernel<D>, dim3((unsigned)groups_upper, (unsigned)cfg.Hkv), dim3(kThreads), lds, stream,
-                     static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), st, sh,
-                     static_cast<const bf16_t*>(panels), cnn.bias[0], static_cast<const bf16_t*>(cnn.w_out),
-                     cnn.b_out, cnn.c_out[0], ks, cnn.dilation[0], sv.cu_seqlens, sv.n_seqs, (int)groups_upper,
-                     sv.total_tokens, logits);
-  return hipGetLastError();
+  auto launch = [&](auto taps, auto waves) {
+    constexpr int KS = decltype(taps)::value, NW = decltype(waves)::value, TM = 32 * NW;
+    // a workgroup's start (sequence, weights, first rows) costs about a tile: 4.3 us and 3.7 us per tile of D = 128, k = 5
+    const int group = pick_group_tiles(sv, cfg.Hkv, TM, kMaxGroup, 1, NW == 4 ? 512 : 256);
+    const int64_t span = (int64_t)group * TM, groups_upper = (sv.total_tokens + span - 1) / span + sv.n_seqs;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_mfma_kernel<D, KS, NW>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_bytes(ks, NW));
+    if (e != hipSuccess) return;
+    hipLaunchKernelGGL((score_mfma_kernel<D, KS, NW>), dim3((unsigned)(groups_upper * cfg.Hkv)), dim3(64 * NW), lds_bytes(ks, NW), stream,
+                       static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), st, sh,
+                       static_cast<const bf16_t*>(panels), cnn.bias[0], static_cast<const bf16_t*>(cnn.w_out),
+                       cnn.b_out, cnn.c_out[0], ks, cnn.dilation[0], sv.cu_seqlens, sv.n_seqs, cfg.Hkv, sv.total_tokens, logits, group);
+    e = hipGetLastError();
+  };
+  constexpr std::integral_constant<int, 4> four{};
+  constexpr std::integral_constant<int, 8> eight{};
+  if (ks == 3) launch(std::integral_constant<int, 3>{}, four);
+  else if (ks == 5) launch(std::integral_constant<int, 5>{}, four);
+  else if (ks == 7) launch(std::integral_constant<int, 7>{}, eight);
+  else launch(std::integral_constant<int, 0>{}, eight);
+  return e;
 }
 
 }  // namespace
@@ -245,8 +310,8 @@ bool score_mfma_supported(const ltea_cfg& cfg, const ltea_cnn& cnn) {
   if (cfg.dtype != LTEA_BF16 || cnn.n_layers != 1 || cnn.c_out[0] > CP) return false;
   if (cfg.D != 64 && cfg.D != 128) return false;
   if ((cnn.kernel[0] - 1) / 2 * cnn.dilation[0] > kMaxRho) return false;
-  static_assert(NT * TM + 2 * kMaxRho + 16 <= kScoreRowsPerDescriptor, "rows one workgroup addresses");
-  return lds_bytes(cnn.kernel[0], cnn.dilation[0]) <= 150 * 1024;
+  static_assert(kMaxGroup * 256 + 2 * kMaxRho + 16 <= kScoreRowsPerDescriptor, "rows one workgroup addresses");
+  return cnn.kernel[0] <= kMaxTaps;
 }
 
 hipError_t launch_score_mfma_panels(const ltea_cfg& cfg, const ltea_cnn& cnn, void* panels, hipStream_t stream) {
