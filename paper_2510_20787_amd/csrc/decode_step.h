@@ -588,27 +588,30 @@ constexpr int kDeepLds = kDeepOffB + kDeepTerms * kDeepSeqs * 5 * kDeepAS * 2;
 static_assert(kDeepTerms * kDeepSeqs * 3 * kDeepAS * 2 <= kDeepOffB, "layer 2's output fits region A");
 
 template <int CH> struct DeepWeights { u32x4 w[CH][3]; };   // [32-channel chunk][tap], as B operands
+template <int CH> struct DeepRaw { u32x4 w[CH][3]; };       // a lane's 24 consecutive elements of its channel's row per chunk
 
 template <int CH>
-__device__ __forceinline__ void load_deep_weights(const CnnDev& cnn, int l, int cin, int h, int ct, int col, int kg,
-                                                  DeepWeights<CH>& W) {
+__device__ __forceinline__ void load_deep_weights(const CnnDev& cnn, int l, int cin, int h, int ct, int col, int kg, DeepRaw<CH>& R) {
   const uint16_t* base = static_cast<const uint16_t*>(cnn.w[l]) + ((int64_t)(h * cnn.c_out[l] + 16 * ct + col) * cin + 8 * kg) * 3;
 #pragma unroll
   for (int ch = 0; ch < CH; ++ch) {
     const u32x4* p = reinterpret_cast<const u32x4*>(base + (32 * ch < cin ? 32 * ch : 0) * 3);
-    uint32_t raw[12];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const u32x4 x = p[i];
-      raw[4 * i] = x[0]; raw[4 * i + 1] = x[1]; raw[4 * i + 2] = x[2]; raw[4 * i + 3] = x[3];
-    }
+    for (int i = 0; i < 3; ++i) R.w[ch][i] = p[i];
+  }
+}
+template <int CH>
+__device__ __forceinline__ void sort_deep_weights(const DeepRaw<CH>& R, DeepWeights<CH>& W) {
+#pragma unroll
+  for (int ch = 0; ch < CH; ++ch) {
+    auto raw = [&](int i) { return R.w[ch][i / 4][i % 4]; };
 #pragma unroll
     for (int tap = 0; tap < 3; ++tap)
 #pragma unroll
       for (int e2 = 0; e2 < 4; ++e2) {
         const int f0 = 2 * e2 * 3 + tap, f1 = f0 + 3;
-        const uint32_t lo16 = (f0 & 1) ? (raw[f0 / 2] >> 16) : (raw[f0 / 2] & 0xFFFFu);
-        const uint32_t hi16 = (f1 & 1) ? (raw[f1 / 2] & 0xFFFF0000u) : (raw[f1 / 2] << 16);
+        const uint32_t lo16 = (f0 & 1) ? (raw(f0 / 2) >> 16) : (raw(f0 / 2) & 0xFFFFu);
+        const uint32_t hi16 = (f1 & 1) ? (raw(f1 / 2) & 0xFFFF0000u) : (raw(f1 / 2) << 16);
         W.w[ch][tap][e2] = lo16 | hi16;
       }
   }
@@ -618,83 +621,128 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
                                                       const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new,
                                                       int h, int b0, unsigned char* lds, int* t_lds, float* __restrict__ ws_logit) {
   constexpr int D = 64;
+  static_assert(kDeepSeqs == 8 && kRoleThreads == 256, "rows are position * 8 + sequence");
   const int tid = threadIdx.x, lane = tid & (kWave - 1), col = lane & 15, kg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int L = cnn.n_layers, dil = P.unit, rho = P.rho, window = P.window;
-  const int n_in = 2 * L + 1;
-  DeepWeights<4> w0;
-  DeepWeights<2> w1;
-  const int nc0 = cnn.c_out[0] / 16, nc1 = cnn.c_out[1] / 16;      // 1, 2 or 4 column tiles
-  load_deep_weights<4>(cnn, 0, 2 * D, h, wv % nc0, col, kg, w0);
-  load_deep_weights<2>(cnn, 1, cnn.c_out[0], h, wv % nc1, col, kg, w1);
-  if (tid < kDeepSeqs) {
-    const int b = b0 + tid;
-    t_lds[tid] = b < P.B ? C.n_seen[b] : -1;                       // -1: no such sequence, no position of it is valid
+  const int n_in = 2 * L + 1;                                      // input positions, rho = L * dil to either side
+  const int nc0 = cnn.c_out[0] / 16, nc1 = cnn.c_out[1] / 16, nc_last = cnn.c_out[L - 1] / 16;      // 1, 2 or 4 column tiles
+  // ---- requests, in the order in which they are needed: token indices, first layer's weights, then (they wait for the token
+  // indices) rows and table entries ----
+  // Row i * 8 + seq is position t - rho + (i - L) * dil of sequence b0 + seq.  A thread brings one piece (8 of keys, 8 of values)
+  // of every second position of one sequence; t = -1: no such sequence, no position of it is valid.
+  const int seq = (tid >> 4) & 7, pc = tid & 15, i_first = tid >> 7;
+  const bool there = b0 + seq < P.B;
+  int t = C.n_seen[there ? b0 + seq : P.B - 1];
+  // rotation: pieces of keys, row (tid >> 3) + 32 * v
+  const bool rotates = P.rope.cos != nullptr;
+  const int rot_seq = (tid >> 3) & 7, rot_e0 = (tid & 7) * 8, rot_i = tid >> 6;
+  int rot_t = -1;
+  if (rotates) {
+    rot_t = C.n_seen[b0 + rot_seq < P.B ? b0 + rot_seq : P.B - 1];
+    if (b0 + rot_seq >= P.B) rot_t = -1;
   }
-  __syncthreads();
-  // ---- inputs: row (sequence, i) is position t - rho + (i - L) * dil; 8 key pieces, 8 value pieces ----
-  bf16_t* xs = reinterpret_cast<bf16_t*>(lds);
-  constexpr int kPerThread = (kDeepSeqs * 7 * 16 + kRoleThreads - 1) / kRoleThreads;    // requested together
+  DeepRaw<4> raw0;
+  load_deep_weights<4>(cnn, 0, 2 * D, h, wv % nc0, col, kg, raw0);
+  if (!there) t = -1;
+  if (pc == 0 && i_first == 0) t_lds[seq] = t;
+  constexpr int kPerThread = 4, kRotPerThread = 2;
   u32x4 piece[kPerThread];
+  const int64_t head = (int64_t)(b0 + seq) * P.Hkv + h;
+  const bool is_v = pc >= 8;
+  const int slot_t = t >= 0 ? (int)((unsigned)t % (unsigned)window) : 0;
+  auto position = [&](int i) { return t - (2 * L - i) * dil; };
 #pragma unroll
   for (int u = 0; u < kPerThread; ++u) {
-    const int idx = tid + u * kRoleThreads, pc = idx & 15, r = idx >> 4, seq = r / n_in, i = r - seq * n_in;
-    const int t = seq < kDeepSeqs ? t_lds[seq] : -1, p = t - rho + (i - L) * dil;
-    piece[u] = u32x4{0u, 0u, 0u, 0u};
-    if (t >= 0 && p >= 0) {
-      const int64_t head = (int64_t)(b0 + seq) * P.Hkv + h;
-      const bool is_v = pc >= 8;
-      const bf16_t* row = p == t ? (is_v ? v_new : k_new) + head * D
-                                 : static_cast<const bf16_t*>(is_v ? C.v_win : C.k_win) + (head * window + p % window) * D;
-      const bool rotated = !is_v && P.rope.cos != nullptr, ready = p == t && P.kf_new != nullptr;
-      if (rotated && ready) row = static_cast<const bf16_t*>(P.kf_new) + head * D;
-      piece[u] = reinterpret_cast<const u32x4*>(row)[pc & 7];
-      if (rotated && !ready && p < P.rope.n_pos) piece[u] = unrotate_piece<bf16_t>(P.rope, p, pc * 8, piece[u], row);
+    const int i = i_first + 2 * u, back = (2 * L - i) * dil;       // window > 2 rho
+    const bf16_t* row;
+    if (i == 2 * L) row = (is_v ? v_new : rotates && P.kf_new != nullptr ? static_cast<const bf16_t*>(P.kf_new) : k_new) + head * D;
+    else row = static_cast<const bf16_t*>(is_v ? C.v_win : C.k_win) + (head * window + (slot_t - back < 0 ? slot_t - back + window : slot_t - back)) * D;
+    if (!(i < n_in && position(i) >= 0 && t >= 0)) row = v_new;    // somewhere readable: not used
+    piece[u] = reinterpret_cast<const u32x4*>(row)[pc & 7];
+  }
+  RopeEntries<bf16_t> entries[kRotPerThread];
+  bool rot[kRotPerThread];
+  if (rotates) {
+#pragma unroll
+    for (int v = 0; v < kRotPerThread; ++v) {
+      const int i = rot_i + 4 * v, p = rot_t - (2 * L - i) * dil;
+      rot[v] = i < n_in && rot_t >= 0 && p >= 0 && p < P.rope.n_pos && rot_e0 < P.rope.rot_dim && (i < 2 * L || P.kf_new == nullptr);
+      entries[v] = load_rope_entries<bf16_t>(P.rope, rot[v] ? p : 0, rot[v] ? rot_e0 : 0);
     }
   }
+  // what the layers' ends need: all of it on its way now
+  const float bias0 = cnn.bias[0][h * cnn.c_out[0] + 16 * (wv % nc0) + col], bias1 = cnn.bias[1][h * cnn.c_out[1] + 16 * (wv % nc1) + col];
+  const float bias2 = L == 3 ? cnn.bias[2][h * cnn.c_out[2] + 16 * (wv % nc_last) + col] : 0.f;
+  const int cl = cnn.c_out[L - 1];
+  float wo[kDeepMaxCh / 16];
+#pragma unroll
+  for (int j = 0; j < kDeepMaxCh / 16; ++j) wo[j] = to_f32(static_cast<const bf16_t*>(cnn.w_out)[h * cl + (16 * j < cl ? 16 * j : 0) + col]);
+  const float b_out = cnn.b_out[h];
+  DeepWeights<4> w0;
+  sort_deep_weights<4>(raw0, w0);
+  bf16_t* xs = reinterpret_cast<bf16_t*>(lds);
 #pragma unroll
   for (int u = 0; u < kPerThread; ++u) {
-    const int idx = tid + u * kRoleThreads;
-    if (idx < kDeepSeqs * n_in * 16) *reinterpret_cast<u32x4*>(xs + (idx >> 4) * kDeepXS + (idx & 15) * 8) = piece[u];
+    const int i = i_first + 2 * u;
+    if (i < n_in) *reinterpret_cast<u32x4*>(xs + (8 * i + seq) * kDeepXS + pc * 8) = position(i) >= 0 && t >= 0 ? piece[u] : u32x4{0u, 0u, 0u, 0u};
   }
+  __syncthreads();
+  if (rotates) {
+    u32x4 back[kRotPerThread];
+#pragma unroll
+    for (int v = 0; v < kRotPerThread; ++v) {
+      const bf16_t* row = xs + (8 * (rot_i + 4 * v) + rot_seq) * kDeepXS;
+      if (rot[v])
+        back[v] = rotate_back<bf16_t>(P.rope, rot_e0, entries[v], *reinterpret_cast<const u32x4*>(row + rot_e0),
+                                      *reinterpret_cast<const u32x4*>(row + rope_partner(P.rope, rot_e0)));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < kRotPerThread; ++v)
+      if (rot[v]) *reinterpret_cast<u32x4*>(xs + (8 * (rot_i + 4 * v) + rot_seq) * kDeepXS + rot_e0) = back[v];
+    __syncthreads();
+  }
+  DeepRaw<2> raw1;
+  load_deep_weights<2>(cnn, 1, cnn.c_out[0], h, wv % nc1, col, kg, raw1);
 
-  // one layer: rows of n_in positions per sequence in `src` (the terms term_off elements apart; 0: one term) to
-  // n_in - 2 positions per sequence in `dst` (three terms) or, from the last layer, fp32 rows of kDeepMaxCh
-  auto layer = [&](int l, const auto& W, int chunks, int rows_in, const bf16_t* src, int stride, int term_off, unsigned char* dst,
-                   bool last) {
+  // one layer: `pos_in` positions in `src` (the terms term_off elements apart; 0: one term) to pos_in - 2 positions in `dst`
+  // (three terms) or, from the last layer, fp32 rows of kDeepMaxCh
+  auto layer = [&](int l, const auto& W, float bias, int chunks, int pos_in, const bf16_t* src, int stride, int term_off, unsigned char* dst,
+                   bool last) __attribute__((always_inline)) {
     constexpr int kCh = sizeof(W.w) / sizeof(W.w[0]);
-    const int nc = cnn.c_out[l] / 16, ct = wv % nc, rows_out = rows_in - 2, n_rows = kDeepSeqs * rows_out;
-    const float bias = cnn.bias[l][h * cnn.c_out[l] + 16 * ct + col];
-    const int half = (rows_out - 1) / 2;
+    const int nc = cnn.c_out[l] / 16, ct = wv % nc, pos_out = pos_in - 2, n_rows = 8 * pos_out, half = (pos_out - 1) / 2;
+    const int4 t4 = *reinterpret_cast<const int4*>(t_lds + 4 * (kg & 1));
+    const int ts[4] = {t4.x, t4.y, t4.z, t4.w};                    // of the sequences of this lane's four rows
     for (int rt = wv / nc; 16 * rt < n_rows; rt += kRoleWaves / nc) {
       const int r = 16 * rt + col < n_rows ? 16 * rt + col : n_rows - 1;
-      const int seq = r / rows_out;
-      const bf16_t* a = src + (seq * rows_in + (r - seq * rows_out)) * stride + 8 * kg;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      const bf16_t* a = src + r * stride + 8 * kg;
+      f32x4 acc[kDeepTerms] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
       for (int ch = 0; ch < kCh; ++ch) {
         if (ch >= chunks) break;
 #pragma unroll
         for (int tap = 0; tap < 3; ++tap) {
-          const bf16_t* ap = a + tap * stride + 32 * ch;
+          const bf16_t* ap = a + 8 * tap * stride + 32 * ch;
           const bf16x8 w = __builtin_bit_cast(bf16x8, W.w[ch][tap]);
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap), w, acc, 0, 0, 0);
+          acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap), w, acc[0], 0, 0, 0);
           if (term_off != 0) {
 #pragma unroll
             for (int u = 1; u < kDeepTerms; ++u)
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap + u * term_off), w, acc, 0, 0, 0);
+              acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(ap + u * term_off), w, acc[u], 0, 0, 0);
           }
         }
       }
+      const int pos = 2 * rt + (kg >> 1);
+      if (pos >= pos_out) continue;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int ro = 16 * rt + 4 * kg + e;
-        if (ro >= n_rows) continue;
-        const int so = ro / rows_out, t = t_lds[so];
-        const int p = t - rho + (ro - so * rows_out - half) * dil;
-        const float y = acc[e] + bias;
+        const int ro = 16 * rt + 4 * kg + e, so = 4 * (kg & 1) + e;
+        float y = acc[0][e];
+        if (term_off != 0) y += acc[1][e] + acc[2][e];
+        y += bias;
         // activations at positions before the sequence start are zero padding, not Swish(bias)
-        const float val = p >= 0 ? y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * y)) : 0.f;
+        const float val = ts[e] - rho + (pos - half) * dil >= 0 ? y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * y)) : 0.f;
         if (last) {
           reinterpret_cast<float*>(dst)[so * kDeepMaxCh + 16 * ct + col] = val;
         } else {
@@ -711,25 +759,30 @@ __device__ __forceinline__ void score_new_tokens_deep(const CnnDev& cnn, const S
   };
   const bf16_t* region_a = reinterpret_cast<const bf16_t*>(lds);
   const bf16_t* region_b = reinterpret_cast<const bf16_t*>(lds + kDeepOffB);
+  layer(0, w0, bias0, 4, n_in, region_a, kDeepXS, 0, lds + kDeepOffB, false);
+  DeepWeights<2> w1;
+  sort_deep_weights<2>(raw1, w1);
+  DeepRaw<2> raw2;
+  if (L == 3) load_deep_weights<2>(cnn, 2, cnn.c_out[1], h, wv % nc_last, col, kg, raw2);
   __syncthreads();
-  layer(0, w0, 4, n_in, region_a, kDeepXS, 0, lds + kDeepOffB, false);
-  DeepWeights<2> w2;
-  if (L == 3) load_deep_weights<2>(cnn, 2, cnn.c_out[1], h, wv % (cnn.c_out[2] / 16), col, kg, w2);
-  __syncthreads();
-  layer(1, w1, cnn.c_out[0] / 32, n_in - 2, region_b, kDeepAS, kDeepSeqs * (n_in - 2) * kDeepAS, lds, L == 2);
+  layer(1, w1, bias1, cnn.c_out[0] / 32, n_in - 2, region_b, kDeepAS, kDeepSeqs * (n_in - 2) * kDeepAS, lds, L == 2);
   __syncthreads();
   if (L == 3) {
-    layer(2, w2, cnn.c_out[1] / 32, n_in - 4, region_a, kDeepAS, kDeepSeqs * (n_in - 4) * kDeepAS, lds + kDeepOffB, true);
+    DeepWeights<2> w2;
+    sort_deep_weights<2>(raw2, w2);
+    layer(2, w2, bias2, cnn.c_out[1] / 32, n_in - 4, region_a, kDeepAS, kDeepSeqs * (n_in - 4) * kDeepAS, lds + kDeepOffB, true);
     __syncthreads();
   }
   const float* act = reinterpret_cast<const float*>(L == 2 ? lds : lds + kDeepOffB);
   if (tid < 16 * kDeepSeqs) {
-    const int seq = tid / 16, b = b0 + seq, cl = cnn.c_out[L - 1], t = t_lds[seq];
+    const int s = tid / 16, b = b0 + s, ts = t_lds[s];
     float z = 0.f;
-    for (int c = tid % 16; c < cl; c += 16) z = fmaf(act[seq * kDeepMaxCh + c], to_f32(static_cast<const bf16_t*>(cnn.w_out)[h * cl + c]), z);
+#pragma unroll
+    for (int j = 0; j < kDeepMaxCh / 16; ++j)
+      if (16 * j < cl) z = fmaf(act[s * kDeepMaxCh + 16 * j + col], wo[j], z);
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, kWave);
-    if (tid % 16 == 0 && b < P.B && t - rho >= 0) put_logit(C, P, (int64_t)b * P.Hkv + h, t, z + cnn.b_out[h], ws_logit);
+    if (col == 0 && b < P.B && ts - rho >= 0) put_logit(C, P, (int64_t)b * P.Hkv + h, ts, z + b_out, ws_logit);
   }
 }
 
@@ -908,7 +961,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   __shared__ __align__(16) float scratch[kMerge > kRole ? kMerge : kRole];
   __shared__ unsigned long long red64[W];
   __shared__ int slot_lds;
-  __shared__ int t_lds[kDeepSeqs];
+  __shared__ __align__(16) int t_lds[kDeepSeqs];
 
   const int Hkv = P.Hkv, window = P.window, budget = P.budget, nsplit = P.nsplit;
   if constexpr (SK != 0) {

@@ -47,57 +47,78 @@ template <> struct Elems<bf16_t> {
   }
 };
 
-// The 16-byte piece starting at element e0 of the key row `row` (the row as cached, i.e. rotated at position p),
-// rotated back and rounded to the storage type.  `piece` is that piece as already loaded.  Elements at or beyond
-// rot_dim pass through.  The caller has checked p < rope.n_pos.
-// Inverse rotation of the pair (a, b): (a cos + b sin, -a sin + b cos).
+// The table entries of the piece at element e0 (below rot_dim) of a key at position p (below n_pos): one per element, or, in
+// the interleaved order, one per pair in the first half.  16-byte loads where the tables are only known to be 4-byte aligned.
+template <typename T> struct RopeEntries { float c[Elems<T>::N], s[Elems<T>::N]; };
 template <typename T>
-__device__ __forceinline__ u32x4 unrotate_piece(const RopeDev& rope, int p, int e0, const u32x4& piece, const T* row) {
+__device__ __forceinline__ RopeEntries<T> load_rope_entries(const RopeDev& rope, int p, int e0) {
   constexpr int EPP = Elems<T>::N;
-  if (e0 >= rope.rot_dim) return piece;
   const int half = rope.rot_dim / 2;
-  const float* ct = rope.cos + (int64_t)p * half;
-  const float* st = rope.sin + (int64_t)p * half;
-  // table entries in 16-byte loads (the tables are only known to be 4-byte aligned)
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
   typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+  RopeEntries<T> E;
+  if (rope.interleaved) {
+    const float *ct = rope.cos + (int64_t)p * half + e0 / 2, *st = rope.sin + (int64_t)p * half + e0 / 2;
+#pragma unroll
+    for (int j = 0; j < EPP / 2; j += 2) {
+      const f32x2_any c2 = *reinterpret_cast<const f32x2_any*>(ct + j), s2 = *reinterpret_cast<const f32x2_any*>(st + j);
+      E.c[j] = c2[0]; E.c[j + 1] = c2[1]; E.s[j] = s2[0]; E.s[j + 1] = s2[1];
+    }
+#pragma unroll
+    for (int j = EPP / 2; j < EPP; ++j) E.c[j] = E.s[j] = 0.f;
+  } else {
+    const int i0 = e0 >= half ? e0 - half : e0;
+    const float *ct = rope.cos + (int64_t)p * half + i0, *st = rope.sin + (int64_t)p * half + i0;
+#pragma unroll
+    for (int j = 0; j < EPP; j += 4) {
+      const f32x4_any c4 = *reinterpret_cast<const f32x4_any*>(ct + j), s4 = *reinterpret_cast<const f32x4_any*>(st + j);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { E.c[j + i] = c4[i]; E.s[j + i] = s4[i]; }
+    }
+  }
+  return E;
+}
+
+// First element of the piece that holds the other members of this piece's pairs (the piece itself in the interleaved order).
+__device__ __forceinline__ int rope_partner(const RopeDev& rope, int e0) {
+  const int half = rope.rot_dim / 2;
+  return rope.interleaved ? e0 : e0 >= half ? e0 - half : e0 + half;
+}
+
+// The piece at element e0, rotated back and rounded to the storage type.  Inverse rotation of the pair (a, b):
+// (a cos + b sin, -a sin + b cos).
+template <typename T>
+__device__ __forceinline__ u32x4 rotate_back(const RopeDev& rope, int e0, const RopeEntries<T>& E, const u32x4& piece,
+                                             const u32x4& partner) {
+  constexpr int EPP = Elems<T>::N;
   float x[EPP], y[EPP];
   Elems<T>::unpack(piece, x);
   if (rope.interleaved) {
-    float cs[EPP / 2], sn[EPP / 2];
-#pragma unroll
-    for (int j = 0; j < EPP / 2; j += 2) {
-      const f32x2_any c2 = *reinterpret_cast<const f32x2_any*>(ct + e0 / 2 + j);
-      const f32x2_any s2 = *reinterpret_cast<const f32x2_any*>(st + e0 / 2 + j);
-      cs[j] = c2[0]; cs[j + 1] = c2[1]; sn[j] = s2[0]; sn[j + 1] = s2[1];
-    }
 #pragma unroll
     for (int j = 0; j < EPP; j += 2) {
-      const float c = cs[j / 2], s = sn[j / 2];
+      const float c = E.c[j / 2], s = E.s[j / 2];
       y[j] = fmaf(x[j + 1], s, x[j] * c);
       y[j + 1] = fmaf(x[j + 1], c, -(x[j] * s));
     }
   } else {
-    const bool is_b = e0 >= half;                       // this piece holds the second members of its pairs
-    const int partner = is_b ? e0 - half : e0 + half;
+    const bool is_b = e0 >= rope.rot_dim / 2;           // this piece holds the second members of its pairs
     float o[EPP];
-    Elems<T>::unpack(*reinterpret_cast<const u32x4*>(row + partner), o);
-    const int i0 = is_b ? e0 - half : e0;
-    float cs[EPP], sn[EPP];
+    Elems<T>::unpack(partner, o);
 #pragma unroll
-    for (int j = 0; j < EPP; j += 4) {
-      const f32x4_any c4 = *reinterpret_cast<const f32x4_any*>(ct + i0 + j);
-      const f32x4_any s4 = *reinterpret_cast<const f32x4_any*>(st + i0 + j);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { cs[j + i] = c4[i]; sn[j + i] = s4[i]; }
-    }
-#pragma unroll
-    for (int j = 0; j < EPP; ++j) {
-      const float c = cs[j], s = sn[j];
-      y[j] = is_b ? fmaf(x[j], c, -(o[j] * s)) : fmaf(o[j], s, x[j] * c);
-    }
+    for (int j = 0; j < EPP; ++j) y[j] = is_b ? fmaf(x[j], E.c[j], -(o[j] * E.s[j])) : fmaf(o[j], E.s[j], x[j] * E.c[j]);
   }
   return Elems<T>::pack(y);
+}
+
+// The 16-byte piece starting at element e0 of the key row `row` (the row as cached, i.e. rotated at position p),
+// rotated back and rounded to the storage type.  `piece` is that piece as already loaded.  Elements at or beyond
+// rot_dim pass through.  The caller has checked p < rope.n_pos.
+template <typename T>
+__device__ __forceinline__ u32x4 unrotate_piece(const RopeDev& rope, int p, int e0, const u32x4& piece, const T* row) {
+  if (e0 >= rope.rot_dim) return piece;
+  const RopeEntries<T> E = load_rope_entries<T>(rope, p, e0);
+  const u32x4 other = rope.interleaved ? piece : *reinterpret_cast<const u32x4*>(row + rope_partner(rope, e0));
+  return rotate_back<T>(rope, e0, E, piece, other);
 }
 
 }  // namespace ltea
