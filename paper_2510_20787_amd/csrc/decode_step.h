@@ -569,15 +569,19 @@ __device__ __forceinline__ void score_new_tokens_mfma(const CnnDev& cnn, const S
 
 // ---- scoring role for stacks of two or three k = 3 layers with one dilation (bf16, D = 64) ---------------------------
 // Workgroup = (KV head, 8 sequences).  The logit of position t - rho depends on 2*L + 1 input positions, dilation apart,
-// 2*L - 1 outputs of the first layer, and so on down to one: those are the rows, (sequence, position) pairs, of small
-// GEMMs on v_mfma_f32_16x16x32_bf16, a wave per 16 output channels (and row tile where a layer has fewer channels).
-// Inputs are staged in LDS once (rotated back there for rotary models); activations stay in LDS as three bf16 terms whose sum
-// is the fp32 activation exactly, each multiplied in its own MFMA: the arithmetic of the per-head scoring.  A lane's weights of 8 input channels and 3 taps are 24
-// consecutive elements of its channel's row.
-// Bound: latency (n_seen -> rows and weights -> three short layers), hidden under the streaming.  The windows of the
-// whole batch packed in the main launch and scored by the prefill kernel in a launch of its own took 9-12 us of the step, and
-// scoring each (sequence, head) in the workgroup that streams it 14 us of a 20 us step: a dozen dependent trips to memory in
-// front of the stream, or, requested ahead, more registers than the stream leaves.
+// 2*L - 1 outputs of the first layer, and so on down to one: those are the rows, position * 8 + sequence, of small GEMMs on
+// v_mfma_f32_16x16x32_bf16, a wave per 16 output channels (and row tile where a layer has fewer channels); a tap is then 8 rows
+// further, and a lane's four accumulator rows are the same four sequences in every layer.
+// Inputs are staged in LDS once and rotated back there for rotary models; activations stay in LDS as three bf16 terms whose sum
+// is the fp32 activation exactly, each multiplied in its own MFMA: the arithmetic of the per-head scoring.  A lane's weights of 8
+// input channels and 3 taps are 24 consecutive elements of its channel's row.
+// Bound: latency.  The role is as long as the streaming beside it where sequences are few, so everything it reads is requested
+// before anything is waited for: one trip to the token indices, one to rows, table entries, weights, biases and output projection.
+// With each of those read where it is used (a row's sequence by a division, a piece's table entries behind the piece, biases at
+// a layer's end) the role ended 10.0 us after the launch's start for one sequence, 16.3 for 32 and 19 for 32 of a rotary model;
+// now 6.8, 8.3 and 9.6.  The step: one sequence 12.2 -> 10.7 us, 32 of a rotary model 22.7 -> 20.6.
+// Earlier forms: the windows of the whole batch packed in the main launch and scored by the prefill kernel in a launch of its own
+// took 9-12 us of the step, and scoring each (sequence, head) in the workgroup that streams it 14 us of a 20 us step.
 constexpr int kDeepSeqs = 8;
 constexpr float kMaxBf16 = 3.3895314e38f;                    // above: infinity in bf16
 constexpr int kDeepMaxCh = 64;                              // output channels per layer
