@@ -96,14 +96,15 @@ template <typename V> __device__ __forceinline__ V load_shared(const V* p) {
 }
 __device__ __forceinline__ void wait_for_own_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// One workgroup is done with n_seen / n_scored of the sequence: the last one advances them.
-__device__ __forceinline__ void arrive_sequence(const CacheDev& C, const StepParams& P, int b, int t) {
+// One workgroup is done with n_seen / n_scored of the sequence (all its waves have read them): the last one advances them.  In two
+// parts, the count and what follows from it, so that the count's trip passes beside other work.
+__device__ __forceinline__ unsigned count_arrival(const CacheDev& C, const StepParams& P, int b) {
   unsigned* word = reinterpret_cast<unsigned*>(C.ret_count + (int64_t)b * P.Hkv);
-  if (P.seq_arrivals > 1) {
-    const unsigned old = atomicAdd(word, 1u << 24);
-    if ((old >> 24) + 1 != (unsigned)P.seq_arrivals) return;
-    atomicSub(word, (unsigned)P.seq_arrivals << 24);
-  }
+  return P.seq_arrivals > 1 ? atomicAdd(word, 1u << 24) >> 24 : 0u;
+}
+__device__ __forceinline__ void advance_if_last(const CacheDev& C, const StepParams& P, int b, int t, unsigned before) {
+  if (before + 1 != (unsigned)P.seq_arrivals) return;
+  if (P.seq_arrivals > 1) atomicSub(reinterpret_cast<unsigned*>(C.ret_count + (int64_t)b * P.Hkv), (unsigned)P.seq_arrivals << 24);
   C.n_seen[b] = t + 1;
   if (!P.lazy) C.n_scored[b] = t + 1 > P.rho ? t + 1 - P.rho : 0;
 }
@@ -150,14 +151,57 @@ template <> struct Piece<bf16_t> {
   }
 };
 
+// A word that no workgroup changes before all that read it are done with it, through the scalar cache: such a load is not one of
+// the vector loads, which return in order, so waiting for it does not wait for rows requested earlier.  read_here: its memory
+// changes later, so the value is taken here, once.
+template <typename V> __device__ __forceinline__ V load_uniform(const V* p) {
+  static_assert(sizeof(V) == 4, "one word");
+  return __builtin_bit_cast(V, *reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uintptr_t>(p)));
+}
+template <typename V> __device__ __forceinline__ void read_here(V& x) { asm volatile("" : "+s"(x)); }
+
+// Smallest value over the wave, in all lanes, on the cross-lane paths of the vector ALU: six steps of a few instructions where
+// LDS permutes would cost about 100 clocks each.
+__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long x) {
+  auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+    constexpr int kCtrl = decltype(ctrl)::value, kRows = decltype(rows)::value;
+    const uint32_t lo = __builtin_amdgcn_update_dpp(~0u, (uint32_t)x, kCtrl, kRows, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(~0u, (uint32_t)(x >> 32), kCtrl, kRows, 0xf, false);
+    const unsigned long long o = (unsigned long long)hi << 32 | lo;
+    x = o < x ? o : x;
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});   // row_shr:2
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});   // row_shr:4
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});   // row_shr:8
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2 and 3
+  return (unsigned long long)__builtin_amdgcn_readlane((uint32_t)(x >> 32), kWave - 1) << 32 |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)x, kWave - 1);
+}
+
+// A thread's first entries of a head's compact segment, requested before it is known whether they are needed.
+constexpr int kHeldKeys = 2;
+struct HeldKeys { float score[kHeldKeys]; int pos[kHeldKeys]; };
+template <int NT>
+__device__ __forceinline__ HeldKeys load_held_keys(int budget, const float* __restrict__ ret_score, const int32_t* __restrict__ ret_pos) {
+  HeldKeys H;
+#pragma unroll
+  for (int i = 0; i < kHeldKeys; ++i) {
+    const int r = (int)threadIdx.x + NT * i, rc = r < budget ? r : budget - 1;
+    H.score[i] = ret_score[rc];
+    H.pos[i] = ret_pos[rc];
+  }
+  return H;
+}
+
 // Where does the token leaving the window go?  Returns the compact slot that receives it (== cnt for an
 // append), or -1 if it is dropped.  A pure function of the state before the step, evaluated identically by
-// every workgroup that needs it.  All threads of the block must call it; `red`/`slot_out` are LDS scratch.
+// every workgroup that needs it.  All threads of the block must call it, once per launch; `red` is LDS scratch.
 template <int NT>
-__device__ __forceinline__ int eviction_target(int t, int window, int budget, int sink, float tau, int cnt,
-                                               float z_e, const float* __restrict__ ret_score,
-                                               const int32_t* __restrict__ ret_pos, unsigned long long* red,
-                                               int* slot_out) {
+__device__ __forceinline__ int eviction_target(int t, int window, int budget, int sink, float tau, int cnt, float z_e,
+                                               const HeldKeys& held, const float* __restrict__ ret_score,
+                                               const int32_t* __restrict__ ret_pos, unsigned long long* red, int* slot_out) {
   constexpr int kWaves = NT / kWave;
   const int e_pos = t - window;
   if (e_pos < 0 || budget <= 0) return -1;
@@ -165,34 +209,32 @@ __device__ __forceinline__ int eviction_target(int t, int window, int budget, in
   if (cnt < budget) return cnt;
   // victim: lowest key, among equal keys the latest position
   const int tid = threadIdx.x;
-  auto composite = [](float key, int pos) {
-    return ((unsigned long long)order_key(key + 0.0f) << 32) | (0xFFFFFFFFu - (uint32_t)pos);
-  };
   unsigned long long best = ~0ull;
-  for (int r = tid; r < budget; r += NT) {
-    const unsigned long long c = composite(ret_score[r], ret_pos[r]);
+  auto look = [&](float key, int pos) {
+    const unsigned long long c = ((unsigned long long)order_key(key + 0.0f) << 32) | (0xFFFFFFFFu - (uint32_t)pos);
     best = c < best ? c : best;
-  }
+  };
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned long long o = __shfl_xor(best, off, kWave);
-    best = o < best ? o : best;
-  }
-  __syncthreads();
+  for (int i = 0; i < kHeldKeys; ++i)
+    if (tid + NT * i < budget) look(held.score[i], held.pos[i]);
+  for (int r = tid + NT * kHeldKeys; r < budget; r += NT) look(ret_score[r], ret_pos[r]);
+  best = wave_min_u64(best);
   if ((tid & (kWave - 1)) == 0) red[tid / kWave] = best;
   if (tid == 0) *slot_out = -1;
   __syncthreads();
   best = red[0];
 #pragma unroll
   for (int w = 1; w < kWaves; ++w) best = red[w] < best ? red[w] : best;
-  const uint32_t worst_u = (uint32_t)(best >> 32);
   const int worst_pos = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));
-  // positions are unique; a caller's duplicates stay deterministic
-  for (int r = tid; r < budget; r += NT)
+  // positions are unique; of a caller's duplicates the last slot
+#pragma unroll
+  for (int i = kHeldKeys - 1; i >= 0; --i)
+    if (tid + NT * i < budget && held.pos[i] == worst_pos) atomicMax(slot_out, tid + NT * i);
+  for (int r = tid + NT * kHeldKeys; r < budget; r += NT)
     if (ret_pos[r] == worst_pos) atomicMax(slot_out, r);
   __syncthreads();
   const int victim = *slot_out;
-  return order_key(select_key(z_e, e_pos, sink)) > worst_u ? victim : -1;
+  return order_key(select_key(z_e, e_pos, sink)) > (uint32_t)(best >> 32) ? victim : -1;
 }
 
 // The finalised logit of position t - rho: straight into the ring when the finishing is part of this launch (its slot is
@@ -838,7 +880,8 @@ template <typename T, int D>
 __device__ __forceinline__ MovingRows load_moving_rows(const CacheDev& C, const StepParams& P, const T* __restrict__ k_new,
                                                        const T* __restrict__ v_new, int64_t head, int t) {
   constexpr int pieces = D * (int)sizeof(T) / 16;
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));       // (its addresses are worked out here)
   MovingRows m = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
   if (tid < 2 * pieces) {
     const bool k = tid < pieces;
@@ -995,7 +1038,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       if (mine && P.status != nullptr && past_tables(P, t)) atomicOr(P.status, LTEA_ROPE_RANGE);
       if (P.fused) {
         __syncthreads();                        // every wave has read the counters
-        if (mine) arrive_sequence(C, P, b, t);
+        if (mine) advance_if_last(C, P, b, t, count_arrival(C, P, b));
       }
       return;
     }
@@ -1004,54 +1047,83 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const int split = work % nsplit;
   const int64_t head = work / nsplit;
   const int b = (int)(head / Hkv), h = (int)(head - (int64_t)b * Hkv);
-  int t = C.n_seen[b];
+  int t = load_uniform(C.n_seen + b);
+  uint32_t count_word = budget > 0 ? (uint32_t)load_uniform(C.ret_count + head) : 0;
+  int scored = P.lazy ? load_uniform(C.n_scored + b) : 0;
   const T* kw = static_cast<const T*>(C.k_win) + head * window * D;
   const T* vw = static_cast<const T*>(C.v_win) + head * window * D;
   const int G = P.Hq / Hkv;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
-  // Matrix stream of a step without scoring workgroups (lazy scoring, logits given): a wave's first block of 32 ring slots is
-  // requested before n_seen has come, whatever it holds; settle() takes out what is not there yet.  One trip to memory less:
-  // 756 lazy steps of 32 sequences of the paper's layer 15 182 -> 14 562 us.  Steps with scoring workgroups keep the order: on
-  // groups of four they took 11.2 -> 11.5 us with it (one sequence, one layer of k = 5), 12.2 -> 12.2 (one, the paper's stack),
-  // 14.5 -> 14.9 (8, the stack), 20.9 -> 21.0 (32, the stack); only D = 128 gained (32 sequences, 8 heads: 30.3 -> 29.9).
-  constexpr bool kBlind = GT >= 5 && SK == 0;
   using MS = MfmaStream<D>;
   typename MS::Rows cur;
   // V: this lane's row of an instruction and its 16-byte piece
   const int kg = lane >> 4, c16 = lane & 15, v_row = lane / (D / 8), v_piece = lane % (D / 8);
   const uint32_t k_off = (uint32_t)(c16 * D + 8 * kg) * 2u, v_off = (uint32_t)(v_row * D + 8 * v_piece) * 2u;
-  // shares are whole blocks of 32 ring slots or 32 compact slots
+  // shares: whole blocks of 32 ring slots or 32 compact slots on the matrix path, rows otherwise
   const int ring_blocks = (window + 31) / 32, all_blocks = ring_blocks + (budget + 31) / 32;
   const int blk_chunk = (all_blocks + nsplit - 1) / nsplit, blk_begin = split * blk_chunk;
   const int blk_end = blk_begin + blk_chunk < all_blocks ? blk_begin + blk_chunk : all_blocks;
   const int first = blk_begin + wave;
-  const bool early = GT >= 5 && first < blk_end && first < ring_blocks;
+  const int chunk = (window + budget + nsplit - 1) / nsplit, r_begin = split * chunk;
+  const int r_end = r_begin + chunk < window + budget ? r_begin + chunk : window + budget;
+  const bool decides = budget > 0 && (GT >= 5 ? blk_end > ring_blocks : r_end > window);      // some of its rows are compact slots
   // 32 rows from ks, vs on, the first `n_rows` of them real (the others read as zeros)
   auto load_rows = [&](const T* ks, const T* vs, int n_rows, typename MS::Rows& R) {
-    const uint32_t bytes = (uint32_t)n_rows * (uint32_t)(D * 2);
-    const auto rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(ks), 0, bytes, 0x00020000);
-    const auto rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(vs), 0, bytes, 0x00020000);
+    // (the compiler does not see that these are the same in all lanes: it would put a loop over the lanes' descriptors around each load)
+    auto same = [](const T* p) {
+      const uint64_t a = reinterpret_cast<uint64_t>(p);
+      return reinterpret_cast<T*>((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(a >> 32)) << 32 |
+                                  (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)a));
+    };
+    const uint32_t bytes = __builtin_amdgcn_readfirstlane((uint32_t)n_rows * (uint32_t)(D * 2));
+    const auto rk = __builtin_amdgcn_make_buffer_rsrc(same(ks), 0, bytes, 0x00020000);
+    const auto rv = __builtin_amdgcn_make_buffer_rsrc(same(vs), 0, bytes, 0x00020000);
     constexpr int kNonTemporal = 2;
+    // the offsets again, known to be small: the constants are then part of the instructions, not six registers kept over the loop
+    uint32_t ko = k_off, vo = v_off;
+    asm volatile("" : "+v"(ko), "+v"(vo));
+    ko &= 4095u;
+    vo &= 4095u;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int i = 0; i < MS::QK; ++i)
-        R.k[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rk, k_off + (uint32_t)(16 * j * D + 32 * i) * 2u, 0, kNonTemporal);
+        R.k[j][i] = __builtin_amdgcn_raw_buffer_load_b128(rk, ko + (uint32_t)(16 * j * D + 32 * i) * 2u, 0, kNonTemporal);
 #pragma unroll
     for (int i = 0; i < MS::NV; ++i)
-      R.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, v_off + (uint32_t)(MS::RPI * i * D) * 2u, 0, kNonTemporal);
+      R.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, vo + (uint32_t)(MS::RPI * i * D) * 2u, 0, kNonTemporal);
   };
-  if constexpr (kBlind) {
-    if (early) {
-      const int64_t row0 = 32 * first;
-      load_rows(kw + row0 * D, vw + row0 * D, window - 32 * first < 32 ? window - 32 * first : 32, cur);
-    }
-    asm volatile("" : "+s"(t));       // waited for here, behind the requests
-  }
+  // Requests, before anything is known of the sequence: the compact segment's keys, where the token leaving the window may go;
+  // the incoming row; a wave's first rows, whatever they hold: settle() takes out what is not there yet.
+  // Then the scalar words, the decision and everything up to the stream's loop pass under the rows' flight.  What it replaces:
+  // the words as vector loads, each waiting for the rows before it, and the keys requested once the count was known, read a
+  // second time for the victim's slot: the decision was there 3 to 4 us after a launch's start.
+  HeldKeys held;
+  held = load_held_keys<NT>(decides ? budget : 1, decides ? C.ret_score + head * budget : reinterpret_cast<const float*>(C.n_seen),
+                            decides ? C.ret_pos + head * budget : C.n_seen);      // (no branch: they would be waited for at its end)
+  constexpr int EPL = Piece<T>::N;  // elements per lane
+  constexpr int LPR = D / EPL;      // lanes per row
+  constexpr int GPW = kWave / LPR;  // row groups per wave
+  constexpr int GPB = GPW * W;
+  constexpr int RIF = GT >= 5 ? 1 : GT >= 4 ? 2 : kRowsInFlight;   // rows in flight per lane group (registers: GT states per lane)
+  const int sub = lane % LPR, grp = lane / LPR, r_first = r_begin + wave * GPW + grp;
+  u32x4 kraw[RIF], vraw[RIF];
+  // (VALU path: if all of a workgroup's first rows are ring slots)
+  const bool early = GT >= 5 ? first < blk_end : r_begin + GPB * RIF <= window && r_begin + GPB * RIF <= r_end;
   const T* kr = static_cast<const T*>(C.k_ret) + head * budget * D;
   const T* vr = static_cast<const T*>(C.v_ret) + head * budget * D;
+  if constexpr (GT >= 5) {
+    const bool ring = first < ring_blocks;
+    const int row0 = 32 * (ring ? first : first - ring_blocks), left = (ring ? window : budget) - row0;
+    load_rows((ring ? kw : kr) + (early ? (int64_t)row0 * D : 0), (ring ? vw : vr) + (early ? (int64_t)row0 * D : 0),
+              !early ? 0 : left < 32 ? left : 32, cur);
+  }
+  read_here(t);
+  read_here(count_word);
+  read_here(scored);
+  const int cnt_old = (int)(count_word & P.count_mask);
   const T* kn = k_new + head * D;
   const T* vn = v_new + head * D;
 
@@ -1064,17 +1136,19 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   const T* v_evicted = vw + (int64_t)slot * D;
   const bool whole = P.fused && nsplit == 1;      // nothing is handed over
   int dst = -1, cnt = 0;
+  MovingRows rows;             // requested when the stream is done: they come beside the merge, like the count of arrivals
+  unsigned arrivals_before = 0;
+  const bool counts = tid == NT - kWave;      // of the last wave: the answer is waited for at once, and merging begins with the others
 
-  // Requests in the order in which their answers are needed; the stream's first rows follow, and everything up to the
-  // stream's loop passes under their flight.
-  const float z_e = t >= window ? C.win_score[head * window + slot] : 0.f;
-  const int cnt_old = budget > 0 ? (int)((uint32_t)C.ret_count[head] & P.count_mask) : 0;
+  float z_e = t >= window ? load_uniform(C.win_score + head * window + slot) : 0.f;
   // lazy mode: the token leaving the window must have been scored by a batched scoring call
-  const bool late = P.lazy && t >= window && C.n_scored[b] <= t - window;
-  auto decide = [&](bool touches_compact) {
-    if (touches_compact && budget > 0) {   // uniform across the workgroup
-      dst = eviction_target<NT>(t, window, budget, P.sink, P.tau, cnt_old, z_e, C.ret_score + head * budget,
-                                C.ret_pos + head * budget, red64, &slot_lds);
+  const bool late = P.lazy && t >= window && scored <= t - window;
+  auto decide = [&]() {
+    read_here(z_e);      // (not before the VALU path's first rows are requested: they need the token index only)
+    if (decides) {   // uniform across the workgroup
+      dst = __builtin_amdgcn_readfirstlane(eviction_target<NT>(t, window, budget, P.sink, P.tau, cnt_old, z_e, held,
+                                                               C.ret_score + head * budget, C.ret_pos + head * budget, red64,
+                                                               &slot_lds));
       cnt = cnt_old + (dst == cnt_old ? 1 : 0);
     }
   };
@@ -1110,15 +1184,17 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       if (special >= 0 && special < 32 && (ring || dst >= 0)) {
         const T* ks = ring ? kn : k_evicted;
         const T* vs = ring ? vn : v_evicted;
+        int k_at = 8 * kg, v_at = 8 * v_piece;       // (worked out here: addresses of every lane are not kept over the loop)
+        asm volatile("" : "+v"(k_at), "+v"(v_at));
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           if (16 * j + c16 == special) {
 #pragma unroll
-            for (int i = 0; i < MS::QK; ++i) R.k[j][i] = *reinterpret_cast<const u32x4*>(ks + 32 * i + 8 * kg);
+            for (int i = 0; i < MS::QK; ++i) R.k[j][i] = *reinterpret_cast<const u32x4*>(ks + 32 * i + k_at);
           }
 #pragma unroll
         for (int i = 0; i < MS::NV; ++i)
-          if (MS::RPI * i + v_row == special) R.v[i] = *reinterpret_cast<const u32x4*>(vs + 8 * v_piece);
+          if (MS::RPI * i + v_row == special) R.v[i] = *reinterpret_cast<const u32x4*>(vs + v_at);
       }
     };
     auto load = [&](int blk, typename MS::Rows& R) {
@@ -1128,7 +1204,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       load_rows((ring ? kw : kr) + (int64_t)row0 * D, (ring ? vw : vr) + (int64_t)row0 * D, n_live, R);
       replace(ring, row0, R);
     };
-    // the block requested before n_seen was known: V rows past the newest token count as zeros (scores are masked)
+    // the block requested before anything was known: V rows past the last one that counts are zeros (scores are masked)
     auto settle = [&]() {
       bool ring;
       int row0, n_live;
@@ -1155,12 +1231,8 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       }
     };
     load_queries(0);
-    // ring blocks do not wait for the eviction decision
-    if (early) {
-      if constexpr (kBlind) settle();
-      else load(first, cur);
-    }
-    decide(blk_end > ring_blocks);
+    decide();
+    if (early) settle();
     for (int g0 = 0; g0 < G; g0 += GT) {
       const int heads_here = G - g0 < GT ? G - g0 : GT;
       if (g0 > 0) load_queries(g0);
@@ -1280,10 +1352,12 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
             for (int r = 0; r < 4; ++r) o[d][r] = fabsf(all[d][r]) < INFINITY ? all[d][r] : o[d][r];
         }
       }
+      rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);      // (in every pass: not kept over the next one)
       // merge of the waves, fixed order; register r of o[d] is head dimension 16*d + 4*kg + r of column c16
       l_run += __shfl_xor(l_run, 16, kWave);
       l_run += __shfl_xor(l_run, 32, kWave);
       __syncthreads();      // every wave is done with its V tile
+      if (whole && g0 == 0 && counts) arrivals_before = count_arrival(C, P, b);
       if (col_head < heads_here && term < 3) {
         if (kg == 0) { red_m[wave][c16] = m_run; red_l[wave][c16] = l_run; }
 #pragma unroll
@@ -1292,20 +1366,28 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       __syncthreads();
       for (int item = tid; item < heads_here * D; item += NT) {
         const int g = item / D, d = item - g * D;
+        // all of it requested before any is used: one trip to LDS instead of one per wave (0.75 -> 0.4 us of a step with 8 waves)
+        constexpr int kParts = kTermColumns ? 3 : 1;
+        float mw[W], lw[W], part[W][kParts];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          mw[w] = red_m[w][g];
+          lw[w] = red_l[w][g];
+#pragma unroll
+          for (int u = 0; u < kParts; ++u) part[w][u] = scratch[(w * kHeads + 5 * u + g) * kRow + d];
+        }
+        __builtin_amdgcn_sched_barrier(0);
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < W; ++w) M = fmaxf(M, red_m[w][g]);
+        for (int w = 0; w < W; ++w) M = fmaxf(M, mw[w]);
         float L = 0.f, A = 0.f;
         if (M != -INFINITY) {
 #pragma unroll
           for (int w = 0; w < W; ++w) {
-            const float f = __builtin_amdgcn_exp2f(red_m[w][g] - M);
-            L = fmaf(red_l[w][g], f, L);
-            float a = scratch[(w * kHeads + g) * kRow + d];
-            if constexpr (kTermColumns) {
-              const float lower = scratch[(w * kHeads + 5 + g) * kRow + d] + scratch[(w * kHeads + 10 + g) * kRow + d];
-              a = fabsf(a) < INFINITY ? a + lower : a;
-            }
+            const float f = __builtin_amdgcn_exp2f(mw[w] - M);
+            L = fmaf(lw[w], f, L);
+            float a = part[w][0];
+            if constexpr (kTermColumns) a = fabsf(a) < INFINITY ? a + (part[w][1] + part[w][2]) : a;
             A = fmaf(a, f, A);
           }
         }
@@ -1314,16 +1396,6 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
       __syncthreads();
     }
   } else {
-    constexpr int EPL = Piece<T>::N;  // elements per lane
-    constexpr int LPR = D / EPL;      // lanes per row
-    constexpr int GPW = kWave / LPR;  // row groups per wave
-    constexpr int GPB = GPW * W;
-    constexpr int RIF = GT >= 4 ? 2 : kRowsInFlight;   // rows in flight per lane group (registers: GT states per lane)
-    const int sub = lane % LPR, grp = lane / LPR;
-    const int chunk = (window + budget + nsplit - 1) / nsplit;
-    const int r_begin = split * chunk;
-    const int r_end = r_begin + chunk < window + budget ? r_begin + chunk : window + budget;
-    u32x4 kraw[RIF], vraw[RIF];
     bool live[RIF];
     auto load = [&](int r0) {
 #pragma unroll
@@ -1346,11 +1418,8 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
         vraw[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + sub * EPL));
       }
     };
-    const int r_first = r_begin + wave * GPW + grp;
-    // the first iteration's rows are all ring slots (uniform): they do not wait for the eviction decision
-    const bool early = r_begin + GPB * RIF <= window && r_begin + GPB * RIF <= r_end;
     if (early) load(r_first);
-    decide(r_end > window);
+    decide();
     for (int g0 = 0; g0 < G; g0 += GT) {
       float qf[GT][EPL];
       float m_run[GT], l_run[GT], acc[GT][EPL];
@@ -1407,6 +1476,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
             for (int i = 0; i < EPL; ++i) acc[g][i] = fmaf(pr[g][u], vf[i], acc[g][i]);
         }
       }
+      rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);      // (in every pass: not kept over the next one)
       // merge: the row groups of a wave by lane exchange, then the waves through LDS (fixed order -> deterministic)
 #pragma unroll
       for (int g = 0; g < GT; ++g) {
@@ -1429,16 +1499,22 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
           for (int i = 0; i < EPL; ++i) scratch[wave * D + sub * EPL + i] = acc[g][i];
         }
         __syncthreads();
+        if (whole && g0 + g == 0 && counts) arrivals_before = count_arrival(C, P, b);
         if (tid < D) {
+          float mw[W], lw[W], part[W];
+#pragma unroll
+          for (int w = 0; w < W; ++w) { mw[w] = red_m[w][0]; lw[w] = red_l[w][0]; part[w] = scratch[w * D + tid]; }
+          __builtin_amdgcn_sched_barrier(0);
           float M = -INFINITY;
-          for (int w = 0; w < W; ++w) M = fmaxf(M, red_m[w][0]);
+#pragma unroll
+          for (int w = 0; w < W; ++w) M = fmaxf(M, mw[w]);
           float L = 0.f, A = 0.f;
           if (M != -INFINITY) {
 #pragma unroll
             for (int w = 0; w < W; ++w) {
-              const float fw = soft_exp<T>(red_m[w][0] - M);
-              L = fmaf(red_l[w][0], fw, L);
-              A = fmaf(scratch[w * D + tid], fw, A);
+              const float fw = soft_exp<T>(mw[w] - M);
+              L = fmaf(lw[w], fw, L);
+              A = fmaf(part[w], fw, A);
             }
           }
           put_row(h * G + g0 + g, tid, M, L, A);
@@ -1452,12 +1528,12 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   unsigned* word = reinterpret_cast<unsigned*>(C.ret_count + head);
   if (whole) {
     const float z_new = puts_logit && tid == 0 ? given_logit(P, b, h, t) : 0.f;
-    update_cache<T, D>(C, P, load_moving_rows<T, D>(C, P, k_new, v_new, head, t), head, t, dst, z_e, z_new, puts_logit);
+    update_cache<T, D>(C, P, rows, head, t, dst, z_e, z_new, puts_logit);
     if (tid == 0) {
       if (dst >= 0 && dst == cnt_old) atomicAdd(word, 1u);
       if (h == 0 && late && P.status != nullptr) atomicOr(P.status, LTEA_LATE_SCORING);
-      arrive_sequence(C, P, b, t);
     }
+    if (counts) advance_if_last(C, P, b, t, arrivals_before);
     return;
   }
   // ---- hand this share over; the last one of the head to get here finishes it ----
@@ -1471,16 +1547,16 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   if (tid == 0) slot_lds = ((atomicAdd(word, 1u << 16) >> 16) & 255u) + 1 == (unsigned)nsplit;
   __syncthreads();
   if (slot_lds == 0) return;
+  if (counts) arrivals_before = count_arrival(C, P, b);      // for the head: its other shares have counted themselves
   dst = load_shared(H.dst + head);
   const float z_new = puts_logit && tid == 0 ? given_logit(P, b, h, t) : 0.f;
-  const MovingRows rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);
   merge_shares<T, D, NT>(P, H.partial, out, b, h, late);
   update_cache<T, D>(C, P, rows, head, t, dst, z_e, z_new, puts_logit);
   if (tid == 0) {
     atomicAdd(word, (dst >= 0 && dst == cnt_old ? 1u : 0u) - ((unsigned)nsplit << 16));
     if (h == 0 && late && P.status != nullptr) atomicOr(P.status, LTEA_LATE_SCORING);
-    arrive_sequence(C, P, b, t);
   }
+  if (counts) advance_if_last(C, P, b, t, arrivals_before);
 }
 
 // Positions between the rows that a logit depends on, of the input of layer `first`: the greatest common divisor of the
