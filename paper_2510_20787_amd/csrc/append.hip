@@ -99,6 +99,7 @@ append_build_kernel(AppendPlan P, BuildArgs a) {
   }
 
   const int cnt = a.budget > 0 ? a.ret_count[head] : 0, pad = F - cnt;
+  if (blockIdx.y == 0 && tid == 0) P.old_count[head] = cnt;
   const int item0 = blockIdx.y * kItems, item_end = min(item0 + kItems, cnt + wo + M);
   if (item0 >= item_end) return;
 
@@ -218,6 +219,7 @@ size_t carve(const ltea_cfg& cfg, int n_seqs, int64_t total_new, int rho, void* 
   P.kv_start = reinterpret_cast<int32_t*>(take(per_seq));
   P.kv_len = reinterpret_cast<int32_t*>(take(per_seq));
   const size_t per_entry = sizeof(int32_t) * (size_t)n_seqs * cfg.Hkv * (size_t)(cfg.budget > 0 ? cfg.budget : 1);
+  P.old_count = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)n_seqs * cfg.Hkv));
   P.sorted_pos = reinterpret_cast<int32_t*>(take(per_entry));
   P.local_pos = reinterpret_cast<int32_t*>(take(per_entry));
   P.ext_key = reinterpret_cast<float*>(take((size_t)ext * cfg.Hkv * sizeof(float)));

@@ -13,6 +13,7 @@ struct AppendPlan {
   int32_t* cu_score;       // [n_seqs + 1] packing of the rows that are scored
   int32_t* kv_start;       // first row of the ring + new part in the extended buffers
   int32_t* kv_len;         // w_old + new tokens
+  int32_t* old_count;      // [n_seqs][Hkv] kept entries before the call (retention sets the cache's own counts)
   int32_t* sorted_pos;     // [n_seqs][Hkv][budget] old kept positions ascending
   int32_t* local_pos;      // [n_seqs][Hkv][budget] kept positions in the ring + new frame (for the attention kernel)
   float* ext_key;          // [Hkv][total_ext] selection keys that were final before the call

@@ -1,6 +1,8 @@
 // Budgeted retention and cache fill (paper eq. 5; Section 3.1.3 "Capped capacity", "Cached prefilling").
 //
-// One launch.  Workgroups with blockIdx.y == 0 own one (sequence, KV head) each:
+// One launch.  Workgroups with blockIdx.y < slices own one (sequence, KV head) each, or, where the heads leave most of the chip
+// idle, a slice of its kept entries: every one of them selects for itself, writes its slice of the kept positions and
+// gathers its slice of the rows.
 //   candidates among the out-of-window positions 0 .. n-window-1 are sinks or logits above the threshold;
 //   their keys (an order-preserving integer image of the fp32 key, 0 for non-candidates) are read once and
 //   stay in registers.  If more than `budget` exist, an exact radix select (up to 4 passes of 8 bits) finds
@@ -8,7 +10,7 @@
 //   The same ordered scan (wave prefix sums, no atomics on results) writes the kept positions and keys
 //   ascending by position, so the result is deterministic; the workgroup then gathers the kept K/V rows into
 //   the compact segment.
-// Workgroups with blockIdx.y >= 1 copy the last min(n, window) tokens and their logits into the ring
+// Workgroups with blockIdx.y >= slices copy the last min(n, window) tokens and their logits into the ring
 // (slot = position % window); that part does not depend on the selection and overlaps with it.
 //
 // The continuation of a prefill runs the same kernel over its extended sequences (append.hip): an element's key then
@@ -57,6 +59,7 @@ struct RetainArgs {
   const char* k; const char* v; int64_t tok_bytes, head_bytes; int row_bytes;   // K/V views in bytes
   char* k_win; char* v_win; float* win_score; char* k_ret; char* v_ret;
   float* ret_score; int32_t* ret_pos; int32_t* ret_count; int32_t* n_seen; int32_t* n_scored;
+  int slices;           // selection workgroups per head
   AppendPlan plan;      // continuation only
 };
 
@@ -78,7 +81,7 @@ template <> struct Elements<true> {
   __device__ Elements(const RetainArgs& a, int b, int h, int64_t head, int64_t lo, int n) {
     const int n_old = a.plan.n_old[b], w_old = a.plan.w_old[b];
     prefix = a.plan.prefix[b];
-    pad = prefix - (a.budget > 0 ? a.ret_count[head] : 0);
+    pad = prefix - a.plan.old_count[head];
     shift = n_old - w_old - prefix;
     first_fresh = n_old - a.rho - shift;
     // fresh[e]: the scored rows begin with the last min(w_old, 2 rho) ring tokens
@@ -119,12 +122,12 @@ retain_kernel(const RetainArgs a) {
   const Elements<APPEND> el(a, b, h, head, lo, n);
   const int pieces = a.row_bytes / 16;
 
-  if (blockIdx.y > 0) {
+  if ((int)blockIdx.y >= a.slices) {
     // ---- ring rows: slot -> the position it holds after n tokens ----
     const int rows_per_pass = kSelThreads / pieces;
     const int sub = tid / pieces, pc = tid - sub * pieces;
-    const int row_end = min((int)blockIdx.y * kRingRows, a.window);
-    for (int slot = ((int)blockIdx.y - 1) * kRingRows + sub; slot < row_end; slot += rows_per_pass) {
+    const int from = ((int)blockIdx.y - a.slices) * kRingRows, row_end = min(from + kRingRows, a.window);
+    for (int slot = from + sub; slot < row_end; slot += rows_per_pass) {
       int p;
       if (n >= a.window) {
         const int first = n - a.window;   // oldest position in the window
@@ -151,13 +154,14 @@ retain_kernel(const RetainArgs a) {
   }
 
   const int n_out = n > a.window ? n - a.window : 0;
-  if (h == 0 && tid == 0) {
+  const int slice = (int)blockIdx.y;
+  if (h == 0 && tid == 0 && slice == 0) {
     const int seen = el.seen(n);
     a.n_seen[b] = seen;
     a.n_scored[b] = seen > a.rho ? seen - a.rho : 0;
   }
   if (a.budget == 0 || n_out == 0) {
-    if (tid == 0) a.ret_count[head] = 0;
+    if (tid == 0 && slice == 0) a.ret_count[head] = 0;
     return;
   }
 
@@ -267,6 +271,7 @@ retain_kernel(const RetainArgs a) {
   }
 
   // ---- ordered compaction: ascending positions ----
+  const int per_slice = (min(a.budget, n_out) + a.slices - 1) / a.slices, s_lo = slice * per_slice, s_hi = s_lo + per_slice;
   int kept_before = 0, eq_before = 0;
 #pragma unroll 1
   for (int c = 0; c < n_chunks; ++c) {
@@ -293,31 +298,34 @@ retain_kernel(const RetainArgs a) {
 #pragma unroll
     for (int e = 0; e < kItems; ++e) {
       if (keep[e]) {
-        a.ret_pos[head * a.budget + off] = el.position(a, head, j0 + e);
-        if constexpr (APPEND) a.plan.local_pos[head * a.budget + off] = j0 + e - el.prefix;
-        a.ret_score[head * a.budget + off] = key_of_order_key(u[e]);
+        if (off >= s_lo && off < s_hi) {
+          a.ret_pos[head * a.budget + off] = el.position(a, head, j0 + e);
+          if constexpr (APPEND) a.plan.local_pos[head * a.budget + off] = j0 + e - el.prefix;
+          a.ret_score[head * a.budget + off] = key_of_order_key(u[e]);
+        }
         ++off;
       }
     }
     kept_before += keep_total;
     eq_before += eq_total;
   }
-  if (tid == 0) a.ret_count[head] = kept_before;
+  if (tid == 0 && slice == 0) a.ret_count[head] = kept_before;
 
-  // ---- gather the kept rows (positions written above by this workgroup) ----
+  // ---- gather the slice's kept rows (positions written above by this workgroup) ----
   __threadfence_block();
   __syncthreads();
   // four pieces per thread in flight: positions first, then all the row loads, then the stores
   constexpr int kGather = 4;
-  const int n_pieces = kept_before * pieces;
+  const int n_pieces = (min(kept_before, s_hi) - s_lo) * pieces;
   for (int i0 = tid; i0 < n_pieces; i0 += kGather * kSelThreads) {
     int r[kGather], pc[kGather], p[kGather];
 #pragma unroll
     for (int u = 0; u < kGather; ++u) {
       const int i = i0 + u * kSelThreads;
       const int ic = i < n_pieces ? i : i0;          // past the end: this thread's first piece once more, not stored
-      r[u] = ic / pieces;
-      pc[u] = ic - r[u] * pieces;
+      const int row = ic / pieces;
+      pc[u] = ic - row * pieces;
+      r[u] = s_lo + row;
       if constexpr (APPEND) p[u] = a.plan.local_pos[head * a.budget + r[u]] + el.prefix;
       else p[u] = a.ret_pos[head * a.budget + r[u]];
     }
@@ -359,9 +367,16 @@ RetainArgs retain_args(const ltea_cfg& cfg, const float* logits, int64_t total, 
 }
 
 template <bool APPEND>
-hipError_t run(const RetainArgs& a, int n_seqs, int64_t longest, hipStream_t stream) {
-  const dim3 grid((unsigned)n_seqs * (unsigned)a.Hkv, 1u + (unsigned)((a.window + kRingRows - 1) / kRingRows));
+hipError_t run(RetainArgs a, int n_seqs, int64_t longest, hipStream_t stream) {
   const int64_t n_out_max = longest > a.window ? longest - a.window : 0;
+  // Slices of at least 64 rows while they and the heads take no more than half of the CUs, which the ring's rows need too.  One CU
+  // moves about 40 KB per us: 32 heads, 1024 rows of D = 128 each 38.5 us with one workgroup per head, 28.5 with four (eight, a
+  // workgroup on every CU: the ring waits, 38), 32 heads, 512 rows of D = 64 11.0 -> 10.3.
+  const int64_t heads = (int64_t)n_seqs * a.Hkv, by_cus = heads > 0 ? 128 / heads : 1;
+  const int64_t most = ((n_out_max < a.budget ? n_out_max : a.budget) + 63) / 64;
+  const int64_t slices = by_cus < most ? by_cus : most;
+  a.slices = (int)(slices < 1 ? 1 : slices > 8 ? 8 : slices);
+  const dim3 grid((unsigned)n_seqs * (unsigned)a.Hkv, (unsigned)(a.slices + (a.window + kRingRows - 1) / kRingRows));
   auto go = [&](auto ch) {
     hipLaunchKernelGGL((retain_kernel<decltype(ch)::value, APPEND>), grid, dim3(kSelThreads), 0, stream, a);
   };
