@@ -166,92 +166,119 @@ template <typename T> struct OutProj {
   float *part_b, *part_wout, *part_bout;
 };
 
-// From the pre-activations y of a lane's tokens of column n (valid: n_ok) to d y and the column's sums.
-template <int U, bool NARROW, typename T, class TokenOf>
-__device__ __forceinline__ void out_proj_backward(const OutProj<T>& P, const f32x16 (&acc)[U], float bv, int h, int Hkv, int n,
-                                                  int N, bool n_ok, int64_t total, const TokenOf& token_of, float* dpre,
-                                                  float* red, int wv, int lane) {
-  const float wo = n_ok ? to_f32(P.w_out[(int64_t)h * N + n]) : 0.f;
+// A workgroup's tokens of an array [Hkv][T][N], as a lane of the epilogues below sees them: accumulator register r of
+// sub-tile u is row 32 u + 8 (r / 4) + r % 4 below the lane's own (row0), column n.  A row past the array's end or a column
+// past N is outside the descriptor: its load gives zero and its store goes nowhere, so that a lane's elements are one straight
+// run of independent chains (exponentials, divisions) without a branch or a 64-bit product in each.  (With both, the first
+// layer's forward was 2025 vector instructions per wave, of which 1440 were the 32 elements.)
+template <int U> struct TileColumn {
+  static constexpr uint32_t kOutside = 0x80000000u;      // at or past the largest descriptor: 128 rows of 64 * 65536 columns
+  int h, rows, row0, n, N;
+  bool n_ok;
+  int64_t first;                                         // h * T + the tile's first token
+
+  __device__ __forceinline__ TileColumn(int h_, int64_t total, int64_t t0, int row0_, int n_, int N_)
+      : h(h_), rows((int)(total - t0 < TMC ? total - t0 : TMC)), row0(row0_), n(n_), N(N_), n_ok(n_ < N_), first(h_ * total + t0) {}
+  static __device__ __forceinline__ constexpr int row_of(int u, int r) { return 32 * u + 8 * (r / 4) + r % 4; }
+  __device__ __forceinline__ bool inside(int u, int r) const { return row0 + row_of(u, r) < rows; }
+  __device__ __forceinline__ uint32_t bytes() const { return (uint32_t)rows * (uint32_t)N * 4u; }
+  __device__ __forceinline__ uint32_t base() const { return n_ok ? ((uint32_t)row0 * (uint32_t)N + (uint32_t)n) * 4u : kOutside; }
+  __device__ __forceinline__ uint32_t at(uint32_t base, int u, int r) const { return base + (uint32_t)row_of(u, r) * (uint32_t)N * 4u; }
+  template <class P> __device__ __forceinline__ auto rows_of(P* p) const {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + first * N, 0, bytes(), 0x00020000);
+  }
+};
+
+// From the pre-activations y of a lane's tokens of its column to d y and the column's sums.
+template <int U, bool NARROW, typename T>
+__device__ __forceinline__ void out_proj_backward(const OutProj<T>& P, const f32x16 (&acc)[U], float bv, const TileColumn<U>& C,
+                                                  int Hkv, float* dpre, float* red, int wv, int lane) {
+  const float wo = C.n_ok ? to_f32(P.w_out[(int64_t)C.h * C.N + C.n]) : 0.f;
+  const float* const dz = P.dz + C.first;
+  const auto rs_d = C.rows_of(dpre);
+  const uint32_t base = C.base();
   float sum[3] = {0.f, 0.f, 0.f};        // of d y, dz * silu(y), dz
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     float g[16];                         // all requested before the first is used
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t t = token_of(16 * u + r);
-      g[r] = P.dz[(int64_t)h * total + (t < total ? t : 0)];
-    }
+    for (int r = 0; r < 16; ++r) g[r] = dz[(uint32_t)min(C.row0 + C.row_of(u, r), C.rows - 1)];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int64_t t = token_of(16 * u + r);
-      if (t >= total || !n_ok) continue;
       const float y = acc[u][r] + bv;
       const float den = 1.0f + expf(-y), s = 1.0f / den;
       const float d = g[r] * wo * (s * (1.0f + y * (1.0f - s)));
-      sum[0] += d;
-      sum[1] += g[r] * (y / den);
-      sum[2] += g[r];
-      dpre[((int64_t)h * total + t) * N + n] = d;
+      const bool keep = C.inside(u, r);
+      sum[0] += keep ? d : 0.f;
+      sum[1] += keep ? g[r] * (y / den) : 0.f;
+      sum[2] += keep ? g[r] : 0.f;
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d), rs_d, C.at(base, u, r), 0, 0);
+      if (r % 4 == 3) {                  // four chains side by side, and their sums taken: 32 would not fit the registers
+        asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
   tile_column_sums<3, NARROW>(sum, red, wv, lane);
   const int col = (int)blockIdx.y * 64 + lane;
-  if (wv == 0 && lane < (NARROW ? 32 : 64) && col < N) {
-    const int64_t row = (int64_t)blockIdx.x * Hkv + h;
-    P.part_b[row * N + col] = sum[0];
-    P.part_wout[row * N + col] = sum[1];
+  if (wv == 0 && lane < (NARROW ? 32 : 64) && col < C.N) {
+    const int64_t row = (int64_t)blockIdx.x * Hkv + C.h;
+    P.part_b[row * C.N + col] = sum[0];
+    P.part_wout[row * C.N + col] = sum[1];
     if (col == 0) P.part_bout[row] = sum[2];
   }
 }
 
 // What a forward launch does with its products: pre-activations and activations, or the output projection's backward.
-template <int U, bool NARROW, typename T, class TokenOf>
-__device__ __forceinline__ void forward_result(const OutProj<T>& P, const f32x16 (&acc)[U], const float* bias, int h, int Hkv, int n,
-                                               int N, bool n_ok, int64_t total, const TokenOf& token_of, float* out0, float* out1,
-                                               float* red, int wv, int lane) {
-  const float bv = n_ok ? bias[(int64_t)h * N + n] : 0.f;
+template <int U, bool NARROW, typename T>
+__device__ __forceinline__ void forward_result(const OutProj<T>& P, const f32x16 (&acc)[U], const float* bias,
+                                               const TileColumn<U>& C, int Hkv, float* out0, float* out1, float* red, int wv,
+                                               int lane) {
+  const float bv = C.n_ok ? bias[(int64_t)C.h * C.N + C.n] : 0.f;
   if (P.dz != nullptr) {
-    out_proj_backward<U, NARROW>(P, acc, bv, h, Hkv, n, N, n_ok, total, token_of, out0, red, wv, lane);
+    out_proj_backward<U, NARROW>(P, acc, bv, C, Hkv, out0, red, wv, lane);
     return;
   }
+  const auto rs0 = C.rows_of(out0), rs1 = C.rows_of(out1);
+  const uint32_t base = C.base();
 #pragma unroll
-  for (int ur = 0; ur < 16 * U; ++ur) {
-    const int64_t t = token_of(ur);
-    if (t >= total || !n_ok) continue;
-    const int64_t o = ((int64_t)h * total + t) * N + n;
-    const float y = acc[ur / 16][ur % 16] + bv;
-    out0[o] = y;
-    out1[o] = silu_f32(y);
-  }
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float y = acc[u][r] + bv;
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y), rs0, C.at(base, u, r), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(silu_f32(y)), rs1, C.at(base, u, r), 0, 0);
+      if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);      // four chains side by side, not 32: registers
+    }
 }
 
 // d y of the layer below from d a (acc), and its column sums over the workgroup's tokens.
-template <int U, bool NARROW, class TokenOf>
-__device__ __forceinline__ void hidden_backward(const f32x16 (&acc)[U], int h, int Hkv, int n, int N, bool n_ok, int64_t total,
-                                                const TokenOf& token_of, const float* pre_prev, float* dpre, float* part_b,
-                                                float* red, int wv, int lane) {
+template <int U, bool NARROW>
+__device__ __forceinline__ void hidden_backward(const f32x16 (&acc)[U], const TileColumn<U>& C, int Hkv, const float* pre_prev,
+                                                float* dpre, float* part_b, float* red, int wv, int lane) {
+  const auto rs_p = C.rows_of(pre_prev), rs_d = C.rows_of(dpre);
+  const uint32_t base = C.base();
   float sum[1] = {0.f};
   // per sub-tile, all of the lane's pre-activations are requested before the first is used
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     float pp[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t t = token_of(16 * u + r);
-      pp[r] = pre_prev[(t < total && n_ok) ? ((int64_t)h * total + t) * N + n : 0];
-    }
+    for (int r = 0; r < 16; ++r) pp[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_p, C.at(base, u, r), 0, 0));
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int64_t t = token_of(16 * u + r);
-      if (t >= total || !n_ok) continue;
       const float d = acc[u][r] * silu_grad_f32(pp[r]);
-      sum[0] += d;
-      dpre[((int64_t)h * total + t) * N + n] = d;
+      sum[0] += C.inside(u, r) ? d : 0.f;
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(d), rs_d, C.at(base, u, r), 0, 0);
+      if (r % 4 == 3) {
+        asm volatile("" : "+v"(sum[0]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
   tile_column_sums<1, NARROW>(sum, red, wv, lane);
   const int col = (int)blockIdx.y * 64 + lane;
-  if (wv == 0 && lane < (NARROW ? 32 : 64) && col < N) part_b[((int64_t)blockIdx.x * Hkv + h) * N + col] = sum[0];
+  if (wv == 0 && lane < (NARROW ? 32 : 64) && col < C.N) part_b[((int64_t)blockIdx.x * Hkv + C.h) * C.N + col] = sum[0];
 }
 
 // out[t][n] = sum_tap sum_k in[t + sign * off(tap)][k] * wt[tap][k][n]   (rows outside t's sequence count as zero)
@@ -383,19 +410,18 @@ conv_product_kernel(const float* __restrict__ in, const float* __restrict__ wt, 
   }
   // accumulator register r of lane half hb: token row 8*(r/4) + 4*hb + r%4 of the sub-tile, output column ql
   const int n = n0 + col0 + ql;
-  const bool n_ok = n < N;
-  auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
+  const TileColumn<U> column(h, total, t0, row0 + 4 * hb, n, N);
   if (mode == 0) {
-    forward_result<U, NARROW>(proj, acc, bias, h, Hkv, n, N, n_ok, total, token_of, out0, out1, &a_s[0][0], wv, lane);
+    forward_result<U, NARROW>(proj, acc, bias, column, Hkv, out0, out1, &a_s[0][0], wv, lane);
   } else if (mode == 1) {
-    hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b, &a_s[0][0], wv, lane);
+    hidden_backward<U, NARROW>(acc, column, Hkv, pre_prev, out0, part_b, &a_s[0][0], wv, lane);
   } else {
     T* dst = n < D ? dk : dv;
     const int col = n < D ? n : n - D;
-    if (dst != nullptr && n_ok) {
+    if (dst != nullptr && column.n_ok) {
 #pragma unroll
       for (int ur = 0; ur < 16 * U; ++ur) {
-        const int64_t t = token_of(ur);
+        const int64_t t = t0 + column.row0 + column.row_of(ur / 16, ur % 16);
         if (t < total) dst[(t * Hkv + h) * D + col] = from_f32<T>(acc[ur / 16][ur % 16]);
       }
     }
@@ -444,64 +470,57 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[u][r] = 0.f;
   const int per_group = min(GT, 1 + HALO / dil);
-  const int groups = (ks + per_group - 1) / per_group;
-  const int slices = K / KCB, stages = groups * slices;   // D is a multiple of KCB
-  auto stage_taps = [&](int stage, int& tap0, int& ntap, int& k0, int& base_off) {
-    const int g = stage / slices;
-    k0 = (stage - g * slices) * KCB;
-    tap0 = g * per_group;
-    ntap = min(per_group, ks - tap0);
-    base_off = (tap0 - half) * dil;
-  };
+  // Staged rows outside the array and columns past N hold values of other rows or zero: what is read of them is masked below
+  // with the sequence's bounds, or belongs to a column that is not written.  Rows past those that the group's taps reach are
+  // not read and all take the last one's line.
+  int64_t row_at[PQA];           // of the group's rows that the thread moves: element offset, clamped into the array
+  uint32_t w_at[PQB];            // of its weight pieces: byte offset from the group's first tap
+#pragma unroll
+  for (int i = 0; i < PQB; ++i) {
+    const int e = tid + 256 * i, jn = e / (KCB / 8), q = e % (KCB / 8);
+    w_at[i] = (((uint32_t)(jn / TN) * (uint32_t)N + jn % TN) * (uint32_t)K + 8 * q) * 2u;
+  }
   u32x4 ra[PQA], rb[PQB];
-  unsigned keep_a, keep_b;       // one bit per 16-byte piece: does it count
-  auto fetch = [&](int stage) {
-    int tap0, ntap, k0, base_off;
-    stage_taps(stage, tap0, ntap, k0, base_off);
-    const int rows = TMC + (ntap - 1) * dil;
-    const bf16_t* src = (k0 < D ? k + k0 : v + (k0 - D)) + (int64_t)h * stride_head;
-    keep_a = keep_b = 0u;
+  auto fetch = [&](int tap0, int ntap, int k0) {
+    if (k0 == 0) {
+      const int first = (int)t0 + (tap0 - half) * dil, last = min(first + TMC - 1 + (ntap - 1) * dil, (int)total - 1);
 #pragma unroll
-    for (int i = 0; i < PQA; ++i) {
-      const int e = tid + 256 * i, row = e / (KCB / 8), q = e % (KCB / 8);
-      const int64_t p = t0 + row + base_off;
-      const bool ok = row < rows && p >= 0 && p < total;
-      ra[i] = *reinterpret_cast<const u32x4*>(src + (ok ? p : 0) * stride_tok + 8 * q);   // unconditional, inside the array
-      keep_a |= ok ? 1u << i : 0u;
+      for (int i = 0; i < PQA; ++i) {
+        const int e = tid + 256 * i;
+        row_at[i] = max(0, min(first + e / (KCB / 8), last)) * stride_tok + 8 * (e % (KCB / 8));
+      }
     }
+    const bf16_t* src = (k0 < D ? k + k0 : v + (k0 - D)) + (int64_t)h * stride_head;      // D is a multiple of KCB
 #pragma unroll
-    for (int i = 0; i < PQB; ++i) {
-      const int e = tid + 256 * i, jn = e / (KCB / 8), q = e % (KCB / 8);
-      const int j = jn / TN, n = jn % TN;
-      const bool ok = j < ntap && n0 + n < N;
-      rb[i] = *reinterpret_cast<const u32x4*>(w_h + (ok ? ((int64_t)(tap0 + j) * N + n0 + n) * K : 0) + k0 + 8 * q);
-      keep_b |= ok ? 1u << i : 0u;
-    }
+    for (int i = 0; i < PQA; ++i) ra[i] = *reinterpret_cast<const u32x4*>(src + row_at[i]);
+    const auto rs_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(w_h) + ((int64_t)tap0 * N + n0) * K + k0, 0,
+                                                        (((uint32_t)ntap * N - n0) * (uint32_t)K - k0) * 2u, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < PQB; ++i) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_at[i], 0, 0);
   };
-  auto masked_piece = [](u32x4 x, bool keep) {
-    asm volatile("" : "+v"(x));      // the loaded value is needed whatever the mask says: the load stays unconditional
-    return keep ? x : u32x4{0u, 0u, 0u, 0u};
-  };
-  fetch(0);
-  for (int stage = 0; stage < stages; ++stage) {
+  auto masked_piece = [](u32x4 x, bool keep) { return keep ? x : u32x4{0u, 0u, 0u, 0u}; };
+  int tap0 = 0, ntap = min(per_group, ks), k0 = 0;
+  fetch(tap0, ntap, k0);
+  while (tap0 < ks) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PQA; ++i) {
       const int e = tid + 256 * i;
-      *reinterpret_cast<u32x4*>(&a_s[e / (KCB / 8)][8 * (e % (KCB / 8))]) = masked_piece(ra[i], keep_a >> i & 1u);
+      *reinterpret_cast<u32x4*>(&a_s[e / (KCB / 8)][8 * (e % (KCB / 8))]) = ra[i];
     }
 #pragma unroll
     for (int i = 0; i < PQB; ++i) {
       const int e = tid + 256 * i, jn = e / (KCB / 8);
-      *reinterpret_cast<u32x4*>(&b_s[jn / TN][jn % TN][8 * (e % (KCB / 8))]) = masked_piece(rb[i], keep_b >> i & 1u);
+      *reinterpret_cast<u32x4*>(&b_s[jn / TN][jn % TN][8 * (e % (KCB / 8))]) = rb[i];
     }
     __syncthreads();
-    int tap0, ntap, k0, base_off;
-    stage_taps(stage, tap0, ntap, k0, base_off);
-    if (stage + 1 < stages) fetch(stage + 1);
-    for (int j = 0; j < ntap; ++j) {
-      const int off = (tap0 + j - half) * dil;
-      const int shift = off - base_off;
+    const int tap_at = tap0, n_taps = ntap;
+    k0 += KCB;
+    if (k0 == K) { k0 = 0; tap0 += per_group; ntap = min(per_group, ks - tap0); }
+    if (tap0 < ks) fetch(tap0, ntap, k0);
+    for (int j = 0; j < n_taps; ++j) {
+      const int off = (tap_at + j - half) * dil;
+      const int shift = j * dil;
       bool valid[U], inside[U];      // inside: the same for all tokens of the sub-tile (no sequence ends under it)
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -526,10 +545,8 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
   }
   // accumulator register r of lane half hb: token row 8*(r/4) + 4*hb + r%4 of the sub-tile, output column ql
   const int n = n0 + col0 + ql;
-  const bool n_ok = n < N;
-  auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
-  forward_result<U, NARROW>(proj, acc, bias, h, Hkv, n, N, n_ok, total, token_of, pre, act, reinterpret_cast<float*>(&a_s[0][0]), wv,
-                            lane);      // one layer only: pre receives d pre
+  const TileColumn<U> column(h, total, t0, row0 + 4 * hb, n, N);
+  forward_result<U, NARROW>(proj, acc, bias, column, Hkv, pre, act, reinterpret_cast<float*>(&a_s[0][0]), wv, lane);      // one layer only: pre receives d pre
 }
 
 // x = t0 + t1 + t2 in bf16 terms (t1, t2: exact residuals), four values packed per term.  Values beyond bf16's largest would
@@ -538,21 +555,23 @@ conv_first_bf16_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ 
 constexpr float kMaxBf16 = 3.3895314e38f;
 __device__ __forceinline__ void split_quad(float4 x, uint2 (&t)[3]) {
   const float xs[4] = {x.x, x.y, x.z, x.w};
-  uint32_t b[3][4];
+  auto pair = [](float lo, float hi) { return __builtin_bit_cast(uint32_t, bf16x2{from_f32<bf16_t>(lo), from_f32<bf16_t>(hi)}); };
+  auto low = [](uint32_t p) { return __uint_as_float(p << 16); };
+  auto high = [](uint32_t p) { return __uint_as_float(p & 0xFFFF0000u); };
+  float r[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const bf16_t b0 = from_f32<bf16_t>(xs[c]);
-    const float r1 = xs[c] - static_cast<float>(b0);
-    const bf16_t b1 = from_f32<bf16_t>(r1);
-    const float r2 = r1 - static_cast<float>(b1);
-    b[0][c] = (uint32_t)__builtin_bit_cast(uint16_t, b0);
-    b[1][c] = (uint32_t)__builtin_bit_cast(uint16_t, b1);
-    b[2][c] = (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(r2));
+  for (int m = 0; m < 3; ++m) {
+    t[m] = make_uint2(pair(r[0], r[1]), pair(r[2], r[3]));
+    r[0] -= low(t[m].x); r[1] -= high(t[m].x);
+    r[2] -= low(t[m].y); r[3] -= high(t[m].y);
   }
   if (fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) > kMaxBf16) {
     auto bits = [](float y) { return (uint32_t)__builtin_bit_cast(uint16_t, from_f32<bf16_t>(y)); };
+    uint32_t b[3][4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int m = 0; m < 3; ++m) b[m][c] = ((c < 2 ? t[m].x : t[m].y) >> (16 * (c % 2))) & 0xFFFFu;
       if (!(fabsf(xs[c]) > kMaxBf16)) continue;
       const bool infinite = fabsf(xs[c]) == INFINITY;
       const float top = __uint_as_float(__float_as_uint(xs[c]) & 0xFFFF0000u);
@@ -560,9 +579,9 @@ __device__ __forceinline__ void split_quad(float4 x, uint2 (&t)[3]) {
       b[1][c] = infinite ? 0u : bits(xs[c] - top);
       b[2][c] = infinite ? bits(xs[c]) : bits((xs[c] - top) - __uint_as_float(bits(xs[c] - top) << 16));
     }
-  }
 #pragma unroll
-  for (int m = 0; m < 3; ++m) t[m] = make_uint2(b[m][0] | b[m][1] << 16, b[m][2] | b[m][3] << 16);
+    for (int m = 0; m < 3; ++m) t[m] = make_uint2(b[m][0] | b[m][1] << 16, b[m][2] | b[m][3] << 16);
+  }
 }
 
 // The convs whose activations are fp32 on bf16 storage: out[t][n] = sum_tap sum_k in[t + sign * off(tap)][k] * W(tap, k, n),
@@ -588,7 +607,7 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
   const int64_t t0 = (int64_t)blockIdx.x * TMC;
   const int n0 = blockIdx.y * TN;
   const int tid = threadIdx.x;
-  const float* in_t = in + ((int64_t)h * total + t0) * K;
+  const float* in_h = in + (int64_t)h * total * K;
   const bf16_t* w_h = w + (int64_t)h * ks * N * K;
   const int half = (ks - 1) / 2;
   const int lane = tid & 63, wv = tid >> 6, ql = lane & 31, hb = lane >> 5;
@@ -608,67 +627,60 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[u][r] = 0.f;
   const int per_group = min(GT, 1 + HALO / dil);
-  const int groups = (ks + per_group - 1) / per_group;
-  const int slices = (K + KCS - 1) / KCS, stages = groups * slices;
-  auto stage_taps = [&](int stage, int& tap0, int& ntap, int& k0, int& base_off) {
-    const int g = stage / slices;
-    k0 = (stage - g * slices) * KCS;
-    tap0 = g * per_group;
-    ntap = min(per_group, ks - tap0);
-    base_off = sign > 0 ? (tap0 - half) * dil : -(tap0 + ntap - 1 - half) * dil;
-  };
-  float4 ra[PSA];
-  u32x4 rb[PSB];
-  unsigned keep_a, keep_b;
-  auto fetch = [&](int stage) {
-    int tap0, ntap, k0, base_off;
-    stage_taps(stage, tap0, ntap, k0, base_off);
-    const int rows = TMC + (ntap - 1) * dil;
-    keep_a = keep_b = 0u;
+  constexpr uint32_t kOutside = 0xFFFFFFF0u;
+  // Staged rows outside the array are zero, those past what the group's taps reach and columns past N hold anything: what is
+  // read of them is masked below with the sequence's bounds, or belongs to a column that is not written.  Channels past K are
+  // zero in both operands.
+  const int qa = 4 * (tid % (KCS / 4)), qb = 8 * (tid % (KCS / 8));
+  uint32_t w_at[PSB];            // of the thread's weight pieces: byte offset from the group's first tap
+#pragma unroll
+  for (int i = 0; i < PSB; ++i) {
+    const int jn = (tid + 256 * i) / (KCS / 8);
+    w_at[i] = (((uint32_t)(jn / TN) * (uint32_t)N + jn % TN) * (uint32_t)K + qb) * 2u;
+  }
+  u32x4 ra[PSA], rb[PSB];
+  auto first_row = [&](int tap0, int ntap) { return sign > 0 ? (tap0 - half) * dil : -(tap0 + ntap - 1 - half) * dil; };
+  auto fetch = [&](int tap0, int ntap, int k0) {
+    const int first = (int)t0 + first_row(tap0, ntap), skip = max(0, -first);        // staged rows in front of the array
+    const int rows = max(0, min(TMC + (ntap - 1) * dil, (int)total - first) - skip);
+    // K % 8 == 0: whole pieces.  A row in front of the array has an offset below zero, i.e. far past the end.
+    const auto rs_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in_h) + (int64_t)(first + skip) * K + k0, 0,
+                                                        rows > 0 ? ((uint32_t)rows * (uint32_t)K - k0) * 4u : 0u, 0x00020000);
 #pragma unroll
     for (int i = 0; i < PSA; ++i) {
-      const int e = tid + 256 * i, row = e / (KCS / 4), q = e % (KCS / 4);
-      const int p = row + base_off;                                                 // from the tile's first token
-      const bool ok = row < rows && (int)t0 + p >= 0 && (int)t0 + p < (int)total && k0 + 4 * q < K;   // K % 4 == 0: whole quads
-      ra[i] = *reinterpret_cast<const float4*>(in_t + (ok ? p * K : 0) + min(k0 + 4 * q, K - 4));
-      keep_a |= ok ? 1u << i : 0u;
+      const uint32_t at = (uint32_t)((tid / (KCS / 4) - skip + 256 / (KCS / 4) * i) * K + qa) * 4u;
+      ra[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, k0 + qa < K ? at : kOutside, 0, 0);
     }
+    const auto rs_w = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(w_h) + ((int64_t)tap0 * N + n0) * K + k0, 0,
+                                                        (((uint32_t)ntap * N - n0) * (uint32_t)K - k0) * 2u, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < PSB; ++i) {
-      const int e = tid + 256 * i, jn = e / (KCS / 8), q = e % (KCS / 8);
-      const int j = jn / TN, n = jn % TN;
-      const bool ok = e < GT * TN * (KCS / 8) && j < ntap && n0 + n < N && k0 + 8 * q < K;   // K % 8 == 0: whole pieces
-      rb[i] = *reinterpret_cast<const u32x4*>(w_h + (ok ? ((tap0 + j) * N + n0 + n) * K : 0) + min(k0 + 8 * q, K - 8));
-      keep_b |= ok ? 1u << i : 0u;
-    }
+    for (int i = 0; i < PSB; ++i) rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, k0 + qb < K ? w_at[i] : kOutside, 0, 0);
   };
-  auto masked_piece = [](u32x4 x, bool keep) {
-    asm volatile("" : "+v"(x));      // the loaded value is needed whatever the mask says: the load stays unconditional
-    return keep ? x : u32x4{0u, 0u, 0u, 0u};
-  };
-  fetch(0);
-  for (int stage = 0; stage < stages; ++stage) {
+  auto masked_piece = [](u32x4 x, bool keep) { return keep ? x : u32x4{0u, 0u, 0u, 0u}; };
+  int tap0 = 0, ntap = min(per_group, ks), k0 = 0;
+  fetch(tap0, ntap, k0);
+  while (tap0 < ks) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PSA; ++i) {
       const int e = tid + 256 * i, row = e / (KCS / 4), q = e % (KCS / 4);
       uint2 t[3];
-      split_quad(masked_quad(ra[i], (keep_a >> i & 1u) ? 0xFu : 0u), t);
+      split_quad(__builtin_bit_cast(float4, ra[i]), t);
 #pragma unroll
       for (int m = 0; m < 3; ++m) *reinterpret_cast<uint2*>(&a_s[m][row][4 * q]) = t[m];
     }
 #pragma unroll
     for (int i = 0; i < PSB; ++i) {
       const int e = tid + 256 * i, jn = e / (KCS / 8);
-      if (e < GT * TN * (KCS / 8))
-        *reinterpret_cast<u32x4*>(&b_s[jn / TN][jn % TN][8 * (e % (KCS / 8))]) = masked_piece(rb[i], keep_b >> i & 1u);
+      if (e < GT * TN * (KCS / 8)) *reinterpret_cast<u32x4*>(&b_s[jn / TN][jn % TN][8 * (e % (KCS / 8))]) = rb[i];
     }
     __syncthreads();
-    int tap0, ntap, k0, base_off;
-    stage_taps(stage, tap0, ntap, k0, base_off);
-    if (stage + 1 < stages) fetch(stage + 1);
-    for (int j = 0; j < ntap; ++j) {
-      const int off = sign * (tap0 + j - half) * dil;
+    const int tap_at = tap0, n_taps = ntap, base_off = first_row(tap0, ntap);
+    k0 += KCS;
+    if (k0 >= K) { k0 = 0; tap0 += per_group; ntap = min(per_group, ks - tap0); }
+    if (tap0 < ks) fetch(tap0, ntap, k0);
+    for (int j = 0; j < n_taps; ++j) {
+      const int off = sign * (tap_at + j - half) * dil;
       const int shift = off - base_off;
       bool valid[U], inside[U];      // inside: the same for all tokens of the sub-tile (no sequence ends under it)
 #pragma unroll
@@ -695,14 +707,11 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
   }
   // accumulator register r of lane half hb: token row 8*(r/4) + 4*hb + r%4 of the sub-tile, output column ql
   const int n = n0 + col0 + ql;
-  const bool n_ok = n < N;
-  auto token_of = [&](int ur) { return t0 + row0 + 32 * (ur / 16) + 8 * ((ur % 16) / 4) + 4 * hb + (ur % 4); };
+  const TileColumn<U> column(h, total, t0, row0 + 4 * hb, n, N);
   if (mode == 0) {
-    forward_result<U, NARROW>(proj, acc, bias, h, Hkv, n, N, n_ok, total, token_of, out0, out1, reinterpret_cast<float*>(&a_s[0][0][0]),
-                              wv, lane);
+    forward_result<U, NARROW>(proj, acc, bias, column, Hkv, out0, out1, reinterpret_cast<float*>(&a_s[0][0][0]), wv, lane);
   } else if (mode == 1) {
-    hidden_backward<U, NARROW>(acc, h, Hkv, n, N, n_ok, total, token_of, pre_prev, out0, part_b,
-                               reinterpret_cast<float*>(&a_s[0][0][0]), wv, lane);
+    hidden_backward<U, NARROW>(acc, column, Hkv, pre_prev, out0, part_b, reinterpret_cast<float*>(&a_s[0][0][0]), wv, lane);
   } else {
     // N = 2 D and D is a multiple of TN: the workgroup's columns are all keys' or all values'
     bf16_t* const dst = n0 < D ? dk : dv;
@@ -888,7 +897,7 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
   const int h = head_group / groups;
   const int chunk = work / (tiles * Hkv * groups);
   const int per = (ks + groups - 1) / groups, tap0 = (head_group % groups) * per, ntap = min(per, ks - tap0);
-  const int off0 = (tap0 - (ks - 1) / 2) * dil, rows = KCT + (ntap - 1) * dil;
+  const int off0 = (tap0 - (ks - 1) / 2) * dil;
   const int tid = threadIdx.x, lane = tid & 63, hb = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wq = wv % (WC * WM), sp = wv / (WC * WM), ci = wq / WM, mi = wq % WM;
@@ -904,28 +913,25 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
   for (int j = 0; j < NTW; ++j)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
-  u32x4 rx[G::PX];
-  float4 rg[G::PG];
+  u32x4 rx[G::PX], rg[G::PG];
   int lo, hi;                    // bounds of the sequence of the slice's token `lane`; empty past the chunk
-  unsigned keep_x, keep_g;
-  auto fetch = [&](int i0) {     // every load unconditional, from addresses inside the arrays
-    keep_x = keep_g = 0u;
+  // Rows of d y past the chunk are zero.  Input rows outside the array and channels past Cin or Cout hold anything: the
+  // sequence's bounds mask them below, or they belong to a sum that is not written.  Rows past those that the taps reach are
+  // not read and all take the last one's line.
+  static_assert(256 % XQ == 0 && 256 % GQ == 0, "a thread keeps its channels");
+  const int mc = min(m0 + EPX * (tid % XQ), Cin - EPX);
+  const X* const x_col = mc < split ? x0_h + mc : x1_h + (mc - split);
+  const uint32_t g_at = ((uint32_t)(tid / GQ) * (uint32_t)Cout + 4 * (tid % GQ)) * 4u;
+  auto fetch = [&](int i0) {
+    const int first = tb32 + i0 + off0, last = min(first + KCT - 1 + (ntap - 1) * dil, total32 - 1);
 #pragma unroll
-    for (int j = 0; j < G::PX; ++j) {
-      const int e = tid + 256 * j, m = m0 + EPX * (e % XQ);
-      const int p = tb32 + i0 + e / XQ + off0;
-      const bool ok = e / XQ < rows && p >= 0 && p < total32 && m < Cin;
-      const int mc = min(m, Cin - EPX);
-      const X* src = (mc < split ? x0_h + mc : x1_h + (mc - split)) + (int64_t)(ok ? p : 0) * stride_tok;
-      rx[j] = *reinterpret_cast<const u32x4*>(src);
-      keep_x |= ok ? 1u << j : 0u;
-    }
+    for (int j = 0; j < G::PX; ++j)
+      rx[j] = *reinterpret_cast<const u32x4*>(x_col + max(0, min(first + tid / XQ + 256 / XQ * j, last)) * stride_tok);
+    const auto rs_g = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g_h) + (int64_t)i0 * Cout + c0, 0,
+                                                        ((uint32_t)min(KCT, len - i0) * (uint32_t)Cout - c0) * 4u, 0x00020000);
 #pragma unroll
-    for (int j = 0; j < G::PG; ++j) {
-      const int e = tid + 256 * j, i = i0 + e / GQ, c = c0 + 4 * (e % GQ);
-      rg[j] = *reinterpret_cast<const float4*>(g_h + (int64_t)(i < len ? i : 0) * Cout + min(c, Cout - 4));
-      keep_g |= (i < len && c < Cout) ? 1u << j : 0u;
-    }
+    for (int j = 0; j < G::PG; ++j)
+      rg[j] = __builtin_amdgcn_raw_buffer_load_b128(rs_g, g_at + (uint32_t)(256 / GQ * j) * (uint32_t)Cout * 4u, 0, 0);
     const int t = i0 + lane < len ? tb32 + i0 + lane : tb32;
     lo = seq_lo[t];
     hi = seq_hi[t];
@@ -941,9 +947,7 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
 #pragma unroll
     for (int j = 0; j < G::PX; ++j) {
       const int e = tid + 256 * j;
-      u32x4 x = rx[j];
-      asm volatile("" : "+v"(x));      // the loaded value is needed whatever the mask says: the load stays unconditional
-      if (!(keep_x >> j & 1u)) x = u32x4{0u, 0u, 0u, 0u};
+      const u32x4 x = rx[j];
       bf16_t* dst = x_s + (e / XQ) * RSX + EPX * (e % XQ);
       if (e < G::XR * XQ) {
         if constexpr (G::kSplit) {
@@ -960,7 +964,7 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
     for (int j = 0; j < G::PG; ++j) {
       const int e = tid + 256 * j;
       uint2 t[3];
-      split_quad(masked_quad(rg[j], (keep_g >> j & 1u) ? 0xFu : 0u), t);
+      split_quad(__builtin_bit_cast(float4, rg[j]), t);
 #pragma unroll
       for (int m = 0; m < 3; ++m) *reinterpret_cast<uint2*>(g_s + (m * KCT + e / GQ) * RSG + 4 * (e % GQ)) = t[m];
     }
@@ -1011,7 +1015,7 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
   }
   const int64_t per_head = (int64_t)Cout * Cin * ks;
   float* out = partial + ((int64_t)chunk * Hkv + h) * per_head;
-  const int ql = lane & 31;
+  const int m = m0 + 32 * mi + (lane & 31), first_c = c0 + 32 * ci;
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
     if (j >= ntap) break;
@@ -1029,13 +1033,18 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
           for (int r = 0; r < 16; ++r) acc[j][r] += red[((k - 1) * WC * WM + wq) * 1024 + r * 64 + lane];
       }
     }
-    if (sp == 0) {
+    // the layout of the weights: [c][m][tap]; a 64-bit row address in scalar registers, the lane's 32 bits beside it
+    if (sp == 0 && m < Cin) {
+      const uint32_t at = ((uint32_t)(4 * hb) * (uint32_t)Cin + m) * (uint32_t)ks + tap0 + j;
+      auto store = [&](bool whole) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = c0 + 32 * ci + 8 * (r / 4) + 4 * hb + (r % 4);
-        const int m = m0 + 32 * mi + ql;
-        if (m < Cin && c < Cout) out[((int64_t)c * Cin + m) * ks + tap0 + j] = acc[j][r];
-      }
+        for (int r = 0; r < 16; ++r) {
+          const int row = 8 * (r / 4) + r % 4;
+          if (whole || first_c + 4 * hb + row < Cout) (out + (int64_t)(first_c + row) * Cin * ks)[at] = acc[j][r];
+        }
+      };
+      if (first_c + 32 <= Cout) store(true);
+      else store(false);
     }
   }
 }
