@@ -737,7 +737,7 @@ conv_split_bf16_kernel(const float* __restrict__ in, const bf16_t* __restrict__ 
   }
 }
 
-// Stage 1 of d W_l: partial[chunk][h][c][m][tap] = sum over the chunk's tokens t of a_{l-1}[t + off][m] * d y_l[t][c],
+// Stage 1 of d W_l: partial[chunk][h][tap][c][m] = sum over the chunk's tokens t of a_{l-1}[t + off][m] * d y_l[t][c],
 // a tiled fp32 product with the tokens as the contraction index (slices of KCW tokens through LDS).  The chunk's
 // sequence bounds are staged in LDS first, so a slice's operands need one round of global loads, not two dependent
 // ones; the output channels are the rows of the matrix tiles, so neighbouring lanes write neighbouring m.
@@ -834,13 +834,12 @@ weight_product_kernel(const float* __restrict__ act_in, const float* __restrict_
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] += red[((k - 1) * WC * WM + wq) * 1024 + r * 64 + lane];
   }
-  const int64_t per_head = (int64_t)Cout * Cin * ks;
-  float* out = partial + ((int64_t)chunk * Hkv + h) * per_head;
+  float* out = partial + (((int64_t)chunk * Hkv + h) * ks + tap) * Cout * Cin;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int c = c0 + 32 * ci + 8 * (r / 4) + 4 * hb + (r % 4);
     const int m = m0 + 32 * mi + ql;
-    if (m < Cin && c < Cout) out[((int64_t)c * Cin + m) * ks + tap] = acc[r];     // the layout of the weights: [c][m][tap]
+    if (m < Cin && c < Cout) out[(int64_t)c * Cin + m] = acc[r];
   }
 }
 
@@ -1013,8 +1012,7 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
       }
     }
   }
-  const int64_t per_head = (int64_t)Cout * Cin * ks;
-  float* out = partial + ((int64_t)chunk * Hkv + h) * per_head;
+  float* out = partial + (((int64_t)chunk * Hkv + h) * ks + tap0) * Cout * Cin;
   const int m = m0 + 32 * mi + (lane & 31), first_c = c0 + 32 * ci;
 #pragma unroll
   for (int j = 0; j < NTW; ++j) {
@@ -1033,14 +1031,15 @@ weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int spli
           for (int r = 0; r < 16; ++r) acc[j][r] += red[((k - 1) * WC * WM + wq) * 1024 + r * 64 + lane];
       }
     }
-    // the layout of the weights: [c][m][tap]; a 64-bit row address in scalar registers, the lane's 32 bits beside it
+    // a 64-bit row address in scalar registers, the lane's 32 bits beside it
     if (sp == 0 && m < Cin) {
-      const uint32_t at = ((uint32_t)(4 * hb) * (uint32_t)Cin + m) * (uint32_t)ks + tap0 + j;
+      float* const out_j = out + (int64_t)j * Cout * Cin;
+      const uint32_t at = (uint32_t)(4 * hb) * (uint32_t)Cin + m;
       auto store = [&](bool whole) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = 8 * (r / 4) + r % 4;
-          if (whole || first_c + 4 * hb + row < Cout) (out + (int64_t)(first_c + row) * Cin * ks)[at] = acc[j][r];
+          if (whole || first_c + 4 * hb + row < Cout) (out_j + (int64_t)(first_c + row) * Cin)[at] = acc[j][r];
         }
       };
       if (first_c + 32 <= Cout) store(true);
@@ -1060,9 +1059,12 @@ chunk_sum_kernel(const float* __restrict__ partial, int64_t n, int chunks, float
   out[i] = acc;
 }
 
-// Stage 2 of every sum of a call in one launch: blockIdx.y picks the sum, out[i] = sum over its chunks in chunk order.
+// Stage 2 of every sum of a call in one launch: blockIdx.y picks the sum, its elements summed over the chunks in chunk order.
+// A weight sum's partials come as [head][tap][c][m], rows of which the workgroups write whole, and go out as [head][c][m][tap]:
+// per is C_l * C_{l-1} there (taps 1: in the order that they come in).  (Partials in the weights' own order, each line written
+// once per tap in pieces of 4 bytes: first layer's weight product 34.1 us, this way 32.0; 4 x 4096 tokens, paper stack.)
 constexpr int kMaxSums = 2 * LTEA_MAX_CNN_LAYERS + 2;
-struct SumSeg { const float* partial; float* out; int64_t n; int chunks; };
+struct SumSeg { const float* partial; float* out; int64_t n; int chunks, taps; int64_t per; };
 struct SumSegs { SumSeg s[kMaxSums]; };
 __global__ void __launch_bounds__(256)
 chunk_sum_all_kernel(const SumSegs S) {
@@ -1072,7 +1074,15 @@ chunk_sum_all_kernel(const SumSegs S) {
   float acc = 0.f;
 #pragma unroll 8
   for (int ch = 0; ch < seg.chunks; ++ch) acc += seg.partial[(int64_t)ch * seg.n + i];
-  seg.out[i] = acc;
+  int64_t o = i;
+  if (seg.taps > 1) {
+    int64_t block, in_block;       // of [head][tap], and the element in it
+    if (seg.n >> 32) { block = i / seg.per; in_block = i - block * seg.per; }
+    else { block = (uint32_t)i / (uint32_t)seg.per; in_block = (uint32_t)i - (uint32_t)block * (uint32_t)seg.per; }
+    const uint32_t head = (uint32_t)block / (uint32_t)seg.taps, tap = (uint32_t)block - head * (uint32_t)seg.taps;
+    o = (head * seg.per + in_block) * seg.taps + tap;
+  }
+  seg.out[o] = acc;
 }
 
 // How a layer's weight product is cut: channel blocks per tile, tiles, tap groups and tokens per partial.
@@ -1117,7 +1127,7 @@ struct Layout {
   float *wf[LTEA_MAX_CNN_LAYERS], *wb[LTEA_MAX_CNN_LAYERS];   // fp32 weight panels of every layer
   void* wq[LTEA_MAX_CNN_LAYERS];              // every layer's weights [Hkv][k][C_l][C_{l-1}] in the storage type (bf16 only)
   void* wqf[LTEA_MAX_CNN_LAYERS];             // every layer's weights [Hkv][k][C_{l-1}][C_l] in the storage type (bf16 only)
-  float* part_w[LTEA_MAX_CNN_LAYERS];         // [chunks][Hkv][C_l][C_{l-1}][k]: partial weight gradients
+  float* part_w[LTEA_MAX_CNN_LAYERS];         // [chunks][Hkv][k][C_l][C_{l-1}]: partial weight gradients
   float* part_b[LTEA_MAX_CNN_LAYERS];         // [tiles of TMC tokens][Hkv][C_l]: partial bias gradients
   float *part_wout, *part_bout;               // [tiles of TMC tokens][Hkv][C_L], [tiles][Hkv]
   size_t bytes;
@@ -1255,8 +1265,8 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
   SumSegs sums;
   int n_sums = 0;
   int64_t n_sum_max = 0;
-  auto second_stage = [&](const float* partial, float* out, int64_t n, int n_chunks) {
-    sums.s[n_sums++] = SumSeg{partial, out, n, n_chunks};
+  auto second_stage = [&](const float* partial, float* out, int64_t n, int n_chunks, int taps = 1, int64_t per = 0) {
+    sums.s[n_sums++] = SumSeg{partial, out, n, n_chunks, taps, per};
     n_sum_max = n > n_sum_max ? n : n_sum_max;
   };
   second_stage(L.part_wout, g.w_out, (int64_t)Hkv * CL, col_chunks);
@@ -1297,7 +1307,7 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
                          L.seq_hi, total, Hkv, W.tiles_n, W.tiles, (int)n_work, W.chunk, L.part_w[l]);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    second_stage(L.part_w[l], g.w[l], (int64_t)Cout * Cin * ks * Hkv, W.chunks);
+    second_stage(L.part_w[l], g.w[l], (int64_t)Cout * Cin * ks * Hkv, W.chunks, ks, (int64_t)Cout * Cin);
     if (l > 0 || dk != nullptr || dv != nullptr) {
       // towards the input: contraction over this layer's output channels, taps mirrored
       bool done = false;
