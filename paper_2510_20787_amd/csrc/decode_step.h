@@ -25,10 +25,13 @@
 // anybody: no fences, which write back a whole L2 each, and no spinning.
 //
 // Measured on the paper's layer (32 query heads on 8, D = 64, 1280 rows): separate streaming, scoring and finishing
-// launches took 28.6 us per eager step of one sequence and 48.3 us for 32 of a rotary model, this launch 12.3 and 23.3 us;
-// a lazy step of 32: 29.8 and 20.1 us.  Handing shares over costs about 5 us at the end (stores, count, records, each a trip
-// past the L2), which is why a head is one workgroup when the heads alone fill the chip and shared out when its rows are
-// long.  With the finishing as a launch of its own for every cache, and nothing counted: 14.7, 25.8 and 22.4 us.  Caches that do
+// launches took 28.6 us per eager step of one sequence and 48.3 us for 32 of a rotary model, the first form of this launch 12.2
+// and 22.7 us; a lazy step of 32: 29.8 and 19.3 us.  With everything that needs no address from memory requested before the first
+// wait (scalar words, eviction keys, the scoring's rows and weights, the first block of rows of either kind, the rows that move)
+// and the descriptors uniform to the compiler: 9.6, 19.8 and 17.4 us.  Handing shares over costs about 5 us at the end (stores,
+// count, records, each a trip past the L2), which is why a head is one workgroup when the heads alone fill the chip and shared
+// out when its rows are long.  The finishing as a launch of its own for every cache, and nothing counted, took 14.7, 25.8 and
+// 22.4 us beside 12.3, 23.3 and 20.1 of the one launch (before those requests).  Caches that do
 // not fit the counting (no budget, or a budget of 2^16 and more, or over 127 KV heads) or whose logit
 // is final at once (rho = 0: the scoring would write the ring slot whose old logit the eviction reads) run the finishing as
 // a launch of its own, decode_finish_kernel.
