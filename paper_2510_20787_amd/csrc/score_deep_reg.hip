@@ -440,7 +440,7 @@ hipError_t launch_score_deep_reg(const ltea_cfg& cfg, const ltea_cnn& cnn, const
   a.d1 = cnn.dilation[0]; a.d2 = cnn.dilation[1]; a.d3 = cnn.dilation[2];
   a.cu = sv.cu_seqlens; a.n_seqs = sv.n_seqs; a.total = sv.total_tokens; a.logits = logits;
   const int TMv = kPos - 2 * (a.d2 + a.d3);
-  a.group_tiles = pick_group_tiles(sv, cfg.Hkv, TMv, kMaxGroupTiles);
+  a.group_tiles = pick_group_tiles(score_batch(sv, cfg.Hkv), TMv, kMaxGroupTiles).tiles;
   a.Hkv = cfg.Hkv;
   const int64_t span = (int64_t)a.group_tiles * TMv;
   const int64_t groups_upper = (sv.total_tokens + span - 1) / span + sv.n_seqs;

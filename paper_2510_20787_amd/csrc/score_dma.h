@@ -3,6 +3,7 @@
 #pragma once
 #include "ltea_common.h"
 #include "ltea_kernels.h"
+#include "score_groups.h"
 
 namespace ltea {
 
@@ -46,22 +47,6 @@ __device__ __forceinline__ float silu_fast(float y) {
   return y * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * y));
 }
 
-// Consecutive tiles per workgroup for a kernel of which `slots` workgroups run at once: the number that makes the launch
-// shortest when a workgroup costs its tiles plus about `startup` tiles' worth of start-up and the grid runs in rounds of
-// `slots` workgroups.  The count of groups is exact for a batch of equal lengths, an upper bound otherwise.
-inline int pick_group_tiles(const SeqView& sv, int Hkv, int tile_tokens, int max_tiles, int startup = 3, int slots = 256) {
-  int best = 1;
-  int64_t best_cost = -1;
-  for (int g = 1; g <= max_tiles; ++g) {
-    const int64_t span = (int64_t)g * tile_tokens;
-    const int64_t groups = (int64_t)sv.n_seqs * sv.max_seqlen == sv.total_tokens
-                               ? (int64_t)sv.n_seqs * ((sv.max_seqlen + span - 1) / span)
-                               : sv.total_tokens / span + sv.n_seqs;
-    const int64_t rounds = (groups * Hkv + slots - 1) / slots;
-    const int64_t cost = rounds * (g + startup);
-    if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = g; }
-  }
-  return best;
-}
+inline ScoreBatch score_batch(const SeqView& sv, int Hkv) { return ScoreBatch{sv.n_seqs, sv.total_tokens, sv.max_seqlen, Hkv}; }
 
 }  // namespace ltea

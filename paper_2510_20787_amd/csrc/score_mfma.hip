@@ -12,22 +12,26 @@
 //                               [Hkv][k][32][2D] (channels zero-padded to 32) in the workspace, so that the main
 //                               kernel can fetch a panel with coalesced 16-byte loads;
 //   score_mfma_kernel           one workgroup = up to 8 consecutive tiles of one (sequence, KV head), 32 tokens per wave in
-//                               a tile.  The weights of 128 input channels (D = 64: all; D = 128: the keys', then the
-//                               values') lie in LDS while all its tiles pass, one accumulator per tile, so they are
-//                               brought there once or twice per workgroup.  A stage is 64 channels of a tile's rows with
+//                               a tile.  The weights of some input channels lie in LDS while all its tiles pass, one
+//                               accumulator per tile: 128 channels (D = 64: all; D = 128: the keys', then the values'), or,
+//                               for a workgroup of a single tile, 64.  A stage is 64 channels of a tile's rows with
 //                               their halo of half*dil rows (zeros outside the sequence): it is multiplied out of one of
 //                               two LDS buffers while the next one is stored into the other and the two after that are
 //                               on their way to registers.  One barrier per stage; operand reads run three matrix
-//                               instructions ahead of their use.
+//                               instructions ahead of their use; a wave past the sequence's end multiplies nothing.
 //
 // What bounds it: the rows' way from memory, 64 channels (128 bytes) out of every token's 2 D Hkv: without the products of all
-// but one tap it takes 194 of 231 us (16 sequences of 1024 to 16384 tokens, 16 heads of D = 128, k = 5) and 125 of 150 (32768
-// tokens, 32 heads, k = 7), 5.5 and 4.3 TB/s where a linear read reaches 6.6.  Rows of all 128 bytes of a channel half at once
-// give 4 % of that, an order of heads that keeps an XCD's neighbouring nothing, non-temporal loads 2 % here and minus 15 % on
-// 4 x 4096 tokens (32.2 -> 37.2 us: the attention's and the next call's rows then come from HBM).  What was slow before, with
-// 128-token tiles of 128 channels in one buffer: at k = 7 one workgroup per CU, in lockstep through load, store and products
-// (the matrix pipe busy for 57 of 197 us).  Before -> now, us per call: the two shapes above 259 -> 231 and 199 -> 150, 2048
-// tokens x 32 heads, k = 7 22.4 -> 14.5, 512 x 16, k = 5 17.4 -> 11, 4 x 4096 x 16, k = 5 32.9 -> 31.9, D = 64, k = 7 30.0 -> 25.2.
+// but one tap it takes 194 of 231 us (119498 tokens in 16 sequences of 1024 to 16384, 16 heads of D = 128, k = 5) and 125 of 150
+// (32768 tokens, 32 heads, k = 7), 5.0 and 4.3 TB/s where a linear read reaches 6.6.  Stages of a whole half of the channels (rows
+// of 256 bytes) give 4 % of that, an order of heads that keeps an XCD's neighbouring nothing, non-temporal loads 2 % here and
+// minus 15 % on 4 x 4096 tokens (32.2 -> 37.2 us: the attention's and the next call's rows then come from HBM).  What was slow
+// before, with 128-token tiles of 128 channels in one buffer, the weights staged for groups of four tiles: at k = 7 one workgroup
+// per CU, in lockstep through load, store and products (the matrix pipe busy for 57 of 197 us).  Before -> groups of up to 8 tiles,
+// us per call: the two shapes above 259 -> 231 and 199 -> 150, 4 x 4096 x 16, k = 5 32.9 -> 31.9, D = 64, k = 7 30.0 -> 25.2.
+// Short sequences: a workgroup's start and, at k >= 7, a CU's whole LDS for it made groups slower than that form (64 x 100 tokens,
+// 32 heads: D = 64, k = 7 47.3 us then, 57.8 in groups; k = 1, for which there was a general instance only, 24.2 and 45.2); with single
+// tiles, and idle waves leaving the matrix pipe to the others, 29.4 and 17.7.  One sequence of 100 tokens, 8 heads, k = 7: D = 64
+// 8.0, 8.8, now 7.0, D = 128 11.4, 11.8, now 9.0.
 // Tried: the weights beside every stage instead of resident (240 and 154 us); direct global-to-LDS rows of 32 channels,
 // five stages deep, shared or private to the waves (274, 290 and 148, 150 us: pieces of 64 bytes).
 #include <type_traits>
@@ -40,13 +44,13 @@ namespace ltea {
 namespace {
 
 constexpr int CP = 32;        // channels padded to one MFMA tile
-constexpr int HC = 128;       // input channels whose weights are in LDS at a time
 constexpr int SC = 64;        // input channels per stage: token rows of 128 bytes, all of them keys' or all values'
 constexpr int kMaxRho = 4;    // largest half receptive field the token tile is sized for
 constexpr int kMaxTaps = 2 * kMaxRho + 1;
-constexpr int kMaxGroup = 8;  // tiles per workgroup
+constexpr int kMaxGroup = kScoreMfmaMaxGroup;      // tiles per workgroup
+constexpr int weight_channels(int max_group) { return max_group == 1 ? 64 : 128; }     // whose weights are in LDS at a time
 constexpr int stage_bytes(int waves) { return (32 * waves + 2 * kMaxRho) * SC * 2; }   // 32 tokens per wave and the halo
-constexpr int kTapB = CP * HC * 2;                 // one tap's weights of HC channels
+constexpr int tap_bytes(int channels) { return CP * channels * 2; }                    // one tap's weights
 
 // panels[h][tap][c][m] = W[h][c][m][tap] for c < C, 0 for C <= c < 32
 __global__ void __launch_bounds__(256)
@@ -62,22 +66,23 @@ score_weight_panels_kernel(const uint16_t* __restrict__ W, uint16_t* __restrict_
   panels[idx] = c < C ? W[((h * C + c) * C2 + m) * ks + tap] : (uint16_t)0;
 }
 
-// KS: the kernel size, 0: any up to kMaxTaps.  NW: waves; four where two workgroups share a CU's LDS (k <= 5: 76 KB each; one hides
-// the start of the other: 265 -> 231 us on the ragged shape above), eight where one fills it.
-template <int D, int KS, int NW>
-__global__ void __launch_bounds__(64 * NW, 2)
+// KS: the kernel size.  NW: waves; four where two workgroups share a CU's LDS (k <= 5, groups: 76 KB each; one hides the start of
+// the other: 265 -> 231 us on the ragged shape above), eight where one fills it.  MG: most tiles per workgroup, kMaxGroup or 1
+// (43 to 71 KB of LDS for k = 1 to 9: two to four workgroups per CU, by the registers too).
+template <int D, int KS, int NW, int MG>
+__global__ void __launch_bounds__(64 * NW, MG == 1 && KS < 5 ? 4 : 2)
 score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int64_t st, int64_t sh,
                   const bf16_t* __restrict__ panels, const float* __restrict__ bias,
-                  const bf16_t* __restrict__ w_out, const float* __restrict__ b_out, int C, int any_ks, int dil,
+                  const bf16_t* __restrict__ w_out, const float* __restrict__ b_out, int C, int dil,
                   const int32_t* __restrict__ cu, int n_seqs, int Hkv, int64_t total, float* __restrict__ logits,
                   int group_tiles) {
   constexpr int kThreads = 64 * NW, TM = 32 * NW, kStageB = stage_bytes(NW);
+  constexpr int HC = weight_channels(MG), kTapB = tap_bytes(HC);
   constexpr int C2 = 2 * D, NH = C2 / HC, SPT = HC / SC;      // input channels, passes over the tiles, stages per tile and pass
   extern __shared__ __align__(1024) unsigned char smem[];
-  const int ks = KS > 0 ? KS : any_ks;
-  const int rho = (ks - 1) / 2 * dil;
+  const int rho = (KS - 1) / 2 * dil;
   unsigned char* const w_lds = smem;                          // [tap][channel] rows of HC inputs
-  unsigned char* const x_lds = smem + ks * kTapB;             // two stages of token rows
+  unsigned char* const x_lds = smem + KS * kTapB;             // two stages of token rows
   float* const out_lds = reinterpret_cast<float*>(x_lds + 2 * kStageB);     // bias, output projection
 
   // heads fastest: workgroups that run together read neighbouring pieces of the same rows, and where the heads are a multiple
@@ -86,25 +91,26 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   const int tid = threadIdx.x, lane = tid & 63, ql = lane & 31, hb = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // weights of one half: 16 pieces of 16 bytes per row, piece p of row c to place p ^ (c & 15)
-  const int w_row = tid >> 4, w_piece = tid & 15;
-  constexpr int kWRows = kThreads / 16, kWTaps = KS > 0 ? KS : kMaxTaps;            // rows per pass
-  const bf16_t* const w_src = panels + ((int64_t)h * ks * CP + w_row) * C2 + w_piece * 8;
-  unsigned char* const w_dst = w_lds + w_row * (HC * 2) + ((w_piece ^ (w_row & 15)) << 4);
-  u32x4 wreg[kWTaps][CP / kWRows];
+  // weights of one pass: piece p of channel c's row to place p ^ (c & 15) or, in rows of half as many, p ^ ((c >> 1) & 7), so that the
+  // operand reads of 16 consecutive channels at one piece cover all 64 banks
+  constexpr int kWPieces = HC / 8, kWRows = kThreads / kWPieces;      // pieces per row, rows per pass of the threads
+  auto w_place = [](int row) { return HC == 128 ? row & 15 : (row >> 1) & 7; };
+  const int w_row = tid / kWPieces, w_piece = tid % kWPieces;
+  const bf16_t* const w_src = panels + ((int64_t)h * KS * CP + w_row) * C2 + w_piece * 8;
+  unsigned char* const w_dst = w_lds + w_row * (HC * 2) + ((w_piece ^ w_place(w_row)) << 4);
+  u32x4 wreg[KS][CP / kWRows];
   auto load_weights = [&](int half) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < kWTaps; ++i)
+    for (int i = 0; i < KS; ++i)
 #pragma unroll
       for (int j = 0; j < CP / kWRows; ++j)
-        wreg[i][j] = *reinterpret_cast<const u32x4*>(w_src + ((int64_t)(KS > 0 || i < ks ? i : 0) * CP + j * kWRows) * C2 + half * HC);
+        wreg[i][j] = *reinterpret_cast<const u32x4*>(w_src + ((int64_t)i * CP + j * kWRows) * C2 + half * HC);
   };
   auto store_weights = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < kWTaps; ++i)
+    for (int i = 0; i < KS; ++i)
 #pragma unroll
-      for (int j = 0; j < CP / kWRows; ++j)
-        if (KS > 0 || i < ks) *reinterpret_cast<u32x4*>(w_dst + i * kTapB + j * kWRows * (HC * 2)) = wreg[i][j];
+      for (int j = 0; j < CP / kWRows; ++j) *reinterpret_cast<u32x4*>(w_dst + i * kTapB + j * kWRows * (HC * 2)) = wreg[i][j];
   };
   load_weights(0);
   if (tid < CP) {
@@ -160,9 +166,9 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   };
   const int n_stages = NH * n_tiles * SPT;
 
-  f32x16 acc[kMaxGroup];
+  f32x16 acc[MG];
 #pragma unroll
-  for (int t = 0; t < kMaxGroup; ++t)
+  for (int t = 0; t < MG; ++t)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
 
@@ -170,14 +176,14 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   constexpr int NS = SC / 16, kAhead = 3, kOps = 4;
   static_assert(NS == kOps, "a step's operands have the place of its channels");
   const unsigned char* const a_base = w_lds + ql * (HC * 2);                  // channel ql
-  const int a_swz = ((ql & 15) ^ hb) << 4;
+  const int a_swz = (w_place(ql) ^ hb) << 4;
   bf16x8 a_op[kOps], b_op[kOps];
   struct TapRow { const unsigned char* row; int swz; };
-  auto multiply = [&](f32x16& sum, int sub) __attribute__((always_inline)) {
+  auto multiply = [&](f32x16& sum, int buf, int sub) __attribute__((always_inline)) {
     auto tap_row = [&](int tap) __attribute__((always_inline)) {
       int row = 32 * wv + ql + tap * dil;
       asm volatile("" : "+v"(row));      // worked out here: kept for all taps these addresses are many registers
-      return TapRow{x_lds + sub * kStageB + row * (SC * 2), (((row >> 1) & 7) ^ hb) << 4};
+      return TapRow{x_lds + buf * kStageB + row * (SC * 2), (((row >> 1) & 7) ^ hb) << 4};
     };
     auto read_step = [&](const TapRow& at, int tap, int mc) __attribute__((always_inline)) {
       a_op[mc] = *reinterpret_cast<const bf16x8*>(a_base + tap * kTapB + (a_swz ^ (SC * 2 * sub + 32 * mc)));
@@ -186,29 +192,22 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
     TapRow at = tap_row(0);
 #pragma unroll
     for (int mc = 0; mc < kAhead; ++mc) read_step(at, 0, mc);
-    auto one_tap = [&](int tap) __attribute__((always_inline)) {
-      const int next = tap + 1 < ks ? tap + 1 : tap;
+#pragma unroll
+    for (int tap = 0; tap < KS; ++tap)
 #pragma unroll
       for (int mc = 0; mc < NS; ++mc) {
-        if (mc + kAhead == NS) at = tap_row(next);
-        const int to = (mc + kAhead) % NS;
-        if (mc + kAhead < NS) read_step(at, tap, to);
-        else if (KS == 0 || tap + 1 < KS) read_step(at, next, to);
+        const int ahead = (mc + kAhead) % NS, tap_ahead = tap + (mc + kAhead) / NS;
+        if (tap_ahead < KS) {
+          if (ahead == 0) at = tap_row(tap_ahead);
+          read_step(at, tap_ahead, ahead);
+        }
         sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_op[mc], b_op[mc], sum, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
-    };
-    if constexpr (KS > 0) {
-#pragma unroll
-      for (int tap = 0; tap < KS; ++tap) one_tap(tap);
-    } else {
-#pragma unroll 1
-      for (int tap = 0; tap < ks; ++tap) one_tap(tap);
-    }
   };
 
   // Stage s: its rows are in buffer s & 1; those of s + 1 go to the other one, s + 2 and s + 3 are on their way.
-  static_assert(SPT == 2, "a stage's buffer and registers are those of its part of the tile");
+  static_assert(SPT == 2 || MG == 1, "a stage's buffer and registers are those of its part of the tile, or of the only tile's pass");
   request(xreg[0]);
   request(xreg[1]);
   deposit(xreg[0], 0);
@@ -216,27 +215,35 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   store_weights();
   __syncthreads();
   int at = 0;
-  auto stage = [&](f32x16& sum, auto sub) __attribute__((always_inline)) {
-    constexpr int S = decltype(sub)::value;
+  auto stage = [&](f32x16& sum, int t, auto buffer, int sub) __attribute__((always_inline)) {
+    constexpr int S = decltype(buffer)::value;
     if (at + 1 < n_stages) deposit(xreg[S ^ 1], S ^ 1);
     if (at + 3 < n_stages) request(xreg[S ^ 1]);
     __builtin_amdgcn_sched_barrier(0);      // the requests leave before the products
-    multiply(sum, S);
+    if (g0 + t * TM + 32 * wv < n) multiply(sum, S, sub);      // (a wave past the sequence's end has no tokens)
     __syncthreads();
     ++at;
   };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
 #pragma unroll
   for (int half = 0; half < NH; ++half) {
     if (half > 0) {          // the other channels' weights; everyone is done with the ones before
-      load_weights(half);
+      if (MG > 1) load_weights(half);
       store_weights();
       __syncthreads();
     }
+    if constexpr (MG == 1) {
+      if (half + 1 < NH) load_weights(half + 1);      // they arrive under this pass's products
+      if (half % 2 == 0) stage(acc[0], 0, even, 0);
+      else stage(acc[0], 0, odd, 0);
+    } else {
 #pragma unroll
-    for (int t = 0; t < kMaxGroup; ++t) {
-      if (t < n_tiles) {     // uniform
-        stage(acc[t], std::integral_constant<int, 0>{});
-        stage(acc[t], std::integral_constant<int, 1>{});
+      for (int t = 0; t < MG; ++t) {
+        if (t < n_tiles) {     // uniform
+          stage(acc[t], t, even, 0);
+          stage(acc[t], t, odd, 1);
+        }
       }
     }
   }
@@ -249,7 +256,7 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
     wo[r] = out_lds[CP + 8 * (r / 4) + 4 * hb + (r % 4)];
   }
 #pragma unroll
-  for (int t = 0; t < kMaxGroup; ++t) {
+  for (int t = 0; t < MG; ++t) {
     if (t < n_tiles) {
       float z = 0.f;
 #pragma unroll
@@ -264,7 +271,9 @@ score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, in
   }
 }
 
-size_t lds_bytes(int ks, int waves) { return (size_t)ks * kTapB + (size_t)2 * stage_bytes(waves) + 2 * CP * sizeof(float); }
+constexpr size_t lds_bytes(int ks, int waves, int group) {
+  return (size_t)ks * tap_bytes(weight_channels(group)) + (size_t)2 * stage_bytes(waves) + 2 * CP * sizeof(float);
+}
 
 template <int D>
 hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v, int64_t st, int64_t sh,
@@ -281,26 +290,38 @@ hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const vo
     panels = workspace;
   }
   if (score_reg_supported(cfg, cnn)) return launch_score_reg(cfg, cnn, k, v, st, sh, sv, logits, panels, stream);
-  auto launch = [&](auto taps, auto waves) {
-    constexpr int KS = decltype(taps)::value, NW = decltype(waves)::value, TM = 32 * NW;
-    // a workgroup's start (sequence, weights, first rows) costs about a tile: 4.3 us and 3.7 us per tile of D = 128, k = 5
-    const int group = pick_group_tiles(sv, cfg.Hkv, TM, kMaxGroup, 1, NW == 4 ? 512 : 256);
-    const int64_t span = (int64_t)group * TM, groups_upper = (sv.total_tokens + span - 1) / span + sv.n_seqs;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_mfma_kernel<D, KS, NW>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds_bytes(ks, NW));
+  const ScoreMfmaTiling tiling = score_mfma_tiling(score_batch(sv, cfg.Hkv), ks);
+  auto launch = [&](auto taps, auto waves, auto tiles) {
+    constexpr int KS = decltype(taps)::value, NW = decltype(waves)::value, MG = decltype(tiles)::value;
+    constexpr size_t lds = lds_bytes(KS, NW, MG);
+    const int64_t span = (int64_t)tiling.tiles * 32 * NW, groups_upper = (sv.total_tokens + span - 1) / span + sv.n_seqs;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_mfma_kernel<D, KS, NW, MG>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return;
-    hipLaunchKernelGGL((score_mfma_kernel<D, KS, NW>), dim3((unsigned)(groups_upper * cfg.Hkv)), dim3(64 * NW), lds_bytes(ks, NW), stream,
+    hipLaunchKernelGGL((score_mfma_kernel<D, KS, NW, MG>), dim3((unsigned)(groups_upper * cfg.Hkv)), dim3(64 * NW), lds, stream,
                        static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), st, sh,
                        static_cast<const bf16_t*>(panels), cnn.bias[0], static_cast<const bf16_t*>(cnn.w_out),
-                       cnn.b_out, cnn.c_out[0], ks, cnn.dilation[0], sv.cu_seqlens, sv.n_seqs, cfg.Hkv, sv.total_tokens, logits, group);
+                       cnn.b_out, cnn.c_out[0], cnn.dilation[0], sv.cu_seqlens, sv.n_seqs, cfg.Hkv, sv.total_tokens, logits,
+                       tiling.tiles);
     e = hipGetLastError();
   };
-  constexpr std::integral_constant<int, 4> four{};
-  constexpr std::integral_constant<int, 8> eight{};
-  if (ks == 3) launch(std::integral_constant<int, 3>{}, four);
-  else if (ks == 5) launch(std::integral_constant<int, 5>{}, four);
-  else if (ks == 7) launch(std::integral_constant<int, 7>{}, eight);
-  else launch(std::integral_constant<int, 0>{}, eight);
+  auto launch_taps = [&](auto taps) {
+    constexpr int KS = decltype(taps)::value;
+    if constexpr (KS > 3) {
+      if (!tiling.single) {
+        constexpr int kWaves = KS <= 5 ? 4 : 8;      // score_mfma_tiling's
+        return launch(taps, std::integral_constant<int, kWaves>{}, std::integral_constant<int, kMaxGroup>{});
+      }
+    }
+    launch(taps, std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+  };
+  if (ks == 1) launch_taps(std::integral_constant<int, 1>{});
+  else if (ks == 7) launch_taps(std::integral_constant<int, 7>{});
+  else if (ks == 9) launch_taps(std::integral_constant<int, 9>{});
+  else if constexpr (D == 128) {      // D = 64: the register-stationary kernel takes k = 3 and 5
+    if (ks == 3) launch_taps(std::integral_constant<int, 3>{});
+    else launch_taps(std::integral_constant<int, 5>{});
+  }
   return e;
 }
 

@@ -271,7 +271,7 @@ score_reg_panels_kernel(const uint16_t* __restrict__ W, uint16_t* __restrict__ p
 template <int KS, bool RAW>
 hipError_t run(const ltea_cfg& cfg, const ltea_cnn& cnn, const void* k, const void* v, int64_t st, int64_t sh,
                const SeqView& sv, float* logits, const void* weights, hipStream_t stream) {
-  const int gt = pick_group_tiles(sv, cfg.Hkv, TM, kMaxGroupTiles);
+  const int gt = pick_group_tiles(score_batch(sv, cfg.Hkv), TM, kMaxGroupTiles).tiles;
   const int64_t groups_upper = (sv.total_tokens + gt * TM - 1) / (gt * TM) + sv.n_seqs;
   hipLaunchKernelGGL((score_reg_kernel<KS, RAW>), dim3((unsigned)(groups_upper * cfg.Hkv)), dim3(kThreads), 0, stream,
                      static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v), st, sh,

@@ -1,6 +1,6 @@
-"""Scoring by the LDS-operand kernel against the oracle where its tiles can go wrong: one token and one tile more or less than a
-group of tiles, tiles of 128 (k <= 5) and 256 tokens, both head sizes, every kernel size and the widest reach, fewer channels than a
-matrix tile, sequences without a whole tile.  Bars as in test_gpu_parity."""
+"""Scoring by the LDS-operand kernel against the oracle where its tiles can go wrong: one token more or less than a tile of 128
+(k <= 5, and single tiles) or 256 tokens, both head sizes, every kernel size and the widest reach, fewer channels than a matrix tile,
+sequences without a whole tile, many short ones.  Bars as in test_gpu_parity."""
 import pytest
 
 from oracle import ltea_oracle as orc
@@ -12,6 +12,8 @@ from tests.test_gpu_parity import logit_eps
 
 pytestmark = pytest.mark.gpu
 
+SHORT = [(i * 37) % 130 for i in range(70)]
+
 
 @pytest.mark.parametrize("D,Hkv,kernel,channels,dilation,lens", [
     (128, 3, 1, 32, 1, [129, 1, 0, 300]),
@@ -22,7 +24,13 @@ pytestmark = pytest.mark.gpu
     (128, 1, 9, 7, 1, [513, 9, 64]),
     (64, 2, 7, 32, 1, [2049, 511, 2, 256]),
     (64, 8, 9, 30, 1, [700, 257]),
-    (64, 3, 5, 32, 2, [1100, 128, 33]),
+    (64, 3, 1, 32, 3, [1100, 128, 33]),
+    (64, 8, 7, 32, 1, SHORT),
+    (64, 2, 9, 32, 1, SHORT),
+    (64, 2, 1, 9, 1, SHORT),
+    (128, 2, 3, 32, 3, SHORT),
+    (128, 2, 5, 32, 2, SHORT),
+    (128, 2, 7, 32, 1, SHORT),
 ])
 def test_score_tiles(D, Hkv, kernel, channels, dilation, lens):
     w = wl.make_prefill("score_tiles", 500 + D + kernel + Hkv, "bf16", lens, Hkv, Hkv, D, 64, 16, 0, 0.0, cnn_kernel=(kernel,),
