@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from tests.test_gpu_score_tiles import CASES
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -34,3 +36,9 @@ def test_short_sequences_take_single_tiles(tiling, lens, Hkv, kernel):
 def test_long_runs_stay_together(tiling, lens, Hkv, kernel):
     waves, tiles, single = tiling(lens, Hkv, kernel)
     assert not single and tiles > 1 and waves == (4 if kernel == 5 else 8)
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_gpu_cases_run_the_tiling_they_are_meant_for(tiling, case):
+    _, Hkv, kernel, _, _, lens, expected = case
+    assert tiling(lens, Hkv, kernel) == expected
