@@ -1098,11 +1098,11 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
     for (int i = 0; i < MS::NV; ++i)
       R.v[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, vo + (uint32_t)(MS::RPI * i * D) * 2u, 0, kNonTemporal);
   };
-  // Requests, before anything is known of the sequence: the compact segment's keys, where the token leaving the window may go;
-  // the incoming row; a wave's first rows, whatever they hold: settle() takes out what is not there yet.
-  // Then the scalar words, the decision and everything up to the stream's loop pass under the rows' flight.  What it replaces:
-  // the words as vector loads, each waiting for the rows before it, and the keys requested once the count was known, read a
-  // second time for the victim's slot: the decision was there 3 to 4 us after a launch's start.
+  // Requests, before anything is known of the sequence: the compact segment's keys, where the token leaving the window may go; on
+  // the matrix path a wave's first rows, whatever they hold: settle() takes out what is not there yet.  Then the scalar words, the
+  // decision and everything up to the stream's loop pass under the rows' flight.  What it replaces: the words as vector loads, each
+  // waiting for the rows before it, and the keys requested once the count was known, read a second time for the victim's slot: the
+  // decision was there 3 to 4 us after a launch's start.
   HeldKeys held;
   held = load_held_keys<NT>(decides ? budget : 1, decides ? C.ret_score + head * budget : reinterpret_cast<const float*>(C.n_seen),
                             decides ? C.ret_pos + head * budget : C.n_seen);      // (no branch: they would be waited for at its end)
@@ -1113,15 +1113,31 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
   constexpr int RIF = GT >= 5 ? 1 : GT >= 4 ? 2 : kRowsInFlight;   // rows in flight per lane group (registers: GT states per lane)
   const int sub = lane % LPR, grp = lane / LPR, r_first = r_begin + wave * GPW + grp;
   u32x4 kraw[RIF], vraw[RIF];
-  // (VALU path: if all of a workgroup's first rows are ring slots)
-  const bool early = GT >= 5 ? first < blk_end : r_begin + GPB * RIF <= window && r_begin + GPB * RIF <= r_end;
+  // Which first rows are requested ahead.  Matrix path, D = 64: all.  Steps of 1 / 8 / 32 / 128 sequences, 32 query heads on 8, a
+  // window of 800, a budget of 512, the paper's stack, us without -> with: full caches 10.2 12.7 19.8 57.7 -> 9.8 13.0 19.5 57.6
+  // (lazy 9.7 10.8 18.5 55.8 -> 9.5 10.6 17.8 54.9); sequences of 200 tokens, where most of the rows do not exist yet, 9.0 11.1
+  // 12.8 27.1 -> 9.0 11.4 13.6 27.7 (lazy 8.3 9.1 11.1 25.3 -> 8.4 9.4 11.0 24.9); of 40 tokens 9.0 10.3 12.1 24.4 -> 9.0 11.6
+  // 13.2 26.5.
+  // D = 128, where eight waves' first rows, 128 KB, keep a CU's vector cache for about a microsecond, beside scoring workgroups:
+  // none (a window of 1024, k = 5: full 12.0 18.1 36.3 124.9 -> 12.5 19.4 37.3 125.3, 200 tokens 10.2 15.4 22.0 52.1 -> 11.1 15.8
+  // 22.8 53.0, 40 tokens 10.2 13.8 20.5 45.1 -> 10.9 15.4 21.7 49.1).  Without scoring, whole heads and halves gain from all of
+  // them (32 sequences: full 36.5 -> 35.9, no budget 25.2 -> 23.8; but 40 tokens 15.2 -> 17.6), shares down to a seventh from the
+  // ring's (8 sequences: full 17.4 -> 17.0, only the ring full 15.7 -> 14.9; but 40 tokens 11.5 -> 13.2), smaller ones from none
+  // (one sequence: full 12.5 -> 12.7, 200 tokens 10.4 -> 11.3).
+  // VALU path: if all of a workgroup's first rows are ring slots, once the token index has come.
+  constexpr bool kAhead = GT >= 5 && (D == 64 || SK == 0);
+  const int ahead = D == 64 || nsplit <= 2 ? all_blocks : nsplit < 8 ? ring_blocks : 0;
+  const bool early = GT >= 5 ? kAhead && first < (blk_end < ahead ? blk_end : ahead)
+                             : r_begin + GPB * RIF <= window && r_begin + GPB * RIF <= r_end;
   const T* kr = static_cast<const T*>(C.k_ret) + head * budget * D;
   const T* vr = static_cast<const T*>(C.v_ret) + head * budget * D;
-  if constexpr (GT >= 5) {
-    const bool ring = first < ring_blocks;
-    const int row0 = 32 * (ring ? first : first - ring_blocks), left = (ring ? window : budget) - row0;
-    load_rows((ring ? kw : kr) + (early ? (int64_t)row0 * D : 0), (ring ? vw : vr) + (early ? (int64_t)row0 * D : 0),
-              !early ? 0 : left < 32 ? left : 32, cur);
+  if constexpr (kAhead) {
+    if (D == 64 || early) {      // (D = 64: a branch costs more than requests of nothing)
+      const bool ring = first < ring_blocks;
+      const int row0 = 32 * (ring ? first : first - ring_blocks), left = (ring ? window : budget) - row0;
+      load_rows((ring ? kw : kr) + (early ? (int64_t)row0 * D : 0), (ring ? vw : vr) + (early ? (int64_t)row0 * D : 0),
+                !early ? 0 : left < 32 ? left : 32, cur);
+    }
   }
   read_here(t);
   read_here(count_word);
