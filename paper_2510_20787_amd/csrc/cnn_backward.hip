@@ -876,6 +876,8 @@ inline int weight_groups(int ks, int dil, bool split) {
 }
 
 // Input channel m is x0's for m < split, else x1's channel m - split (the keys and the values; one array for X = float).
+// <float, 2, 1> runs two waves per SIMD: 30.1 and 56.1 us (4 x 4096 tokens, 8 heads, a k = 3 layer of 32 -> 64 and a k = 5 layer of
+// 32 -> 128 channels); held to the registers of three 31.9 and 58.8.
 template <class X, int WC, int WM>
 __global__ void __launch_bounds__(256)
 weight_split_kernel(const X* __restrict__ x0, const X* __restrict__ x1, int split, int64_t stride_tok, int64_t stride_head,

@@ -24,17 +24,16 @@
 // atomics, which go past the XCD's own L2; a workgroup waits for its stores before it counts itself, and nobody waits for
 // anybody: no fences, which write back a whole L2 each, and no spinning.
 //
-// Measured on the paper's layer (32 query heads on 8, D = 64, 1280 rows): separate streaming, scoring and finishing
-// launches took 28.6 us per eager step of one sequence and 48.3 us for 32 of a rotary model, the first form of this launch 12.2
-// and 22.7 us; a lazy step of 32: 29.8 and 19.3 us.  With everything that needs no address from memory requested before the first
-// wait (scalar words, eviction keys, the scoring's rows and weights, the first block of rows of either kind, the rows that move)
-// and the descriptors uniform to the compiler: 9.6, 19.8 and 17.4 us.  Handing shares over costs about 5 us at the end (stores,
-// count, records, each a trip past the L2), which is why a head is one workgroup when the heads alone fill the chip and shared
-// out when its rows are long.  The finishing as a launch of its own for every cache, and nothing counted, took 14.7, 25.8 and
-// 22.4 us beside 12.3, 23.3 and 20.1 of the one launch (before those requests).  Caches that do
-// not fit the counting (no budget, or a budget of 2^16 and more, or over 127 KV heads) or whose logit
-// is final at once (rho = 0: the scoring would write the ring slot whose old logit the eviction reads) run the finishing as
-// a launch of its own, decode_finish_kernel.
+// Measured on the paper's layer (32 query heads on 8, D = 64, 1280 rows), us per eager step of one sequence, per eager step of
+// 32 of a rotary model and per lazy step of 32: separate streaming, scoring and finishing launches 28.6, 48.3 and 29.8; one
+// streaming launch with the finishing as a launch of its own and nothing counted 14.7, 25.8 and 22.4, with the finishing inside
+// 12.3, 23.3 and 20.1, after changes of the merge 12.2, 22.7 and 19.3; with everything that needs no address from memory
+// requested before the first wait (scalar words, eviction keys, the scoring's rows and weights, at D = 64 the first block of
+// rows of either kind, the rows that move) and the descriptors uniform to the compiler 9.6, 19.8 and 17.4. Handing shares over
+// costs about 5 us at the end (stores, count, records, each a trip past the L2), which is why a head is one workgroup when the
+// heads alone fill the chip and shared out when its rows are long. Caches that do not fit the counting (no budget, or a budget
+// of 2^16 and more, or over 127 KV heads) or whose logit is final at once (rho = 0: the scoring would write the ring slot whose
+// old logit the eviction reads) run the finishing as a launch of its own, decode_finish_kernel.
 //
 // The lazy step (Section 3.1.3, lazy scoring) is the same launch without the scoring: logits are
 // produced between steps by the batched scoring of lazy.hip, n_scored is left alone and a token that leaves the window
@@ -1371,7 +1370,9 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
             for (int r = 0; r < 4; ++r) o[d][r] = fabsf(all[d][r]) < INFINITY ? all[d][r] : o[d][r];
         }
       }
-      rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);      // (in every pass: not kept over the next one)
+      // (in every pass: not kept over the next one; also where the finishing is a launch of its own: a branch around it costs more than
+      // the 16 bytes a thread, 32 query heads on 2 of D = 64, 128 sequences 21.7 -> 24.9 us, one sequence of 32 on 8 9.7 -> 10.0)
+      rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);
       // merge of the waves, fixed order; register r of o[d] is head dimension 16*d + 4*kg + r of column c16
       l_run += __shfl_xor(l_run, 16, kWave);
       l_run += __shfl_xor(l_run, 32, kWave);
@@ -1495,7 +1496,7 @@ decode_step_kernel(CnnDev cnn, CacheDev C, StepParams P, const T* __restrict__ q
             for (int i = 0; i < EPL; ++i) acc[g][i] = fmaf(pr[g][u], vf[i], acc[g][i]);
         }
       }
-      rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);      // (in every pass: not kept over the next one)
+      rows = load_moving_rows<T, D>(C, P, k_new, v_new, head, t);      // (as above)
       // merge: the row groups of a wave by lane exchange, then the waves through LDS (fixed order -> deterministic)
 #pragma unroll
       for (int g = 0; g < GT; ++g) {

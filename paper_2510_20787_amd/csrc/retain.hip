@@ -376,8 +376,9 @@ template <bool APPEND>
 hipError_t run(RetainArgs a, int n_seqs, int64_t longest, hipStream_t stream) {
   const int64_t n_out_max = longest > a.window ? longest - a.window : 0;
   // Slices of at least 64 rows while they and the heads take no more than half of the CUs, which the ring's rows need too.  One CU
-  // moves about 40 KB per us: 32 heads, 1024 rows of D = 128 each 38.5 us with one workgroup per head, 28.5 with four (eight, a
-  // workgroup on every CU: the ring waits, 38), 32 heads, 512 rows of D = 64 11.0 -> 10.3.
+  // moves about 40 KB per us.  us per call with one workgroup per head, with four and with eight, a workgroup on every CU, for which
+  // the ring waits: 32768 tokens, 32 heads, 1024 kept entries of D = 128 each 45.6, 35.3, 42.7; 4 x 4096 tokens, 8 heads, 512
+  // entries of D = 64 12.5, 11.7, 13.1.
   const int64_t heads = (int64_t)n_seqs * a.Hkv, by_cus = heads > 0 ? 128 / heads : 1;
   const int64_t most = ((n_out_max < a.budget ? n_out_max : a.budget) + 63) / 64;
   const int64_t slices = by_cus < most ? by_cus : most;

@@ -68,7 +68,7 @@ score_weight_panels_kernel(const uint16_t* __restrict__ W, uint16_t* __restrict_
 
 // KS: the kernel size.  NW: waves; four where two workgroups share a CU's LDS (k <= 5, groups: 76 KB each; one hides the start of
 // the other: 265 -> 231 us on the ragged shape above), eight where one fills it.  MG: most tiles per workgroup, kMaxGroup or 1
-// (43 to 71 KB of LDS for k = 1 to 9: two to four workgroups per CU, by the registers too).
+// (39 to 72 KB of LDS for k = 1 to 9: two to four workgroups per CU, by the registers too).
 template <int D, int KS, int NW, int MG>
 __global__ void __launch_bounds__(64 * NW, MG == 1 && KS < 5 ? 4 : 2)
 score_mfma_kernel(const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int64_t st, int64_t sh,
